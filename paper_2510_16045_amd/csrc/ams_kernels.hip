@@ -129,6 +129,15 @@ __device__ constexpr int slot_channel(int s) {
   return tab.v[s];
 }
 
+// The inverse: operand slot (inside its permutation block) of every input channel of the block.
+template <int FMT>
+__device__ constexpr int channel_slot(int j) {
+  int s = 0;
+  for (int i = 0; i < Fmt<FMT>::PB; i++)
+    if (slot_channel<FMT>(i) == j) s = i;
+  return s;
+}
+
 // What one lane holds of one record: the words of its chunk and, for formats with side bits,
 // the lane's side dword of the record's unit (the record's own byte(s) are picked where it is restored).
 template <int SIDE>
@@ -1336,42 +1345,73 @@ __global__ void __launch_bounds__(512) multi_kernel(LinearArgs a) {
     if (valid[i]) finish_strip<MT>(a, gk, sidx[i], acc[i], scales_from_bits(sb[i], kTwo14), lane);
 }
 
-// Restore a whole packed matrix to row-major fp16: one wavefront per record.
+// Restore a whole packed matrix to row-major fp16: one wavefront per record, the records of a strip on neighbouring
+// wavefronts.  Bound by the stores (2 bytes out per 0.5-0.75 in).  A lane owns a K-quarter of a row, 48 or 64 bytes of
+// the result, so the record goes through the wavefront's own LDS tile and leaves it row by row in 16-byte stores, each
+// row of the record one contiguous 192- or 256-byte run.  28672 x 4096 FP4.25: 55 us, 5.4 TB/s, what a copy of 1 GiB reaches (element by element,
+// two bytes at a stride of a K-quarter per lane: 551 us).
+constexpr int kDequantWaves = 4;  // of a workgroup
 template <int FMT>
-__global__ void __launch_bounds__(256) dequant_kernel(const uint8_t* W, const uint16_t* scales, uint16_t* out, int N, int K,
-                                                      int n_rec, int64_t total_recs, int scaled, int n_sg, int sg_shift) {
+__global__ void __launch_bounds__(64 * kDequantWaves) dequant_kernel(const uint8_t* W, const uint16_t* scales, uint16_t* out, int N, int K,
+                                                                     int n_rec, int64_t total_recs, int scaled, int n_sg, int sg_shift) {
+  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+  constexpr int SG = Fmt<FMT>::SG, REC_K = Fmt<FMT>::REC_K, PB = Fmt<FMT>::PB, LANE_K = REC_K / 4, PIECES = REC_K / 8;
+  constexpr int TILE = REC_K + 8;  // halfs between the rows of a tile: neighbouring rows start 16 bytes apart in the banks
+  __shared__ __attribute__((aligned(16))) uint16_t tiles[kDequantWaves][16 * TILE];
   const int lane = threadIdx.x & 63;
-  const int64_t rec_id = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t rec_id = (int64_t)blockIdx.x * kDequantWaves + wave;
   if (rec_id >= total_recs) return;
   const int strip = (int)(rec_id / n_rec), rec = (int)(rec_id - (int64_t)strip * n_rec);
-  constexpr int SG = Fmt<FMT>::SG;
   const int64_t n_strips = (N + 15) / 16;
   const uint8_t* unit = W + ((size_t)(rec / SG) * n_strips + strip) * Fmt<FMT>::UNIT;
   LaneRec<FMT> r;
-  load_lane_rec<FMT, false>(r, unit + (rec % SG) * Fmt<FMT>::CB, unit + SG * Fmt<FMT>::CB, lane);
-  const int n = strip * 16 + (lane & 15);
-  if (n >= N) return;
-  float mul = kTwo14;
+  load_lane_rec<FMT, true>(r, unit + (rec % SG) * Fmt<FMT>::CB, unit + SG * Fmt<FMT>::CB, lane);
   // one scale per row (sg_shift < 0) or per run of 2^sg_shift records: [strip][run][row in strip]
-  if (scaled) mul *= (float)__builtin_bit_cast(_Float16, sg_shift < 0 ? scales[n] : scales[((size_t)strip * n_sg + (rec >> sg_shift)) * 16 + (lane & 15)]);
-  const int kbase = rec * Fmt<FMT>::REC_K + (lane >> 4) * (Fmt<FMT>::REC_K / 4);
-  auto put = [&](int k, uint32_t bits16) {
-    if (k < K) {
-      // magnitude and sign apart: the exact product is rounded once, and a negative
-      // zero code keeps its sign (a fused multiply-add with +0 would drop it)
-      const float v = (float)__builtin_bit_cast(_Float16, (uint16_t)(bits16 & 0x7FFF)) * mul;
-      out[(size_t)n * K + k] = (uint16_t)(__builtin_bit_cast(uint16_t, (_Float16)v) | (bits16 & 0x8000));
-    }
-  };
+  _Float16 s = 1;
+  if (scaled) {
+    const int n = min(strip * 16 + (lane & 15), N - 1);  // rows beyond N are never stored
+    s = __builtin_bit_cast(_Float16, sg_shift < 0 ? scales[n] : scales[((size_t)strip * n_sg + (rec >> sg_shift)) * 16 + (lane & 15)]);
+  }
   uint32_t o[4 * Fmt<FMT>::N_MFMA];
   restore_rec<FMT>(r, 8 * Fmt<FMT>::SIDE * (rec % SG), o);
-  constexpr int PB = Fmt<FMT>::PB;
+  // Magnitudes times 2^14 (exact) times the scale (the exact product, rounded once); the sign bit apart, so that a
+  // negative zero code keeps it.
 #pragma unroll
   for (int m = 0; m < 4 * Fmt<FMT>::N_MFMA; m++) {
-    // pair m = operand slots 2m and 2m+1 of the lane chunk
-    const int blk = (2 * m) / PB * PB;
-    put(kbase + blk + slot_channel<FMT>(2 * m - blk), o[m] & 0xFFFF);
-    put(kbase + blk + slot_channel<FMT>(2 * m + 1 - blk), o[m] >> 16);
+    const h2 v = __builtin_bit_cast(h2, o[m] & 0x7FFF7FFFu) * h2{(_Float16)kTwo14, (_Float16)kTwo14} * h2{s, s};
+    o[m] = __builtin_bit_cast(uint32_t, v) | (o[m] & 0x80008000u);
+  }
+  // from operand order into input-channel order, into the tile
+  uint16_t* tile = tiles[wave];
+  u4* mine = (u4*)(tile + (lane & 15) * TILE + (lane >> 4) * LANE_K);
+#pragma unroll
+  for (int d = 0; d < LANE_K / 8; d++) {
+    u4 v;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int j = 8 * d + 2 * e, blk = j / PB * PB;  // input channels j, j + 1 of the lane's K-quarter
+      v[e] = pick2(o + blk / 2, channel_slot<FMT>(j - blk), channel_slot<FMT>(j + 1 - blk));
+    }
+    mine[d] = v;
+  }
+  __builtin_amdgcn_wave_barrier();  // the tile is this wavefront's own, LDS serves it in order
+  const int k0 = rec * REC_K;
+#pragma unroll
+  for (int i = 0; i < PIECES / 4; i++) {
+    const int q = i * 64 + lane, row = q / PIECES, p = q - row * PIECES;  // 8 channels of one row
+    const u4 v = *(const u4*)(tile + row * TILE + 8 * p);
+    const int n = strip * 16 + row, k = k0 + 8 * p;
+    if (n < N && k < K) {
+      uint16_t* dst = out + (size_t)n * K + k;
+      if (k + 8 <= K) {
+        __builtin_memcpy(dst, &v, 16);  // rows start anywhere where K is no multiple of 8: one unaligned store
+      } else {
+#pragma unroll
+        for (int e = 0; e < 7; e++)
+          if (e < K - k) dst[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+      }
+    }
   }
 }
 
@@ -2021,10 +2061,10 @@ int ams_dequant_grouped(int fmt, const void* W_packed, const uint16_t* scales, i
   }
   const int n_rec = (int)((K + fi->rec_k - 1) / fi->rec_k);
   const int64_t total = ((N + 15) / 16) * n_rec;
-  const unsigned grid = (unsigned)((total + 3) / 4);
+  const unsigned grid = (unsigned)((total + kDequantWaves - 1) / kDequantWaves);
   hipStream_t st = (hipStream_t)stream;
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, (const uint8_t*)W_packed, scales, W_out, (int)N, (int)K, n_rec, total, scaled, n_sg,
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kDequantWaves), 0, st, (const uint8_t*)W_packed, scales, W_out, (int)N, (int)K, n_rec, total, scaled, n_sg,
                        sg_shift);
   };
   switch (fmt) {
