@@ -346,7 +346,10 @@ struct XRegs {
 };
 
 // Units u0 + i * nthr + idx, i < NU.
-template <int FMT, int NU>
+// RAGGED: rows of X start anywhere (K no multiple of 8, at least 8); a chunk that runs past its row's end is read from
+// the row's last eight channels and shifted into place by x_store.  11003 x 4099 at M = 5: 9.7 us; 23.5 us when such
+// rows went element by element (a division and a search for its slot each).
+template <bool RAGGED = false, int FMT, int NU>
 __device__ __forceinline__ void x_load(XRegs<FMT, NU>& xr, const LinearArgs& a, int k0, int nk, int u0, int idx, int nthr) {
   constexpr int UNIT = XUnit<FMT>::UNIT, CH = XUnit<FMT>::CH;
   const int upr = nk / UNIT;
@@ -359,13 +362,31 @@ __device__ __forceinline__ void x_load(XRegs<FMT, NU>& xr, const LinearArgs& a, 
 #pragma unroll
     for (int e = 0; e < CH; e++) {
       const bool ok = row_ok && k + 8 * e < a.K;
-      const size_t off = ok ? (size_t)m * a.K + k + 8 * e : 0;  // redirected loads are zeroed by x_store
-      xr.c[i][e] = *(const u4*)(a.X + off);
+      // redirected loads are zeroed by x_store
+      if constexpr (RAGGED) {
+        const size_t off = ok ? (size_t)m * a.K + min(k + 8 * e, a.K - 8) : 0;
+        __builtin_memcpy(&xr.c[i][e], a.X + off, 16);  // one unaligned load
+      } else {
+        const size_t off = ok ? (size_t)m * a.K + k + 8 * e : 0;
+        xr.c[i][e] = *(const u4*)(a.X + off);
+      }
     }
   }
 }
 
-template <int FMT, int NU>
+// Eight halfs (packed pairs) moved down by n places with zeros behind (n <= 0: as they are; n >= 8 does not matter,
+// such a chunk lies beyond K and is zero already).
+__device__ __forceinline__ void shift_tail(uint32_t* v, int n) {
+  n = max(n, 0);
+  if (n & 4) v[0] = v[2], v[1] = v[3], v[2] = 0, v[3] = 0;
+  if (n & 2) v[0] = v[1], v[1] = v[2], v[2] = v[3], v[3] = 0;
+  if (n & 1) {
+    v[0] = v[0] >> 16 | v[1] << 16, v[1] = v[1] >> 16 | v[2] << 16;
+    v[2] = v[2] >> 16 | v[3] << 16, v[3] = v[3] >> 16;
+  }
+}
+
+template <bool RAGGED = false, int FMT, int NU>
 __device__ __forceinline__ void x_store(const XRegs<FMT, NU>& xr, _Float16* xs, const LinearArgs& a, int k0, int nk, int u0,
                                         int idx, int nthr) {
   constexpr int UNIT = XUnit<FMT>::UNIT, CH = XUnit<FMT>::CH;
@@ -381,6 +402,7 @@ __device__ __forceinline__ void x_store(const XRegs<FMT, NU>& xr, _Float16* xs, 
       const uint32_t keep = k + 8 * e < a.K ? 0xFFFFFFFFu : 0u;  // zero beyond K
       in[4 * e] = xr.c[i][e][0] & keep, in[4 * e + 1] = xr.c[i][e][1] & keep;
       in[4 * e + 2] = xr.c[i][e][2] & keep, in[4 * e + 3] = xr.c[i][e][3] & keep;
+      if constexpr (RAGGED) shift_tail(&in[4 * e], k + 8 * e + 8 - a.K);
     }
     permute_unit<FMT>(in, out);
     if (m < a.M && j < upr) {
@@ -391,9 +413,9 @@ __device__ __forceinline__ void x_store(const XRegs<FMT, NU>& xr, _Float16* xs, 
   }
 }
 
-// Element-by-element staging for activations whose rows are not 16-byte aligned (K % 8 != 0).
+// Element-by-element staging for rows shorter than one 16-byte load (K < 8).
 template <int FMT>
-__device__ __forceinline__ void stage_x_unaligned(_Float16* xs, const LinearArgs& a, int k0, int nk, int idx0, int nthr) {
+__device__ __forceinline__ void stage_x_short(_Float16* xs, const LinearArgs& a, int k0, int nk, int idx0, int nthr) {
   for (int idx = idx0; idx < a.M * nk; idx += nthr) {
     const int m = idx / nk, kk = idx - m * nk;
     const int k = k0 + kk;
@@ -502,30 +524,24 @@ __global__ void __launch_bounds__(1024) stream_kernel(LinearArgs a) {
   const _Float16* x0 = xs + (m_lo < a.M ? m_lo : 0) * a.x_stride + lane_off;
   const _Float16* x1 = xs + (m_lo + 16 < a.M ? m_lo + 16 : 0) * a.x_stride + lane_off;
 
-  const bool vec_x = (a.K & 7) == 0;
   const int total_units = a.M << a.x_shift;
   const int units_per_pass = nthr * XUnit<FMT>::XU;
-  const bool wave_has_x = vec_x && wave * 64 < total_units;  // wave-uniform
+  const bool wave_has_x = wave * 64 < total_units;  // wave-uniform
   const int chunk_k = RC * REC_K;
   __builtin_amdgcn_sched_barrier(0);
 
   for (int rec_base = 0; rec_base < a.n_rec; rec_base += RC) {
     // Activations of the phase, in operand order.  Units beyond the first pass (large M)
-    // and unaligned rows are staged by loops that run to completion first; the first
-    // pass is only requested here and stored after the head of the weight stream has
+    // are staged by a loop that runs to completion first; the first pass is only requested here and stored after the head of the weight stream has
     // been requested too, so both are in flight together and the stream starts as soon
     // as its first record lands.  Waves whose units all fall outside skip the pass.
     if (rec_base > 0) __syncthreads();  // everyone is done with the previous phase's activations
     const int k0 = rec_base * REC_K;
     XRegs<FMT> xr;
-    if (vec_x) {
-      for (int u0 = units_per_pass; u0 < total_units; u0 += nthr * XUnit<FMT>::XB) {
-        XRegs<FMT, XUnit<FMT>::XB> xb;
-        x_load(xb, a, k0, chunk_k, u0, tid, nthr);
-        x_store(xb, xs, a, k0, chunk_k, u0, tid, nthr);
-      }
-    } else {
-      stage_x_unaligned<FMT>(xs, a, k0, chunk_k, tid, nthr);
+    for (int u0 = units_per_pass; u0 < total_units; u0 += nthr * XUnit<FMT>::XB) {
+      XRegs<FMT, XUnit<FMT>::XB> xb;
+      x_load(xb, a, k0, chunk_k, u0, tid, nthr);
+      x_store(xb, xs, a, k0, chunk_k, u0, tid, nthr);
     }
     if (wave_has_x) x_load(xr, a, k0, chunk_k, 0, tid, nthr);
     __builtin_amdgcn_sched_barrier(0);
@@ -691,10 +707,9 @@ __global__ void __launch_bounds__(1024) sweep_kernel(LinearArgs a) {
   f4* const my_part = parts + (size_t)((ns_v > 0 ? vs : 0) * wps + vw) * part_f4 + kq * mc + m_lo;
   const int part_step = sg * wps * part_f4;
 
-  const bool vec_x = (a.K & 7) == 0;
   const int total_units = a.M << a.x_shift;
   const int units_per_pass = nthr * XUnit<FMT>::XU;
-  const bool wave_has_x = vec_x && wave * 64 < total_units;  // wave-uniform
+  const bool wave_has_x = wave * 64 < total_units;  // wave-uniform
   const int chunk_k = RC * REC_K;
   __builtin_amdgcn_sched_barrier(0);
 
@@ -706,18 +721,14 @@ __global__ void __launch_bounds__(1024) sweep_kernel(LinearArgs a) {
     if (rec_base > rec_lo) __syncthreads();  // everyone is done with the previous phase's activations
     const int k0 = rec_base * REC_K;
 
-    // Activations: units beyond the first pass (large M) and unaligned rows are staged by loops
-    // that run to completion; the first pass is only requested here and stored behind the
+    // Activations: units beyond the first pass (large M) are staged by a loop that
+    // runs to completion; the first pass is only requested here and stored behind the
     // head of the weight stream, so both are in flight together.
     XRegs<FMT> xr;
-    if (vec_x) {
-      for (int u0 = units_per_pass; u0 < total_units; u0 += nthr * XUnit<FMT>::XB) {
-        XRegs<FMT, XUnit<FMT>::XB> xb;
-        x_load(xb, a, k0, chunk_k, u0, tid, nthr);
-        x_store(xb, xs, a, k0, chunk_k, u0, tid, nthr);
-      }
-    } else {
-      stage_x_unaligned<FMT>(xs, a, k0, chunk_k, tid, nthr);
+    for (int u0 = units_per_pass; u0 < total_units; u0 += nthr * XUnit<FMT>::XB) {
+      XRegs<FMT, XUnit<FMT>::XB> xb;
+      x_load(xb, a, k0, chunk_k, u0, tid, nthr);
+      x_store(xb, xs, a, k0, chunk_k, u0, tid, nthr);
     }
     if (wave_has_x) x_load(xr, a, k0, chunk_k, 0, tid, nthr);
     __builtin_amdgcn_sched_barrier(0);
@@ -1007,7 +1018,9 @@ __device__ __forceinline__ void finish_strip(const LinearArgs& a, int gk, int ou
 // QD (formats with side bits): the records are dealt to a strip's wavefronts in whole side groups,
 // so that a group's side dword is loaded once per group and not once per record; used where the
 // groups of a phase divide evenly enough among the wavefronts (the host decides).
-template <int FMT, int MT, bool NT, bool GS, bool QD = false, int LR = 2>
+// RAGGED: rows of X that are not 16-byte aligned (K % 8 != 0).  An instantiation of its own: with the choice made at
+// run time the aligned launches of M = 16 and 32 took 5-10 % longer (4096 x 4096 FP4.25 at M = 32 13.4 -> 14.9 us).
+template <int FMT, int MT, bool NT, bool GS, bool QD = false, int LR = 2, bool RAGGED = false>
 __global__ void __launch_bounds__(1024) column_kernel(LinearArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int REC_K = Fmt<FMT>::REC_K, SG = Fmt<FMT>::SG, RS = LR + 1;
@@ -1043,10 +1056,9 @@ __global__ void __launch_bounds__(1024) column_kernel(LinearArgs a) {
   const _Float16* x1 = xs + (m_lo + 16 < a.M ? m_lo + 16 : 0) * a.x_stride + lane_off;
   const int part_f4 = MT * 4 * mc;  // f4 per parked tile
 
-  const bool vec_x = (a.K & 7) == 0;
   const int total_units = a.M << a.x_shift;
   const int units_per_pass = nthr * XUnit<FMT>::XU;
-  const bool wave_has_x = vec_x && wave * 64 < total_units;  // wave-uniform
+  const bool wave_has_x = (!RAGGED || a.K >= 8) && wave * 64 < total_units;  // wave-uniform
   const int chunk_k = RC * REC_K;
   // Scales of the strip this wave finishes (wave w finishes strip w of the workgroup): requested first, kept as raw
   // bits until the epilogue.  (With one scale per run of input channels, GS, the scales travel with the records.)
@@ -1069,16 +1081,16 @@ __global__ void __launch_bounds__(1024) column_kernel(LinearArgs a) {
     // that run to completion; the first pass is only requested here and stored behind the
     // head of the weight stream, so both are in flight together.
     XRegs<FMT> xr;
-    if (vec_x) {
+    if (!RAGGED || a.K >= 8) {
       for (int u0 = units_per_pass; u0 < total_units; u0 += nthr * XUnit<FMT>::XB) {
         XRegs<FMT, XUnit<FMT>::XB> xb;
-        x_load(xb, a, k0, chunk_k, u0, tid, nthr);
-        x_store(xb, xs, a, k0, chunk_k, u0, tid, nthr);
+        x_load<RAGGED>(xb, a, k0, chunk_k, u0, tid, nthr);
+        x_store<RAGGED>(xb, xs, a, k0, chunk_k, u0, tid, nthr);
       }
+      if (wave_has_x) x_load<RAGGED>(xr, a, k0, chunk_k, 0, tid, nthr);
     } else {
-      stage_x_unaligned<FMT>(xs, a, k0, chunk_k, tid, nthr);
+      stage_x_short<FMT>(xs, a, k0, chunk_k, tid, nthr);
     }
-    if (wave_has_x) x_load(xr, a, k0, chunk_k, 0, tid, nthr);
     __builtin_amdgcn_sched_barrier(0);
 
     if constexpr (QD) {
@@ -1110,7 +1122,7 @@ __global__ void __launch_bounds__(1024) column_kernel(LinearArgs a) {
         request(q, ring[q], side[(q / SG) & 1], q % SG == 0);
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (wave_has_x) x_store(xr, xs, a, k0, chunk_k, 0, tid, nthr);
+      if (wave_has_x) x_store<RAGGED>(xr, xs, a, k0, chunk_k, 0, tid, nthr);
       __syncthreads();
 
       int rel = g_first * SG;  // first record of the group being multiplied, relative to the phase
@@ -1153,7 +1165,7 @@ __global__ void __launch_bounds__(1024) column_kernel(LinearArgs a) {
         request(ring[q]);
         __builtin_amdgcn_sched_barrier(0);  // issue in ring order: the oldest load is the first one needed
       }
-      if (wave_has_x) x_store(xr, xs, a, k0, chunk_k, 0, tid, nthr);
+      if (wave_has_x) x_store<RAGGED>(xr, xs, a, k0, chunk_k, 0, tid, nthr);
       __syncthreads();
 
       // One record: request the one LR ahead, restore, multiply, move on by wps records.
@@ -1236,7 +1248,7 @@ __global__ void __launch_bounds__(1024) column_kernel(LinearArgs a) {
 // staged as there, and every strip is finished straight from its wavefront's accumulators: no tiles in LDS, no
 // barrier after the last record.  For the formats whose records carry no side groups (with the side groups of two
 // strips dealt in turn FP4.25 was 1-3 % slower than with sixteen wavefronts on one strip each: measured, not kept).
-template <int FMT, int MT, bool NT, int NS>
+template <int FMT, int MT, bool NT, int NS, bool RAGGED = false>
 __global__ void __launch_bounds__(512) multi_kernel(LinearArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int REC_K = Fmt<FMT>::REC_K, SG = Fmt<FMT>::SG, LR = 3;
@@ -1267,10 +1279,9 @@ __global__ void __launch_bounds__(512) multi_kernel(LinearArgs a) {
   const int lane_off = (REC_K / 4) * kq;
   const _Float16* x0 = xs + (m_lo < a.M ? m_lo : 0) * a.x_stride + lane_off;
   const _Float16* x1 = xs + (m_lo + 16 < a.M ? m_lo + 16 : 0) * a.x_stride + lane_off;
-  const bool vec_x = (a.K & 7) == 0;
   const int total_units = a.M << a.x_shift;
   const int units_per_pass = nthr * XUnit<FMT>::XU;
-  const bool wave_has_x = vec_x && wave * 64 < total_units;  // wave-uniform
+  const bool wave_has_x = (!RAGGED || a.K >= 8) && wave * 64 < total_units;  // wave-uniform
   const int chunk_k = RC * REC_K;
   ScaleBits sb[NS];
 #pragma unroll
@@ -1288,16 +1299,16 @@ __global__ void __launch_bounds__(512) multi_kernel(LinearArgs a) {
     if (rec_base > rec_lo) __syncthreads();  // everyone is done with the previous phase's activations
     const int k0 = rec_base * REC_K;
     XRegs<FMT> xr;
-    if (vec_x) {
+    if (!RAGGED || a.K >= 8) {
       for (int u0 = units_per_pass; u0 < total_units; u0 += nthr * XUnit<FMT>::XB) {
         XRegs<FMT, XUnit<FMT>::XB> xb;
-        x_load(xb, a, k0, chunk_k, u0, tid, nthr);
-        x_store(xb, xs, a, k0, chunk_k, u0, tid, nthr);
+        x_load<RAGGED>(xb, a, k0, chunk_k, u0, tid, nthr);
+        x_store<RAGGED>(xb, xs, a, k0, chunk_k, u0, tid, nthr);
       }
+      if (wave_has_x) x_load<RAGGED>(xr, a, k0, chunk_k, 0, tid, nthr);
     } else {
-      stage_x_unaligned<FMT>(xs, a, k0, chunk_k, tid, nthr);
+      stage_x_short<FMT>(xs, a, k0, chunk_k, tid, nthr);
     }
-    if (wave_has_x) x_load(xr, a, k0, chunk_k, 0, tid, nthr);
     __builtin_amdgcn_sched_barrier(0);
 
     LaneRec<FMT> ring[4];
@@ -1314,7 +1325,7 @@ __global__ void __launch_bounds__(512) multi_kernel(LinearArgs a) {
         request(ring[q], q % NS);
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (wave_has_x) x_store(xr, xs, a, k0, chunk_k, 0, tid, nthr);
+      if (wave_has_x) x_store<RAGGED>(xr, xs, a, k0, chunk_k, 0, tid, nthr);
       __syncthreads();
       int cr = 0;  // record being multiplied, relative to the phase
       auto step = [&](auto uc) {
@@ -1826,28 +1837,35 @@ int launch_gemv(int M, bool nt, const LinearArgs& a, unsigned grid, size_t lds, 
 }
 
 // The packed formats' kernel: nt = non-temporal weight loads, gs = one scale per run of input channels.
-template <int FMT, int MT>
-int launch_column(bool nt, bool gs, bool qd, int lr, const LinearArgs& a, unsigned grid, int S, size_t lds, hipStream_t st) {
-  if (gs) return launch(column_kernel<FMT, MT, true, true>, a, grid, S, lds, st);
+template <int FMT, int MT, bool RAGGED>
+int launch_column_rows(bool nt, bool gs, bool qd, int lr, const LinearArgs& a, unsigned grid, int S, size_t lds, hipStream_t st) {
+  if (gs) return launch(column_kernel<FMT, MT, true, true, false, 2, RAGGED>, a, grid, S, lds, st);
   if constexpr (Fmt<FMT>::SG == 1) {
-    if (lr == 3) return nt ? launch(column_kernel<FMT, MT, true, false, false, 3>, a, grid, S, lds, st) : AMS_ERR_LAUNCH;
+    if (lr == 3) return nt ? launch(column_kernel<FMT, MT, true, false, false, 3, RAGGED>, a, grid, S, lds, st) : AMS_ERR_LAUNCH;
   }
   if constexpr (Fmt<FMT>::SG == 4) {
-    if (qd && lr == 3) return nt ? launch(column_kernel<FMT, MT, true, false, true, 3>, a, grid, S, lds, st) : AMS_ERR_LAUNCH;
+    if (qd && lr == 3) return nt ? launch(column_kernel<FMT, MT, true, false, true, 3, RAGGED>, a, grid, S, lds, st) : AMS_ERR_LAUNCH;
   }
   if constexpr (Fmt<FMT>::SG > 1) {
     if (qd)
-      return nt ? launch(column_kernel<FMT, MT, true, false, true>, a, grid, S, lds, st)
-                : launch(column_kernel<FMT, MT, false, false, true>, a, grid, S, lds, st);
+      return nt ? launch(column_kernel<FMT, MT, true, false, true, 2, RAGGED>, a, grid, S, lds, st)
+                : launch(column_kernel<FMT, MT, false, false, true, 2, RAGGED>, a, grid, S, lds, st);
   }
-  return nt ? launch(column_kernel<FMT, MT, true, false>, a, grid, S, lds, st)
-            : launch(column_kernel<FMT, MT, false, false>, a, grid, S, lds, st);
+  return nt ? launch(column_kernel<FMT, MT, true, false, false, 2, RAGGED>, a, grid, S, lds, st)
+            : launch(column_kernel<FMT, MT, false, false, false, 2, RAGGED>, a, grid, S, lds, st);
+}
+template <int FMT, int MT>
+int launch_column(bool nt, bool gs, bool qd, int lr, const LinearArgs& a, unsigned grid, int S, size_t lds, hipStream_t st) {
+  return (a.K & 7) == 0 ? launch_column_rows<FMT, MT, false>(nt, gs, qd, lr, a, grid, S, lds, st)
+                        : launch_column_rows<FMT, MT, true>(nt, gs, qd, lr, a, grid, S, lds, st);
 }
 
 // Wavefronts that own two strips each (non-temporal loads, one scale per row).
 template <int FMT, int MT>
 int launch_multi(const LinearArgs& a, unsigned grid, int S, size_t lds, hipStream_t st) {
-  if constexpr (Fmt<FMT>::SG == 1) return launch(multi_kernel<FMT, MT, true, 2>, a, grid, S, lds, st);
+  if constexpr (Fmt<FMT>::SG == 1)
+    return (a.K & 7) == 0 ? launch(multi_kernel<FMT, MT, true, 2, false>, a, grid, S, lds, st)
+                          : launch(multi_kernel<FMT, MT, true, 2, true>, a, grid, S, lds, st);
   return AMS_ERR_LAUNCH;
 }
 
@@ -1973,20 +1991,22 @@ int prepare_format() {
   LinearArgs a = {};
   bool ok = true;
   if constexpr (FMT != FMT_FP16) {
-    for (int nt = 0; nt < 2; nt++)
-      for (int gs = 0; gs < 2; gs++)
-        for (int qd = 0; qd < 2; qd++) {
-          if (gs && (!nt || qd)) continue;
-          ok &= launch_column<FMT, 1>(nt, gs, qd, 2, a, 0, 16, 0, nullptr) == AMS_OK;
-          ok &= launch_column<FMT, 2>(nt, gs, qd, 2, a, 0, 16, 0, nullptr) == AMS_OK;
-        }
-    if constexpr (Fmt<FMT>::SG == 1) {
-      ok &= launch_multi<FMT, 1>(a, 0, 8, 0, nullptr) == AMS_OK;
-      ok &= launch_multi<FMT, 2>(a, 0, 8, 0, nullptr) == AMS_OK;
-    }
-    if constexpr (Fmt<FMT>::SG == 1 || Fmt<FMT>::SG == 4) {
-      ok &= launch_column<FMT, 1>(true, false, Fmt<FMT>::SG == 4, 3, a, 0, 8, 0, nullptr) == AMS_OK;
-      ok &= launch_column<FMT, 2>(true, false, Fmt<FMT>::SG == 4, 3, a, 0, 8, 0, nullptr) == AMS_OK;
+    for (a.K = 8; a.K < 10; a.K++) {  // aligned and ragged rows of X
+      for (int nt = 0; nt < 2; nt++)
+        for (int gs = 0; gs < 2; gs++)
+          for (int qd = 0; qd < 2; qd++) {
+            if (gs && (!nt || qd)) continue;
+            ok &= launch_column<FMT, 1>(nt, gs, qd, 2, a, 0, 16, 0, nullptr) == AMS_OK;
+            ok &= launch_column<FMT, 2>(nt, gs, qd, 2, a, 0, 16, 0, nullptr) == AMS_OK;
+          }
+      if constexpr (Fmt<FMT>::SG == 1) {
+        ok &= launch_multi<FMT, 1>(a, 0, 8, 0, nullptr) == AMS_OK;
+        ok &= launch_multi<FMT, 2>(a, 0, 8, 0, nullptr) == AMS_OK;
+      }
+      if constexpr (Fmt<FMT>::SG == 1 || Fmt<FMT>::SG == 4) {
+        ok &= launch_column<FMT, 1>(true, false, Fmt<FMT>::SG == 4, 3, a, 0, 8, 0, nullptr) == AMS_OK;
+        ok &= launch_column<FMT, 2>(true, false, Fmt<FMT>::SG == 4, 3, a, 0, 8, 0, nullptr) == AMS_OK;
+      }
     }
   } else {
     for (int m = 1; m <= 4; m++)
