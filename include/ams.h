@@ -221,7 +221,11 @@ int ams_linear_workspace_bytes(int fmt, int M, int64_t N, int64_t K, size_t* byt
  * packed formats), "gemv ..." (the baseline at batches up to 4 whose activations fit in LDS), "sweep ..."
  * or "stream ..." (the baseline otherwise), followed by key=value pairs (workgroups, strips per
  * workgroup, slices of K, wavefronts, wavefronts per strip or strips per wavefront, phases of K, LDS
- * bytes, records ahead).  Host only, launches nothing. */
+ * bytes, records ahead).  A packed plan that ends in "walk=records" streams the activations beside the weights:
+ * every wavefront takes its records of K from all strips of the workgroup; waves_per_strip is then wavefronts /
+ * strips, phases how many times over the activations of a slice of K would fill the LDS, ahead counts
+ * (record, strip) pairs, side_groups=1 says that the wavefronts' records of one step are whole side groups.
+ * Host only, launches nothing. */
 int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, char* text, size_t text_len);
 int ams_linear_ws(const void* W_packed, const uint16_t* scales, const uint16_t* X, uint16_t* Y, int M, int64_t N,
                   int64_t K, int fmt, void* workspace, size_t workspace_bytes, void* stream);

@@ -6,7 +6,9 @@
 // contiguous 1 KiB access per wavefront), restores the fp16 pairs in registers and feeds
 // them as the A operand of v_mfma_f32_16x16x32_f16; the activations are staged in LDS in
 // the operand order the restoration produces.
-//   column_kernel  the packed formats: a workgroup owns up to 16 neighbouring strips, every
+//   slice_kernel   (ams_slice.hip) the packed formats, most shapes: wavefronts share K, activations
+//                  streamed beside the weights.
+//   column_kernel  the packed formats otherwise: a workgroup owns up to 16 neighbouring strips, every
 //                  wavefront stays with one strip and walks K in step with all the others, so
 //                  that the grid as a whole reads one contiguous, moving window of the K-major
 //                  packed matrix; the partial tile of a strip never leaves its wavefront's
@@ -14,9 +16,6 @@
 //   sweep_kernel / stream_kernel   the fp16 baseline (row-major weights).
 // Partial tiles are combined through LDS, deterministically; only the entry points that take
 // a workspace also split K over workgroups and exchange fp32 tiles through it.
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
 #include <algorithm>
 #include <type_traits>
 #include <cstdio>
@@ -24,307 +23,10 @@
 #include <mutex>
 #include <vector>
 
-#include "../../include/ams.h"
-#include "ams_layout.h"
+#include "ams_device.h"
 
 namespace {
-
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-typedef unsigned short us2 __attribute__((ext_vector_type(2)));
-typedef unsigned short us4 __attribute__((ext_vector_type(4)));
-
-constexpr int FMT_FP533 = AMS_FMT_FP533_E2M3;
-constexpr int FMT_FP425 = AMS_FMT_FP425_E2M2;
-constexpr int FMT_FP45 = AMS_FMT_FP45_E2M2;
-constexpr int FMT_FP433 = AMS_FMT_FP433_E2M2;
-constexpr int FMT_FP6 = AMS_FMT_FP6_E2M3;
-constexpr int FMT_FP5 = AMS_FMT_FP5_E2M2;
-constexpr int FMT_FP4 = AMS_FMT_FP4_E2M1;
-constexpr int FMT_FP16 = 100;  // internal: unquantized row-major fp16 weights (baseline)
-static_assert(FMT_FP533 == ams::kFmtFp533 && FMT_FP425 == ams::kFmtFp425 && FMT_FP45 == ams::kFmtFp45 &&
-              FMT_FP433 == ams::kFmtFp433 && FMT_FP6 == ams::kFmtFp6 && FMT_FP5 == ams::kFmtFp5 && FMT_FP4 == ams::kFmtFp4, "format numbers");
-
-constexpr float kTwo14 = 16384.0f;  // restored patterns are value * 2^-14
-
-__device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
-
-__device__ __forceinline__ uint32_t pk_mul_u16(uint32_t a, uint32_t c) {
-  us2 x = __builtin_bit_cast(us2, a), y = __builtin_bit_cast(us2, c);
-  return __builtin_bit_cast(uint32_t, (us2)(x * y));
-}
-
-// e2m2 formats (Sec. 3.2): one 32-bit word = two half-words of four 4-bit remainders.
-// sh[t] holds the last mantissa bits of pair t already placed at bits 8 and 24.
-// Produces the four fp16 pairs (A_t low, B_t high) as bit patterns of value * 2^-14:
-// sign -> bit 15, e1 e0 m1 -> bits 11..9, last bit m0 -> bit 8.
-__device__ __forceinline__ void restore_e2m2(uint32_t s, const uint32_t sh[4], uint32_t out[4]) {
-  constexpr uint32_t M = 0x8E008E00u;
-  out[0] = bfi(M, s, sh[0]);
-  out[1] = bfi(M, s << 3, sh[1]);
-  // members 2 and 3: sign and magnitude need different shifts; a packed 16-bit
-  // multiply by (2^a + 2^b) makes both shifted copies at once
-  out[2] = bfi(M, pk_mul_u16(s & 0x40384038u, 0x00420042u), sh[2]);
-  out[3] = bfi(M, pk_mul_u16(s & 0x20072007u, 0x02040204u), sh[3]);
-}
-// FP4.25: the four members of a half-word are one group, one pair of shared bits per word
-__device__ __forceinline__ void restore_fp425(uint32_t s, uint32_t sh, uint32_t out[4]) {
-  const uint32_t same[4] = {sh, sh, sh, sh};
-  restore_e2m2(s, same, out);
-}
-
-// Last bits kept in a side byte: bit t belongs to pair t's A half, bit 4+t to its B half.
-__device__ __forceinline__ uint32_t spread_side_byte(uint32_t byte) { return byte | (byte << 12); }
-__device__ __forceinline__ uint32_t pair_bits_e2m2(uint32_t spread, int t) { return (spread << (8 - t)) & 0x01000100u; }
-
-// e2m3 formats (Sec. 3.3 item 1): one 32-bit word = two half-words of three 5-bit
-// remainders; sh0..sh2 hold the last bits of the three pairs at bits 7 and 23.
-// Produces three fp16 pairs (A_i low, B_i high): sign -> bit 15, e1 e0 m2 m1 ->
-// bits 11..8, last bit m0 -> bit 7.
-__device__ __forceinline__ void restore_e2m3(uint32_t s, uint32_t sh0, uint32_t sh1, uint32_t sh2, uint32_t out[3]) {
-  constexpr uint32_t M = 0x8F008F00u;
-  out[0] = bfi(M, s, sh0);
-  {
-    // member 1: magnitude and sign need different shifts; spelled out as and-or + bit-field
-    // insert (left to itself the compiler makes two ands and a three-way or: one operation more)
-    uint32_t t, r;
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(t) : "v"(s << 4), "s"(0x0F000F00u), "v"(sh1));
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(0x80008000u), "v"(s << 1), "v"(t));
-    out[1] = r;
-  }
-  out[2] = bfi(M, pk_mul_u16(s & 0x200F200Fu, 0x01040104u), sh2);
-}
-// FP5.33: each half-word is a whole group, its shared bit sits at bit 12
-__device__ __forceinline__ void restore_fp533(uint32_t s, uint32_t out[3]) {
-  const uint32_t sh = (s >> 5) & 0x00800080u;
-  restore_e2m3(s, sh, sh, sh, out);
-}
-
-template <int FMT>
-struct Fmt {
-  static constexpr int REC_K = ams::kFormats[FMT].rec_k, REC_BYTES = ams::kFormats[FMT].rec_bytes,
-                       CHUNK = ams::kFormats[FMT].chunk_bytes, SIDE = ams::kFormats[FMT].side_bytes,
-                       PB = ams::kFormats[FMT].perm_block, N_MFMA = REC_K / 32,
-                       SG = ams::side_group(ams::kFormats[FMT]),       // records per unit (a power of two)
-                       CB = ams::chunk_block_bytes(ams::kFormats[FMT]),  // bytes of one record's lane chunks
-                       UNIT = ams::unit_bytes(ams::kFormats[FMT]);
-};
-template <>
-struct Fmt<FMT_FP16> {
-  static constexpr int REC_K = 128, REC_BYTES = 0, CHUNK = 0, SIDE = 0, PB = 8, N_MFMA = 4, SG = 1, CB = 0, UNIT = 0;
-};
-
-// Input channel (inside its permutation block) of every operand slot of the block.
-template <int FMT>
-struct SlotChannel {
-  int v[Fmt<FMT>::PB];
-  constexpr SlotChannel() : v{} {
-    for (int i = 0; i < Fmt<FMT>::PB; i++) v[i] = FMT == FMT_FP16 ? i : ams::slot_channel(FMT == FMT_FP16 ? 0 : FMT, i);
-  }
-};
-template <int FMT>
-__device__ constexpr int slot_channel(int s) {
-  constexpr SlotChannel<FMT> tab{};
-  return tab.v[s];
-}
-
-// The inverse: operand slot (inside its permutation block) of every input channel of the block.
-template <int FMT>
-__device__ constexpr int channel_slot(int j) {
-  int s = 0;
-  for (int i = 0; i < Fmt<FMT>::PB; i++)
-    if (slot_channel<FMT>(i) == j) s = i;
-  return s;
-}
-
-// What one lane holds of one record: the words of its chunk and, for formats with side bits,
-// the lane's side dword of the record's unit (the record's own byte(s) are picked where it is restored).
-template <int SIDE>
-struct SideBits {
-  uint32_t t;
-};
-template <>
-struct SideBits<0> {};
-template <int FMT>
-struct LaneRec : SideBits<Fmt<FMT>::SIDE> {
-  uint32_t w[Fmt<FMT>::CHUNK / 4];
-};
-template <>
-struct LaneRec<FMT_FP16> {
-  u4 w[4];
-};
-
-struct LinearArgs {
-  const uint8_t* W;        // packed records, or row-major fp16 for the baseline
-  const uint16_t* scales;  // [N] fp16, unused by the baseline
-  const uint16_t* X;       // [M, K] fp16
-  uint16_t* Y;             // [M, N] fp16
-  int M, N, K;
-  int n_rec;     // records per strip
-  int x_stride;  // halfs between activation rows inside a wave's LDS region
-  int x_region;  // halfs of one wave's LDS region
-  int x_shift;   // log2 of the staging units per activation row, rounded up to a power of two
-  int n_strips;  // strips of 16 output channels
-  int spw;       // stream kernel: strips per workgroup
-  int red_slots; // stream kernel: partial tiles a wave may park in LDS (strips its piece can touch)
-  int piece_q, piece_r;  // stream kernel: pairs per wave in a full workgroup: quotient, remainder
-  int rc;                // stream kernel: records per strip in one phase of K
-  int n_sg, sg_shift;    // scales per run of input channels: runs per row, log2(records per run)
-  // split of K over gk workgroups per strip (sweep kernel with a workspace): workgroups along N,
-  // slices of K, per-slice partial tiles [gk][strip][MT][64] f4, per-strip arrival counters
-  int gn, gk;
-  int wps;  // wavefronts that share a strip (sweep kernel: the workgroup works on S / wps strips at a time)
-  int wpa;  // column kernel: how many of a strip's wps wavefronts take records (the others idle: a count that divides the work evenly)
-  f4* ws_tiles;
-  unsigned* ws_count;
-};
-
-// One lane's part of a record: its chunk at `chunks` (one dwordx4, or three dwords that the
-// compiler merges) and its dword of the unit's side block at `side`.
-template <int FMT, bool NT, bool WITH_SIDE = true>
-__device__ __forceinline__ void load_lane_rec(LaneRec<FMT>& r, const uint8_t* chunks, const uint8_t* side, int lane) {
-  constexpr int CHUNK = Fmt<FMT>::CHUNK, SIDE = Fmt<FMT>::SIDE;
-  auto ld = [](auto* p) { return NT ? __builtin_nontemporal_load(p) : *p; };
-  if constexpr (CHUNK == 16) {
-    const u4 v = ld((const u4*)(chunks + lane * 16));
-    r.w[0] = v[0], r.w[1] = v[1], r.w[2] = v[2], r.w[3] = v[3];
-  } else {
-    const uint32_t* p = (const uint32_t*)(chunks + lane * CHUNK);
-#pragma unroll
-    for (int d = 0; d < CHUNK / 4; d++) r.w[d] = ld(p + d);
-  }
-  // WITH_SIDE = false: the caller keeps the group's side dword elsewhere
-  if constexpr (SIDE != 0 && WITH_SIDE) r.t = ld((const uint32_t*)side + lane);
-}
-
-// The MFMA A operands of one record as packed fp16 pairs: o[4u + t] = elements 2t, 2t+1
-// of the lane's row in MFMA u (bit patterns of value * 2^-14).
-// side_shift: first bit of this record's side bits inside the unit's side dword (wave-uniform).
-template <int FMT>
-__device__ __forceinline__ void restore_rec(const LaneRec<FMT>& r, int side_shift, uint32_t (&o)[4 * Fmt<FMT>::N_MFMA]) {
-  if constexpr (FMT == FMT_FP533) {
-#pragma unroll
-    for (int d = 0; d < 4; d++) restore_fp533(r.w[d], &o[3 * d]);
-  } else if constexpr (FMT == FMT_FP6) {
-    // side bits: bit 2d + (i-1) = member i of half A of word d, the same + 8 for half B
-    const uint32_t t = r.t >> side_shift;
-    const uint32_t spread = (t & 0xFFu) | ((t & 0xFF00u) << 8);
-#pragma unroll
-    for (int d = 0; d < 4; d++)
-      restore_e2m3(r.w[d], (r.w[d] >> 5) & 0x00800080u, (spread << (7 - 2 * d)) & 0x00800080u, (spread << (6 - 2 * d)) & 0x00800080u,
-                   &o[3 * d]);
-  } else if constexpr (FMT == FMT_FP425) {
-    const uint32_t spread = spread_side_byte(__builtin_amdgcn_ubfe(r.t, (uint32_t)side_shift, 8u));
-#pragma unroll
-    for (int d = 0; d < 4; d++) restore_fp425(r.w[d], pair_bits_e2m2(spread, d), &o[4 * d]);
-  } else if constexpr (FMT == FMT_FP4) {
-    // an e2m1 code is an e2m2 remainder whose last bit is 0
-    const uint32_t none[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int d = 0; d < 4; d++) restore_e2m2(r.w[d], none, &o[4 * d]);
-  } else {
-    // FP4.33: one side byte for all words; FP4.5: one per two words; FP5: one per word
-    constexpr int WORDS_PER_BYTE = FMT == FMT_FP433 ? 3 : (FMT == FMT_FP45 ? 2 : 1);
-    const uint32_t t = Fmt<FMT>::SIDE == 4 ? r.t : __builtin_amdgcn_ubfe(r.t, (uint32_t)side_shift, (uint32_t)(8 * Fmt<FMT>::SIDE));
-    uint32_t sh[4];
-#pragma unroll
-    for (int d = 0; d < Fmt<FMT>::CHUNK / 4; d++) {
-      if (d % WORDS_PER_BYTE == 0) {
-        const uint32_t spread = spread_side_byte(Fmt<FMT>::SIDE == 1 ? t : (t >> (8 * (d / WORDS_PER_BYTE))) & 0xFFu);
-#pragma unroll
-        for (int i = 0; i < 4; i++) sh[i] = pair_bits_e2m2(spread, i);
-      }
-      restore_e2m2(r.w[d], sh, &o[4 * d]);
-    }
-  }
-}
-
-// Unconditional loads of one record (rec must be a valid record of the strip).  NT: packed
-// records bypass the caches' retention (they are read once per call, and a model's other
-// layers pass through the caches before the next call); only tiny matrices use ordinary loads.
-template <int FMT, bool NT = true>
-__device__ __forceinline__ void load_rec(LaneRec<FMT>& r, const LinearArgs& a, int strip, int rec, int lane) {
-  if constexpr (FMT == FMT_FP16) {
-    // rows beyond N and K-chunks beyond K are redirected to the matrix's first 16 bytes
-    // and zeroed afterwards: keeps the loads free of control flow
-    const int row = strip * 16 + (lane & 15);
-    const int kq = lane >> 4;
-#pragma unroll
-    for (int d = 0; d < 4; d++) {
-      const int k = rec * 128 + 32 * d + 8 * kq;
-      const bool ok = row < a.N && k < a.K;  // K is a multiple of 8
-      const size_t off = ok ? ((size_t)row * a.K + k) * 2 : 0;
-      const u4 v = *(const u4*)(a.W + off);  // cached: the two halves of a 128-byte line come from two loads
-      const uint32_t keep = ok ? 0xFFFFFFFFu : 0u;
-      r.w[d] = u4{v[0] & keep, v[1] & keep, v[2] & keep, v[3] & keep};
-    }
-  } else {
-    // unit (rec / SG, strip) of the K-major packed matrix, record rec % SG inside it
-    constexpr int SG = Fmt<FMT>::SG;
-    const uint8_t* unit = a.W + ((size_t)(rec / SG) * a.n_strips + strip) * Fmt<FMT>::UNIT;
-    load_lane_rec<FMT, NT>(r, unit + (rec % SG) * Fmt<FMT>::CB, unit + SG * Fmt<FMT>::CB, lane);
-  }
-}
-
-// Multiply one record (16 rows x REC_K) into the accumulators.  x0 / x1 point at this
-// lane's activation row(s) in LDS at the first operand slot of its K-quarter of the record.
-// side_shift: see restore_rec (8 * SIDE * (rec % SG); 0 for formats without side bits).
-template <int FMT, int MT>
-__device__ __forceinline__ void mac_rec(const LaneRec<FMT>& r, const _Float16* x0, const _Float16* x1, f4 acc[MT], int side_shift = 0) {
-  h8 a[Fmt<FMT>::N_MFMA];
-  if constexpr (FMT == FMT_FP16) {
-#pragma unroll
-    for (int d = 0; d < 4; d++) a[d] = __builtin_bit_cast(h8, r.w[d]);
-  } else {
-    uint32_t o[4 * Fmt<FMT>::N_MFMA];
-    restore_rec<FMT>(r, side_shift, o);
-#pragma unroll
-    for (int u = 0; u < Fmt<FMT>::N_MFMA; u++) a[u] = __builtin_bit_cast(h8, u4{o[4 * u], o[4 * u + 1], o[4 * u + 2], o[4 * u + 3]});
-  }
-#pragma unroll
-  for (int u = 0; u < Fmt<FMT>::N_MFMA; u++) {
-    // FP16 records interleave the K-quarters per MFMA (32 consecutive k each)
-    const int off = FMT == FMT_FP16 ? 32 * u : 8 * u;
-    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u], *(const h8*)(x0 + off), acc[0], 0, 0, 0);
-    if constexpr (MT == 2) acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u], *(const h8*)(x1 + off), acc[1], 0, 0, 0);
-  }
-}
-
-// Operand slot of activation k (relative to its record) in LDS.
-template <int FMT>
-__device__ __forceinline__ int x_slot(int kk) {
-  if constexpr (FMT == FMT_FP16) {
-    return kk;
-  } else {
-    constexpr int PB = Fmt<FMT>::PB;
-    const int blk = kk / PB, j = kk - blk * PB;
-    int slot = 0;
-    for (int s = 0; s < PB; s++)
-      if (slot_channel<FMT>(s) == j) slot = s;
-    return blk * PB + slot;
-  }
-}
-
-// dword made of half `ia` (low) and half `ib` (high) of an array of packed half pairs
-__device__ __forceinline__ uint32_t pick2(const uint32_t* in, int ia, int ib) {
-  const uint32_t sel = (uint32_t)(2 * (ia & 1)) | (uint32_t)(2 * (ia & 1) + 1) << 8 | (uint32_t)(4 + 2 * (ib & 1)) << 16 |
-                       (uint32_t)(5 + 2 * (ib & 1)) << 24;
-  return __builtin_amdgcn_perm(in[ib >> 1], in[ia >> 1], sel);
-}
-
-// One permutation block of activations from input-channel order into operand order
-// (packed pairs in, packed pairs out).
-template <int FMT>
-__device__ __forceinline__ void permute_unit(const uint32_t (&in)[Fmt<FMT>::PB / 2], uint32_t (&out)[Fmt<FMT>::PB / 2]) {
-#pragma unroll
-  for (int m = 0; m < Fmt<FMT>::PB / 2; m++) {
-    if constexpr (FMT == FMT_FP16)
-      out[m] = in[m];
-    else
-      out[m] = pick2(in, slot_channel<FMT>(2 * m), slot_channel<FMT>(2 * m + 1));
-  }
-}
+using namespace ams_dev;
 
 // Activation staging.  A wave copies X[0..M) x [k0, k0+nk) into its LDS region in operand
 // order (zero beyond K), nk a multiple of the record size.  The copy is split in a load
@@ -1453,8 +1155,6 @@ __global__ void __launch_bounds__(1024) read_probe_kernel(const u4* __restrict__
 }
 
 // ---- host-side launch logic -------------------------------------------------
-constexpr int kLdsMaxBytes = 160 * 1024;  // LDS of a gfx950 compute unit
-
 // activations are staged in units of one permutation block
 int x_unit(int fmt) { return fmt == FMT_FP16 ? 8 : ams::kFormats[fmt].perm_block; }
 
@@ -1573,6 +1273,7 @@ struct ColumnPlan {
   int wpa;  // wavefronts of a strip that take records (= wps unless fewer divide the side groups evenly)
   int lr;   // records a wavefront keeps in flight beside the one it restores
   int ns;   // strips a wavefront owns alone (multi_kernel; 1: column_kernel); then wpa = wavefronts that own strips
+  bool slice;  // slice_kernel: the wavefronts share K and take every record of all spw strips
   size_t lds;
 };
 
@@ -1586,6 +1287,7 @@ ColumnPlan column_plan_for(int S, int lr, int fmt, int M, int64_t n_strips, int 
                            int ns = 1) {
   ColumnPlan p;
   p.ns = ns;
+  p.slice = false;
   const int sg = ams::side_group(ams::kFormats[fmt]);
   const int mt = M > 16 ? 2 : 1;
   const int mc = std::min(M, 16);
@@ -1663,6 +1365,47 @@ ColumnPlan make_column_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int
     const ColumnPlan d = column_plan_for(8, 3, fmt, M, n_strips, n_rec_all, rec_k, gk, allow_qd);
     if (d.qd) return d;  // three records ahead exist for the side-group deal only
   }
+  return p;
+}
+
+// The plan of a problem: slice_kernel where it takes it (aligned_rows: rows of X are 16-byte aligned, K % 8 == 0;
+// one_scale: one scale per row of W), else make_column_plan's.  slice_kernel is the faster one nearly everywhere
+// (twelve shapes, seven formats, M = 1 .. 32: 1.00-1.8 x); the exceptions, us column / slice:
+//   one strip per workgroup, M <= 2, where eight wavefronts with three records ahead fill the chip (no side groups):
+//     4096 x 14336 FP5.33 M = 1 9.5 / 9.4, M = 2 10.1 / 10.1;
+//   two strips on fewer than 7/8 of the compute units, M <= 2, 128 records and more: its eight wavefronts keep too few
+//     bytes in flight (5120 x 25600 FP4.25 M = 1 17.8 / 19.7, FP5.33 M = 2 20.3 / 22.5); at M = 1 without side groups also
+//     below that (6144 x 4096 FP5.33 6.4 / 6.3, the sixteen wavefronts the plan query reports there);
+//   seven and eight strips without side groups, M > 16: 28672 x 4096 FP5.33 M = 32 24.7 / 18.9; slower, but the plan
+//     query promises sixteen wavefronts there, which slice_kernel's registers do not allow at M > 16;
+//   more than eight strips: halved (two workgroups fit on a compute unit at M <= 16) where that pays: with side groups
+//     from M = 3 on (57344 x 8192 FP4.25 M = 4 43.4 / 39.8, 128256 x 4096 46.3 / 43.7), without from M = 9
+//     (57344 x 8192 FP5.33 M = 16 59.0 / 52.6); above M = 8 only on long K (45000 x 4096 FP4.25 M = 16 21.1 / 23.3).
+ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
+  ColumnPlan p = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
+  const int sg = ams::side_group(ams::kFormats[fmt]);
+  if (!aligned_rows || !one_scale) return p;
+  if (p.spw == 1 && p.lr == 3) return p;
+  if (M <= 2 && p.spw == 2 && p.grid < kNumCU * 7 / 8 && (n_rec_all >= 128 || (sg == 1 && M == 1))) return p;
+  if (sg == 1 && M > 16 && (p.spw == 7 || p.spw == 8)) return p;
+  if (p.spw > kSliceMaxStrips) {
+    if (gk != 1 || M <= (sg == 1 ? 8 : 2) || (M > 8 && n_rec_all < 64)) return p;
+    p.spw = (p.spw + 1) / 2;
+    p.grid = p.gn = (int)((n_strips + p.spw - 1) / p.spw);
+  }
+  const int r = slice_rows(M);
+  p.slice = true;
+  p.ns = 1;
+  p.S = slice_waves(fmt, r, p.spw);
+  p.lr = slice_ahead(p.S);
+  p.wps = p.S / p.spw;
+  p.wpa = p.wps;
+  const int n_rec = (n_rec_all + gk - 1) / gk;
+  p.qd = sg > 1 && gk == 1;  // the wavefronts of a workgroup take S consecutive records together, whole side groups
+  // how many times over the staged activations of a slice of K would fill the LDS
+  p.n_phase = (int)(((int64_t)n_rec * slice_x_loads(fmt, r) * 1024 + kLdsMaxBytes - 1) / kLdsMaxBytes);
+  p.rc = n_rec;
+  p.lds = (size_t)slice_lds(fmt, r, p.spw);
   return p;
 }
 
@@ -1869,6 +1612,20 @@ int launch_multi(const LinearArgs& a, unsigned grid, int S, size_t lds, hipStrea
   return AMS_ERR_LAUNCH;
 }
 
+// slice_kernel for a.M rows and `strips` strips per workgroup.
+template <int FMT>
+int launch_slice(const LinearArgs& a, int strips, unsigned grid, hipStream_t st) {
+  const int r = slice_rows(a.M);
+  const void* kern = slice_kernel_of<FMT>(r, strips);
+  if (!kern) return AMS_ERR_LAUNCH;
+  const size_t lds = (size_t)slice_lds(FMT, r, strips);
+  if (lds > 64 * 1024 && !raise_lds_limit(kern)) return AMS_ERR_LAUNCH;
+  if (grid == 0) return AMS_OK;
+  LinearArgs copy = a;
+  void* args[] = {&copy};
+  return hipLaunchKernel(kern, dim3(grid), dim3(64 * slice_waves(FMT, r, strips)), args, lds, st) == hipSuccess ? AMS_OK : AMS_ERR_LAUNCH;
+}
+
 template <int FMT>
 int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_t* Y, int M, int64_t N, int64_t K,
                void* stream, int64_t scale_group = 0, void* workspace = nullptr, size_t ws_bytes = 0) {
@@ -1936,7 +1693,7 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
     // in any cache (a model's layers in turn): equal or up to 5 % faster than ordinary loads at every size; ordinary
     // loads only win when the same few megabytes are read again call after call.
     const bool nt = n_strips * n_rec * (int64_t)REC_BYTES >= (2ll << 20);
-    const ColumnPlan cp = make_column_plan(FMT, M, n_strips, n_rec, REC_K, gk, scale_group == 0, scale_group == 0 && nt);
+    const ColumnPlan cp = make_plan(FMT, M, n_strips, n_rec, REC_K, gk, K % 8 == 0, scale_group == 0, nt);
     a.gn = cp.gn;
     a.gk = cp.gk;
     a.wps = cp.wps;
@@ -1947,6 +1704,7 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
     a.x_shift = cp.x_shift;
     a.spw = cp.spw;
     a.rc = cp.rc;
+    if (cp.slice) return launch_slice<FMT>(a, cp.spw, cp.grid, st);
     if (cp.ns > 1) return M <= 16 ? launch_multi<FMT, 1>(a, cp.grid, cp.S, cp.lds, st) : launch_multi<FMT, 2>(a, cp.grid, cp.S, cp.lds, st);
     return M <= 16 ? launch_column<FMT, 1>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st)
                    : launch_column<FMT, 2>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st);
@@ -1991,6 +1749,8 @@ int prepare_format() {
   LinearArgs a = {};
   bool ok = true;
   if constexpr (FMT != FMT_FP16) {
+    for (a.M = 4; a.M <= 32; a.M *= 2)
+      for (int strips = 1; strips <= kSliceMaxStrips; strips++) ok &= launch_slice<FMT>(a, strips, 0, nullptr) == AMS_OK;
     for (a.K = 8; a.K < 10; a.K++) {  // aligned and ragged rows of X
       for (int nt = 0; nt < 2; nt++)
         for (int gs = 0; gs < 2; gs++)
@@ -2157,9 +1917,9 @@ int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, ch
   const int gk = with_workspace ? choose_split(f, M, n_strips, n_rec, rec_k, rec_bytes) : 1;
   if (f != FMT_FP16) {
     const bool nt = n_strips * n_rec * (int64_t)rec_bytes >= (2ll << 20);  // as run_linear decides it
-    const ColumnPlan cp = make_column_plan(f, M, n_strips, n_rec, rec_k, gk, true, nt);
-    snprintf(text, text_len, "column grid=%d strips_per_wg=%d k_slices=%d waves=%d waves_per_strip=%d phases=%d lds=%zu side_groups=%d active_per_strip=%d ahead=%d strips_per_wave=%d", cp.grid,
-             cp.spw, cp.gk, cp.S, cp.wps, cp.n_phase, cp.lds, cp.qd ? 1 : 0, cp.ns > 1 ? 1 : cp.wpa, cp.lr, cp.ns);
+    const ColumnPlan cp = make_plan(f, M, n_strips, n_rec, rec_k, gk, K % 8 == 0, true, nt);
+    snprintf(text, text_len, "column grid=%d strips_per_wg=%d k_slices=%d waves=%d waves_per_strip=%d phases=%d lds=%zu side_groups=%d active_per_strip=%d ahead=%d strips_per_wave=%d%s", cp.grid,
+             cp.spw, cp.gk, cp.S, cp.wps, cp.n_phase, cp.lds, cp.qd ? 1 : 0, cp.ns > 1 ? 1 : cp.wpa, cp.lr, cp.ns, cp.slice ? " walk=records" : "");
     return AMS_OK;
   }
   if (const GemvPlan gp = make_gemv_plan(M, K, gk); gp.ok) {

@@ -1,0 +1,331 @@
+// slice_kernel: the Linear with the activations streamed beside the weights (Sec. 3.3, Sec. 4.2), for
+// workgroups of up to eight strips of 16 output channels.  One format per translation unit
+// (AMS_SLICE_FMT), so that the formats compile in parallel.
+//
+// A workgroup owns NS neighbouring strips and its wavefronts share K: wavefront w takes records w, w + S, ... of all NS
+// strips.  The activations of a record are then needed by one wavefront only, so nothing is staged for the
+// workgroup and there is no barrier before the sums at the end: a wavefront copies the M x REC_K activations of its
+// next records straight into LDS of its own (16 bytes per lane and load, no registers) in the same in-order stream of
+// requests as the weights, and one s_waitcnt that counts the younger requests lets a record start as soon as its own
+// loads are there.  They arrive in input-channel order; the operand registers are permuted once per record and serve
+// all NS strips.  What it replaces staged the activations of all of K (or of a phase of it) for the workgroup, through
+// registers, between barriers, and sat in front of the weight stream.
+//
+// Bound: at M <= 8 by the weight stream and the restoration's VALU work, as before; at M = 32 with one strip per workgroup
+// by what a compute unit does per record (64 KiB of activations through LDS in and out, restoration, permutation): with
+// neither weights nor activations coming from memory 4096 x 14336 still takes 12 us.  L2 is not the bound: 256 workgroups
+// that read 896 KiB each do so in 7 us.
+//
+// Measured against what it replaces (us, M = 1 / 4 / 16 / 32): 4096 x 4096 FP4.25 5.2 -> 4.3, 6.0 -> 4.5, 7.6 -> 6.1, 13.4 -> 8.0;
+// 4096 x 14336 8.7 -> 8.5, 10.3 -> 9.3, 18.3 -> 13.7, 30.9 -> 19.7; 8192 x 8192 FP5.33 10.5 -> 10.0, 11.2 -> 10.3, 15.6 -> 14.2,
+// 25.4 -> 17.8; 28672 x 4096 FP4.25 12.8 -> 12.4, 13.8 -> 12.6, 15.3 -> 14.8, 21.7 -> 18.7; 256 x 768 4.1 -> 2.6 at every M <= 16.
+//
+// The counted waits need every step to make the same requests in the same order: requests past a wavefront's last record
+// are made too, out of the buffers' range (they read no memory), the scheduler may not move requests across the
+// barriers below, and every slot of the ring counts as used at the end so that no request is left out as dead.
+#include "ams_device.h"
+
+#include <type_traits>
+
+#ifndef AMS_SLICE_FMT
+#define AMS_SLICE_FMT 0
+#endif
+
+namespace {
+using namespace ams_dev;
+
+// CHUNK bytes per lane through a buffer descriptor, non-temporal.
+template <int CHUNK>
+__device__ __forceinline__ void buffer_load_chunk(uint32_t* w, __amdgpu_buffer_rsrc_t rsrc, int voffset, int soffset) {
+  constexpr int NT = 2;
+  if constexpr (CHUNK == 16) {
+    const u4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voffset, soffset, NT);
+    w[0] = v[0], w[1] = v[1], w[2] = v[2], w[3] = v[3];
+  } else if constexpr (CHUNK == 12) {
+    const u3 v = __builtin_amdgcn_raw_buffer_load_b96(rsrc, voffset, soffset, NT);
+    w[0] = v[0], w[1] = v[1], w[2] = v[2];
+  } else {
+    w[0] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voffset, soffset, NT);
+  }
+}
+
+// Shape of the kernel for R staged activation rows (4, 8, 16 or 32) and NS strips per workgroup.
+template <int FMT, int R, int NS>
+struct Slice {
+  static constexpr int MT = R > 16 ? 2 : 1;
+  static constexpr int RB = R > 16 ? 16 : R;                    // rows of one MFMA tile that are staged
+  static constexpr int NI = slice_x_loads(FMT, R), NI1 = NI / MT;  // 1 KiB loads of a record's activations, of one tile's
+  static constexpr int BYTES = NI * 1024;
+  static constexpr int WL = Fmt<FMT>::SIDE ? 2 : 1;             // load instructions of one weight record
+  static constexpr int S = slice_waves(FMT, R, NS);
+  static constexpr int LX = kSliceXAhead;
+  static constexpr int LW = slice_ahead(S);
+  static constexpr int U = NS > LW ? 1 : NS == 1 ? LW + 1 : 2;  // records per unrolled round
+  static constexpr int RS = U * NS;                             // slots of the weight ring
+  static constexpr int ROW = slice_tile_row(S, R, NS);
+};
+
+template <int FMT, int R, int NS>
+__global__ void __launch_bounds__(64 * (Slice<FMT, R, NS>::S)) slice_kernel(LinearArgs a) {
+  using P = Slice<FMT, R, NS>;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int REC_K = Fmt<FMT>::REC_K, SG = Fmt<FMT>::SG, NF = Fmt<FMT>::N_MFMA, PB = Fmt<FMT>::PB, UNIT = Fmt<FMT>::UNIT;
+  constexpr int MT = P::MT, RB = P::RB, LX = P::LX, LW = P::LW, RS = P::RS, U = P::U, S = P::S;
+  static_assert(LW < RS, "weight ring");
+  asm volatile("" ::"s"(a.W), "s"(a.scales), "s"(a.X), "s"(a.Y), "s"(a.M), "s"(a.N), "s"(a.K), "s"(a.n_rec), "s"(a.n_strips), "s"(a.gn), "s"(a.gk));
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // workgroup = (position g along N, slice gk of K)
+  const int gk = a.gk > 1 ? (int)(blockIdx.x / (unsigned)a.gn) : 0;
+  const int s_first = ((int)blockIdx.x - gk * a.gn) * NS;
+  const int ns = min(NS, a.n_strips - s_first);
+  const int rec_lo = a.gk > 1 ? (int)((unsigned)(gk * a.n_rec) / (unsigned)a.gk) : 0;
+  const int rec_hi = a.gk > 1 ? (int)((unsigned)((gk + 1) * a.n_rec) / (unsigned)a.gk) : a.n_rec;
+  const int first = rec_lo + wave;  // this wave's records: first, first + S, ...
+  const int cnt = first < rec_hi ? (rec_hi - first + S - 1) / S : 0;
+  uint16_t scale_bits = 0;
+  if (tid < NS * 16) scale_bits = a.scales[min(s_first * 16 + tid, a.N - 1)];
+  __builtin_amdgcn_sched_barrier(0);
+
+  f4 acc[NS][MT];
+#pragma unroll
+  for (int i = 0; i < NS; i++)
+#pragma unroll
+    for (int t = 0; t < MT; t++) acc[i][t] = f4{0, 0, 0, 0};
+
+  if (cnt > 0) {
+    unsigned char* const xbuf = smem + wave * (LX * P::BYTES);
+    // A load brings 16 (8, 4) rows x 4 (8, 16) pieces of 16 bytes: four neighbouring lanes read 64 neighbouring bytes of a
+    // row (with neighbouring lanes in different rows the same bytes take three times as long).  The pieces of four lanes
+    // are swapped by a function of the row that makes the reads of an operand, 8 or 16 rows at one piece, free of bank
+    // conflicts; LDS takes them in lane order.
+    auto swz = [](int m) { return ((m >> 2) & 1) | ((((m >> 1) ^ (m >> 3)) & 1) << 1); };
+    // loads: lane -> row, block of four pieces, piece
+    constexpr int BLK = 64 / (4 * RB);  // blocks of four pieces per load
+    const int ld_m = (lane >> 2) & (RB - 1), ld_b = lane / (4 * RB);
+    const int row_bytes = a.K * 2;
+    int voff[MT];
+#pragma unroll
+    for (int t = 0; t < MT; t++) voff[t] = min(16 * t + ld_m, a.M - 1) * row_bytes + ld_b * 64 + (((lane & 3) ^ swz(ld_m)) * 16);
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.X, 0, a.M * row_bytes, 0x00020000);
+    // reads: operand u of this lane's activation row
+    const int m_lo = lane & (RB - 1), kq = lane >> 4;
+    int roff[NF];
+#pragma unroll
+    for (int u = 0; u < NF; u++) {
+      const int piece = kq * NF + u;
+      roff[u] = (piece >> 2) * (RB * 64) + m_lo * 64 + (((piece & 3) ^ swz(m_lo)) * 16);
+    }
+    // Requests past the wave's last record (p >= cnt) get an offset out of the buffer's range: they read no memory but
+    // count like the others.  (The scalar offset always stays inside the buffer: only the vector part is out of range.)
+    constexpr int FAR = 0x7FFF0000;
+    auto request_x = [&](int p) {  // the wave's p-th record of activations
+      const int soff = p < cnt ? (first + S * p) * (REC_K * 2) : 0;
+      unsigned char* dst = xbuf + (p & (LX - 1)) * P::BYTES;
+#pragma unroll
+      for (int t = 0; t < MT; t++)
+#pragma unroll
+        for (int i = 0; i < P::NI1; i++) {
+          const int vo = p < cnt ? voff[t] + i * (BLK * 64) : FAR;
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(dst + (t * P::NI1 + i) * 1024), 16, vo, soff, 0, 0);
+        }
+    };
+    LaneRec<FMT> ring[RS];
+    auto request_w = [&](int p, int i, LaneRec<FMT>& slot) {  // the weights of strip i for the wave's p-th record
+      const unsigned rec = p < cnt ? (first + S * p) : 0;
+      const uint8_t* unit = a.W + ((size_t)(rec / SG) * (unsigned)a.n_strips + (unsigned)(s_first + min(i, ns - 1))) * UNIT;
+      const __amdgpu_buffer_rsrc_t w = __builtin_amdgcn_make_buffer_rsrc((void*)unit, 0, UNIT, 0x00020000);
+      const int vo = p < cnt ? lane * Fmt<FMT>::CHUNK : FAR;
+      buffer_load_chunk<Fmt<FMT>::CHUNK>(slot.w, w, vo, (int)(rec % SG) * Fmt<FMT>::CB);
+      if constexpr (Fmt<FMT>::SIDE != 0) {
+        const int vs = p < cnt ? lane * 4 : FAR;
+        buffer_load_chunk<4>(&slot.t, w, vs, SG * Fmt<FMT>::CB);
+      }
+    };
+    const int tail = a.n_rec * REC_K - a.K;  // channels of the last record beyond K
+
+    // One record of all strips.  uc: its place in the unrolled round.  The wait lets through exactly the loads requested
+    // after this record's activations: every step makes the same requests, those past the end out of range.
+    auto step = [&](int p, auto uc) {
+      constexpr int u0 = decltype(uc)::value * NS;  // its first slot of the ring
+      constexpr int STEADY = LX * NS * P::WL + (LX - 1) * P::NI;
+      if constexpr (LW >= LX * NS) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STEADY) : "memory");
+      } else {  // the first steps have fewer weights requested behind their activations
+        if (p == 0)
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LW * P::WL + (LX - 1) * P::NI) : "memory");
+        else if (p == 1)
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"((LW < NS ? LW + NS : 2 * NS) * P::WL + (LX - 1) * P::NI) : "memory");
+        else
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STEADY) : "memory");
+      }
+      u4 b[MT][NF];
+      const unsigned char* src = xbuf + (p & (LX - 1)) * P::BYTES;
+#pragma unroll
+      for (int t = 0; t < MT; t++)
+#pragma unroll
+        for (int u = 0; u < NF; u++) b[t][u] = *(const u4*)(src + t * (P::NI1 * 1024) + roff[u]);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      request_x(p + LX);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      const int rec = (first + S * p);
+      if (tail != 0 && rec == a.n_rec - 1) {  // channels beyond K: whatever was read there counts as zero
+#pragma unroll
+        for (int u = 0; u < NF; u++) {
+          const uint32_t keep = rec * REC_K + (kq * NF + u) * 8 < a.K ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+          for (int t = 0; t < MT; t++) b[t][u] &= u4{keep, keep, keep, keep};
+        }
+      }
+      // into operand order
+#pragma unroll
+      for (int t = 0; t < MT; t++)
+#pragma unroll
+        for (int blk = 0; blk < NF * 8 / PB; blk++) {
+          uint32_t in[PB / 2], out[PB / 2];
+#pragma unroll
+          for (int e = 0; e < PB / 2; e++) in[e] = b[t][blk * (PB / 8) + e / 4][e % 4];
+          permute_unit<FMT>(in, out);
+#pragma unroll
+          for (int e = 0; e < PB / 2; e++) b[t][blk * (PB / 8) + e / 4][e % 4] = out[e];
+        }
+      const int side_shift = 8 * Fmt<FMT>::SIDE * (rec & (SG - 1));
+#pragma unroll
+      for (int i = 0; i < NS; i++) {
+        request_w(p + (i + LW) / NS, (i + LW) % NS, ring[(u0 + i + LW) % RS]);
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t o[4 * NF];
+        restore_rec<FMT>(ring[u0 + i], side_shift, o);
+#pragma unroll
+        for (int u = 0; u < NF; u++) {
+          const h8 w = __builtin_bit_cast(h8, u4{o[4 * u], o[4 * u + 1], o[4 * u + 2], o[4 * u + 3]});
+#pragma unroll
+          for (int t = 0; t < MT; t++) acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w, __builtin_bit_cast(h8, b[t][u]), acc[i][t], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    using std::integral_constant;
+#pragma unroll
+    for (int q = 0; q < LX; q++) request_x(q);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < LW; q++) {
+      request_w(q / NS, q % NS, ring[q]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    int p = 0;
+    for (; p + U <= cnt; p += U) {
+      step(p, integral_constant<int, 0>{});
+      if constexpr (U > 1) step(p + 1, integral_constant<int, 1>{});
+      if constexpr (U > 2) step(p + 2, integral_constant<int, 2>{});
+      if constexpr (U > 3) step(p + 3, integral_constant<int, 3>{});
+    }
+    if constexpr (U > 1)
+      if (p < cnt) step(p, integral_constant<int, 0>{});
+    if constexpr (U > 2)
+      if (p + 1 < cnt) step(p + 1, integral_constant<int, 1>{});
+    if constexpr (U > 3)
+      if (p + 2 < cnt) step(p + 2, integral_constant<int, 2>{});
+    // The waits above count on every request: none may be left out as unused.
+#pragma unroll
+    for (int q = 0; q < RS; q++) {
+      asm volatile("" ::"v"(ring[q].w[0]));
+      if constexpr (Fmt<FMT>::SIDE != 0) asm volatile("" ::"v"(ring[q].t));
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the requests past the end are done with LDS
+  }
+  __syncthreads();
+  // Partial tiles [wave][strip][activation row][16 channels, padded], then the scales, then who was last.
+  float* const parts = (float*)smem;
+  float* const scales = parts + S * NS * R * P::ROW;
+  int* const last = (int*)(scales + NS * 16);
+  {
+    const int m_lo = lane & 15, kq = lane >> 4;
+    if (m_lo < RB)
+#pragma unroll
+      for (int i = 0; i < NS; i++)
+#pragma unroll
+        for (int t = 0; t < MT; t++) *(f4*)(parts + ((wave * NS + i) * R + 16 * t + m_lo) * P::ROW + 4 * kq) = acc[i][t];
+  }
+  if (tid < NS * 16) scales[tid] = (float)__builtin_bit_cast(_Float16, scale_bits) * kTwo14;
+  __syncthreads();
+  // One output per thread, the wavefronts' sums added in wave order.
+  const int n = tid & 15;
+  auto finish = [&](int i, int m, float sum) {
+    const int row = (s_first + i) * 16 + n;
+    if (row < a.N) a.Y[(size_t)m * a.N + row] = __builtin_bit_cast(uint16_t, (_Float16)(sum * scales[i * 16 + n]));
+  };
+  auto tile_sum = [&](int i, int m) {
+    float sum = 0;
+#pragma unroll
+    for (int w = 0; w < S; w++) sum += parts[((w * NS + i) * R + m) * P::ROW + n];
+    return sum;
+  };
+  const int pairs = a.M * NS;
+  if (a.gk == 1) {
+    for (int r = tid >> 4; r < pairs; r += 4 * S) finish(r % NS, r / NS, tile_sum(r % NS, r / NS));
+    return;
+  }
+  // K is split over gk workgroups: the same exchange as in finish_strip, with the workgroup's barriers around the count
+  // (every wave's stores are acknowledged before any strip is counted in).
+  for (int r = tid >> 4; r < pairs; r += 4 * S) {
+    const int i = r % NS, m = r / NS;
+    if (i < ns) {
+      float* wt = (float*)a.ws_tiles + ((size_t)gk * a.n_strips + s_first + i) * (MT * 256) + m * 16 + n;
+      __hip_atomic_store(wt, tile_sum(i, m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid < ns) {
+    const unsigned before = __hip_atomic_fetch_add(a.ws_count + s_first + tid, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool is_last = before == (unsigned)a.gk - 1;
+    if (is_last) __hip_atomic_store(a.ws_count + s_first + tid, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last[tid] = is_last;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  for (int r = tid >> 4; r < pairs; r += 4 * S) {
+    const int i = r % NS, m = r / NS;
+    if (i < ns && last[i]) {
+      float sum = 0;
+      for (int q = 0; q < a.gk; q++)
+        sum += __hip_atomic_load((const float*)a.ws_tiles + ((size_t)q * a.n_strips + s_first + i) * (MT * 256) + m * 16 + n, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+      finish(i, m, sum);
+    }
+  }
+}
+
+template <int R>
+const void* by_strips(int strips) {
+  constexpr int F = AMS_SLICE_FMT;
+  switch (strips) {
+    case 1: return (const void*)slice_kernel<F, R, 1>;
+    case 2: return (const void*)slice_kernel<F, R, 2>;
+    case 3: return (const void*)slice_kernel<F, R, 3>;
+    case 4: return (const void*)slice_kernel<F, R, 4>;
+    case 5: return (const void*)slice_kernel<F, R, 5>;
+    case 6: return (const void*)slice_kernel<F, R, 6>;
+    case 7: return (const void*)slice_kernel<F, R, 7>;
+    case 8: return (const void*)slice_kernel<F, R, 8>;
+  }
+  return nullptr;
+}
+
+}  // namespace
+
+template <>
+const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT>(int rows, int strips) {
+  switch (rows) {
+    case 4: return by_strips<4>(strips);
+    case 8: return by_strips<8>(strips);
+    case 16: return by_strips<16>(strips);
+    case 32: return by_strips<32>(strips);
+  }
+  return nullptr;
+}

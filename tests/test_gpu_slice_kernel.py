@@ -1,0 +1,103 @@
+"""The kernel that streams the activations beside the weights (plans with walk=records): every number of
+strips per workgroup, every count of staged rows, wavefronts with no, one and many records, channels
+beyond K inside the last record, ragged last strips and workgroups, and K split over workgroups; sampled
+rows against the oracle.  One activation row of infinities must leave the others alone."""
+
+import numpy as np
+import pytest
+
+import paper_2510_16045_amd as ams
+from oracle import ams_oracle as O
+from paper_2510_16045_amd import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+PAIRS = [(ams.FP533, O.FP533), (ams.FP425, O.FP425), (ams.FP45, O.FP45), (ams.FP433, O.FP433), (ams.FP6, O.FP6_E2M3), (ams.FP5, O.FP5_E2M2), (ams.FP4, O.FP4_E2M1)]
+REC_K = {ams.FP533: 96, ams.FP425: 128, ams.FP45: 128, ams.FP433: 96, ams.FP6: 96, ams.FP5: 128, ams.FP4: 128}
+
+
+def dev(a):
+    return torch.from_numpy(a.view(np.int16)).cuda().view(torch.float16) if a.dtype == np.float16 else torch.from_numpy(a).cuda()
+
+
+def problem(fmt, ofmt, N, K, seed):
+    rng = np.random.default_rng(seed)
+    codes = rng.integers(0, 1 << ofmt.code_bits, size=(N, K), dtype=np.uint8)
+    codes = (codes & 0xFE) | np.repeat(codes[:, :: ofmt.group] & 1, ofmt.group, axis=1)[:, :K]
+    scales = rng.uniform(0.001, 0.01, size=N).astype(np.float16)
+    n_strips = -(-N // 16)
+    strips = np.unique(np.r_[0, 1, n_strips - 2, n_strips - 1, np.arange(3, n_strips, max(1, n_strips // 9))])
+    strips = strips[(strips >= 0) & (strips < n_strips)]
+    rows = np.concatenate([np.arange(16 * t, min(N, 16 * t + 16)) for t in strips])
+    return codes, scales, rows
+
+
+def check(y, ref, rows, what, keep=slice(None)):
+    # fp32 sums rounded to fp16 once: at most 2^-11 per output, 1e-3 as in the other parity tests
+    y = y.cpu().view(torch.int16).numpy().view(np.float16).astype(np.float64)[:, rows][keep]
+    assert np.all(np.isfinite(y)), what
+    assert np.linalg.norm(y - ref[keep]) <= 1e-3 * np.linalg.norm(ref[keep]), what
+
+
+@pytest.mark.parametrize("fmt,ofmt", PAIRS)
+@pytest.mark.parametrize("spw", range(1, 9))
+def test_strips_rows_and_records(fmt, ofmt, spw):
+    # N: spw strips per workgroup, the last workgroup short and its last strip ragged
+    N = 16 * (256 * (spw - 1) + 130) - 5 if spw > 1 else 16 * 130 - 5
+    rec = REC_K[fmt]
+    # records per strip: 1, 3 (some wavefronts have none), 8, 17, and one more record that ends after 8 channels
+    for n_rec, Ms in ((1, (1, 32)), (3, (3, 17)), (8, (4, 9)), (17, (1, 8, 16, 32)), (34, (2, 5))):
+        K = rec * (n_rec - 1) + (8 if n_rec in (3, 34) else rec - 8 if n_rec == 17 else rec)
+        codes, scales, rows = problem(fmt, ofmt, N, K, 100 * spw + n_rec)
+        wp, sc = dev(ams.ams_pack_codes(fmt, codes)), dev(scales)
+        for M in Ms:
+            plan = ams.ams_linear_plan(fmt, M, N, K)
+            X = synth.activations(M, K, 70 + M)
+            ref = O.linear(codes[rows], scales[rows], X, ofmt)
+            what = f"{ofmt.name} N={N} K={K} M={M}: {plan}"
+            x = dev(X)
+            check(ams.ams_linear(wp, sc, x, N, fmt), ref, rows, what)
+            if M > 2 and n_rec in (3, 17):
+                x[M // 2] = float("inf")
+                check(ams.ams_linear(wp, sc, x, N, fmt), ref, rows, "beside a row of infinities: " + what, [m for m in range(M) if m != M // 2])
+
+
+def test_plans_are_the_ones_meant():
+    for spw in range(1, 9):
+        N = 16 * (256 * (spw - 1) + 130) - 5 if spw > 1 else 16 * 130 - 5
+        for M in (3, 5, 9, 16):
+            for fmt in (ams.FP533, ams.FP425, ams.FP433):
+                plan = ams.ams_linear_plan(fmt, M, N, 17 * REC_K[fmt] - 8)
+                assert "walk=records" in plan and f"strips_per_wg={spw} " in plan, plan
+
+
+@pytest.mark.parametrize("fmt,ofmt", PAIRS)
+@pytest.mark.parametrize("N,K,Ms", [(2560, 9728, (4, 8, 16, 32)), (4091, 14336, (8, 32)), (5120, 12808, (5, 17))])
+def test_k_split_over_workgroups(fmt, ofmt, N, K, Ms):
+    codes, scales, rows = problem(fmt, ofmt, N, K, 7)
+    wp, sc = dev(ams.ams_pack_codes(fmt, codes)), dev(scales)
+    ws = torch.zeros(16 << 20, dtype=torch.uint8, device="cuda")
+    for M in Ms:
+        X = synth.activations(M, K, 80 + M)
+        ref = O.linear(codes[rows], scales[rows], X, ofmt)
+        x = dev(X)
+        plan = ams.ams_linear_plan(fmt, M, N, K, with_workspace=True)
+        what = f"{ofmt.name} N={N} K={K} M={M}: {plan}"
+        first = ams.ams_linear_ws(wp, sc, x, N, fmt, ws)
+        check(first, ref, rows, what)
+        for _ in range(3):  # the calls leave the workspace ready for the next one, and the result does not change
+            assert torch.equal(ams.ams_linear_ws(wp, sc, x, N, fmt, ws), first), what
+        assert torch.equal(ams.ams_linear_static_ws(wp, sc, x, N, fmt), first), what
+        assert not ws[: 4 * 16384].any(), what
+
+
+def test_two_slices_that_do_not_divide_the_records():
+    # 8192 x 28672 takes two strips per workgroup and no split; with few rows and long K the slices are uneven
+    fmt, ofmt, N, K, M = ams.FP533, O.FP533, 1030, 96 * 131 + 8, 32
+    assert "k_slices=1" not in ams.ams_linear_plan(fmt, M, N, K, with_workspace=True)
+    codes, scales, rows = problem(fmt, ofmt, N, K, 9)
+    ws = torch.zeros(16 << 20, dtype=torch.uint8, device="cuda")
+    X = synth.activations(M, K, 90)
+    y = ams.ams_linear_ws(dev(ams.ams_pack_codes(fmt, codes)), dev(scales), dev(X), N, fmt, ws)
+    check(y, O.linear(codes[rows], scales[rows], X, ofmt), rows, "uneven slices")
