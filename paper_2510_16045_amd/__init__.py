@@ -9,6 +9,7 @@ memory and streams.  There is no fallback: if the library has not been built
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import numpy as np
@@ -90,6 +91,7 @@ def ams_init() -> None:
     _check(load_library().ams_init(), "ams_init")
 
 
+@functools.lru_cache(maxsize=4096)  # a pure function of its arguments, asked on every call of the Linear
 def ams_packed_bytes(fmt: int, N: int, K: int) -> int:
     out = ctypes.c_size_t()
     _check(load_library().ams_packed_bytes(fmt, N, K, ctypes.byref(out)), "ams_packed_bytes")
@@ -148,9 +150,11 @@ def ams_unpack_host(fmt: int, packed: np.ndarray, N: int, K: int) -> np.ndarray:
 
 
 def _stream():
+    """The current stream of the current device.  Read as the raw handle: building torch's Stream object
+    took 2.8 us of the 8.4 us that a whole call of ams_linear took, the handle takes 0.3."""
     import torch
 
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev_ptr(t, dtype=None):

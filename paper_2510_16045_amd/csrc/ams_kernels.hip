@@ -21,7 +21,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
-#include <vector>
+#include <unordered_set>
 
 #include "ams_device.h"
 
@@ -1522,20 +1522,15 @@ int device_state(DeviceState** out = nullptr) {
 // Kernels that use more than 64 KiB of dynamic LDS must have their limit raised first;
 // that is a per-function, per-device property, remembered here so it is done once.
 bool raise_lds_limit(const void* kern) {
-  struct Entry {
-    const void* kern;
-    int dev;
-  };
   static std::mutex mu;
-  static std::vector<Entry> done;
+  static std::unordered_set<const void*> done[kMaxDevices];
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
   std::lock_guard<std::mutex> lock(mu);
-  for (const Entry& e : done)
-    if (e.kern == kern && e.dev == dev) return true;
+  if (done[dev].count(kern)) return true;
   if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMaxBytes) != hipSuccess) return false;
   try {
-    done.push_back({kern, dev});
+    done[dev].insert(kern);
   } catch (...) {  // out of host memory: the limit is raised, it is just not remembered
   }
   return true;
