@@ -1380,7 +1380,8 @@ ColumnPlan make_column_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int
 //     query promises sixteen wavefronts there, which slice_kernel's registers do not allow at M > 16;
 //   more than eight strips: halved (two workgroups fit on a compute unit at M <= 16) where that pays: with side groups
 //     from M = 3 on (57344 x 8192 FP4.25 M = 4 43.4 / 39.8, 128256 x 4096 46.3 / 43.7), without from M = 9
-//     (57344 x 8192 FP5.33 M = 16 59.0 / 52.6); above M = 8 only on long K (45000 x 4096 FP4.25 M = 16 21.1 / 23.3).
+//     (57344 x 8192 FP5.33 M = 16 59.0 / 52.6); above M = 4 only on long K (128256 x 4096 FP4.25 M = 8 49.6 / 50.2,
+//     45000 x 4096 M = 16 21.1 / 23.3).
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
   ColumnPlan p = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
   const int sg = ams::side_group(ams::kFormats[fmt]);
@@ -1389,7 +1390,7 @@ ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k,
   if (M <= 2 && p.spw == 2 && p.grid < kNumCU * 7 / 8 && (n_rec_all >= 128 || (sg == 1 && M == 1))) return p;
   if (sg == 1 && M > 16 && (p.spw == 7 || p.spw == 8)) return p;
   if (p.spw > kSliceMaxStrips) {
-    if (gk != 1 || M <= (sg == 1 ? 8 : 2) || (M > 8 && n_rec_all < 64)) return p;
+    if (gk != 1 || M <= (sg == 1 ? 8 : 2) || (M > 4 && n_rec_all < 64)) return p;
     p.spw = (p.spw + 1) / 2;
     p.grid = p.gn = (int)((n_strips + p.spw - 1) / p.spw);
   }
