@@ -16,6 +16,7 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u3 __attribute__((ext_vector_type(3)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 typedef unsigned short us4 __attribute__((ext_vector_type(4)));
 
@@ -337,7 +338,8 @@ constexpr int slice_lds(int fmt, int R, int NS) {
   return staged > tiles ? staged : tiles;
 }
 // The kernel for `rows` staged rows and `strips` strips per workgroup (nullptr: there is none).
-template <int FMT>
+// GS: one scale per run of input channels.
+template <int FMT, bool GS>
 const void* slice_kernel_of(int rows, int strips);
 
 }  // namespace ams_dev

@@ -1385,12 +1385,12 @@ ColumnPlan make_column_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
   ColumnPlan p = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
   const int sg = ams::side_group(ams::kFormats[fmt]);
-  if (!aligned_rows || !one_scale) return p;
+  if (!aligned_rows) return p;
   if (p.spw == 1 && p.lr == 3) return p;
-  if (M <= 2 && p.spw == 2 && p.grid < kNumCU * 7 / 8 && (n_rec_all >= 128 || (sg == 1 && M == 1))) return p;
-  if (sg == 1 && M > 16 && (p.spw == 7 || p.spw == 8)) return p;
+  if (M <= 2 && p.spw == 2 && p.grid < kNumCU * 7 / 8 && (n_rec_all >= 128 || (one_scale && sg == 1 && M == 1))) return p;
+  if (one_scale && sg == 1 && M > 16 && (p.spw == 7 || p.spw == 8)) return p;
   if (p.spw > kSliceMaxStrips) {
-    if (gk != 1 || M <= (sg == 1 ? 8 : 2) || (M > 4 && n_rec_all < 64)) return p;
+    if (gk != 1 || M <= (one_scale && sg == 1 ? 8 : 2) || (M > 4 && n_rec_all < 64)) return p;
     p.spw = (p.spw + 1) / 2;
     p.grid = p.gn = (int)((n_strips + p.spw - 1) / p.spw);
   }
@@ -1610,9 +1610,9 @@ int launch_multi(const LinearArgs& a, unsigned grid, int S, size_t lds, hipStrea
 
 // slice_kernel for a.M rows and `strips` strips per workgroup.
 template <int FMT>
-int launch_slice(const LinearArgs& a, int strips, unsigned grid, hipStream_t st) {
+int launch_slice(const LinearArgs& a, bool gs, int strips, unsigned grid, hipStream_t st) {
   const int r = slice_rows(a.M);
-  const void* kern = slice_kernel_of<FMT>(r, strips);
+  const void* kern = gs ? slice_kernel_of<FMT, true>(r, strips) : slice_kernel_of<FMT, false>(r, strips);
   if (!kern) return AMS_ERR_LAUNCH;
   const size_t lds = (size_t)slice_lds(FMT, r, strips);
   if (lds > 64 * 1024 && !raise_lds_limit(kern)) return AMS_ERR_LAUNCH;
@@ -1700,7 +1700,7 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
     a.x_shift = cp.x_shift;
     a.spw = cp.spw;
     a.rc = cp.rc;
-    if (cp.slice) return launch_slice<FMT>(a, cp.spw, cp.grid, st);
+    if (cp.slice) return launch_slice<FMT>(a, scale_group != 0, cp.spw, cp.grid, st);
     if (cp.ns > 1) return M <= 16 ? launch_multi<FMT, 1>(a, cp.grid, cp.S, cp.lds, st) : launch_multi<FMT, 2>(a, cp.grid, cp.S, cp.lds, st);
     return M <= 16 ? launch_column<FMT, 1>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st)
                    : launch_column<FMT, 2>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st);
@@ -1746,7 +1746,8 @@ int prepare_format() {
   bool ok = true;
   if constexpr (FMT != FMT_FP16) {
     for (a.M = 4; a.M <= 32; a.M *= 2)
-      for (int strips = 1; strips <= kSliceMaxStrips; strips++) ok &= launch_slice<FMT>(a, strips, 0, nullptr) == AMS_OK;
+      for (int strips = 1; strips <= kSliceMaxStrips; strips++)
+        for (int gs = 0; gs < 2; gs++) ok &= launch_slice<FMT>(a, gs != 0, strips, 0, nullptr) == AMS_OK;
     for (a.K = 8; a.K < 10; a.K++) {  // aligned and ragged rows of X
       for (int nt = 0; nt < 2; nt++)
         for (int gs = 0; gs < 2; gs++)

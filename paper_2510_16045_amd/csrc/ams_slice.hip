@@ -1,6 +1,6 @@
 // slice_kernel: the Linear with the activations streamed beside the weights (Sec. 3.3, Sec. 4.2), for
 // workgroups of up to eight strips of 16 output channels.  One format per translation unit
-// (AMS_SLICE_FMT), so that the formats compile in parallel.
+// (AMS_SLICE_FMT; AMS_SLICE_GS: with one scale per run of input channels), so that they compile in parallel.
 //
 // A workgroup owns NS neighbouring strips and its wavefronts share K: wavefront w takes records w, w + S, ... of all NS
 // strips.  The activations of a record are then needed by one wavefront only, so nothing is staged for the
@@ -30,33 +30,38 @@
 #ifndef AMS_SLICE_FMT
 #define AMS_SLICE_FMT 0
 #endif
+#ifndef AMS_SLICE_GS
+#define AMS_SLICE_GS 0
+#endif
 
 namespace {
 using namespace ams_dev;
 
-// CHUNK bytes per lane through a buffer descriptor, non-temporal.
-template <int CHUNK>
+// CHUNK bytes per lane through a buffer descriptor; NT = 2: non-temporal.
+template <int CHUNK, int NT = 2>
 __device__ __forceinline__ void buffer_load_chunk(uint32_t* w, __amdgpu_buffer_rsrc_t rsrc, int voffset, int soffset) {
-  constexpr int NT = 2;
   if constexpr (CHUNK == 16) {
     const u4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voffset, soffset, NT);
     w[0] = v[0], w[1] = v[1], w[2] = v[2], w[3] = v[3];
   } else if constexpr (CHUNK == 12) {
     const u3 v = __builtin_amdgcn_raw_buffer_load_b96(rsrc, voffset, soffset, NT);
     w[0] = v[0], w[1] = v[1], w[2] = v[2];
+  } else if constexpr (CHUNK == 8) {
+    const u2 v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, voffset, soffset, NT);
+    w[0] = v[0], w[1] = v[1];
   } else {
     w[0] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voffset, soffset, NT);
   }
 }
 
 // Shape of the kernel for R staged activation rows (4, 8, 16 or 32) and NS strips per workgroup.
-template <int FMT, int R, int NS>
+template <int FMT, int R, int NS, bool GS>
 struct Slice {
   static constexpr int MT = R > 16 ? 2 : 1;
   static constexpr int RB = R > 16 ? 16 : R;                    // rows of one MFMA tile that are staged
   static constexpr int NI = slice_x_loads(FMT, R), NI1 = NI / MT;  // 1 KiB loads of a record's activations, of one tile's
   static constexpr int BYTES = NI * 1024;
-  static constexpr int WL = Fmt<FMT>::SIDE ? 2 : 1;             // load instructions of one weight record
+  static constexpr int WL = (Fmt<FMT>::SIDE ? 2 : 1) + GS;      // load instructions of one weight record (and its scales)
   static constexpr int S = slice_waves(FMT, R, NS);
   static constexpr int LX = kSliceXAhead;
   static constexpr int LW = slice_ahead(S);
@@ -65,9 +70,12 @@ struct Slice {
   static constexpr int ROW = slice_tile_row(S, R, NS);
 };
 
-template <int FMT, int R, int NS>
-__global__ void __launch_bounds__(64 * (Slice<FMT, R, NS>::S)) slice_kernel(LinearArgs a) {
-  using P = Slice<FMT, R, NS>;
+// GS: one scale per run of 2^a.sg_shift records.  A record goes through a fresh tile, times its run's scales, into the
+// sum; the four scales of a lane's output channels are one 8-byte load that travels with the record.  28672 x 4096
+// FP4.25, a scale per 128: M = 1 15.7 -> 12.8 us, M = 4 15.9 -> 13.5, M = 32 23.5 -> 20.2 (column_kernel before).
+template <int FMT, int R, int NS, bool GS>
+__global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(LinearArgs a) {
+  using P = Slice<FMT, R, NS, GS>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int REC_K = Fmt<FMT>::REC_K, SG = Fmt<FMT>::SG, NF = Fmt<FMT>::N_MFMA, PB = Fmt<FMT>::PB, UNIT = Fmt<FMT>::UNIT;
   constexpr int MT = P::MT, RB = P::RB, LX = P::LX, LW = P::LW, RS = P::RS, U = P::U, S = P::S;
@@ -83,8 +91,8 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS>::S)) slice_kernel(Line
   const int rec_hi = a.gk > 1 ? (int)((unsigned)((gk + 1) * a.n_rec) / (unsigned)a.gk) : a.n_rec;
   const int first = rec_lo + wave;  // this wave's records: first, first + S, ...
   const int cnt = first < rec_hi ? (rec_hi - first + S - 1) / S : 0;
-  uint16_t scale_bits = 0;
-  if (tid < NS * 16) scale_bits = a.scales[min(s_first * 16 + tid, a.N - 1)];
+  uint16_t scale_bits = 0x3C00;
+  if (!GS && tid < NS * 16) scale_bits = a.scales[min(s_first * 16 + tid, a.N - 1)];
   __builtin_amdgcn_sched_barrier(0);
 
   f4 acc[NS][MT];
@@ -130,8 +138,12 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS>::S)) slice_kernel(Line
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(dst + (t * P::NI1 + i) * 1024), 16, vo, soff, 0, 0);
         }
     };
+    struct Scales {
+      uint32_t h[2];  // four halfs
+    };
     LaneRec<FMT> ring[RS];
-    auto request_w = [&](int p, int i, LaneRec<FMT>& slot) {  // the weights of strip i for the wave's p-th record
+    Scales ring_sc[GS ? RS : 1];
+    auto request_w = [&](int p, int i, LaneRec<FMT>& slot, Scales& sc) {  // the weights of strip i for the wave's p-th record
       const unsigned rec = p < cnt ? (first + S * p) : 0;
       const uint8_t* unit = a.W + ((size_t)(rec / SG) * (unsigned)a.n_strips + (unsigned)(s_first + min(i, ns - 1))) * UNIT;
       const __amdgpu_buffer_rsrc_t w = __builtin_amdgcn_make_buffer_rsrc((void*)unit, 0, UNIT, 0x00020000);
@@ -140,6 +152,12 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS>::S)) slice_kernel(Line
       if constexpr (Fmt<FMT>::SIDE != 0) {
         const int vs = p < cnt ? lane * 4 : FAR;
         buffer_load_chunk<4>(&slot.t, w, vs, SG * Fmt<FMT>::CB);
+      }
+      if constexpr (GS) {  // cached: a run spans many records and rows of lanes
+        const uint16_t* run = a.scales + ((size_t)(s_first + min(i, ns - 1)) * a.n_sg + (rec >> a.sg_shift)) * 16;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)run, 0, 32, 0x00020000);
+        const int vg = p < cnt ? kq * 8 : FAR;
+        buffer_load_chunk<8, 0>(sc.h, rs, vg, 0);
       }
     };
     const int tail = a.n_rec * REC_K - a.K;  // channels of the last record beyond K
@@ -194,15 +212,31 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS>::S)) slice_kernel(Line
       const int side_shift = 8 * Fmt<FMT>::SIDE * (rec & (SG - 1));
 #pragma unroll
       for (int i = 0; i < NS; i++) {
-        request_w(p + (i + LW) / NS, (i + LW) % NS, ring[(u0 + i + LW) % RS]);
+        request_w(p + (i + LW) / NS, (i + LW) % NS, ring[(u0 + i + LW) % RS], ring_sc[GS ? (u0 + i + LW) % RS : 0]);
         __builtin_amdgcn_sched_barrier(0);
         uint32_t o[4 * NF];
         restore_rec<FMT>(ring[u0 + i], side_shift, o);
+        f4 own[MT];  // GS: this record's tile
+        if constexpr (GS) {
+#pragma unroll
+          for (int t = 0; t < MT; t++) own[t] = f4{0, 0, 0, 0};
+        }
 #pragma unroll
         for (int u = 0; u < NF; u++) {
           const h8 w = __builtin_bit_cast(h8, u4{o[4 * u], o[4 * u + 1], o[4 * u + 2], o[4 * u + 3]});
 #pragma unroll
-          for (int t = 0; t < MT; t++) acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w, __builtin_bit_cast(h8, b[t][u]), acc[i][t], 0, 0, 0);
+          for (int t = 0; t < MT; t++) {
+            f4& c = GS ? own[t] : acc[i][t];
+            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(w, __builtin_bit_cast(h8, b[t][u]), c, 0, 0, 0);
+          }
+        }
+        if constexpr (GS) {
+          const Scales h = ring_sc[u0 + i];
+          f4 sc;
+#pragma unroll
+          for (int r = 0; r < 4; r++) sc[r] = (float)__builtin_bit_cast(_Float16, (uint16_t)(h.h[r >> 1] >> (16 * (r & 1))));
+#pragma unroll
+          for (int t = 0; t < MT; t++) acc[i][t] += own[t] * sc;
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -214,7 +248,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS>::S)) slice_kernel(Line
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int q = 0; q < LW; q++) {
-      request_w(q / NS, q % NS, ring[q]);
+      request_w(q / NS, q % NS, ring[q], ring_sc[GS ? q : 0]);
       __builtin_amdgcn_sched_barrier(0);
     }
     int p = 0;
@@ -235,6 +269,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS>::S)) slice_kernel(Line
     for (int q = 0; q < RS; q++) {
       asm volatile("" ::"v"(ring[q].w[0]));
       if constexpr (Fmt<FMT>::SIDE != 0) asm volatile("" ::"v"(ring[q].t));
+      if constexpr (GS) asm volatile("" ::"v"(ring_sc[q].h[0]));
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the requests past the end are done with LDS
   }
@@ -305,14 +340,14 @@ template <int R>
 const void* by_strips(int strips) {
   constexpr int F = AMS_SLICE_FMT;
   switch (strips) {
-    case 1: return (const void*)slice_kernel<F, R, 1>;
-    case 2: return (const void*)slice_kernel<F, R, 2>;
-    case 3: return (const void*)slice_kernel<F, R, 3>;
-    case 4: return (const void*)slice_kernel<F, R, 4>;
-    case 5: return (const void*)slice_kernel<F, R, 5>;
-    case 6: return (const void*)slice_kernel<F, R, 6>;
-    case 7: return (const void*)slice_kernel<F, R, 7>;
-    case 8: return (const void*)slice_kernel<F, R, 8>;
+    case 1: return (const void*)slice_kernel<F, R, 1, AMS_SLICE_GS != 0>;
+    case 2: return (const void*)slice_kernel<F, R, 2, AMS_SLICE_GS != 0>;
+    case 3: return (const void*)slice_kernel<F, R, 3, AMS_SLICE_GS != 0>;
+    case 4: return (const void*)slice_kernel<F, R, 4, AMS_SLICE_GS != 0>;
+    case 5: return (const void*)slice_kernel<F, R, 5, AMS_SLICE_GS != 0>;
+    case 6: return (const void*)slice_kernel<F, R, 6, AMS_SLICE_GS != 0>;
+    case 7: return (const void*)slice_kernel<F, R, 7, AMS_SLICE_GS != 0>;
+    case 8: return (const void*)slice_kernel<F, R, 8, AMS_SLICE_GS != 0>;
   }
   return nullptr;
 }
@@ -320,7 +355,7 @@ const void* by_strips(int strips) {
 }  // namespace
 
 template <>
-const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT>(int rows, int strips) {
+const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, AMS_SLICE_GS != 0>(int rows, int strips) {
   switch (rows) {
     case 4: return by_strips<4>(strips);
     case 8: return by_strips<8>(strips);

@@ -101,3 +101,27 @@ def test_two_slices_that_do_not_divide_the_records():
     X = synth.activations(M, K, 90)
     y = ams.ams_linear_ws(dev(ams.ams_pack_codes(fmt, codes)), dev(scales), dev(X), N, fmt, ws)
     check(y, O.linear(codes[rows], scales[rows], X, ofmt), rows, "uneven slices")
+
+
+@pytest.mark.parametrize("fmt,ofmt", PAIRS)
+@pytest.mark.parametrize("spw", [1, 2, 3, 5, 7, 8])
+def test_one_scale_per_run(fmt, ofmt, spw):
+    # runs of one, two and four records, a short last run, ragged last strips and workgroups, all staged row counts
+    N = 16 * (256 * (spw - 1) + 130) - 5 if spw > 1 else 16 * 130 - 5
+    rec = REC_K[fmt]
+    for n_rec, mult, Ms in ((2, 1, (1, 32)), (17, 1, (4, 16, 32)), (18, 2, (3, 8)), (35, 4, (1, 17))):
+        K, sg = rec * (n_rec - 1) + 8 * (n_rec % 3 + 1), rec * mult
+        codes, _, rows = problem(fmt, ofmt, N, K, 100 * spw + n_rec)
+        runs, n_strips = -(-K // sg), -(-N // 16)
+        scales = np.random.default_rng(n_rec).uniform(0.001, 0.01, size=(n_strips * 16, runs)).astype(np.float16)
+        packed = np.ascontiguousarray(scales.reshape(n_strips, 16, runs).transpose(0, 2, 1))  # [strip][run][row in strip]
+        wp, sc = dev(ams.ams_pack_codes(fmt, codes)), dev(packed)
+        for M in Ms:
+            X = synth.activations(M, K, 60 + M)
+            ref = O.linear(codes[rows], scales[rows], X, ofmt, sg)
+            what = f"{ofmt.name} N={N} K={K} M={M} run={sg}"
+            x = dev(X)
+            check(ams.ams_linear_grouped(wp, sc, sg, x, N, fmt), ref, rows, what)
+            if M > 2:
+                x[M // 2] = float("inf")
+                check(ams.ams_linear_grouped(wp, sc, sg, x, N, fmt), ref, rows, "beside a row of infinities: " + what, [m for m in range(M) if m != M // 2])
