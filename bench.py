@@ -244,6 +244,13 @@ def profile_kernel(args, shapes, torch, ams, synth):
     print(json.dumps({"profiled": args.profile_kernel, "launches": args.steps}))
 
 
+def dominant_kernel(ams, layer, fmt_name, M):
+    """The kernel the library's plan gives this Linear."""
+    fmt = next(f for f, name in FMT_NAMES.items() if name == fmt_name)
+    plan = ams.ams_linear_plan(fmt, M, layer.N, layer.K)
+    return "slice_kernel" if "walk=records" in plan else "multi_kernel" if "strips_per_wave=2" in plan else "column_kernel"
+
+
 def measured_traffic(ams, layer, fmt_name, M):
     """HBM bytes per launch from the tracked counter summaries (profiles/*hbm_traffic*.md carry one line
     `traffic-json: {...}` each), or None when there is none for this launch or it was measured with another
@@ -415,7 +422,7 @@ def main():
     t_dom = time_launches(torch, lambda i: linear(dl.packed[dfmt][i % len(dl.packed[dfmt])], dl.scales[dfmt], xs[dl.name], dl.N, dfmt, ys[dl.name]), n_launch, replays=20)
     achieved = alg_bytes / t_dom / 1e3
     roofline = {
-        "bound": "hbm", "kernel": f"column_kernel<{dom['fmt']}> {dl.N}x{dl.K} M={M}",
+        "bound": "hbm", "kernel": f"{dominant_kernel(ams, dl, dom['fmt'], M)}<{dom['fmt']}> {dl.N}x{dl.K} M={M}",
         "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
         "us_per_launch": round(t_dom, 3), "algorithmic_bytes": alg_bytes,
         "traffic": measured_traffic(ams, dl.name, dom["fmt"], M) if args.layers == "8b" else None,
