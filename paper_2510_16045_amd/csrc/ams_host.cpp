@@ -48,11 +48,18 @@ inline uint16_t double_to_half_bits(double a) {
 }
 
 // ---- Sec. 2.2: magnitude of a magnitude code, bias 1 ----------------------
-inline double magnitude(int mag_code, int mbits) {
-  int e = mag_code >> mbits, m = mag_code & ((1 << mbits) - 1);
-  if (e == 0) return std::ldexp((double)m, -mbits);
-  return std::ldexp((double)((1 << mbits) + m), e - 1 - mbits);
-}
+struct Magnitudes {
+  double v[4][32];  // [mantissa bits][code]
+  Magnitudes() {
+    for (int mbits = 0; mbits < 4; mbits++)
+      for (int c = 0; c < 32; c++) {
+        const int e = c >> mbits, m = c & ((1 << mbits) - 1);
+        v[mbits][c] = e == 0 ? std::ldexp((double)m, -mbits) : std::ldexp((double)((1 << mbits) + m), e - 1 - mbits);
+      }
+  }
+};
+const Magnitudes g_magnitudes;
+inline double magnitude(int mag_code, int mbits) { return g_magnitudes.v[mbits][mag_code]; }
 
 // Round half to even of 0 <= x < 2^51: adding 1.5 * 2^52 leaves no bits below the units.
 inline double round_even(double x) { return (x + 0x1.8p52) - 0x1.8p52; }
@@ -180,8 +187,9 @@ bool quantize_row(const RowQuant& q, const uint16_t* w, int64_t K, uint8_t* code
   *scale_out = sb;
   const double s = half_to_double(sb);
   const int sign_shift = 2 + q.mbits;
-  // Looking codes up pays from about 500 weights per scale on (building the intervals takes about as long as 300 weights)
-  const bool lookup = K >= 512;
+  // Looking codes up pays from about 200 weights per scale on (finding the intervals takes as long as evaluating that
+  // many): 3971 x 400 FP5.33 3.3 -> 2.0 ms on 8 threads, 8000 x 200 3.5 -> 3.3, 16384 x 128 4.8 -> 5.9.
+  const bool lookup = K >= 192;
   if (lookup) steps.build(q, s, absmax);
   auto finish = [&](int64_t k, int mag_code) {
     const uint16_t wk = w[k];
