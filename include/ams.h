@@ -217,14 +217,13 @@ int ams_fp16_linear(const uint16_t* W, const uint16_t* X, uint16_t* Y, int M, in
  */
 int ams_linear_workspace_bytes(int fmt, int M, int64_t N, int64_t K, size_t* bytes);
 /* Which kernel and launch shape ams_linear (with_workspace = 0) or ams_linear_ws (1) would use for
- * this problem (fmt = -1: the fp16 baseline), as a short text for logs and tests: "column ..." (the
+ * this problem (fmt = -1: the fp16 baseline), as a short text for logs and tests: "slice ..." or "column ..." (the
  * packed formats), "gemv ..." (the baseline at batches up to 4 whose activations fit in LDS), "sweep ..."
  * or "stream ..." (the baseline otherwise), followed by key=value pairs (workgroups, strips per
- * workgroup, slices of K, wavefronts, wavefronts per strip or strips per wavefront, phases of K, LDS
- * bytes, records ahead).  A packed plan that ends in "walk=records" streams the activations beside the weights:
- * every wavefront takes its records of K from all strips of the workgroup; waves_per_strip is then wavefronts /
- * strips, phases how many times over the activations of a slice of K would fill the LDS, ahead counts
- * (record, strip) pairs, side_groups=1 says that the wavefronts' records of one step are whole side groups.
+ * workgroup, slices of K, wavefronts, LDS bytes; of the kernels that have them: wavefronts per strip or strips per
+ * wavefront, phases of K, whether side groups are dealt whole, records ahead).  In a "slice" plan every wavefront takes
+ * its records of K from all strips of the workgroup, so it has no wavefronts per strip, phases or side groups, and
+ * `ahead` counts (record, strip) pairs.
  * Host only, launches nothing. */
 int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, char* text, size_t text_len);
 int ams_linear_ws(const void* W_packed, const uint16_t* scales, const uint16_t* X, uint16_t* Y, int M, int64_t N,

@@ -1273,7 +1273,7 @@ struct ColumnPlan {
   int wpa;  // wavefronts of a strip that take records (= wps unless fewer divide the side groups evenly)
   int lr;   // records a wavefront keeps in flight beside the one it restores
   int ns;   // strips a wavefront owns alone (multi_kernel; 1: column_kernel); then wpa = wavefronts that own strips
-  bool slice;  // slice_kernel: the wavefronts share K and take every record of all spw strips
+  bool slice;  // slice_kernel: the wavefronts share K and take every record of all spw strips; S, spw, grid, gn, gk, lr and lds hold
   size_t lds;
 };
 
@@ -1396,16 +1396,8 @@ ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k,
   }
   const int r = slice_rows(M);
   p.slice = true;
-  p.ns = 1;
   p.S = slice_waves(fmt, r, p.spw);
   p.lr = slice_ahead(p.S);
-  p.wps = p.S / p.spw;
-  p.wpa = p.wps;
-  const int n_rec = (n_rec_all + gk - 1) / gk;
-  p.qd = sg > 1 && gk == 1;  // the wavefronts of a workgroup take S consecutive records together, whole side groups
-  // how many times over the staged activations of a slice of K would fill the LDS
-  p.n_phase = (int)(((int64_t)n_rec * slice_x_loads(fmt, r) * 1024 + kLdsMaxBytes - 1) / kLdsMaxBytes);
-  p.rc = n_rec;
   p.lds = (size_t)slice_lds(fmt, r, p.spw);
   return p;
 }
@@ -1915,8 +1907,11 @@ int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, ch
   if (f != FMT_FP16) {
     const bool nt = n_strips * n_rec * (int64_t)rec_bytes >= (2ll << 20);  // as run_linear decides it
     const ColumnPlan cp = make_plan(f, M, n_strips, n_rec, rec_k, gk, K % 8 == 0, true, nt);
-    snprintf(text, text_len, "column grid=%d strips_per_wg=%d k_slices=%d waves=%d waves_per_strip=%d phases=%d lds=%zu side_groups=%d active_per_strip=%d ahead=%d strips_per_wave=%d%s", cp.grid,
-             cp.spw, cp.gk, cp.S, cp.wps, cp.n_phase, cp.lds, cp.qd ? 1 : 0, cp.ns > 1 ? 1 : cp.wpa, cp.lr, cp.ns, cp.slice ? " walk=records" : "");
+    if (cp.slice)
+      snprintf(text, text_len, "slice grid=%d strips_per_wg=%d k_slices=%d waves=%d lds=%zu ahead=%d", cp.grid, cp.spw, cp.gk, cp.S, cp.lds, cp.lr);
+    else
+      snprintf(text, text_len, "column grid=%d strips_per_wg=%d k_slices=%d waves=%d waves_per_strip=%d phases=%d lds=%zu side_groups=%d active_per_strip=%d ahead=%d strips_per_wave=%d", cp.grid,
+               cp.spw, cp.gk, cp.S, cp.wps, cp.n_phase, cp.lds, cp.qd ? 1 : 0, cp.ns > 1 ? 1 : cp.wpa, cp.lr, cp.ns);
     return AMS_OK;
   }
   if (const GemvPlan gp = make_gemv_plan(M, K, gk); gp.ok) {

@@ -132,16 +132,19 @@ def test_extreme_aspect_ratios(N, K, Ms):
     check_shape_against_oracle(N, K, W, Ms, 4999, with_workspace=N < 100, with_static=N < 100)
 
 
-@pytest.mark.parametrize("N,K,Ms,ws", [(30000, 16384, (8, 32), True), (14336, 4096, (1, 2, 3), False)])
+@pytest.mark.parametrize("N,K,Ms,ws", [(30000, 16384, (8, 32), True), (14336, 4096, (1, 2, 3), False), (14336, 4099, (1, 2), False)])
 def test_lone_wavefronts_and_eight_wavefront_plans(N, K, Ms, ws):
     # 30000 x 16384 with a workspace: K in two slices and fifteen strips per workgroup, every wavefront alone on its
     # strip, so the partial tiles go to the workspace straight from the accumulators (the last workgroup is ragged);
-    # 14336 x 4096: four strips per workgroup, eight wavefronts with three records ahead, two on each strip
+    # 14336 x 4099: four strips per workgroup, eight wavefronts with three records ahead, two on each strip (14336 x
+    # 4096: the same four strips on slice_kernel)
     if ws:
         assert "k_slices=2" in ams.ams_linear_plan(ams.FP533, Ms[0], N, K, with_workspace=True)
         assert "waves_per_strip=1 " in ams.ams_linear_plan(ams.FP533, Ms[0], N, K, with_workspace=True)
     else:
-        assert "waves=8 waves_per_strip=2 " in ams.ams_linear_plan(ams.FP533, Ms[0], N, K)
+        for M in Ms:
+            plan = ams.ams_linear_plan(ams.FP533, M, N, K)
+            assert "strips_per_wg=4 " in plan and (plan.startswith("slice ") if K == 4096 else "waves=8 waves_per_strip=2 " in plan), plan
     W = synth.gaussian_weights(N, K, 760 + (N % 5))
     check_shape_against_oracle(N, K, W, Ms, 97, with_workspace=ws, with_static=ws)
 
@@ -160,12 +163,13 @@ def test_wavefronts_with_two_strips_each(N, K, Ms):
 
 
 @pytest.mark.parametrize("fmt,ofmt", [(ams.FP5, O.FP5_E2M2), (ams.FP4, O.FP4_E2M1)])
-@pytest.mark.parametrize("N,K,Ms", [(45000, 4096, (1, 8)), (28672, 4096, (1, 4))])
+@pytest.mark.parametrize("N,K,Ms", [(45000, 4096, (1, 8)), (28672, 4096, (1, 4)), (28672, 4099, (1, 4))])
 def test_other_formats_without_side_groups_on_the_eight_wavefront_plans(fmt, ofmt, N, K, Ms):
     # FP5 (four side bytes per lane and record, no side groups) and FP4 take the same plans as FP5.33: two strips per
-    # wavefront on 45000 rows, one wavefront alone on each of seven strips on 28672
-    want = "strips_per_wave=2" if N == 45000 else "waves=8 waves_per_strip=1 "
-    assert want in ams.ams_linear_plan(fmt, Ms[0], N, K)
+    # wavefront on 45000 rows, one wavefront alone on each of seven strips on 28672 (slice_kernel where rows are aligned)
+    want = "strips_per_wave=2" if N == 45000 else "slice " if K == 4096 else "waves=8 waves_per_strip=1 "
+    for M in Ms:
+        assert want in ams.ams_linear_plan(fmt, M, N, K)
     W = synth.gaussian_weights(N, K, 780)
     packed, scales = ams.ams_pack(fmt, W)
     n_strips = -(-N // 16)
@@ -196,7 +200,7 @@ def test_random_shapes_with_many_strips_per_workgroup():
         plan = ams.ams_linear_plan(fmt, M, N, K)
         print(f"case {case}: {ofmt.name} N={N} K={K} M={M}: {plan}", flush=True)
         kv = dict(x.split("=") for x in plan.split()[1:])
-        seen.add((kv["waves"], kv["strips_per_wave"], kv["waves_per_strip"]))
+        seen.add("slice" if plan.startswith("slice ") else (kv["waves"], kv["strips_per_wave"], kv["waves_per_strip"]))
         W = synth.gaussian_weights(N, K, 800 + case)
         packed, scales = ams.ams_pack(fmt, W)
         n_strips = -(-N // 16)

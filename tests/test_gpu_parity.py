@@ -246,9 +246,12 @@ def test_linear_large_shapes_sampled_rows(fmt, ofmt, N, K, Ms):
 @pytest.mark.parametrize(
     "N,K,Ms",
     [
-        (200, 6000, (16, 17, 32)),  # one strip per workgroup, many phases
+        (200, 6000, (16, 17, 32)),  # one strip per workgroup; slice_kernel
+        (200, 6003, (16, 17, 32)),  # the same in column_kernel: many phases
         (90, 6004, (32,)),  # activation rows not 16-byte aligned
-        (4400, 3000, (24, 32)),  # two strips per workgroup, the last workgroup has one
+        (4400, 3000, (24, 32)),  # two strips per workgroup, the last workgroup has one; slice_kernel
+        (4400, 3001, (24, 32)),  # the same in column_kernel
+        (33000, 5120, (16, 32)),  # nine strips per workgroup, aligned rows: column_kernel, with side groups dealt whole where there are any
     ],
 )
 def test_linear_activations_in_several_phases(fmt, ofmt, N, K, Ms):
@@ -257,10 +260,15 @@ def test_linear_activations_in_several_phases(fmt, ofmt, N, K, Ms):
     W = synth.gaussian_weights(N, K, 91)
     packed, scales = ams.ams_pack(fmt, W)
     wp, sc = dev(packed), dev(scales)
-    rows = np.unique(np.r_[0:32, N - 32 : N, np.arange(5, N, 37)])
+    rows = np.unique(np.r_[0:32, N - 32 : N, np.arange(5, N, max(37, N // 200))])
     codes, o_scales, _ = O.ams_quantize(W[rows], ofmt)
     for M in Ms:
-        assert "phases=1 " not in ams.ams_linear_plan(fmt, M, N, K)
+        plan = ams.ams_linear_plan(fmt, M, N, K)
+        if K % 8 == 0 and N < 33000:
+            assert plan.startswith("slice "), plan
+        else:
+            assert plan.startswith("column ") and "phases=1 " not in plan, plan
+            assert N < 33000 or ("side_groups=1" in plan) == (fmt in (ams.FP425, ams.FP45, ams.FP433, ams.FP6)), plan
         X = synth.activations(M, K, 92 + M)
         y = host16(ams.ams_linear(wp, sc, dev(X), N, fmt)).astype(np.float64)
         assert np.all(np.isfinite(y))
@@ -347,7 +355,7 @@ def test_linear_random_large_shapes_sampled_rows():
             y = host16(ams.ams_linear_ws(wp, sc, x, N, fmt, ws) if use_ws else ams.ams_linear(wp, sc, x, N, fmt)).astype(np.float64)
             assert np.all(np.isfinite(y)), what
             check_linear(y[:, rows].astype(np.float16), ref, what + (" (workspace)" if use_ws else ""))
-    assert kinds == {"column"}  # every packed format takes the one kernel, whatever the shape
+    assert kinds == {"column", "slice"}
 
 
 def test_linear_random_shapes_all_entry_points():

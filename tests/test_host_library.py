@@ -252,31 +252,47 @@ def test_launch_plans_cover_the_kernels_and_the_split():
     # host logic only: which kernel and launch shape a problem gets (the GPU tests run these very shapes)
     plan = lambda *a, **k: dict(kv.split("=") for kv in ams.ams_linear_plan(*a, **k).split()[1:])
     kind = lambda *a, **k: ams.ams_linear_plan(*a, **k).split()[0]
-    assert kind(ams.FP533, 1, 28672, 4096) == "column"
-    p = plan(ams.FP533, 1, 28672, 4096)  # seven strips per workgroup: eight wavefronts, one alone on each strip, three records ahead
+    # slice_kernel: the wavefronts share K, so there are no wavefronts per strip, phases or side groups to report
+    for fmt in (ams.FP533, ams.FP425):
+        p = plan(fmt, 1, 28672, 4096)
+        assert kind(fmt, 1, 28672, 4096) == "slice" and set(p) == {"grid", "strips_per_wg", "k_slices", "waves", "lds", "ahead"}
+        assert (p["grid"], p["strips_per_wg"], p["k_slices"], p["waves"], p["ahead"]) == ("256", "7", "1", "8", "3")
+    p = plan(ams.FP425, 1, 4096, 14336)  # one strip per workgroup at M <= 4: sixteen wavefronts with two records ahead
+    assert (p["grid"], p["strips_per_wg"], p["waves"], p["ahead"]) == ("256", "1", "16", "2")
+    assert plan(ams.FP533, 4, 4096, 14336)["waves"] == "16" and plan(ams.FP533, 1, 4096, 4096)["waves"] == "16"
+    p = plan(ams.FP425, 8, 4096, 14336)
+    assert (p["grid"], p["strips_per_wg"], p["waves"]) == ("256", "1", "8")
+    p = plan(ams.FP425, 8, 4096, 14336, with_workspace=True)
+    assert (p["grid"], p["strips_per_wg"], p["k_slices"]) == ("256", "4", "4")
+    assert plan(ams.FP425, 1, 4096, 14336, with_workspace=True)["k_slices"] == "1"
+    p = plan(ams.FP533, 16, 57344, 8192)  # fourteen strips for every compute unit: two workgroups of seven
+    assert kind(ams.FP533, 16, 57344, 8192) == "slice" and (p["grid"], p["strips_per_wg"]) == ("512", "7")
+    # column_kernel: activation rows that are not 16-byte aligned, and what slice_kernel does not take
+    for M, K in ((1, 4099), (8, 4096 + 3)):
+        assert kind(ams.FP533, M, 28672, K) == "column"
+    p = plan(ams.FP533, 1, 28672, 4099)  # seven strips per workgroup: eight wavefronts, one alone on each strip, three records ahead
     assert (p["grid"], p["strips_per_wg"], p["k_slices"], p["waves"], p["waves_per_strip"], p["phases"], p["ahead"]) == ("256", "7", "1", "8", "1", "1", "3")
-    p = plan(ams.FP425, 1, 28672, 4096)  # the same with the side groups dealt whole
+    p = plan(ams.FP425, 1, 28672, 4091)  # the same with the side groups dealt whole
     assert (p["grid"], p["strips_per_wg"], p["waves"], p["waves_per_strip"], p["ahead"], p["side_groups"]) == ("256", "7", "8", "1", "3", "1")
-    p = plan(ams.FP433, 1, 28672, 4096)  # the other formats with side groups keep sixteen wavefronts, two on each strip
+    p = plan(ams.FP433, 1, 28672, 4099)  # the other formats with side groups keep sixteen wavefronts, two on each strip
     assert (p["waves"], p["waves_per_strip"], p["ahead"]) == ("16", "2", "2")
-    assert plan(ams.FP533, 32, 28672, 4096)["waves"] == "16" and plan(ams.FP533, 8, 28672, 4096)["waves"] == "8"
-    assert plan(ams.FP425, 1, 4096, 14336)["waves"] == "16"  # one strip per workgroup: sixteen wavefronts share it
-    assert plan(ams.FP533, 1, 4096, 14336)["waves"] == "8" and plan(ams.FP533, 4, 4096, 14336)["waves"] == "16"
-    assert plan(ams.FP533, 1, 4096, 4096)["waves"] == "16"  # 43 records for 8 wavefronts: too short a stream
-    assert plan(ams.FP533, 1, 6144, 4096)["waves"] == "16"  # 192 workgroups do not fill the chip
-    p = plan(ams.FP425, 1, 4096, 14336)  # one strip per workgroup: all 16 wavefronts on it
+    assert plan(ams.FP533, 32, 28672, 4099)["waves"] == "16" and plan(ams.FP533, 8, 28672, 4099)["waves"] == "8"
+    assert plan(ams.FP425, 1, 4096, 14339)["waves"] == "16"  # one strip per workgroup: sixteen wavefronts share it
+    assert plan(ams.FP533, 1, 4096, 14336)["waves"] == "8" and plan(ams.FP533, 4, 4096, 14339)["waves"] == "16"
+    assert plan(ams.FP533, 1, 4096, 4099)["waves"] == "16"  # 43 records for 8 wavefronts: too short a stream
+    assert plan(ams.FP533, 1, 6144, 4099)["waves"] == "16"  # 192 workgroups do not fill the chip
+    p = plan(ams.FP425, 1, 4096, 14339)  # one strip per workgroup: all 16 wavefronts on it
     assert (p["grid"], p["strips_per_wg"], p["waves_per_strip"], p["phases"]) == ("256", "1", "16", "1")
     p = plan(ams.FP533, 1, 57344, 8192)  # fourteen strips per workgroup: eight wavefronts (seven busy) with two strips each
     assert (p["grid"], p["strips_per_wg"], p["waves"], p["waves_per_strip"], p["strips_per_wave"], p["ahead"]) == ("256", "14", "8", "1", "2", "3")
     p = plan(ams.FP425, 1, 57344, 8192)  # with side groups: sixteen wavefronts, fourteen of them alone on a strip
     assert (p["grid"], p["strips_per_wg"], p["waves"], p["waves_per_strip"], p["strips_per_wave"]) == ("256", "14", "16", "1", "1")
-    assert plan(ams.FP533, 16, 57344, 8192)["strips_per_wave"] == "1"
+    assert plan(ams.FP533, 16, 57344, 8195)["strips_per_wave"] == "1"
     assert plan(ams.FP533, 1, 128256, 4096)["strips_per_wg"] == "16"  # more strips than 16 x 256: more workgroups
     assert int(plan(ams.FP533, 1, 128256, 4096)["grid"]) == -(-(-(-128256 // 16)) // 16)
-    assert kind(ams.FP533, 32, 57344, 8192) == "column" and int(plan(ams.FP533, 32, 57344, 8192)["phases"]) > 1
-    assert int(plan(ams.FP425, 8, 4096, 14336)["phases"]) > 1
-    assert plan(ams.FP425, 8, 4096, 14336, with_workspace=True)["k_slices"] == "4"
-    assert plan(ams.FP425, 1, 4096, 14336, with_workspace=True)["k_slices"] == "1"
+    assert kind(ams.FP533, 32, 57344, 8195) == "column" and int(plan(ams.FP533, 32, 57344, 8195)["phases"]) > 1
+    assert int(plan(ams.FP425, 8, 4096, 14339)["phases"]) > 1
+    assert plan(ams.FP425, 8, 4096, 14339, with_workspace=True)["k_slices"] == "4"
     assert kind(-1, 1, 4096, 4096) == "gemv" and kind(-1, 4, 28672, 4096) == "gemv"  # small batches: rows dealt to wavefronts
     assert kind(-1, 4, 8192, 28672) == "sweep"  # four rows of 28672 activations do not fit in LDS
     assert kind(-1, 8, 4096, 4096) == "sweep"
@@ -355,9 +371,9 @@ def test_launch_plans_random_shapes_stay_inside_the_machine():
         for ws in (False, True):
             text = ams.ams_linear_plan(fmt, M, N, K, with_workspace=ws)
             kind, kv = text.split()[0], dict(x.split("=") for x in text.split()[1:])
-            assert kind == ("column" if fmt >= 0 else kind) and kind in ("column", "gemv", "sweep", "stream"), text
+            assert kind in (("column", "slice") if fmt >= 0 else ("gemv", "sweep", "stream")), text
             assert 0 < int(kv["lds"]) <= 160 * 1024, text
-            assert 1 <= int(kv["waves"]) <= 16 and int(kv["phases"]) >= 1 and int(kv["grid"]) >= 1, text
+            assert 1 <= int(kv["waves"]) <= 16 and int(kv["grid"]) >= 1 and ("phases" not in kv if kind == "slice" else int(kv["phases"]) >= 1), text
             n_strips = -(-N // 16)
             if kind == "gemv":
                 assert M <= 4 and int(kv["rows_per_wave"]) * int(kv["grid"]) * 16 >= N and int(kv["lds"]) >= 2 * M * K, text
@@ -365,6 +381,8 @@ def test_launch_plans_random_shapes_stay_inside_the_machine():
             assert int(kv["strips_per_wg"]) * int(kv["grid"]) >= n_strips * int(kv["k_slices"]) or kind == "stream", text
             if kind == "sweep":
                 assert 16 % int(kv["waves_per_strip"]) == 0 or int(kv["waves_per_strip"]) == int(kv["waves"]), text
+            if kind == "slice":
+                assert K % 8 == 0 and 1 <= int(kv["strips_per_wg"]) <= 8 and (kv["waves"], kv["ahead"]) in (("16", "2"), ("8", "3")), text
             if kind == "column":
                 if kv["strips_per_wave"] == "1":
                     assert int(kv["strips_per_wg"]) <= 16 and int(kv["waves_per_strip"]) == int(kv["waves"]) // int(kv["strips_per_wg"]) >= 1, text
