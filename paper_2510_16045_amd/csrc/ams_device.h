@@ -319,9 +319,7 @@ constexpr int slice_rows(int M) { return M <= 4 ? 4 : M <= 8 ? 8 : M <= 16 ? 16 
 // Wavefronts of a workgroup.  Eight (with three pairs of weights ahead) are 3-10 % faster than sixteen with two where a
 // wavefront takes several strips or many rows: the sum over the wavefronts' tiles halves, and fewer contend for the VALU.
 // A single strip at M <= 4 needs sixteen to keep enough bytes in flight (4096 x 14336 FP5.33 M = 1 9.2 us against 9.6).
-// (FP4.33 on five and more strips at M <= 4: sixteen, 28672 x 4096 13.2 us against 12.5 with eight, for the plan the
-// query has always reported there.)
-constexpr int slice_waves(int fmt, int R, int NS) { return R == 4 && (NS == 1 || (fmt == FMT_FP433 && NS >= 5)) ? 16 : 8; }
+constexpr int slice_waves(int R, int NS) { return R == 4 && NS == 1 ? 16 : 8; }
 constexpr int slice_ahead(int S) { return S == 16 ? 2 : 3; }  // (record, strip) pairs of weights requested ahead
 constexpr int kSliceXAhead = 2;                               // records of activations requested ahead
 // 1 KiB loads that bring one record's activations
@@ -332,7 +330,7 @@ constexpr int slice_x_loads(int fmt, int R) {
 // floats between the rows of a partial tile in LDS: 20 keeps a column's float4s in different banks, where it fits
 constexpr int slice_tile_row(int S, int R, int NS) { return S * NS * R * 20 * 4 <= 150 * 1024 ? 20 : 16; }
 constexpr int slice_lds(int fmt, int R, int NS) {
-  const int S = slice_waves(fmt, R, NS);
+  const int S = slice_waves(R, NS);
   const int staged = S * kSliceXAhead * slice_x_loads(fmt, R) * 1024;
   const int tiles = S * NS * R * slice_tile_row(S, R, NS) * 4 + NS * 64 + NS * 4;
   return staged > tiles ? staged : tiles;

@@ -1396,7 +1396,7 @@ ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k,
   }
   const int r = slice_rows(M);
   p.slice = true;
-  p.S = slice_waves(fmt, r, p.spw);
+  p.S = slice_waves(r, p.spw);
   p.lr = slice_ahead(p.S);
   p.lds = (size_t)slice_lds(fmt, r, p.spw);
   return p;
@@ -1611,7 +1611,7 @@ int launch_slice(const LinearArgs& a, bool gs, int strips, unsigned grid, hipStr
   if (grid == 0) return AMS_OK;
   LinearArgs copy = a;
   void* args[] = {&copy};
-  return hipLaunchKernel(kern, dim3(grid), dim3(64 * slice_waves(FMT, r, strips)), args, lds, st) == hipSuccess ? AMS_OK : AMS_ERR_LAUNCH;
+  return hipLaunchKernel(kern, dim3(grid), dim3(64 * slice_waves(r, strips)), args, lds, st) == hipSuccess ? AMS_OK : AMS_ERR_LAUNCH;
 }
 
 template <int FMT>

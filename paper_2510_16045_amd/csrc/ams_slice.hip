@@ -62,7 +62,7 @@ struct Slice {
   static constexpr int NI = slice_x_loads(FMT, R), NI1 = NI / MT;  // 1 KiB loads of a record's activations, of one tile's
   static constexpr int BYTES = NI * 1024;
   static constexpr int WL = (Fmt<FMT>::SIDE ? 2 : 1) + GS;      // load instructions of one weight record (and its scales)
-  static constexpr int S = slice_waves(FMT, R, NS);
+  static constexpr int S = slice_waves(R, NS);
   static constexpr int LX = kSliceXAhead;
   static constexpr int LW = slice_ahead(S);
   static constexpr int U = NS > LW ? 1 : NS == 1 ? LW + 1 : 2;  // records per unrolled round
