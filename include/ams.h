@@ -216,7 +216,7 @@ int ams_fp16_linear(const uint16_t* W, const uint16_t* X, uint16_t* Y, int M, in
  *   ams_linear_workspace_bytes  fmt = AMS_FMT_*, or -1 for the fp16 baseline; may return 0
  */
 int ams_linear_workspace_bytes(int fmt, int M, int64_t N, int64_t K, size_t* bytes);
-/* Which kernel and launch shape ams_linear (with_workspace = 0) or ams_linear_ws (1) would use for
+/* Which kernel and launch shape ams_linear (with_workspace = 0), ams_linear_ws (1) or ams_linear_grouped (2) would use for
  * this problem (fmt = -1: the fp16 baseline), as a short text for logs and tests: "slice ..." or "column ..." (the
  * packed formats), "gemv ..." (the baseline at batches up to 4 whose activations fit in LDS), "sweep ..."
  * or "stream ..." (the baseline otherwise), followed by key=value pairs (workgroups, strips per

@@ -338,7 +338,8 @@ def ams_fp16_linear_ws(W, X, workspace, out=None):
 
 
 def ams_linear_plan(fmt: int, M: int, N: int, K: int, with_workspace: bool = False) -> str:
-    """Which kernel and launch shape the library would use for this problem (fmt = -1: the fp16 baseline)."""
+    """Which kernel and launch shape the library would use for this problem (fmt = -1: the fp16 baseline; with_workspace = 2:
+    ams_linear_grouped)."""
     buf = ctypes.create_string_buffer(256)
     _check(load_library().ams_linear_plan(fmt, M, N, K, int(with_workspace), buf, len(buf)), "ams_linear_plan")
     return buf.value.decode()

@@ -335,6 +335,12 @@ constexpr int slice_lds(int fmt, int R, int NS) {
   const int tiles = S * NS * R * slice_tile_row(S, R, NS) * 4 + NS * 64 + NS * 4;
   return staged > tiles ? staged : tiles;
 }
+// Whether two workgroups of `strips` strips fit on a compute unit at M <= 4 with one scale per run of input channels: at
+// most 128 registers (as the compiler reports them; the formats of 96 weights per record take 126 at most, FP4.25, FP4.5
+// and FP5 124 with six strips and 134 with seven, FP4 126 with seven and 130 with eight).
+constexpr bool slice_two_fit(int fmt, int strips) {
+  return ams::kFormats[fmt].rec_k == 96 || strips <= (fmt == FMT_FP4 ? 7 : 6);
+}
 // The kernel for `rows` staged rows and `strips` strips per workgroup (nullptr: there is none).
 // GS: one scale per run of input channels.
 template <int FMT, bool GS>

@@ -1368,6 +1368,29 @@ ColumnPlan make_column_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int
   return p;
 }
 
+// More than eight strips for every compute unit (spw of them): whether two workgroups of slice_kernel with half the strips
+// each beat the one of column_kernel / multi_kernel.  Formats without side groups and one scale per row from M = 9 on,
+// the others from M = 3 on.  Bounds, us column / slice; 1500 shapes per class, in one round of workgroups unless said:
+//   M > 4: long K, where the staging of the activations starts to cost (128256 x 4096 FP4.25 M = 8 49.6 / 50.2, 45000 x 4096
+//     M = 16 21.1 / 23.3; 64 to 80 records at M > 16 0.92-1.0 x);
+//   M <= 4, one scale per row: everything but two records per side group with a count that is even but no multiple of
+//     four, which column_kernel deals without a rest while most of the eight wavefronts idle (65536 x 256 FP4.5 0.87 x,
+//     x 768 0.90 x, x 1792 0.93 x; from 24 records on +- 3 %);
+//   M <= 4, one scale per run: a wavefront's strips follow each other and the sum over eight wavefronts' tiles is the same
+//     for one record as for a hundred, so a few records do not pay (65536 x 96 FP5.33 0.83 x, x 1152 0.96 x), and where
+//     the scales push the kernel beyond 128 registers the two workgroups take turns (65536 x 128 FP4.25 0.61 x, x 1024
+//     0.87 x; FP4 0.57 x, 0.80 x); with more than one round of workgroups the turns fill each other's gaps earlier.
+bool halved_is_faster(int fmt, int M, int64_t n_strips, int spw, int n_rec, bool one_scale) {
+  const int sg = ams::side_group(ams::kFormats[fmt]);
+  const bool one_round = n_strips <= 16 * kNumCU;
+  if (M <= (one_scale && sg == 1 ? 8 : 2)) return false;
+  if (M > 4) return n_rec >= (M > 16 && one_round ? 80 : 64);
+  if (one_scale) return sg != 2 || (one_round ? n_rec % 4 != 2 || n_rec >= 24 : n_rec > 2);
+  const int half = (spw + 1) / 2;
+  if (slice_two_fit(fmt, half)) return n_rec >= (one_round && half > 5 ? 16 : 3);
+  return n_rec >= (!one_round ? 32 : half == kSliceMaxStrips && fmt != FMT_FP425 ? 64 : 24);
+}
+
 // The plan of a problem: slice_kernel where it takes it (aligned_rows: rows of X are 16-byte aligned, K % 8 == 0;
 // one_scale: one scale per row of W), else make_column_plan's.  slice_kernel is the faster one nearly everywhere
 // (twelve shapes, seven formats, M = 1 .. 32: 1.00-1.8 x); the exceptions, us column / slice:
@@ -1378,10 +1401,7 @@ ColumnPlan make_column_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int
 //     below that (6144 x 4096 FP5.33 6.4 / 6.3, the sixteen wavefronts the plan query reports there);
 //   seven and eight strips without side groups, M > 16: 28672 x 4096 FP5.33 M = 32 24.7 / 18.9; slower, but the plan
 //     query promises sixteen wavefronts there, which slice_kernel's registers do not allow at M > 16;
-//   more than eight strips: halved (two workgroups fit on a compute unit at M <= 16) where that pays: with side groups
-//     from M = 3 on (57344 x 8192 FP4.25 M = 4 43.4 / 39.8, 128256 x 4096 46.3 / 43.7), without from M = 9
-//     (57344 x 8192 FP5.33 M = 16 59.0 / 52.6); above M = 4 only on long K (128256 x 4096 FP4.25 M = 8 49.6 / 50.2,
-//     45000 x 4096 M = 16 21.1 / 23.3).
+//   more than eight strips: see halved_is_faster.
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
   ColumnPlan p = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
   const int sg = ams::side_group(ams::kFormats[fmt]);
@@ -1390,7 +1410,7 @@ ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k,
   if (M <= 2 && p.spw == 2 && p.grid < kNumCU * 7 / 8 && (n_rec_all >= 128 || (one_scale && sg == 1 && M == 1))) return p;
   if (one_scale && sg == 1 && M > 16 && (p.spw == 7 || p.spw == 8)) return p;
   if (p.spw > kSliceMaxStrips) {
-    if (gk != 1 || M <= (one_scale && sg == 1 ? 8 : 2) || (M > 4 && n_rec_all < 64)) return p;
+    if (gk != 1 || !halved_is_faster(fmt, M, n_strips, p.spw, n_rec_all, one_scale)) return p;
     p.spw = (p.spw + 1) / 2;
     p.grid = p.gn = (int)((n_strips + p.spw - 1) / p.spw);
   }
@@ -1903,10 +1923,11 @@ int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, ch
   }
   const int64_t n_strips = (N + 15) / 16;
   const int n_rec = (int)((K + rec_k - 1) / rec_k);
-  const int gk = with_workspace ? choose_split(f, M, n_strips, n_rec, rec_k, rec_bytes) : 1;
+  const bool grouped = with_workspace == 2;  // ams_linear_grouped
+  const int gk = with_workspace && !grouped ? choose_split(f, M, n_strips, n_rec, rec_k, rec_bytes) : 1;
   if (f != FMT_FP16) {
     const bool nt = n_strips * n_rec * (int64_t)rec_bytes >= (2ll << 20);  // as run_linear decides it
-    const ColumnPlan cp = make_plan(f, M, n_strips, n_rec, rec_k, gk, K % 8 == 0, true, nt);
+    const ColumnPlan cp = make_plan(f, M, n_strips, n_rec, rec_k, gk, K % 8 == 0, !grouped, nt);
     if (cp.slice)
       snprintf(text, text_len, "slice grid=%d strips_per_wg=%d k_slices=%d waves=%d lds=%zu ahead=%d", cp.grid, cp.spw, cp.gk, cp.S, cp.lds, cp.lr);
     else

@@ -18,3 +18,44 @@ def test_two_workgroups_of_fp433_fit_on_a_compute_unit(M, N, K):
     # sixteen wavefronts of 88 to 106 registers each they took turns
     kind, p = plan(ams.FP433, M, N, K)
     assert kind == "slice" and int(p["strips_per_wg"]) in (6, 8) and p["waves"] == "8", p
+
+
+GROUPED = 2  # of the plan query's with_workspace
+
+
+@pytest.mark.parametrize(
+    "fmt,M,N,K,entry",
+    [
+        (ams.FP45, 4, 65536, 256, 0),  # an even number of records that is no multiple of four, two to a side group
+        (ams.FP6, 3, 65536, 96 * 14, 0),
+        (ams.FP6, 3, 128256, 96, 0),
+        (ams.FP533, 3, 65536, 96, GROUPED),  # few records per wavefront
+        (ams.FP433, 4, 65536, 96 * 15, GROUPED),
+        (ams.FP533, 4, 128256, 192, GROUPED),
+        (ams.FP425, 4, 65536, 128, GROUPED),  # workgroups that do not fit on a compute unit together
+        (ams.FP425, 3, 128256, 28 * 128, GROUPED),
+        (ams.FP5, 4, 65536, 63 * 128, GROUPED),
+        (ams.FP4, 4, 65536, 63 * 128, GROUPED),
+        (ams.FP425, 32, 45000, 79 * 128, 0),
+        (ams.FP533, 24, 45000, 70 * 96, GROUPED),
+        (ams.FP533, 16, 45000, 63 * 96, 0),
+    ],
+)
+def test_more_than_eight_strips_where_one_workgroup_is_faster(fmt, M, N, K, entry):
+    assert plan(fmt, M, N, K, with_workspace=entry)[0] == "column"
+
+
+@pytest.mark.parametrize(
+    "fmt,M,N,K,entry",
+    [
+        (ams.FP45, 4, 65536, 384, 0), (ams.FP45, 4, 65536, 26 * 128, 0), (ams.FP6, 3, 128256, 288, 0), (ams.FP425, 4, 65536, 128, 0),
+        (ams.FP533, 3, 65536, 96 * 16, GROUPED), (ams.FP533, 3, 36000, 96 * 3, GROUPED), (ams.FP533, 4, 128256, 96 * 3, GROUPED),
+        (ams.FP425, 4, 65536, 24 * 128, GROUPED), (ams.FP425, 3, 128256, 32 * 128, GROUPED), (ams.FP5, 4, 65536, 64 * 128, GROUPED),
+        (ams.FP4, 4, 56000, 16 * 128, GROUPED), (ams.FP425, 32, 45000, 80 * 128, 0), (ams.FP425, 32, 128256, 64 * 128, 0),
+        (ams.FP533, 16, 45000, 64 * 96, 0),
+    ],
+)
+def test_more_than_eight_strips_where_two_workgroups_are_faster(fmt, M, N, K, entry):
+    kind, p = plan(fmt, M, N, K, with_workspace=entry)
+    strips = min(16, -(-(-(-N // 16)) // 256))
+    assert kind == "slice" and int(p["strips_per_wg"]) == (strips + 1) // 2, p
