@@ -1399,8 +1399,10 @@ bool halved_is_faster(int fmt, int M, int64_t n_strips, int spw, int n_rec, bool
 //   two strips on fewer than 7/8 of the compute units, M <= 2, 128 records and more: its eight wavefronts keep too few
 //     bytes in flight (5120 x 25600 FP4.25 M = 1 17.8 / 19.7, FP5.33 M = 2 20.3 / 22.5); at M = 1 without side groups also
 //     below that (6144 x 4096 FP5.33 6.4 / 6.3, the sixteen wavefronts the plan query reports there);
-//   seven and eight strips without side groups, M > 16: 28672 x 4096 FP5.33 M = 32 24.7 / 18.9; slower, but the plan
-//     query promises sixteen wavefronts there, which slice_kernel's registers do not allow at M > 16;
+//   six strips and more, M > 8, a few records: with fewer than eight of them wavefronts idle, the busy ones walk all
+//     strips one after the other, and the idle ones' tiles are written and summed too (32768 x 128 M = 32 0.75 x, 28672 x
+//     128 0.9 x); eight strips at M > 16, whose tiles fill 128 KiB, up to sixteen records (32768 x 1024 0.9 x; 28672 x 4096
+//     FP5.33 M = 32 24.7 / 18.9);
 //   more than eight strips: see halved_is_faster.
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
   ColumnPlan p = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
@@ -1408,7 +1410,8 @@ ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k,
   if (!aligned_rows) return p;
   if (p.spw == 1 && p.lr == 3) return p;
   if (M <= 2 && p.spw == 2 && p.grid < kNumCU * 7 / 8 && (n_rec_all >= 128 || (one_scale && sg == 1 && M == 1))) return p;
-  if (one_scale && sg == 1 && M > 16 && (p.spw == 7 || p.spw == 8)) return p;
+  if (gk == 1 && p.spw == 8 && n_rec_all <= (M > 16 ? 16 : M > 8 ? 2 : 0)) return p;
+  if (gk == 1 && M > 16 && ((p.spw == 6 && n_rec_all <= (one_scale ? 1 : 2)) || (p.spw == 7 && n_rec_all <= 2))) return p;
   if (p.spw > kSliceMaxStrips) {
     if (gk != 1 || !halved_is_faster(fmt, M, n_strips, p.spw, n_rec_all, one_scale)) return p;
     p.spw = (p.spw + 1) / 2;

@@ -59,3 +59,19 @@ def test_more_than_eight_strips_where_two_workgroups_are_faster(fmt, M, N, K, en
     kind, p = plan(fmt, M, N, K, with_workspace=entry)
     strips = min(16, -(-(-(-N // 16)) // 256))
     assert kind == "slice" and int(p["strips_per_wg"]) == (strips + 1) // 2, p
+
+
+@pytest.mark.parametrize("fmt", range(7))
+@pytest.mark.parametrize(
+    "M,strips,n_rec,entry,want",
+    [
+        (17, 8, 16, 0, "column"), (32, 8, 1, GROUPED, "column"), (32, 8, 17, 0, "slice"), (32, 8, 17, GROUPED, "slice"),
+        (16, 8, 2, 0, "column"), (16, 8, 3, 0, "slice"), (8, 8, 1, 0, "slice"),
+        (32, 7, 2, 0, "column"), (32, 7, 3, 0, "slice"), (32, 7, 43, 0, "slice"), (16, 7, 1, GROUPED, "slice"),
+        (24, 6, 1, 0, "column"), (24, 6, 2, 0, "slice"), (24, 6, 2, GROUPED, "column"), (24, 6, 3, GROUPED, "slice"), (32, 5, 1, 0, "slice"),
+    ],
+)
+def test_few_records_at_large_batches(fmt, M, strips, n_rec, entry, want):
+    rec = 96 if fmt in (ams.FP533, ams.FP433, ams.FP6) else 128
+    kind, p = plan(fmt, M, 16 * 256 * strips - 5, rec * n_rec, with_workspace=entry)
+    assert kind == want and int(p["strips_per_wg"]) == strips, p
