@@ -1391,14 +1391,34 @@ bool halved_is_faster(int fmt, int M, int64_t n_strips, int spw, int n_rec, bool
   return n_rec >= (!one_round ? 32 : half == kSliceMaxStrips && fmt != FMT_FP425 ? 64 : 24);
 }
 
+// Long K at M <= 2, where both kernels live on the bytes in flight: column_kernel has sixteen wavefronts on one, two and
+// four strips alike, slice_kernel eight from two strips on (and keeps fewer records ahead the more loads a record takes:
+// its side dword, its scales).  Column / slice, 6800 shapes of 80 to 280 records and those of models, on five GPUs (+- 3 %):
+//   two strips on fewer than 7/8 of the compute units: from 128 records on (5120 x 25600 FP4.25 M = 1 17.8 / 19.7 us, FP5.33
+//     M = 2 20.3 / 22.5), at M = 1 from 97 on (6144 x 14336 FP4.25 11.6 / 12.5; 6144 x 4096 FP5.33 6.1 / 5.8) but for the
+//     plain FP5 and FP4 (1.0-1.07 x);
+//   two and four strips, one scale per run, records with two and more side bytes: from 97 records on at M = 1 (8192 x 14400
+//     FP6 19.8 / 21.5, 16384 x 14336 FP5 27.9 / 28.9), from 145 on at M = 2 (14336 x 18944 FP6 38.5 / 42.5; FP4.5 from 201);
+//   more than 200 records at M = 1 with a scale per run or side bytes (8192 x 25600 FP4.33 22.0 / 24.2, 4096 x 28672 with
+//     scales per run 15.9 / 16.6), but for FP4 (1.00-1.08 x), FP4.25 with one scale per row (1.02-1.08 x), and on one strip
+//     FP4.25, FP6 and FP5 with a scale per run (1.0-1.07 x).
+bool long_k_on_column(int fmt, int M, int spw, int grid, int n_rec, bool one_scale) {
+  if (M > 2 || (spw != 1 && spw != 2 && spw != 4)) return false;
+  const int side = ams::kFormats[fmt].side_bytes;
+  const bool plain = one_scale && (fmt == FMT_FP5 || fmt == FMT_FP4);
+  if (spw == 2 && grid < kNumCU * 7 / 8 && (n_rec >= 128 || (M == 1 && n_rec > 96 && !plain))) return true;
+  if (!one_scale && side >= 2 && spw > 1 && n_rec > (M == 1 ? 96 : fmt == FMT_FP45 ? 200 : 144)) return true;
+  if (M > 1 || n_rec <= 200) return false;
+  if (one_scale) return fmt == FMT_FP45 || fmt == FMT_FP433 || fmt == FMT_FP6;
+  return spw == 1 ? fmt == FMT_FP533 || fmt == FMT_FP45 || fmt == FMT_FP433 : fmt != FMT_FP4;
+}
+
 // The plan of a problem: slice_kernel where it takes it (aligned_rows: rows of X are 16-byte aligned, K % 8 == 0;
 // one_scale: one scale per row of W), else make_column_plan's.  slice_kernel is the faster one nearly everywhere
 // (twelve shapes, seven formats, M = 1 .. 32: 1.00-1.8 x); the exceptions, us column / slice:
 //   one strip per workgroup, M <= 2, where eight wavefronts with three records ahead fill the chip (no side groups):
 //     4096 x 14336 FP5.33 M = 1 9.5 / 9.4, M = 2 10.1 / 10.1;
-//   two strips on fewer than 7/8 of the compute units, M <= 2, 128 records and more: its eight wavefronts keep too few
-//     bytes in flight (5120 x 25600 FP4.25 M = 1 17.8 / 19.7, FP5.33 M = 2 20.3 / 22.5); at M = 1 without side groups also
-//     below that (6144 x 4096 FP5.33 6.4 / 6.3, the sixteen wavefronts the plan query reports there);
+//   one, two and four strips, M <= 2, long K: see long_k_on_column;
 //   six strips and more, M > 8, a few records: with fewer than eight of them wavefronts idle, the busy ones walk all
 //     strips one after the other, and the idle ones' tiles are written and summed too (32768 x 128 M = 32 0.75 x, 28672 x
 //     128 0.9 x); eight strips at M > 16, whose tiles fill 128 KiB, up to sixteen records (32768 x 1024 0.9 x; 28672 x 4096
@@ -1406,10 +1426,9 @@ bool halved_is_faster(int fmt, int M, int64_t n_strips, int spw, int n_rec, bool
 //   more than eight strips: see halved_is_faster.
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
   ColumnPlan p = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
-  const int sg = ams::side_group(ams::kFormats[fmt]);
   if (!aligned_rows) return p;
   if (p.spw == 1 && p.lr == 3) return p;
-  if (M <= 2 && p.spw == 2 && p.grid < kNumCU * 7 / 8 && (n_rec_all >= 128 || (one_scale && sg == 1 && M == 1))) return p;
+  if (long_k_on_column(fmt, M, p.spw, p.grid, n_rec_all, one_scale)) return p;
   if (gk == 1 && p.spw == 8 && n_rec_all <= (M > 16 ? 16 : M > 8 ? 2 : 0)) return p;
   if (gk == 1 && M > 16 && ((p.spw == 6 && n_rec_all <= (one_scale ? 1 : 2)) || (p.spw == 7 && n_rec_all <= 2))) return p;
   if (p.spw > kSliceMaxStrips) {

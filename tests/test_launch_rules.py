@@ -75,3 +75,22 @@ def test_few_records_at_large_batches(fmt, M, strips, n_rec, entry, want):
     rec = 96 if fmt in (ams.FP533, ams.FP433, ams.FP6) else 128
     kind, p = plan(fmt, M, 16 * 256 * strips - 5, rec * n_rec, with_workspace=entry)
     assert kind == want and int(p["strips_per_wg"]) == strips, p
+
+
+@pytest.mark.parametrize(
+    "fmt,M,N,n_rec,entry,want",
+    [
+        (ams.FP425, 1, 6144, 97, 0, "column"), (ams.FP533, 1, 6144, 97, GROUPED, "column"), (ams.FP533, 1, 6144, 96, 0, "slice"),
+        (ams.FP533, 1, 6144, 43, 0, "slice"), (ams.FP5, 1, 6144, 127, 0, "slice"), (ams.FP5, 1, 6144, 97, GROUPED, "column"), (ams.FP425, 2, 6144, 127, 0, "slice"), (ams.FP425, 2, 6144, 128, 0, "column"),
+        (ams.FP425, 1, 8192, 128, 0, "slice"),  # every compute unit has two strips
+        (ams.FP6, 1, 8192, 97, GROUPED, "column"), (ams.FP5, 1, 16384, 96, GROUPED, "slice"), (ams.FP5, 2, 16384, 145, GROUPED, "column"),
+        (ams.FP45, 2, 8192, 200, GROUPED, "slice"), (ams.FP45, 2, 8192, 201, GROUPED, "column"), (ams.FP6, 2, 12288, 150, GROUPED, "slice"),
+        (ams.FP533, 1, 16384, 201, GROUPED, "column"), (ams.FP533, 1, 16384, 200, GROUPED, "slice"), (ams.FP533, 1, 16384, 250, 0, "slice"),
+        (ams.FP6, 1, 16384, 201, 0, "column"), (ams.FP433, 1, 1000, 201, 0, "column"), (ams.FP425, 1, 1000, 250, 0, "slice"),
+        (ams.FP533, 1, 1000, 201, GROUPED, "column"), (ams.FP5, 1, 1000, 201, GROUPED, "slice"), (ams.FP4, 1, 16384, 250, GROUPED, "slice"),
+        (ams.FP6, 2, 16384, 250, 0, "slice"), (ams.FP6, 3, 6144, 250, 0, "slice"),
+    ],
+)
+def test_long_k_at_small_batches(fmt, M, N, n_rec, entry, want):
+    rec = 96 if fmt in (ams.FP533, ams.FP433, ams.FP6) else 128
+    assert plan(fmt, M, N, rec * n_rec, with_workspace=entry)[0] == want
