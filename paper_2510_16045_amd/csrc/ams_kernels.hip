@@ -1413,6 +1413,24 @@ bool long_k_on_column(int fmt, int M, int spw, int grid, int n_rec, bool one_sca
   return spw == 1 ? fmt == FMT_FP533 || fmt == FMT_FP45 || fmt == FMT_FP433 : fmt != FMT_FP4;
 }
 
+// Short slices of a split K at M > 8, several strips per workgroup: the tiles of eight wavefronts cost the same however few
+// records lie behind them (column_kernel's sixteen leave 16 / strips of them per strip), and the workgroup's sum waits
+// for the slowest.  Column / slice over twelve N, thirteen K, seven formats, M = 12, 16, 24, 32:
+//   four slices: up to 16 records of 128 weights or 29 of 96, five strips and more at M > 16 (5120 x 6144 0.87-0.94 x, x 11008
+//     FP5.33 0.92 x), six and more below (7168 x 8192 0.84-0.94 x; x 14336 1.0 x);
+//   eight slices: as many records with three strips at M > 16 (1536 x 13824 0.91-0.99 x, x 18944 FP4.25 1.02 x); any number
+//     measured, up to 40, with four strips and more at M > 16 (2048 x 25600 0.94-0.97 x) and with seven and eight below
+//     (3584 x 22016 0.80 x); with five and six below up to 24 of 128 or 29 of 96 (2560 x 18944 0.86-0.97 x, x 25600 1.0 x).
+// Longer slices and fewer strips: 0.96-1.4 x.
+bool short_slices_on_column(int fmt, int M, int spw, int gk, int n_rec_all) {
+  if (M <= 8 || gk < 4) return false;
+  const int n_rec = (n_rec_all + gk - 1) / gk;
+  const bool rec96 = ams::kFormats[fmt].rec_k == 96;
+  if (gk == 4) return spw >= (M > 16 ? 5 : 6) && n_rec <= (rec96 ? 29 : 16);
+  if (spw >= (M > 16 ? 4 : 7)) return n_rec <= 40;
+  return M > 16 ? spw == 3 && n_rec <= (rec96 ? 29 : 16) : spw >= 5 && n_rec <= (rec96 ? 29 : 24);
+}
+
 // The plan of a problem: slice_kernel where it takes it (aligned_rows: rows of X are 16-byte aligned, K % 8 == 0;
 // one_scale: one scale per row of W), else make_column_plan's.  slice_kernel is the faster one nearly everywhere
 // (twelve shapes, seven formats, M = 1 .. 32: 1.00-1.8 x); the exceptions, us column / slice:
@@ -1423,12 +1441,14 @@ bool long_k_on_column(int fmt, int M, int spw, int grid, int n_rec, bool one_sca
 //     strips one after the other, and the idle ones' tiles are written and summed too (32768 x 128 M = 32 0.75 x, 28672 x
 //     128 0.9 x); eight strips at M > 16, whose tiles fill 128 KiB, up to sixteen records (32768 x 1024 0.9 x; 28672 x 4096
 //     FP5.33 M = 32 24.7 / 18.9);
+//   short slices of a split K: see short_slices_on_column;
 //   more than eight strips: see halved_is_faster.
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
   ColumnPlan p = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
   if (!aligned_rows) return p;
   if (p.spw == 1 && p.lr == 3) return p;
   if (long_k_on_column(fmt, M, p.spw, p.grid, n_rec_all, one_scale)) return p;
+  if (short_slices_on_column(fmt, M, p.spw, gk, n_rec_all)) return p;
   if (gk == 1 && p.spw == 8 && n_rec_all <= (M > 16 ? 16 : M > 8 ? 2 : 0)) return p;
   if (gk == 1 && M > 16 && ((p.spw == 6 && n_rec_all <= (one_scale ? 1 : 2)) || (p.spw == 7 && n_rec_all <= 2))) return p;
   if (p.spw > kSliceMaxStrips) {

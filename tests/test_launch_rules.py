@@ -94,3 +94,19 @@ def test_few_records_at_large_batches(fmt, M, strips, n_rec, entry, want):
 def test_long_k_at_small_batches(fmt, M, N, n_rec, entry, want):
     rec = 96 if fmt in (ams.FP533, ams.FP433, ams.FP6) else 128
     assert plan(fmt, M, N, rec * n_rec, with_workspace=entry)[0] == want
+
+
+@pytest.mark.parametrize(
+    "fmt,M,N,K,slices,want",
+    [
+        (ams.FP533, 16, 2560, 18944, 8, "column"), (ams.FP533, 16, 2560, 25600, 8, "slice"), (ams.FP425, 16, 2560, 25600, 8, "slice"),
+        (ams.FP6, 16, 3584, 22016, 8, "column"), (ams.FP425, 32, 2048, 25600, 8, "column"), (ams.FP425, 16, 1536, 13824, 8, "slice"),
+        (ams.FP425, 32, 1536, 13824, 8, "column"), (ams.FP425, 32, 1536, 18944, 8, "slice"), (ams.FP533, 32, 1536, 18944, 8, "column"),
+        (ams.FP533, 32, 5120, 6144, 4, "column"), (ams.FP433, 32, 5120, 11008, 4, "column"), (ams.FP425, 32, 5120, 11008, 4, "slice"),
+        (ams.FP45, 16, 7168, 8192, 4, "column"), (ams.FP45, 16, 7168, 9728, 4, "slice"), (ams.FP433, 16, 7168, 13824, 4, "slice"),
+        (ams.FP425, 8, 4096, 14336, 4, "slice"), (ams.FP533, 16, 5120, 25600, 4, "slice"),
+    ],
+)
+def test_short_slices_of_a_split(fmt, M, N, K, slices, want):
+    kind, p = plan(fmt, M, N, K, with_workspace=True)
+    assert kind == want and int(p["k_slices"]) == slices, p
