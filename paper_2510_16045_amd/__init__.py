@@ -91,11 +91,21 @@ def ams_init() -> None:
     _check(load_library().ams_init(), "ams_init")
 
 
-@functools.lru_cache(maxsize=4096)  # a pure function of its arguments, asked on every call of the Linear
-def ams_packed_bytes(fmt: int, N: int, K: int) -> int:
+def _packed_bytes(fmt, N, K):
     out = ctypes.c_size_t()
     _check(load_library().ams_packed_bytes(fmt, N, K, ctypes.byref(out)), "ams_packed_bytes")
     return out.value
+
+
+_packed_bytes_of_ints = functools.lru_cache(maxsize=4096)(_packed_bytes)
+
+
+def ams_packed_bytes(fmt: int, N: int, K: int) -> int:
+    # a pure function of its arguments, asked on every call of the Linear; only plain ints may share an answer (16.0 equals
+    # 16 but is refused by ctypes, and a ctypes integer can change its value)
+    if type(fmt) is int and type(N) is int and type(K) is int:
+        return _packed_bytes_of_ints(fmt, N, K)
+    return _packed_bytes(fmt, N, K)
 
 
 def ams_canonical_bytes(fmt: int, N: int, K: int) -> int:
