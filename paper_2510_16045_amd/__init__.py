@@ -164,7 +164,10 @@ def _stream():
     took 2.8 us of the 8.4 us that a whole call of ams_linear took, the handle takes 0.3."""
     import torch
 
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # not a public name: a torch without it goes the long way
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _dev_ptr(t, dtype=None):

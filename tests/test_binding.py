@@ -19,3 +19,23 @@ def test_packed_bytes_of_a_changed_ctypes_integer():
     small = ams.ams_packed_bytes(ams.FP425, n, 128)
     n.value = 32
     assert ams.ams_packed_bytes(ams.FP425, n, 128) == 2 * small
+
+
+def test_stream_without_torchs_private_name(monkeypatch):
+    torch = pytest.importorskip("torch")
+
+    class Stream:
+        cuda_stream = 123
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    assert ams._stream() == 123
+
+
+@pytest.mark.gpu
+def test_stream_is_the_current_one():
+    torch = pytest.importorskip("torch")
+    side = torch.cuda.Stream()
+    assert ams._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert ams._stream() == side.cuda_stream
