@@ -251,26 +251,25 @@ inline int sign_pos(int fmt, int i) {
 inline int mag_pos(int fmt, int i) { return is_e2m3(fmt) ? 8 - 4 * i : 9 - 3 * i; }
 
 // What one code adds to its lane chunk: the low half to the 32-bit word of its place, the high half to the side bits.
+template <int FMT>
 struct PlaceTable {
-  uint64_t add[ams::kNumFormats][32][64];  // [format][weight of the lane chunk][code]
+  uint64_t add[ams::kFormats[FMT].lane_k][64];  // [weight of the lane chunk][code]
   PlaceTable() {
-    for (int fmt = 0; fmt < ams::kNumFormats; fmt++) {
-      const FormatInfo& fi = *ams::format_info(fmt);
-      // FP4-e2m1 has no last bit beside its remainder: the nibble is the whole code
-      const bool whole = fmt == ams::kFmtFp4;
-      const int mag_bits = whole ? fi.code_bits - 1 : fi.code_bits - 2;  // bits of a remainder without its sign
-      for (int q = 0; q < 32; q++)
-        for (int c = 0; c < 64; c++) {
-          add[fmt][q][c] = 0;
-          if (q >= fi.lane_k || (c >> fi.code_bits)) continue;
-          const ams::Place p = ams::place(fmt, q);
-          const uint32_t rem = whole ? (uint32_t)c : (uint32_t)c >> 1, lsb = whole ? 0u : (uint32_t)c & 1;
-          uint32_t hw = (rem >> mag_bits) << sign_pos(fmt, p.i) | (rem & ((1u << mag_bits) - 1)) << mag_pos(fmt, p.i);
-          const int sb = ams::side_bit(fmt, q);
-          if (sb < 0) hw |= lsb << 12;
-          add[fmt][q][c] = (uint64_t)(hw << (16 * p.h)) | (sb >= 0 ? (uint64_t)lsb << (32 + sb) : 0);
-        }
-    }
+    constexpr FormatInfo fi = ams::kFormats[FMT];
+    // FP4-e2m1 has no last bit beside its remainder: the nibble is the whole code
+    constexpr bool whole = FMT == ams::kFmtFp4;
+    constexpr int mag_bits = whole ? fi.code_bits - 1 : fi.code_bits - 2;  // bits of a remainder without its sign
+    for (int q = 0; q < fi.lane_k; q++)
+      for (int c = 0; c < 64; c++) {
+        add[q][c] = 0;
+        if (c >> fi.code_bits) continue;
+        const ams::Place p = ams::place(FMT, q);
+        const uint32_t rem = whole ? (uint32_t)c : (uint32_t)c >> 1, lsb = whole ? 0u : (uint32_t)c & 1;
+        uint32_t hw = (rem >> mag_bits) << sign_pos(FMT, p.i) | (rem & ((1u << mag_bits) - 1)) << mag_pos(FMT, p.i);
+        const int sb = ams::side_bit(FMT, q);
+        if (sb < 0) hw |= lsb << 12;
+        add[q][c] = (uint64_t)(hw << (16 * p.h)) | (sb >= 0 ? (uint64_t)lsb << (32 + sb) : 0);
+      }
   }
 };
 
@@ -278,7 +277,7 @@ struct PlaceTable {
 // (row pointer NULL = padding row).  Records beyond K that pad the last side group hold zero codes.
 template <int FMT>
 void pack_strip_of(const uint8_t* const rows[16], int64_t K, uint8_t* packed, int64_t n_strips, int64_t t) {
-  static const PlaceTable table;
+  static const PlaceTable<FMT> table;
   constexpr FormatInfo fi = ams::kFormats[FMT];
   const int64_t n_rec = ams::round_up(ams::round_up(K, fi.rec_k) / fi.rec_k, ams::side_group(fi));
   for (int64_t j = 0; j < n_rec; j++) {
@@ -289,9 +288,9 @@ void pack_strip_of(const uint8_t* const rows[16], int64_t K, uint8_t* packed, in
       uint64_t words[4] = {0, 0, 0, 0};
       if (row && kbase + fi.lane_k <= K) {
 #pragma unroll
-        for (int q = 0; q < fi.lane_k; q++) words[ams::place(FMT, q).d] |= table.add[FMT][q][row[kbase + q] & 63];
+        for (int q = 0; q < fi.lane_k; q++) words[ams::place(FMT, q).d] |= table.add[q][row[kbase + q] & 63];
       } else if (row) {  // the rest is padding: code 0 adds nothing
-        for (int q = 0; q < fi.lane_k && kbase + q < K; q++) words[ams::place(FMT, q).d] |= table.add[FMT][q][row[kbase + q] & 63];
+        for (int q = 0; q < fi.lane_k && kbase + q < K; q++) words[ams::place(FMT, q).d] |= table.add[q][row[kbase + q] & 63];
       }
       uint32_t chunk[4];
       for (int d = 0; d < 4; d++) chunk[d] = (uint32_t)words[d];
