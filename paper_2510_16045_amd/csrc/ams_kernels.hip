@@ -1633,12 +1633,15 @@ int launch_gemv(int M, bool nt, const LinearArgs& a, unsigned grid, size_t lds, 
 template <int FMT, int MT, bool RAGGED>
 int launch_column_rows(bool nt, bool gs, bool qd, int lr, const LinearArgs& a, unsigned grid, int S, size_t lds, hipStream_t st) {
   if (gs) return launch(column_kernel<FMT, MT, true, true, false, 2, RAGGED>, a, grid, S, lds, st);
-  if constexpr (Fmt<FMT>::SG == 1) {
+  // Three records ahead: make_column_plan's plans for M <= 16; FP4.25's with the side groups dealt whole are seven and
+  // eight strips, which slice_kernel takes where rows are aligned.
+  if constexpr (MT == 1 && Fmt<FMT>::SG == 1) {
     if (lr == 3) return nt ? launch(column_kernel<FMT, MT, true, false, false, 3, RAGGED>, a, grid, S, lds, st) : AMS_ERR_LAUNCH;
   }
-  if constexpr (Fmt<FMT>::SG == 4) {
+  if constexpr (MT == 1 && FMT == FMT_FP425 && RAGGED) {
     if (qd && lr == 3) return nt ? launch(column_kernel<FMT, MT, true, false, true, 3, RAGGED>, a, grid, S, lds, st) : AMS_ERR_LAUNCH;
   }
+  if (lr != 2) return AMS_ERR_LAUNCH;
   if constexpr (Fmt<FMT>::SG > 1) {
     if (qd)
       return nt ? launch(column_kernel<FMT, MT, true, false, true, 2, RAGGED>, a, grid, S, lds, st)
@@ -1653,12 +1656,12 @@ int launch_column(bool nt, bool gs, bool qd, int lr, const LinearArgs& a, unsign
                         : launch_column_rows<FMT, MT, true>(nt, gs, qd, lr, a, grid, S, lds, st);
 }
 
-// Wavefronts that own two strips each (non-temporal loads, one scale per row).
-template <int FMT, int MT>
+// Wavefronts that own two strips each (non-temporal loads, one scale per row; planned up to M = 8).
+template <int FMT>
 int launch_multi(const LinearArgs& a, unsigned grid, int S, size_t lds, hipStream_t st) {
   if constexpr (Fmt<FMT>::SG == 1)
-    return (a.K & 7) == 0 ? launch(multi_kernel<FMT, MT, true, 2, false>, a, grid, S, lds, st)
-                          : launch(multi_kernel<FMT, MT, true, 2, true>, a, grid, S, lds, st);
+    return (a.K & 7) == 0 ? launch(multi_kernel<FMT, 1, true, 2, false>, a, grid, S, lds, st)
+                          : launch(multi_kernel<FMT, 1, true, 2, true>, a, grid, S, lds, st);
   return AMS_ERR_LAUNCH;
 }
 
@@ -1755,7 +1758,7 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
     a.spw = cp.spw;
     a.rc = cp.rc;
     if (cp.slice) return launch_slice<FMT>(a, scale_group != 0, cp.spw, cp.grid, st);
-    if (cp.ns > 1) return M <= 16 ? launch_multi<FMT, 1>(a, cp.grid, cp.S, cp.lds, st) : launch_multi<FMT, 2>(a, cp.grid, cp.S, cp.lds, st);
+    if (cp.ns > 1) return launch_multi<FMT>(a, cp.grid, cp.S, cp.lds, st);
     return M <= 16 ? launch_column<FMT, 1>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st)
                    : launch_column<FMT, 2>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st);
   } else {
@@ -1811,14 +1814,12 @@ int prepare_format() {
             ok &= launch_column<FMT, 2>(nt, gs, qd, 2, a, 0, 16, 0, nullptr) == AMS_OK;
           }
       if constexpr (Fmt<FMT>::SG == 1) {
-        ok &= launch_multi<FMT, 1>(a, 0, 8, 0, nullptr) == AMS_OK;
-        ok &= launch_multi<FMT, 2>(a, 0, 8, 0, nullptr) == AMS_OK;
-      }
-      if constexpr (Fmt<FMT>::SG == 1 || Fmt<FMT>::SG == 4) {
-        ok &= launch_column<FMT, 1>(true, false, Fmt<FMT>::SG == 4, 3, a, 0, 8, 0, nullptr) == AMS_OK;
-        ok &= launch_column<FMT, 2>(true, false, Fmt<FMT>::SG == 4, 3, a, 0, 8, 0, nullptr) == AMS_OK;
+        ok &= launch_multi<FMT>(a, 0, 8, 0, nullptr) == AMS_OK;
+        ok &= launch_column<FMT, 1>(true, false, false, 3, a, 0, 8, 0, nullptr) == AMS_OK;
       }
     }
+    a.K = 9;
+    if constexpr (FMT == FMT_FP425) ok &= launch_column<FMT, 1>(true, false, true, 3, a, 0, 8, 0, nullptr) == AMS_OK;
   } else {
     for (int m = 1; m <= 4; m++)
       for (int nt = 0; nt < 2; nt++) ok &= launch_gemv(m, nt != 0, a, 0, 0, nullptr) == AMS_OK;

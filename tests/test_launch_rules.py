@@ -1,6 +1,7 @@
 """Which kernel a Linear gets where the choice was measured to matter: shapes on which slice_kernel was the slower one
 stay on column_kernel, and slice_kernel's workgroups keep the sizes that its rules assume.  Host only."""
 
+import numpy as np
 import pytest
 
 import paper_2510_16045_amd as ams
@@ -110,3 +111,25 @@ def test_long_k_at_small_batches(fmt, M, N, n_rec, entry, want):
 def test_short_slices_of_a_split(fmt, M, N, K, slices, want):
     kind, p = plan(fmt, M, N, K, with_workspace=True)
     assert kind == want and int(p["k_slices"]) == slices, p
+
+
+def test_deep_and_two_strip_plans_stay_where_their_kernels_exist():
+    # the kernels with three records ahead are built for M <= 16 (FP4.25: unaligned rows only), the ones with two strips
+    # per wavefront for one row tile and formats without side groups
+    rng = np.random.default_rng(20)
+    deep = two = 0
+    for _ in range(30000):
+        fmt, M = int(rng.integers(7)), int(rng.integers(1, 33))
+        N, K = 16 * int(rng.integers(1, 4500)), int(2 ** rng.uniform(3, 16))
+        if rng.random() < 0.5:
+            K = K // 8 * 8
+        kind, p = plan(fmt, M, N, K, with_workspace=int(rng.integers(3)))
+        if kind != "column":
+            continue
+        if p["strips_per_wave"] != "1":
+            two += 1
+            assert M <= 8 and fmt in (ams.FP533, ams.FP5, ams.FP4), (fmt, M, N, K, p)
+        elif p["ahead"] != "2":
+            deep += 1
+            assert M <= 16 and (fmt in (ams.FP533, ams.FP5, ams.FP4) or (fmt == ams.FP425 and K % 8 and p["side_groups"] == "1")), (fmt, M, N, K, p)
+    assert deep > 50 and two > 50
