@@ -251,10 +251,10 @@ def dominant_kernel(ams, layer, fmt_name, M):
     return "slice_kernel" if plan.startswith("slice ") else "multi_kernel" if "strips_per_wave=2" in plan else "column_kernel"
 
 
-def measured_traffic(ams, layer, fmt_name, M):
+def measured_traffic(ams, layer, fmt_name, M, kernel):
     """HBM bytes per launch from the tracked counter summaries (profiles/*hbm_traffic*.md carry one line
-    `traffic-json: {...}` each), or None when there is none for this launch or it was measured with another
-    packed layout (major version of the library)."""
+    `traffic-json: {...}` each), or None when there is none for this launch by this kernel or it was measured with
+    another packed layout (major version of the library)."""
     import glob
 
     for path in sorted(glob.glob(os.path.join(PROFILES_DIR, "*hbm_traffic*.md"))):
@@ -263,7 +263,7 @@ def measured_traffic(ams, layer, fmt_name, M):
                 lines = [ln for ln in f if ln.startswith("traffic-json:")]
             for ln in lines:
                 e = json.loads(ln[len("traffic-json:"):])
-                if e.get("layout_version") == ams.ams_version() // 100 and (e.get("layer"), e.get("fmt"), e.get("M")) == (layer, fmt_name, M):
+                if e.get("layout_version") == ams.ams_version() // 100 and (e.get("layer"), e.get("fmt"), e.get("M"), e.get("kernel")) == (layer, fmt_name, M, kernel):
                     return int(e["fetch_bytes"]) + int(e["write_bytes"])
         except (OSError, ValueError, KeyError):
             continue
@@ -421,11 +421,12 @@ def main():
     alg_bytes = dl.canon[dfmt] + 2 * dl.N + 2 * M * dl.K + 2 * M * dl.N
     t_dom = time_launches(torch, lambda i: linear(dl.packed[dfmt][i % len(dl.packed[dfmt])], dl.scales[dfmt], xs[dl.name], dl.N, dfmt, ys[dl.name]), n_launch, replays=20)
     achieved = alg_bytes / t_dom / 1e3
+    dom_kernel = dominant_kernel(ams, dl, dom["fmt"], M)
     roofline = {
-        "bound": "hbm", "kernel": f"{dominant_kernel(ams, dl, dom['fmt'], M)}<{dom['fmt']}> {dl.N}x{dl.K} M={M}",
+        "bound": "hbm", "kernel": f"{dom_kernel}<{dom['fmt']}> {dl.N}x{dl.K} M={M}",
         "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
         "us_per_launch": round(t_dom, 3), "algorithmic_bytes": alg_bytes,
-        "traffic": measured_traffic(ams, dl.name, dom["fmt"], M) if args.layers == "8b" else None,
+        "traffic": measured_traffic(ams, dl.name, dom["fmt"], M, dom_kernel) if args.layers == "8b" else None,
     }
 
     # launch floor: an empty launch of the Linear kernel's shape (256 workgroups x 1024 threads)
