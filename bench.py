@@ -9,15 +9,15 @@ launches whose packed weights all stream from HBM.  To keep every launch cold, t
 step rotates through several resident copies of each packed matrix (a real decode
 step touches each layer's weights once per token and the model never fits a cache).
 
-stdout carries ONE JSON line: whole-step packed-weight GB/s as `value`, per-layer
-figures (us per Linear with percentiles, cache-resident time, GB/s, fraction of the
-8 TB/s HBM peak and of a bare read of the same bytes, speed-up over the in-build fp16
-Linear and the library GEMM) under `layers`, a `roofline` object for the dominant kernel,
+stdout carries ONE JSON line of less than 8000 characters (a record that keeps the end of stdout
+keeps all of it): whole-step packed-weight GB/s as `value`, per-layer figures (us per Linear,
+fraction of the 8 TB/s HBM peak and of a bare read of the same bytes, speed-up over the in-build
+fp16 Linear and the library GEMM) under `layers`, a `roofline` object for the dominant kernel,
 a `cpu_baseline` object (the numpy oracle timed on this host) and, unless switched off,
 `batch_sweep` (M = 1..32 on the 8B gate/up and down projections, both formats, plain
 ams_linear and the split of K through the library's static scratch, against the faster of
-the two fp16 baselines) and `llama70b` (the Llama-70B-shaped layers on heavy-tailed weights
-at M = 1, 4, 8).
+the two fp16 baselines), `llama70b` (the Llama-70B-shaped layers on heavy-tailed weights
+at M = 1, 4, 8), `lm_head` and `qwen_down`, as tables.  --out FILE writes every column of every row.
 """
 
 from __future__ import annotations
@@ -55,7 +55,7 @@ def parse_args():
     ap.add_argument("--no-70b", action="store_true", help="skip the Llama-70B-shaped layers at M=1,4,8")
     ap.add_argument("--no-lm-head", action="store_true", help="skip the Llama-3-8B vocabulary projection (128256 x 4096) at M=1,8")
     ap.add_argument("--no-qwen", action="store_true", help="skip the Qwen MLP-down shapes of the paper's Table 3 at batch 1, 4, 16, 32")
-    ap.add_argument("--out", default=None, help="also write the sweep table to this file")
+    ap.add_argument("--out", default=None, help="also write the sweep and the whole record, every column of every row, to this file")
     ap.add_argument("--all-formats", action="store_true", help="per-layer figures and the sweep for all seven formats (the step keeps the paper's two)")
     ap.add_argument("--group-scales", action="store_true", help="also time ams_linear_grouped (one scale per record-sized run of K) per layer")
     ap.add_argument("--workspace", action="store_true", help="the step and the per-layer table call ams_linear_ws / ams_fp16_linear_ws with a workspace")
@@ -298,6 +298,30 @@ def batch_sweep(layers, fmts, ams, torch, synth, n_launch, ws, batches=None):
     return rows
 
 
+def printed_record(line):
+    """The record as it is printed: the headline whole, of the tables the columns that are read most, four digits each."""
+
+    def short(v):
+        return float(f"{v:.4g}") if isinstance(v, float) else v
+
+    def rows(table, keys):
+        return table and [{k: short(r[k]) for k in keys if k != "us_group_scales" or r[k] is not None} for r in table]
+
+    def columns(table, keys):
+        return table and {"columns": list(keys), "rows": [[short(r[k]) if k != "fmt" else r[k].split("-")[0] for k in keys] for r in table]}
+
+    out = dict(line)
+    out["layers"] = rows(line["layers"], ("layer", "fmt", "us", "hbm_frac", "frac_of_bare_read", "us_group_scales", "fp16_us", "speedup_vs_best_fp16"))
+    out["batch_sweep"] = rows(line["batch_sweep"], ("layer", "M", "fmt", "us", "us_static_ws", "speedup_vs_best_fp16"))
+    for name in ("llama70b", "lm_head"):
+        out[name] = columns(line[name], ("layer", "M", "fmt", "us", "us_static_ws", "hbm_frac", "speedup_vs_best_fp16"))
+    out["qwen_down"] = columns(line["qwen_down"], ("layer", "M", "fmt", "us", "us_static_ws", "best_speedup_vs_best_fp16"))
+    if line["cpu_baseline"]:
+        out["cpu_baseline"] = {k: short(v) for k, v in line["cpu_baseline"].items() if k not in ("per_layer", "full_configs")}
+        out["cpu_baseline"]["sample"] = line["cpu_baseline"]["sample"].split("; `full_configs`")[0]
+    return out
+
+
 def main():
     args = parse_args()
     if args.gpus != 1:
@@ -437,9 +461,6 @@ def main():
     if not args.no_sweep:
         sweep_layers = layers if (args.sweep_all_layers or args.layers != "8b") else [l for l in layers if l.name in ("gate_up", "down")]
         sweep = batch_sweep(sweep_layers, all_fmts, ams, torch, synth, n_launch, ws)
-        if args.out:
-            with open(args.out, "w") as f:
-                json.dump({"layers": args.layers, "sweep": sweep}, f, indent=1)
 
     # ---- larger layers, each set built, timed and freed by itself
     def measure_set(shape_set, maker, seed, batches, label):
@@ -529,7 +550,10 @@ def main():
         "qwen_down": qwen_down,
         "paper_context": "paper reports 2.8x / 3.2x decode speed-up over fp16 (FP5.33 / FP4.25) on an unnamed GPU of ~22 TFLOPS, 290 GB/s",
     }
-    print(json.dumps(line))
+    if args.out:
+        with open(args.out, "w") as f:
+            json.dump({"layers": args.layers, "sweep": sweep, "record": line}, f, indent=1)
+    print(json.dumps(printed_record(line), separators=(",", ":")))
 
 
 if __name__ == "__main__":
