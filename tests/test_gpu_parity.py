@@ -221,8 +221,8 @@ def test_linear_full_size_sampled_rows(fmt, ofmt):
 @pytest.mark.parametrize(
     "N,K,Ms",
     [
-        (28672, 4096, (1, 4, 16, 32)),  # Llama-8B gate/up: 7 strips per workgroup, two wavefronts on each; M=32 walks K in phases
-        (4200, 14336, (1, 8)),  # long K, workgroups with 2 strips and with 1; M=8 walks K in phases
+        (28672, 4096, (1, 4, 16, 32)),  # Llama-8B gate/up: 7 strips per workgroup
+        (4200, 14336, (1, 8)),  # long K, workgroups with 2 strips and with 1
         (8200, 1000, (1, 32)),  # ragged everything, 3 strips per workgroup, two MFMA row tiles
     ],
 )

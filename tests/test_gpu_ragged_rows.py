@@ -58,7 +58,7 @@ def test_every_remainder(fmt, ofmt, K):
         (ams.FP533, O.FP533, 16 * 11 * 230, 1003, 3, "strips_per_wave=2"),
         (ams.FP6, O.FP6_E2M3, 20496, 96 * 12 - 5, 5, "side_groups=1"),
         (ams.FP433, O.FP433, 20496, 96 * 24 - 3, 1, "side_groups=1"),
-        (ams.FP45, O.FP45, 48, 9001, 32, "k_slices=1"),  # K in several phases
+        (ams.FP45, O.FP45, 48, 9001, 32, "phases=5 "),  # K in several phases
     ],
 )
 def test_every_launch_variant(fmt, ofmt, N, K, M, want):

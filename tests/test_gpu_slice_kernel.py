@@ -53,6 +53,8 @@ def test_strips_rows_and_records(fmt, ofmt, spw):
         wp, sc = dev(ams.ams_pack_codes(fmt, codes)), dev(scales)
         for M in Ms:
             plan = ams.ams_linear_plan(fmt, M, N, K)
+            few = (spw == 8 and n_rec <= 16) or (spw in (6, 7) and n_rec == 1)  # at M > 16 those are column_kernel's
+            assert plan.startswith("column " if M > 16 and few else "slice ") and f"strips_per_wg={spw} " in plan, plan
             X = synth.activations(M, K, 70 + M)
             ref = O.linear(codes[rows], scales[rows], X, ofmt)
             what = f"{ofmt.name} N={N} K={K} M={M}: {plan}"
@@ -83,6 +85,7 @@ def test_k_split_over_workgroups(fmt, ofmt, N, K, Ms):
         ref = O.linear(codes[rows], scales[rows], X, ofmt)
         x = dev(X)
         plan = ams.ams_linear_plan(fmt, M, N, K, with_workspace=True)
+        assert plan.startswith("slice ") and ("k_slices=1 " in plan) == (M == 4), plan
         what = f"{ofmt.name} N={N} K={K} M={M}: {plan}"
         first = ams.ams_linear_ws(wp, sc, x, N, fmt, ws)
         check(first, ref, rows, what)
@@ -92,10 +95,10 @@ def test_k_split_over_workgroups(fmt, ofmt, N, K, Ms):
         assert not ws[: 4 * 16384].any(), what
 
 
-def test_two_slices_that_do_not_divide_the_records():
-    # 8192 x 28672 takes two strips per workgroup and no split; with few rows and long K the slices are uneven
-    fmt, ofmt, N, K, M = ams.FP533, O.FP533, 1030, 96 * 131 + 8, 32
-    assert "k_slices=1" not in ams.ams_linear_plan(fmt, M, N, K, with_workspace=True)
+def test_slices_that_do_not_divide_the_records():
+    fmt, ofmt, N, K, M = ams.FP533, O.FP533, 1030, 96 * 131 + 8, 16  # 132 records in eight slices
+    plan = ams.ams_linear_plan(fmt, M, N, K, with_workspace=True)
+    assert plan.startswith("slice ") and "k_slices=8 " in plan, plan
     codes, scales, rows = problem(fmt, ofmt, N, K, 9)
     ws = torch.zeros(16 << 20, dtype=torch.uint8, device="cuda")
     X = synth.activations(M, K, 90)
@@ -119,9 +122,62 @@ def test_one_scale_per_run(fmt, ofmt, spw):
         for M in Ms:
             X = synth.activations(M, K, 60 + M)
             ref = O.linear(codes[rows], scales[rows], X, ofmt, sg)
-            what = f"{ofmt.name} N={N} K={K} M={M} run={sg}"
+            plan = ams.ams_linear_plan(fmt, M, N, K, with_workspace=2)
+            assert plan.startswith("column " if M > 16 and (spw == 8 and n_rec <= 16 or spw >= 6 and n_rec <= 2) else "slice "), plan
+            what = f"{ofmt.name} N={N} K={K} M={M} run={sg}: {plan}"
             x = dev(X)
             check(ams.ams_linear_grouped(wp, sc, sg, x, N, fmt), ref, rows, what)
             if M > 2:
                 x[M // 2] = float("inf")
                 check(ams.ams_linear_grouped(wp, sc, sg, x, N, fmt), ref, rows, "beside a row of infinities: " + what, [m for m in range(M) if m != M // 2])
+
+
+def scales_per_run(N, K, sg, seed):
+    """[rows padded to strips, runs] and the same in the order the kernels read."""
+    runs, n_strips = -(-K // sg), -(-N // 16)
+    scales = np.random.default_rng(seed).uniform(0.001, 0.01, size=(n_strips * 16, runs)).astype(np.float16)
+    return scales, np.ascontiguousarray(scales.reshape(n_strips, 16, runs).transpose(0, 2, 1))
+
+
+# (format, M, N, records, entry, kernel): both sides of the lines between slice_kernel and column_kernel on aligned rows
+LINES = [
+    ("FP433", 4, 48000, 1, "plain", "slice"), ("FP433", 3, 40965, 11, "grouped", "column"), ("FP433", 3, 40965, 16, "grouped", "slice"),
+    ("FP45", 4, 65536, 2, "plain", "column"), ("FP45", 4, 65531, 3, "plain", "slice"), ("FP6", 3, 128251, 1, "plain", "column"), ("FP6", 3, 128256, 3, "plain", "slice"),
+    ("FP425", 4, 65531, 1, "grouped", "column"), ("FP425", 3, 57339, 24, "grouped", "slice"), ("FP533", 3, 65536, 15, "grouped", "column"),
+    ("FP533", 4, 128251, 2, "grouped", "column"), ("FP533", 4, 128251, 3, "grouped", "slice"), ("FP4", 4, 65531, 9, "grouped", "column"),
+    ("FP533", 17, 32787, 79, "plain", "column"), ("FP533", 17, 32787, 80, "plain", "slice"), ("FP533", 32, 32787, 80, "plain", "slice"), ("FP4", 32, 32787, 80, "plain", "slice"),
+    ("FP4", 32, 32763, 16, "plain", "column"), ("FP533", 32, 32763, 17, "plain", "slice"), ("FP5", 32, 28667, 3, "plain", "slice"), ("FP5", 17, 28667, 2, "grouped", "column"),
+    ("FP425", 24, 24571, 1, "plain", "column"), ("FP425", 24, 24571, 2, "grouped", "column"), ("FP45", 16, 32763, 2, "plain", "column"),
+    ("FP425", 1, 4107, 97, "plain", "column"), ("FP533", 1, 6139, 97, "grouped", "column"), ("FP533", 1, 6139, 96, "plain", "slice"), ("FP6", 1, 7163, 97, "grouped", "column"),
+    ("FP5", 2, 7163, 145, "grouped", "column"), ("FP433", 1, 1003, 201, "plain", "column"), ("FP533", 1, 1003, 201, "grouped", "column"), ("FP45", 1, 1003, 250, "grouped", "column"),
+    ("FP533", 16, 2555, 198, "ws", "column"), ("FP425", 32, 2043, 200, "ws", "column"), ("FP533", 32, 5115, 64, "ws", "column"), ("FP45", 16, 7163, 64, "ws", "column"),
+    ("FP6", 16, 3579, 230, "ws", "column"), ("FP425", 32, 1531, 108, "ws", "column"), ("FP533", 16, 5115, 100, "ws", "slice"),
+]
+
+
+@pytest.mark.parametrize("name,M,N,n_rec,entry,kernel", LINES)
+def test_both_sides_of_the_lines(name, M, N, n_rec, entry, kernel):
+    fmt = getattr(ams, name)
+    ofmt = dict(PAIRS)[fmt]
+    K = REC_K[fmt] * n_rec - 8 * (n_rec % 3)  # the last record whole, or 8 or 16 channels short
+    plan = ams.ams_linear_plan(fmt, M, N, K, with_workspace={"plain": 0, "ws": 1, "grouped": 2}[entry])
+    assert plan.startswith(kernel + " ") and ("k_slices=1 " in plan) == (entry != "ws"), plan
+    codes, scales, rows = problem(fmt, ofmt, N, K, N + n_rec)
+    X = synth.activations(M, K, 50 + M)
+    wp, x = dev(ams.ams_pack_codes(fmt, codes)), dev(X)
+    what = f"{name} N={N} K={K} M={M} {entry}: {plan}"
+    if entry == "grouped":
+        sg = REC_K[fmt]
+        scales, packed = scales_per_run(N, K, sg, n_rec)
+        call = lambda: ams.ams_linear_grouped(wp, sc, sg, x, N, fmt)
+        sc, ref = dev(packed), O.linear(codes[rows], scales[rows], X, ofmt, sg)
+    else:
+        sc, ref = dev(scales), O.linear(codes[rows], scales[rows], X, ofmt)
+        ws = torch.zeros(16 << 20, dtype=torch.uint8, device="cuda")
+        call = lambda: ams.ams_linear_ws(wp, sc, x, N, fmt, ws) if entry == "ws" else ams.ams_linear(wp, sc, x, N, fmt)
+    first = call()
+    check(first, ref, rows, what)
+    assert torch.equal(call(), first), what
+    if entry == "ws":
+        assert torch.equal(ams.ams_linear_static_ws(wp, sc, x, N, fmt), first), what
+        assert not ws[: 4 * 16384].any(), what
