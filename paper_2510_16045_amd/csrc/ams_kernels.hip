@@ -1438,8 +1438,8 @@ bool short_slices_on_column(int fmt, int M, int spw, int gk, int n_rec_all) {
 //     4096 x 14336 FP5.33 M = 1 9.5 / 9.4, M = 2 10.1 / 10.1;
 //   one, two and four strips, M <= 2, long K: see long_k_on_column;
 //   six strips and more, M > 8, a few records: with fewer than eight of them wavefronts idle, the busy ones walk all
-//     strips one after the other, and the idle ones' tiles are written and summed too (32768 x 128 M = 32 0.75 x, 28672 x
-//     128 0.9 x); eight strips at M > 16, whose tiles fill 128 KiB, up to sixteen records (32768 x 1024 0.9 x; 28672 x 4096
+//     strips one after the other, and the idle ones' tiles are written and summed too (32768 x 128 M = 32 0.75 x, 24576
+//     x 192 0.9 x); eight strips at M > 16, whose tiles fill 128 KiB, up to sixteen records (32768 x 1024 0.9 x; 28672 x 4096
 //     FP5.33 M = 32 24.7 / 18.9);
 //   short slices of a split K: see short_slices_on_column;
 //   more than eight strips: see halved_is_faster.
@@ -1450,7 +1450,7 @@ ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k,
   if (long_k_on_column(fmt, M, p.spw, p.grid, n_rec_all, one_scale)) return p;
   if (short_slices_on_column(fmt, M, p.spw, gk, n_rec_all)) return p;
   if (gk == 1 && p.spw == 8 && n_rec_all <= (M > 16 ? 16 : M > 8 ? 2 : 0)) return p;
-  if (gk == 1 && M > 16 && ((p.spw == 6 && n_rec_all <= (one_scale ? 1 : 2)) || (p.spw == 7 && n_rec_all <= 2))) return p;
+  if (gk == 1 && M > 16 && (p.spw == 6 || p.spw == 7) && n_rec_all <= 2) return p;
   if (p.spw > kSliceMaxStrips) {
     if (gk != 1 || !halved_is_faster(fmt, M, n_strips, p.spw, n_rec_all, one_scale)) return p;
     p.spw = (p.spw + 1) / 2;

@@ -69,7 +69,7 @@ def test_more_than_eight_strips_where_two_workgroups_are_faster(fmt, M, N, K, en
         (17, 8, 16, 0, "column"), (32, 8, 1, GROUPED, "column"), (32, 8, 17, 0, "slice"), (32, 8, 17, GROUPED, "slice"),
         (16, 8, 2, 0, "column"), (16, 8, 3, 0, "slice"), (8, 8, 1, 0, "slice"),
         (32, 7, 2, 0, "column"), (32, 7, 3, 0, "slice"), (32, 7, 43, 0, "slice"), (16, 7, 1, GROUPED, "slice"),
-        (24, 6, 1, 0, "column"), (24, 6, 2, 0, "slice"), (24, 6, 2, GROUPED, "column"), (24, 6, 3, GROUPED, "slice"), (32, 5, 1, 0, "slice"),
+        (24, 6, 1, 0, "column"), (24, 6, 2, 0, "column"), (24, 6, 3, 0, "slice"), (24, 6, 2, GROUPED, "column"), (24, 6, 3, GROUPED, "slice"), (32, 5, 1, 0, "slice"),
     ],
 )
 def test_few_records_at_large_batches(fmt, M, strips, n_rec, entry, want):
