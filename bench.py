@@ -9,7 +9,7 @@ launches whose packed weights all stream from HBM.  To keep every launch cold, t
 step rotates through several resident copies of each packed matrix (a real decode
 step touches each layer's weights once per token and the model never fits a cache).
 
-stdout carries ONE JSON line of less than 8000 characters (a record that keeps the end of stdout
+stdout carries ONE JSON line, in a default run of less than 8000 characters (a record that keeps the end of stdout
 keeps all of it): whole-step packed-weight GB/s as `value`, per-layer figures (us per Linear,
 fraction of the 8 TB/s HBM peak and of a bare read of the same bytes, speed-up over the in-build
 fp16 Linear and the library GEMM) under `layers`, a `roofline` object for the dominant kernel,

@@ -1498,7 +1498,9 @@ void* const kStaticScratch = (void*)(uintptr_t)1;
 // moves: its weight records, half weight for the activations it stages (they come from
 // L2), and a fixed charge for the exchange through the workspace (fitted to measurements on
 // the Llama and Qwen shapes: below a batch of 4 the stream is bound by the memory system as a
-// whole and a split never paid).
+// whole and a split never paid).  For the packed formats it prices column_kernel, to which it was fitted; slice_kernel, which takes
+// the slices but for the short ones, stages nothing per phase and is now and then faster without the split (2560 x 9728
+// FP4.25 M = 16 9.7 us, split 10.0).
 int choose_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int rec_bytes) {
   if (M < 4) return 1;
   int best = 1;
