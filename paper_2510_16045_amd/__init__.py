@@ -159,15 +159,26 @@ def ams_unpack_host(fmt: int, packed: np.ndarray, N: int, K: int) -> np.ndarray:
     return codes
 
 
-def _stream():
-    """The current stream of the current device.  Read as the raw handle: building torch's Stream object
-    took 2.8 us of the 8.4 us that a whole call of ams_linear took, the handle takes 0.3."""
+_current_stream = None
+
+
+def _bind_current_stream():
     import torch
 
     raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # not a public name: a torch without it goes the long way
     if raw is None:
-        return torch.cuda.current_stream().cuda_stream
-    return raw(torch.cuda.current_device())
+        return lambda: torch.cuda.current_stream().cuda_stream
+    device = torch.cuda.current_device
+    return lambda: raw(device())
+
+
+def _stream():
+    """The current stream of the current device.  Read as the raw handle: building torch's Stream object
+    took 2.8 us of the 8.4 us that a whole call of ams_linear took, the handle takes 0.3."""
+    global _current_stream
+    if _current_stream is None:
+        _current_stream = _bind_current_stream()
+    return _current_stream()
 
 
 def _dev_ptr(t, dtype=None):

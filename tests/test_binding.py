@@ -27,6 +27,7 @@ def test_stream_without_torchs_private_name(monkeypatch):
     class Stream:
         cuda_stream = 123
 
+    monkeypatch.setattr(ams, "_current_stream", None)  # bound anew, and as before afterwards
     monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
     assert ams._stream() == 123
