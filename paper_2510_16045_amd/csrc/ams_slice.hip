@@ -111,10 +111,19 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
     // loads: lane -> row, block of four pieces, piece
     constexpr int BLK = 64 / (4 * RB);  // blocks of four pieces per load
     const int ld_m = (lane >> 2) & (RB - 1), ld_b = lane / (4 * RB);
+    // Requests past the wave's last record (p >= cnt) get an offset out of the buffer's range: they read no memory but
+    // count like the others.  (The scalar offset always stays inside the buffer: only the vector part is out of range.)
+    constexpr int FAR = 0x7FFE0000;
     const int row_bytes = a.K * 2;
-    int voff[MT];
+    // Lanes whose row does not exist, or whose block lies behind the record, ask for nothing (FAR, below): what they would
+    // bring takes cache lines from the weight stream.
+    int voff[MT], voff_last[MT];
 #pragma unroll
-    for (int t = 0; t < MT; t++) voff[t] = min(16 * t + ld_m, a.M - 1) * row_bytes + ld_b * 64 + (((lane & 3) ^ swz(ld_m)) * 16);
+    for (int t = 0; t < MT; t++) {
+      const int off = (16 * t + ld_m) * row_bytes + ld_b * 64 + (((lane & 3) ^ swz(ld_m)) * 16);
+      voff[t] = 16 * t + ld_m < a.M ? off : FAR;
+      voff_last[t] = ld_b + (P::NI1 - 1) * BLK < REC_K / 32 ? voff[t] : FAR;
+    }
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.X, 0, a.M * row_bytes, 0x00020000);
     // reads: operand u of this lane's activation row
     const int m_lo = lane & (RB - 1), kq = lane >> 4;
@@ -124,9 +133,6 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
       const int piece = kq * NF + u;
       roff[u] = (piece >> 2) * (RB * 64) + m_lo * 64 + (((piece & 3) ^ swz(m_lo)) * 16);
     }
-    // Requests past the wave's last record (p >= cnt) get an offset out of the buffer's range: they read no memory but
-    // count like the others.  (The scalar offset always stays inside the buffer: only the vector part is out of range.)
-    constexpr int FAR = 0x7FFF0000;
     auto request_x = [&](int p) {  // the wave's p-th record of activations
       const int soff = p < cnt ? (first + S * p) * (REC_K * 2) : 0;
       unsigned char* dst = xbuf + (p & (LX - 1)) * P::BYTES;
@@ -134,7 +140,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
       for (int t = 0; t < MT; t++)
 #pragma unroll
         for (int i = 0; i < P::NI1; i++) {
-          const int vo = p < cnt ? voff[t] + i * (BLK * 64) : FAR;
+          const int vo = p < cnt ? (i == P::NI1 - 1 ? voff_last[t] : voff[t]) + i * (BLK * 64) : FAR;
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(dst + (t * P::NI1 + i) * 1024), 16, vo, soff, 0, 0);
         }
     };
