@@ -159,6 +159,7 @@ struct LinearArgs {
   // split of K over gk workgroups per strip (sweep kernel with a workspace): workgroups along N,
   // slices of K, per-slice partial tiles [gk][strip][MT][64] f4, per-strip arrival counters
   int gn, gk;
+  int row_tiles, tile_rows;  // slice kernel: workgroups that share the rows of X, rows each of them takes (the last what is left)
   int wps;  // wavefronts that share a strip (sweep kernel: the workgroup works on S / wps strips at a time)
   int wpa;  // column kernel: how many of a strip's wps wavefronts take records (the others idle: a count that divides the work evenly)
   f4* ws_tiles;
@@ -341,6 +342,15 @@ constexpr int slice_lds(int fmt, int R, int NS) {
 constexpr bool slice_two_fit(int fmt, int strips) {
   return ams::kFormats[fmt].rec_k == 96 || strips <= (fmt == FMT_FP4 ? 7 : 6);
 }
+// Its arguments but for those that are needed before the first request: those are plain parameters, 14 dwords in all, which
+// the build has preloaded into scalar registers (with the address of one struct instead, every wavefront of a launch starts
+// with a trip to memory: 4096 x 4096 at M = 12 5.84 us, preloaded 5.69; 256 x 768 2.84, 2.78).
+struct SliceArgs {
+  uint16_t* Y;
+  f4* ws_tiles;
+  unsigned* ws_count;
+  int n_sg, sg_shift;
+};
 // The kernel for `rows` staged rows and `strips` strips per workgroup (nullptr: there is none).
 // GS: one scale per run of input channels.
 template <int FMT, bool GS>

@@ -1274,6 +1274,7 @@ struct ColumnPlan {
   int lr;   // records a wavefront keeps in flight beside the one it restores
   int ns;   // strips a wavefront owns alone (multi_kernel; 1: column_kernel); then wpa = wavefronts that own strips
   bool slice;  // slice_kernel: the wavefronts share K and take every record of all spw strips; S, spw, grid, gn, gk, lr and lds hold
+  int rows, row_tiles;  // slice_kernel: staged rows of X per workgroup, workgroups that share the rows
   size_t lds;
 };
 
@@ -1288,6 +1289,8 @@ ColumnPlan column_plan_for(int S, int lr, int fmt, int M, int64_t n_strips, int 
   ColumnPlan p;
   p.ns = ns;
   p.slice = false;
+  p.rows = M;
+  p.row_tiles = 1;
   const int sg = ams::side_group(ams::kFormats[fmt]);
   const int mt = M > 16 ? 2 : 1;
   const int mc = std::min(M, 16);
@@ -1431,6 +1434,34 @@ bool short_slices_on_column(int fmt, int M, int spw, int gk, int n_rec_all) {
   return M > 16 ? spw == 3 && n_rec <= (rec96 ? 29 : 16) : spw >= 5 && n_rec <= (rec96 ? 29 : 24);
 }
 
+// The rows of X dealt to several workgroups.  A compute unit draws its weights and its activations through one in-order path
+// that keeps 32 KiB (the lines of its cache) in flight, and every workgroup needs all of its rows' activations: at M = 32 on
+// one strip they are seven times the weights.  With `tiles` workgroups on one position along N, each with its share of the rows
+// and `tiles` times the strips, a compute unit moves fewer bytes; the weights are then read `tiles` times, once from memory
+// and else from the XCD's L2.  The cost of a step of K: the records of the strips, and 0.72 of the activations' cache lines (a
+// line out of L2 comes quicker than one out of memory); fitted to 108 shapes.  One scale per run costs every strip another 384
+// bytes' worth (4608 x 2368 FP5.33 M = 16 5.47 / 5.71, FP4.25 5888 x 22656 26.7 / 27.9).  us, one / two tiles: 4096 x 14336 FP4.25 M = 32
+// 20.3 / 16.4, M = 24 17.8 / 16.3, M = 16 13.9 / 13.2, M = 12 12.5 / 12.7; FP5.33 M = 32 22.6 / 18.3; 8192 x 8192 M = 32 15.7 / 14.5,
+// M = 16 11.7 / 12.9; 14336 x 4096 M = 32 12.9 / 13.1; 2560 x 9728 M = 24 12.8 / 11.1, three tiles 9.6.  Tiles of fewer than eight rows never
+// pay (2419 x 20352 FP5.33 M = 12 16.9, three tiles 19.2).  The bound on the records keeps a third record for some wavefront.
+constexpr int64_t kSplitMaxStrips = 16384;  // strips that the counters of a split of K have room for
+struct RowSplit {
+  int strips, positions;  // strips per workgroup; workgroups of one tile: whole groups of eight, so that the tiles of a position meet on one XCD
+  double cost;
+};
+double row_split_cost(int fmt, int strips, int rows, bool one_scale) {
+  return strips * (double)(ams::kFormats[fmt].rec_bytes + (one_scale ? 0 : 384)) + 0.72 * 256 * rows;
+}
+RowSplit row_split(int fmt, int M, int64_t n_strips, int gk, int tiles, bool one_scale) {
+  RowSplit s;
+  const int64_t most = kNumCU / tiles & ~7;
+  s.strips = (int)((n_strips * gk + most - 1) / most);
+  while ((s.positions = (int)(ams::round_up((n_strips + s.strips - 1) / s.strips * gk, 8))) > most) s.strips++;
+  s.cost = row_split_cost(fmt, s.strips, (M + tiles - 1) / tiles, one_scale);
+  return s;
+}
+constexpr int kMaxRowTiles = 4, kRowSplitMinRecords = 18, kRowSplitMinRows = 8;
+
 // The plan of a problem: slice_kernel where it takes it (aligned_rows: rows of X are 16-byte aligned, K % 8 == 0;
 // one_scale: one scale per row of W), else make_column_plan's.  slice_kernel is the faster one nearly everywhere
 // (twelve shapes, seven formats, M = 1 .. 32: 1.00-1.8 x); the exceptions, us column / slice:
@@ -1456,18 +1487,29 @@ ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k,
     p.spw = (p.spw + 1) / 2;
     p.grid = p.gn = (int)((n_strips + p.spw - 1) / p.spw);
   }
-  const int r = slice_rows(M);
+  if (M >= 2 * kRowSplitMinRows && n_rec_all / gk >= kRowSplitMinRecords && n_strips <= kSplitMaxStrips / kMaxRowTiles) {
+    double best = 0.97 * row_split_cost(fmt, p.spw, M, one_scale);
+    for (int t = 2; t <= kMaxRowTiles && t * kRowSplitMinRows <= M; t++) {
+      const RowSplit s = row_split(fmt, M, n_strips, gk, t, one_scale);
+      if (s.strips > kSliceMaxStrips || s.cost >= best) continue;
+      best = s.cost;
+      p.row_tiles = t;
+      p.spw = s.strips;
+      p.gn = (int)((n_strips + s.strips - 1) / s.strips);
+      p.grid = s.positions * t;
+    }
+  }
   p.slice = true;
-  p.S = slice_waves(r, p.spw);
+  p.rows = slice_rows((M + p.row_tiles - 1) / p.row_tiles);
+  p.S = slice_waves(p.rows, p.spw);
   p.lr = slice_ahead(p.S);
-  p.lds = (size_t)slice_lds(fmt, r, p.spw);
+  p.lds = (size_t)slice_lds(fmt, p.rows, p.spw);
   return p;
 }
 
 // Workspace of a split in gk slices: per-strip arrival counters, then the partial tiles.  The
 // counter area has one size for every shape, so that a workspace that is reused for another
 // shape never finds old tile data where it expects counters at zero.
-constexpr int64_t kSplitMaxStrips = 16384;
 constexpr size_t kSplitCounterBytes = (size_t)kSplitMaxStrips * 4;
 size_t split_workspace_bytes(int M, int64_t n_strips, int gk) {
   return gk <= 1 ? 0 : kSplitCounterBytes + (size_t)gk * n_strips * (M > 16 ? 2 : 1) * 1024;
@@ -1667,18 +1709,20 @@ int launch_multi(const LinearArgs& a, unsigned grid, int S, size_t lds, hipStrea
   return AMS_ERR_LAUNCH;
 }
 
-// slice_kernel for a.M rows and `strips` strips per workgroup.
+// slice_kernel for r staged rows and `strips` strips per workgroup.
 template <int FMT>
-int launch_slice(const LinearArgs& a, bool gs, int strips, unsigned grid, hipStream_t st) {
-  const int r = slice_rows(a.M);
+int launch_slice(const LinearArgs& a, bool gs, int r, int strips, unsigned grid, hipStream_t st) {
   const void* kern = gs ? slice_kernel_of<FMT, true>(r, strips) : slice_kernel_of<FMT, false>(r, strips);
   if (!kern) return AMS_ERR_LAUNCH;
   const size_t lds = (size_t)slice_lds(FMT, r, strips);
   if (lds > 64 * 1024 && !raise_lds_limit(kern)) return AMS_ERR_LAUNCH;
   if (grid == 0) return AMS_OK;
-  LinearArgs copy = a;
-  void* args[] = {&copy};
-  return hipLaunchKernel(kern, dim3(grid), dim3(64 * slice_waves(r, strips)), args, lds, st) == hipSuccess ? AMS_OK : AMS_ERR_LAUNCH;
+  const uint8_t* W = a.W;
+  const uint16_t *X = a.X, *scales = a.scales;
+  int M = a.M, N = a.N, K = a.K, n_rec = a.n_rec, n_strips = a.n_strips, gn = a.gn, gk = a.gk, tile_rows = a.tile_rows;
+  SliceArgs rest = {a.Y, a.ws_tiles, a.ws_count, a.n_sg, a.sg_shift};
+  void* args[] = {&W, &X, &scales, &M, &N, &K, &n_rec, &n_strips, &gn, &gk, &tile_rows, &rest};
+  return hipLaunchKernel(kern, dim3(grid / a.row_tiles, a.row_tiles), dim3(64 * slice_waves(r, strips)), args, lds, st) == hipSuccess ? AMS_OK : AMS_ERR_LAUNCH;
 }
 
 template <int FMT>
@@ -1721,6 +1765,8 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
   }
   a.gn = 1;
   a.gk = 1;
+  a.row_tiles = 1;
+  a.tile_rows = M;
   a.wps = 1;
   a.wpa = 1;
   a.ws_tiles = nullptr;
@@ -1751,6 +1797,8 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
     const ColumnPlan cp = make_plan(FMT, M, n_strips, n_rec, REC_K, gk, K % 8 == 0, scale_group == 0, nt);
     a.gn = cp.gn;
     a.gk = cp.gk;
+    a.row_tiles = cp.row_tiles;
+    a.tile_rows = (M + cp.row_tiles - 1) / cp.row_tiles;
     a.wps = cp.wps;
     a.wpa = cp.wpa;
     use_split(cp.gk);
@@ -1759,7 +1807,7 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
     a.x_shift = cp.x_shift;
     a.spw = cp.spw;
     a.rc = cp.rc;
-    if (cp.slice) return launch_slice<FMT>(a, scale_group != 0, cp.spw, cp.grid, st);
+    if (cp.slice) return launch_slice<FMT>(a, scale_group != 0, cp.rows, cp.spw, cp.grid, st);
     if (cp.ns > 1) return launch_multi<FMT>(a, cp.grid, cp.S, cp.lds, st);
     return M <= 16 ? launch_column<FMT, 1>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st)
                    : launch_column<FMT, 2>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st);
@@ -1804,9 +1852,9 @@ int prepare_format() {
   LinearArgs a = {};
   bool ok = true;
   if constexpr (FMT != FMT_FP16) {
-    for (a.M = 4; a.M <= 32; a.M *= 2)
+    for (int r = 4; r <= 32; r *= 2)
       for (int strips = 1; strips <= kSliceMaxStrips; strips++)
-        for (int gs = 0; gs < 2; gs++) ok &= launch_slice<FMT>(a, gs != 0, strips, 0, nullptr) == AMS_OK;
+        for (int gs = 0; gs < 2; gs++) ok &= launch_slice<FMT>(a, gs != 0, r, strips, 0, nullptr) == AMS_OK;
     for (a.K = 8; a.K < 10; a.K++) {  // aligned and ragged rows of X
       for (int nt = 0; nt < 2; nt++)
         for (int gs = 0; gs < 2; gs++)
@@ -1973,11 +2021,14 @@ int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, ch
   if (f != FMT_FP16) {
     const bool nt = n_strips * n_rec * (int64_t)rec_bytes >= (2ll << 20);  // as run_linear decides it
     const ColumnPlan cp = make_plan(f, M, n_strips, n_rec, rec_k, gk, K % 8 == 0, !grouped, nt);
-    if (cp.slice)
-      snprintf(text, text_len, "slice grid=%d strips_per_wg=%d k_slices=%d waves=%d lds=%zu ahead=%d", cp.grid, cp.spw, cp.gk, cp.S, cp.lds, cp.lr);
-    else
+    if (cp.slice) {
+      const int len = snprintf(text, text_len, "slice grid=%d strips_per_wg=%d k_slices=%d waves=%d lds=%zu ahead=%d", cp.grid, cp.spw, cp.gk, cp.S, cp.lds, cp.lr);
+      if (cp.row_tiles > 1 && len > 0 && (size_t)len < text_len)
+        snprintf(text + len, text_len - len, " row_tiles=%d rows_per_tile=%d", cp.row_tiles, (M + cp.row_tiles - 1) / cp.row_tiles);
+    } else {
       snprintf(text, text_len, "column grid=%d strips_per_wg=%d k_slices=%d waves=%d waves_per_strip=%d phases=%d lds=%zu side_groups=%d active_per_strip=%d ahead=%d strips_per_wave=%d", cp.grid,
                cp.spw, cp.gk, cp.S, cp.wps, cp.n_phase, cp.lds, cp.qd ? 1 : 0, cp.ns > 1 ? 1 : cp.wpa, cp.lr, cp.ns);
+    }
     return AMS_OK;
   }
   if (const GemvPlan gp = make_gemv_plan(M, K, gk); gp.ok) {

@@ -74,25 +74,38 @@ struct Slice {
 // sum; the four scales of a lane's output channels are one 8-byte load that travels with the record.  28672 x 4096
 // FP4.25, a scale per 128: M = 1 15.7 -> 12.8 us, M = 4 15.9 -> 13.5, M = 32 23.5 -> 20.2 (column_kernel before).
 template <int FMT, int R, int NS, bool GS>
-__global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(LinearArgs a) {
+__global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(const uint8_t* W, const uint16_t* X, const uint16_t* scales, int M, int N, int K, int n_rec,
+                                                                         int n_strips, int gn, int gk_slices, int tile_rows, SliceArgs a) {
   using P = Slice<FMT, R, NS, GS>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int FAR = 0x7FFE0000;  // an offset beyond the range of every buffer
   constexpr int REC_K = Fmt<FMT>::REC_K, SG = Fmt<FMT>::SG, NF = Fmt<FMT>::N_MFMA, PB = Fmt<FMT>::PB, UNIT = Fmt<FMT>::UNIT;
   constexpr int MT = P::MT, RB = P::RB, LX = P::LX, LW = P::LW, RS = P::RS, U = P::U, S = P::S;
   static_assert(LW < RS, "weight ring");
-  asm volatile("" ::"s"(a.W), "s"(a.scales), "s"(a.X), "s"(a.Y), "s"(a.M), "s"(a.N), "s"(a.K), "s"(a.n_rec), "s"(a.n_strips), "s"(a.gn), "s"(a.gk));
+  asm volatile("" ::"s"(W), "s"(X), "s"(scales), "s"(M), "s"(K), "s"(n_rec), "s"(n_strips), "s"(gn), "s"(gk_slices));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // workgroup = (position g along N, slice gk of K)
-  const int gk = a.gk > 1 ? (int)(blockIdx.x / (unsigned)a.gn) : 0;
-  const int s_first = ((int)blockIdx.x - gk * a.gn) * NS;
-  const int ns = min(NS, a.n_strips - s_first);
-  const int rec_lo = a.gk > 1 ? (int)((unsigned)(gk * a.n_rec) / (unsigned)a.gk) : 0;
-  const int rec_hi = a.gk > 1 ? (int)((unsigned)((gk + 1) * a.n_rec) / (unsigned)a.gk) : a.n_rec;
+  // Workgroup = (position wg along N and slice of K, row tile of X).  The row tiles of a position read the same weights at
+  // the same time: the grid is then rounded up to whole groups of eight along x, which puts them on one XCD and its L2.
+  const int wg = blockIdx.x;
+  if (wg >= gn * gk_slices) return;
+  const int m_first = (int)blockIdx.y * tile_rows;
+  const int rows = min(tile_rows, M - m_first);
+  const int gk = gk_slices > 1 ? (int)((unsigned)wg / (unsigned)gn) : 0;
+  const int s_first = (wg - gk * gn) * NS;
+  const int ns = min(NS, n_strips - s_first);
+  const int rec_lo = gk_slices > 1 ? (int)((unsigned)(gk * n_rec) / (unsigned)gk_slices) : 0;
+  const int rec_hi = gk_slices > 1 ? (int)((unsigned)((gk + 1) * n_rec) / (unsigned)gk_slices) : n_rec;
   const int first = rec_lo + wave;  // this wave's records: first, first + S, ...
   const int cnt = first < rec_hi ? (rec_hi - first + S - 1) / S : 0;
-  uint16_t scale_bits = 0x3C00;
-  if (!GS && tid < NS * 16) scale_bits = a.scales[min(s_first * 16 + tid, a.N - 1)];
+  // The scales of the workgroup's channels are asked for ahead of the stream and not touched before its end.  (Behind a
+  // branch, the compiler moved their conversion up to the load: the first wavefront then waited for memory before its
+  // first record.)  Threads beyond them, and channels beyond N, ask for nothing and get 0.
+  uint32_t scale_bits = 0x3C00;
+  if (!GS && wave < (NS * 16 + 63) / 64) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)scales, 0, N * 2, 0x00020000);
+    scale_bits = __builtin_amdgcn_raw_buffer_load_b16(rs, tid < NS * 16 ? (s_first * 16 + tid) * 2 : FAR, 0, 0);
+  }
   __builtin_amdgcn_sched_barrier(0);
 
   f4 acc[NS][MT];
@@ -113,18 +126,17 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
     const int ld_m = (lane >> 2) & (RB - 1), ld_b = lane / (4 * RB);
     // Requests past the wave's last record (p >= cnt) get an offset out of the buffer's range: they read no memory but
     // count like the others.  (The scalar offset always stays inside the buffer: only the vector part is out of range.)
-    constexpr int FAR = 0x7FFE0000;
-    const int row_bytes = a.K * 2;
+    const int row_bytes = K * 2;
     // Lanes whose row does not exist, or whose block lies behind the record, ask for nothing (FAR, below): what they would
     // bring takes cache lines from the weight stream.
     int voff[MT], voff_last[MT];
 #pragma unroll
     for (int t = 0; t < MT; t++) {
       const int off = (16 * t + ld_m) * row_bytes + ld_b * 64 + (((lane & 3) ^ swz(ld_m)) * 16);
-      voff[t] = 16 * t + ld_m < a.M ? off : FAR;
-      voff_last[t] = ld_b + (P::NI1 - 1) * BLK < REC_K / 32 ? voff[t] : FAR;
+      voff[t] = 16 * t + ld_m < rows ? off : FAR;
+      voff_last[t] = P::NI1 * BLK == REC_K / 32 || ld_b + (P::NI1 - 1) * BLK < REC_K / 32 ? voff[t] : FAR;
     }
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.X, 0, a.M * row_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(X + (size_t)m_first * K), 0, rows * row_bytes, 0x00020000);
     // reads: operand u of this lane's activation row
     const int m_lo = lane & (RB - 1), kq = lane >> 4;
     int roff[NF];
@@ -151,7 +163,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
     Scales ring_sc[GS ? RS : 1];
     auto request_w = [&](int p, int i, LaneRec<FMT>& slot, Scales& sc) {  // the weights of strip i for the wave's p-th record
       const unsigned rec = p < cnt ? (first + S * p) : 0;
-      const uint8_t* unit = a.W + ((size_t)(rec / SG) * (unsigned)a.n_strips + (unsigned)(s_first + min(i, ns - 1))) * UNIT;
+      const uint8_t* unit = W + ((size_t)(rec / SG) * (unsigned)n_strips + (unsigned)(s_first + min(i, ns - 1))) * UNIT;
       const __amdgpu_buffer_rsrc_t w = __builtin_amdgcn_make_buffer_rsrc((void*)unit, 0, UNIT, 0x00020000);
       const int vo = p < cnt ? lane * Fmt<FMT>::CHUNK : FAR;
       buffer_load_chunk<Fmt<FMT>::CHUNK>(slot.w, w, vo, (int)(rec % SG) * Fmt<FMT>::CB);
@@ -160,13 +172,13 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
         buffer_load_chunk<4>(&slot.t, w, vs, SG * Fmt<FMT>::CB);
       }
       if constexpr (GS) {  // cached: a run spans many records and rows of lanes
-        const uint16_t* run = a.scales + ((size_t)(s_first + min(i, ns - 1)) * a.n_sg + (rec >> a.sg_shift)) * 16;
+        const uint16_t* run = scales + ((size_t)(s_first + min(i, ns - 1)) * a.n_sg + (rec >> a.sg_shift)) * 16;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)run, 0, 32, 0x00020000);
         const int vg = p < cnt ? kq * 8 : FAR;
         buffer_load_chunk<8, 0>(sc.h, rs, vg, 0);
       }
     };
-    const int tail = a.n_rec * REC_K - a.K;  // channels of the last record beyond K
+    const int tail = n_rec * REC_K - K;  // channels of the last record beyond K
 
     // One record of all strips.  uc: its place in the unrolled round.  The wait lets through exactly the loads requested
     // after this record's activations: every step makes the same requests, those past the end out of range.
@@ -195,10 +207,10 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
       asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
       const int rec = (first + S * p);
-      if (tail != 0 && rec == a.n_rec - 1) {  // channels beyond K: whatever was read there counts as zero
+      if (tail != 0 && rec == n_rec - 1) {  // channels beyond K: whatever was read there counts as zero
 #pragma unroll
         for (int u = 0; u < NF; u++) {
-          const uint32_t keep = rec * REC_K + (kq * NF + u) * 8 < a.K ? 0xFFFFFFFFu : 0u;
+          const uint32_t keep = rec * REC_K + (kq * NF + u) * 8 < K ? 0xFFFFFFFFu : 0u;
 #pragma unroll
           for (int t = 0; t < MT; t++) b[t][u] &= u4{keep, keep, keep, keep};
         }
@@ -279,11 +291,12 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the requests past the end are done with LDS
   }
+  asm volatile("" : "+v"(scale_bits));
   __syncthreads();
   // Partial tiles [wave][strip][activation row][16 channels, padded], then the scales, then who was last.
   float* const parts = (float*)smem;
-  float* const scales = parts + S * NS * R * P::ROW;
-  int* const last = (int*)(scales + NS * 16);
+  float* const scale_of = parts + S * NS * R * P::ROW;
+  int* const last = (int*)(scale_of + NS * 16);
   {
     const int m_lo = lane & 15, kq = lane >> 4;
     if (m_lo < RB)
@@ -292,13 +305,14 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
 #pragma unroll
         for (int t = 0; t < MT; t++) *(f4*)(parts + ((wave * NS + i) * R + 16 * t + m_lo) * P::ROW + 4 * kq) = acc[i][t];
   }
-  if (tid < NS * 16) scales[tid] = (float)__builtin_bit_cast(_Float16, scale_bits) * kTwo14;
+  if (tid < NS * 16) scale_of[tid] = (float)__builtin_bit_cast(_Float16, (uint16_t)scale_bits) * kTwo14;
   __syncthreads();
   // One output per thread, the wavefronts' sums added in wave order.
+  uint16_t* const Y = a.Y + (size_t)m_first * N;
   const int n = tid & 15;
   auto finish = [&](int i, int m, float sum) {
     const int row = (s_first + i) * 16 + n;
-    if (row < a.N) a.Y[(size_t)m * a.N + row] = __builtin_bit_cast(uint16_t, (_Float16)(sum * scales[i * 16 + n]));
+    if (row < N) Y[(size_t)m * N + row] = __builtin_bit_cast(uint16_t, (_Float16)(sum * scale_of[i * 16 + n]));
   };
   auto tile_sum = [&](int i, int m) {
     float sum = 0;
@@ -306,26 +320,29 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
     for (int w = 0; w < S; w++) sum += parts[((w * NS + i) * R + m) * P::ROW + n];
     return sum;
   };
-  const int pairs = a.M * NS;
-  if (a.gk == 1) {
+  const int pairs = rows * NS;
+  if (gk_slices == 1) {
     for (int r = tid >> 4; r < pairs; r += 4 * S) finish(r % NS, r / NS, tile_sum(r % NS, r / NS));
     return;
   }
   // K is split over gk workgroups: the same exchange as in finish_strip, with the workgroup's barriers around the count
   // (every wave's stores are acknowledged before any strip is counted in).
+  const int tile = M > 16 ? 512 : 256;  // floats of a strip's tile: the rows of all row tiles
+  float* const tiles = (float*)a.ws_tiles + m_first * 16;
+  unsigned* const counts = a.ws_count + s_first * (int)gridDim.y + blockIdx.y;  // of this row tile: one per strip
   for (int r = tid >> 4; r < pairs; r += 4 * S) {
     const int i = r % NS, m = r / NS;
     if (i < ns) {
-      float* wt = (float*)a.ws_tiles + ((size_t)gk * a.n_strips + s_first + i) * (MT * 256) + m * 16 + n;
+      float* wt = tiles + ((size_t)gk * n_strips + s_first + i) * tile + m * 16 + n;
       __hip_atomic_store(wt, tile_sum(i, m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid < ns) {
-    const unsigned before = __hip_atomic_fetch_add(a.ws_count + s_first + tid, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const bool is_last = before == (unsigned)a.gk - 1;
-    if (is_last) __hip_atomic_store(a.ws_count + s_first + tid, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned before = __hip_atomic_fetch_add(counts + tid * gridDim.y, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool is_last = before == (unsigned)gk_slices - 1;
+    if (is_last) __hip_atomic_store(counts + tid * gridDim.y, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     last[tid] = is_last;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -334,9 +351,8 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
     const int i = r % NS, m = r / NS;
     if (i < ns && last[i]) {
       float sum = 0;
-      for (int q = 0; q < a.gk; q++)
-        sum += __hip_atomic_load((const float*)a.ws_tiles + ((size_t)q * a.n_strips + s_first + i) * (MT * 256) + m * 16 + n, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
+      for (int q = 0; q < gk_slices; q++)
+        sum += __hip_atomic_load(tiles + ((size_t)q * n_strips + s_first + i) * tile + m * 16 + n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       finish(i, m, sum);
     }
   }
