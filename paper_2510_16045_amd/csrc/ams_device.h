@@ -313,6 +313,9 @@ __device__ __forceinline__ void permute_unit(const uint32_t (&in)[Fmt<FMT>::PB /
 }
 
 constexpr int kLdsMaxBytes = 160 * 1024;  // LDS of a gfx950 compute unit
+constexpr int kOutOfRange = 0x7FFE0000;   // an offset beyond the range of every buffer: such a lane's load reads no memory and gives 0
+constexpr int kDeviceScope = 16;          // cache policy (sc1) of a buffer load or store that the whole device sees
+constexpr int kMaxSlices = 8;             // slices of K that workgroups may share
 
 // ---- slice_kernel (ams_slice.hip): what its launch needs ------------------------------------------
 constexpr int kSliceMaxStrips = 8;  // strips per workgroup it is built for

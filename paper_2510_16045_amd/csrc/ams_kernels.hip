@@ -176,6 +176,45 @@ __device__ __forceinline__ void store_tile_scaled(const f4 t[MT], const f4 sc, c
   }
 }
 
+// K is split over gk workgroups: every one leaves its partial tile in the workspace and counts itself in; the one that
+// arrives last adds all gk tiles in slice order (so the result does not depend on who was last) and clears the counter
+// for the next call.  Nobody waits for anybody.  True, with the sum, for the one that arrived last.
+// The tiles travel by stores and loads with the device's cache policy (they go to the level of the memory system all
+// compute units share).  What orders them: the wave waits until every one of its tile stores has been acknowledged
+// (s_waitcnt vmcnt(0): on this target stores count in vmcnt) before it counts itself in, and the last arriver's tile loads
+// are issued only after its own count has come back (the branch below depends on it).  A device-scope fence would
+// instead write back and invalidate the whole L2, which costs more than the Linear itself.
+// 16 bytes per lane, and the tiles of all slices are asked for before the first is added: element by element and slice by
+// slice every one of them was a trip to memory (7168 x 8192 FP5.33 M = 16, four slices, 14.4 -> 12.8 us).
+template <int MT>
+__device__ __forceinline__ bool exchange_tile(const LinearArgs& a, int gk, int strip, f4 (&sum)[MT], int lane) {
+  const __amdgpu_buffer_rsrc_t tiles = __builtin_amdgcn_make_buffer_rsrc((void*)a.ws_tiles, 0, a.gk * a.n_strips * MT * 1024, 0x00020000);
+  auto offset = [&](int slice, int t) { return (((slice * a.n_strips + strip) * MT + t) * 64 + lane) * 16; };
+#pragma unroll
+  for (int t = 0; t < MT; t++) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, sum[t]), tiles, offset(gk, t), 0, kDeviceScope);
+  // all tile stores of this wave acknowledged; the compiler moves no memory access across either statement
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  unsigned before = 0;
+  if (lane == 0) before = __hip_atomic_fetch_add(a.ws_count + strip, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  before = __builtin_amdgcn_readfirstlane(before);
+  if (before != (unsigned)a.gk - 1) return false;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the count has returned; the tile loads below are issued after it
+  f4 part[kMaxSlices][MT];
+#pragma unroll
+  for (int q = 0; q < kMaxSlices; q++)
+#pragma unroll
+    for (int t = 0; t < MT; t++)  // slices that do not exist read nothing and add 0
+      part[q][t] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(tiles, q < a.gk ? offset(q, t) : kOutOfRange, 0, kDeviceScope));
+#pragma unroll
+  for (int t = 0; t < MT; t++) {
+    sum[t] = f4{0, 0, 0, 0};
+#pragma unroll
+    for (int q = 0; q < kMaxSlices; q++) sum[t] += part[q][t];
+  }
+  if (lane == 0) __hip_atomic_store(a.ws_count + strip, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+
 // The streaming Linear.  A workgroup owns `spw` consecutive strips and walks K in
 // phases of `rc` records per strip (one phase when the activations M x K fit in LDS).
 // Inside a phase its work is the list of (strip, record) pairs in strip-major order;
@@ -535,41 +574,7 @@ __global__ void __launch_bounds__(1024) sweep_kernel(LinearArgs a) {
       }
     }
     const int strip = g + j * G;
-    if (a.gk > 1) {
-      // K is split over gk workgroups: every one leaves its partial tile in the workspace and
-      // counts itself in; the one that arrives last adds all gk tiles in slice order (so the
-      // result does not depend on who was last), finishes the strip and clears the counter
-      // for the next call.  Nobody waits for anybody.
-      // The tiles travel as device-scope relaxed atomic stores and loads (they go to the level
-      // of the memory system all compute units share).  What orders them: the wave waits until
-      // every one of its tile stores has been acknowledged (s_waitcnt vmcnt(0): on this target
-      // stores count in vmcnt) before it counts itself in, and the last arriver's tile loads are
-      // issued only after its own count has come back (the branch below depends on it).  A
-      // device-scope fence would instead write back and invalidate the whole L2, which costs
-      // more than the Linear itself.
-      float* wt = (float*)(a.ws_tiles + ((size_t)gk * a.n_strips + strip) * MT * 64 + lane);
-#pragma unroll
-      for (int t = 0; t < MT; t++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) __hip_atomic_store(wt + t * 256 + r, sum[t][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      // all tile stores of this wave acknowledged; the compiler moves no memory access across either statement
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      unsigned before = 0;
-      if (lane == 0) before = __hip_atomic_fetch_add(a.ws_count + strip, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      before = __builtin_amdgcn_readfirstlane(before);
-      if (before != (unsigned)a.gk - 1) continue;
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the count has returned; the tile loads below are issued after it
-#pragma unroll
-      for (int t = 0; t < MT; t++) sum[t] = f4{0, 0, 0, 0};
-      for (int q = 0; q < a.gk; q++) {
-        const float* rt = (const float*)(a.ws_tiles + ((size_t)q * a.n_strips + strip) * MT * 64 + lane);
-#pragma unroll
-        for (int t = 0; t < MT; t++)
-#pragma unroll
-          for (int r = 0; r < 4; r++) sum[t][r] += __hip_atomic_load(rt + t * 256 + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      if (lane == 0) __hip_atomic_store(a.ws_count + strip, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (a.gk > 1 && !exchange_tile<MT>(a, gk, strip, sum, lane)) continue;
     store_tile_scaled<MT>(sum, f4{1.0f, 1.0f, 1.0f, 1.0f}, a, strip, lane);  // the baseline has no scales
   }
 }
@@ -666,41 +671,7 @@ __global__ void __launch_bounds__(1024) gemv_fp16_kernel(LinearArgs a) {
 // K split over gk workgroups, through the workspace.
 template <int MT>
 __device__ __forceinline__ void finish_strip(const LinearArgs& a, int gk, int out_strip, f4 (&sum)[MT], const f4 sc, int lane) {
-  if (a.gk > 1) {
-    // K is split over gk workgroups: every one leaves its partial tile in the workspace and
-    // counts itself in; the one that arrives last adds all gk tiles in slice order (so the
-    // result does not depend on who was last), finishes the strip and clears the counter
-    // for the next call.  Nobody waits for anybody.
-    // The tiles travel as device-scope relaxed atomic stores and loads (they go to the level
-    // of the memory system all compute units share).  What orders them: the wave waits until
-    // every one of its tile stores has been acknowledged (s_waitcnt vmcnt(0): on this target
-    // stores count in vmcnt) before it counts itself in, and the last arriver's tile loads are
-    // issued only after its own count has come back (the branch below depends on it).  A
-    // device-scope fence would instead write back and invalidate the whole L2, which costs
-    // more than the Linear itself.
-    float* wt = (float*)(a.ws_tiles + ((size_t)gk * a.n_strips + out_strip) * MT * 64 + lane);
-#pragma unroll
-    for (int t = 0; t < MT; t++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) __hip_atomic_store(wt + t * 256 + r, sum[t][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // all tile stores of this wave acknowledged; the compiler moves no memory access across either statement
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    unsigned before = 0;
-    if (lane == 0) before = __hip_atomic_fetch_add(a.ws_count + out_strip, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    before = __builtin_amdgcn_readfirstlane(before);
-    if (before != (unsigned)a.gk - 1) return;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the count has returned; the tile loads below are issued after it
-#pragma unroll
-    for (int t = 0; t < MT; t++) sum[t] = f4{0, 0, 0, 0};
-    for (int q = 0; q < a.gk; q++) {
-      const float* rt = (const float*)(a.ws_tiles + ((size_t)q * a.n_strips + out_strip) * MT * 64 + lane);
-#pragma unroll
-      for (int t = 0; t < MT; t++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) sum[t][r] += __hip_atomic_load(rt + t * 256 + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (lane == 0) __hip_atomic_store(a.ws_count + out_strip, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (a.gk > 1 && !exchange_tile<MT>(a, gk, out_strip, sum, lane)) return;
   store_tile_scaled<MT>(sum, sc, a, out_strip, lane);
 }
 
@@ -1529,7 +1500,7 @@ GemvPlan make_gemv_plan(int M, int64_t K, int gk) {
   return p;
 }
 
-constexpr int kMaxSplit = 8;  // most slices of K choose_split ever takes
+constexpr int kMaxSplit = kMaxSlices;  // most slices of K choose_split ever takes
 // passed as the workspace by the entry point that uses the library's static scratch instead
 void* const kStaticScratch = (void*)(uintptr_t)1;
 
