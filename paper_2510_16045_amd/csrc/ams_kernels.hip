@@ -1501,6 +1501,7 @@ GemvPlan make_gemv_plan(int M, int64_t K, int gk) {
 }
 
 constexpr int kMaxSplit = kMaxSlices;  // most slices of K choose_split ever takes
+constexpr size_t kStaticScratchBytes = ((size_t)64 << 10) + ((size_t)8 << 20);  // of ams_linear_static_ws
 // passed as the workspace by the entry point that uses the library's static scratch instead
 void* const kStaticScratch = (void*)(uintptr_t)1;
 
@@ -1514,7 +1515,7 @@ void* const kStaticScratch = (void*)(uintptr_t)1;
 // whole and a split never paid).  For the packed formats it prices column_kernel, to which it was fitted; slice_kernel, which takes
 // the slices but for the short ones, stages nothing per phase and is now and then faster without the split (2560 x 9728
 // FP4.25 M = 16 9.7 us, split 10.0).
-int choose_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int rec_bytes) {
+int cheapest_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int rec_bytes) {
   if (M < 4) return 1;
   int best = 1;
   double best_cost = 0;
@@ -1549,6 +1550,30 @@ int choose_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int rec
   return best;
 }
 
+// Time of a plan in us, slices with aligned rows: the bytes of row_split_cost at 47 KB a microsecond, the sum over the
+// wavefronts' tiles, and for a split the exchange.  Fitted to 197 shapes with and without their split (9 % r.m.s.).
+double plan_time(const ColumnPlan& p, int fmt, int M, int n_rec) {
+  const int rows = (M + p.row_tiles - 1) / p.row_tiles;
+  const double tiles = p.spw * rows / 100.0;
+  const double t = 2.1 + (n_rec + p.gk - 1) / p.gk * row_split_cost(fmt, p.spw, rows, true) / 46500.0 + 3.25 * tiles;
+  return p.gk > 1 ? t + 3.05 - 1.7 * tiles : t;
+}
+
+// The split that a call with a workspace uses.  On short K the exchange costs more than the slices save, now that the plain
+// call deals the rows of X: whichever plan_time prefers.  us, split / whole: 896 x 2880 FP4.25 M = 32 7.0 / 4.0, 4096 x 4096 M = 32 8.4 /
+// 7.2, 1226 x 5760 FP5.33 M = 16 6.4 / 5.2; 82 shapes 1.22x, none slower by more than 3 %.  From K = 9216 on the two are
+// within their spread of each other (2560 x 9728 M = 16 9.7 / 8.1) and the split stays.
+constexpr int kSplitShortK = 9216;
+int choose_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int rec_bytes, int64_t K) {
+  const int gk = cheapest_split(fmt, M, n_strips, n_rec, rec_k, rec_bytes);
+  if (gk == 1 || fmt == FMT_FP16 || K >= kSplitShortK || K % 8 != 0) return gk;
+  // a split that the static scratch refuses stays refused
+  if (split_workspace_bytes(M, n_strips, gk) > kStaticScratchBytes) return gk;
+  const ColumnPlan split = make_plan(fmt, M, n_strips, n_rec, rec_k, gk, true, true, true);
+  const ColumnPlan whole = make_plan(fmt, M, n_strips, n_rec, rec_k, 1, true, true, true);
+  return whole.slice && split.slice && plan_time(whole, fmt, M, n_rec) < plan_time(split, fmt, M, n_rec) ? 1 : gk;
+}
+
 // Per-device state, set up once per device with that device current: whether it is the GPU
 // this library is written for, and where this device's copy of the static scratch lives.
 constexpr int kMaxDevices = 64;
@@ -1562,7 +1587,6 @@ DeviceState g_dev[kMaxDevices];
 // Scratch of the entry point that may not allocate (ams_linear_static_ws): the arrival counters
 // and partial tiles of a split of K.  One copy per GPU, held until the process ends.  In host
 // code this name is only a handle for hipGetSymbolAddress, never a device address.
-constexpr size_t kStaticScratchBytes = ((size_t)64 << 10) + ((size_t)8 << 20);
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 // AMS_OK when the current device is a gfx950 with the compute units and LDS the launch plans
@@ -1748,7 +1772,7 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
   int gk = 1;
   if (workspace && scale_group == 0) {
     if (!aligned16(workspace)) return AMS_ERR_ALIGN;
-    gk = choose_split(FMT, M, n_strips, n_rec, REC_K, REC_BYTES);
+    gk = choose_split(FMT, M, n_strips, n_rec, REC_K, REC_BYTES, K);
     if (split_workspace_bytes(M, n_strips, gk) > ws_bytes) {
       if (static_ws) return AMS_ERR_SCRATCH;  // beyond the static array: refused, never silently another plan
       gk = 1;                                 // a caller's workspace that is too small: no split
@@ -1972,7 +1996,7 @@ int ams_linear_workspace_bytes(int fmt, int M, int64_t N, int64_t K, size_t* byt
   }
   const int64_t n_strips = (N + 15) / 16;
   const int n_rec = (int)((K + rec_k - 1) / rec_k);
-  *bytes = split_workspace_bytes(M, n_strips, choose_split(f, M, n_strips, n_rec, rec_k, rec_bytes));
+  *bytes = split_workspace_bytes(M, n_strips, choose_split(f, M, n_strips, n_rec, rec_k, rec_bytes, K));
   return AMS_OK;
 }
 
@@ -1988,7 +2012,7 @@ int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, ch
   const int64_t n_strips = (N + 15) / 16;
   const int n_rec = (int)((K + rec_k - 1) / rec_k);
   const bool grouped = with_workspace == 2;  // ams_linear_grouped
-  const int gk = with_workspace && !grouped ? choose_split(f, M, n_strips, n_rec, rec_k, rec_bytes) : 1;
+  const int gk = with_workspace && !grouped ? choose_split(f, M, n_strips, n_rec, rec_k, rec_bytes, K) : 1;
   if (f != FMT_FP16) {
     const bool nt = n_strips * n_rec * (int64_t)rec_bytes >= (2ll << 20);  // as run_linear decides it
     const ColumnPlan cp = make_plan(f, M, n_strips, n_rec, rec_k, gk, K % 8 == 0, !grouped, nt);
