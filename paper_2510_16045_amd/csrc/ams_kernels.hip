@@ -1562,11 +1562,12 @@ double plan_time(const ColumnPlan& p, int fmt, int M, int n_rec) {
 // The split that a call with a workspace uses.  On short K the exchange costs more than the slices save, now that the plain
 // call deals the rows of X: whichever plan_time prefers.  us, split / whole: 896 x 2880 FP4.25 M = 32 7.0 / 4.0, 4096 x 4096 M = 32 8.4 /
 // 7.2, 1226 x 5760 FP5.33 M = 16 6.4 / 5.2; 82 shapes 1.22x, none slower by more than 3 %.  From K = 9216 on the two are
-// within their spread of each other (2560 x 9728 M = 16 9.7 / 8.1) and the split stays.
-constexpr int kSplitShortK = 9216;
+// within their spread of each other (2560 x 9728 M = 16 9.7 / 8.1) and the split stays; at M = 4 and one strip per workgroup from
+// 12800 on (1920 x 9920 FP5.33 7.6 / 6.6, 1117 x 14080 FP4.25 7.0 / 7.7; with two strips 4480 x 10240 9.5 / 10.3).
+constexpr int64_t split_short_k(int M, int64_t n_strips) { return M == 4 && n_strips <= kNumCU ? 12800 : 9216; }
 int choose_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int rec_bytes, int64_t K) {
   const int gk = cheapest_split(fmt, M, n_strips, n_rec, rec_k, rec_bytes);
-  if (gk == 1 || fmt == FMT_FP16 || K >= kSplitShortK || K % 8 != 0) return gk;
+  if (gk == 1 || fmt == FMT_FP16 || K >= split_short_k(M, n_strips) || K % 8 != 0) return gk;
   // a split that the static scratch refuses stays refused
   if (split_workspace_bytes(M, n_strips, gk) > kStaticScratchBytes) return gk;
   const ColumnPlan split = make_plan(fmt, M, n_strips, n_rec, rec_k, gk, true, true, true);

@@ -355,15 +355,26 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
     if (i >= ns || !last[i]) continue;
     f4 part[kMaxSlices];
 #pragma unroll
-    for (int q = 0; q < kMaxSlices; q++)  // slices that do not exist read nothing and add 0
+    for (int q = 0; q < kMaxSlices; q++) part[q] = f4{0, 0, 0, 0};
+    auto request = [&](int q) {  // slices that do not exist read nothing and add 0
       part[q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(tiles, q < gk_slices ? tile_offset(q, i, m, c) : FAR, 0, kDeviceScope));
+    };
+    request(0), request(1);
+    if (gk_slices > 2) request(2), request(3);
+    if (gk_slices > 4) request(4), request(5), request(6), request(7);
     f4 sum = f4{0, 0, 0, 0};
 #pragma unroll
     for (int q = 0; q < kMaxSlices; q++) sum += part[q];
+    const int row = (s_first + i) * 16 + c;
+    us4 h;
 #pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const int row = (s_first + i) * 16 + c + r;
-      if (row < N) Y[(size_t)m * N + row] = __builtin_bit_cast(uint16_t, (_Float16)(sum[r] * scale_of[i * 16 + c + r]));
+    for (int r = 0; r < 4; r++) h[r] = __builtin_bit_cast(uint16_t, (_Float16)(sum[r] * scale_of[i * 16 + c + r]));
+    if ((N & 3) == 0) {  // whole quads of channels, eight aligned bytes of Y's row
+      if (row < N) *(us4*)(Y + (size_t)m * N + row) = h;
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; r++)
+        if (row + r < N) Y[(size_t)m * N + row + r] = h[r];
     }
   }
 }
