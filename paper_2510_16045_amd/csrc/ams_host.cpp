@@ -90,7 +90,7 @@ inline int reround_magnitude_code(double a, int mbits, int m0) {
 }
 
 struct RowQuant {
-  int mbits, group;
+  int fmt, mbits, group;
   double fmax;
   int search;  // AMS_SEARCH_*
 };
@@ -176,10 +176,236 @@ struct Steps {
   }
 };
 
+// ---- many groups at a time ----------------------------------------------------
+// The quantizer of Sec. 3.1 on vectors of L groups (16 with AVX-512, 8 with AVX2): lane g of member vector p is weight p
+// of group g.  The codes are the ones of candidates() and of the search in quantize_row, bit for bit: what is decided in
+// binary32 is decided again in binary64, with their operations in their order, wherever the first decision is closer than
+// its error allows.  Plain vector arithmetic, compiled for both instruction sets and called where the processor has them.
+// Bound by vector arithmetic (about 50 operations per member vector).  A strip of 16 x 4096 FP5.33 weights on one core of an EPYC with
+// AVX-512: quantized and packed 92 -> 32 us (codes looked up and placed by table -> wide_records), FP6, codes then table, 109 -> 50.
+#define AMS_INLINE __attribute__((always_inline)) inline
+template <class T, int L>
+using Vec = T __attribute__((ext_vector_type(L)));
+
+template <class V>
+AMS_INLINE V load_vec(const void* p) {
+  V v;
+  std::memcpy(&v, p, sizeof(v));
+  return v;
+}
+
+// Members 0 .. G-1 of L groups of G neighbouring weights.
+template <int G, int L>
+AMS_INLINE void load_members(const uint16_t* w, Vec<uint16_t, L> (&m)[G]) {
+  if constexpr (G == 1) {
+    m[0] = load_vec<Vec<uint16_t, L>>(w);
+  } else {
+    constexpr int HALF = G == 2 ? L : 2 * L;  // weights of the first of the two vectors that are shuffled
+    typedef Vec<uint16_t, HALF> V;
+    const V a = load_vec<V>(w);
+    V b = 0;
+    std::memcpy(&b, w + HALF, (G * L - HALF) * 2);
+#define AMS_PICK8(p, o) (o) * G + p, (o + 1) * G + p, (o + 2) * G + p, (o + 3) * G + p, (o + 4) * G + p, (o + 5) * G + p, (o + 6) * G + p, (o + 7) * G + p
+#define AMS_PICK(p)                                                              \
+  if constexpr (p < G) {                                                         \
+    if constexpr (L == 8)                                                        \
+      m[p < G ? p : 0] = __builtin_shufflevector(a, b, AMS_PICK8(p, 0));                  \
+    else                                                                         \
+      m[p < G ? p : 0] = __builtin_shufflevector(a, b, AMS_PICK8(p, 0), AMS_PICK8(p, 8)); \
+  }
+    AMS_PICK(0) AMS_PICK(1) AMS_PICK(2) AMS_PICK(3)
+#undef AMS_PICK
+#undef AMS_PICK8
+  }
+}
+
+// Codes without their last bit (the candidates with shared bit 0) and the chosen last bit of L groups, in binary64.
+template <int G, int L, int MBITS>
+AMS_INLINE void quantize_groups_exactly(const Vec<uint16_t, L> (&w)[G], double s, Vec<int32_t, L> (&upper)[G], Vec<int32_t, L>& last) {
+  typedef Vec<double, L> D;
+  constexpr double one = 1 << MBITS;  // code of 1.0
+  D sse0 = 0, sse1 = 0;
+#pragma unroll
+  for (int p = 0; p < G; p++) {
+    const Vec<uint16_t, L> mag = w[p] & (uint16_t)0x7FFF;
+    const D aw = __builtin_convertvector(__builtin_convertvector(__builtin_bit_cast(Vec<_Float16, L>, mag), Vec<float, L>), D);
+    const D a = aw / s;
+    // the grid is uniform below 2, in [2, 4) and from 4 on (rtn_magnitude_code)
+    const D scale = a < 2.0 ? (D)one : (a < 4.0 ? (D)(one * 0.5) : (D)(one * 0.25));
+    const D first = a < 2.0 ? (D)0.0 : (a < 4.0 ? (D)one : (D)(2 * one));
+    D code = first + ((a * scale + 0x1.8p52) - 0x1.8p52);
+    code = code < 4 * one - 1 ? code : (D)(4 * one - 1);
+    upper[p] = __builtin_convertvector(code, Vec<int32_t, L>) & ~1;
+    // magnitudes of the candidates: both lie in one piece of the grid, neighbours a step apart
+    const D c0 = __builtin_convertvector(upper[p], D);
+    const D base = c0 < 2 * one ? (D)0.0 : (c0 < 3 * one ? (D)one : (D)(2 * one));
+    const D step = c0 < 2 * one ? (D)(1 / one) : (c0 < 3 * one ? (D)(2 / one) : (D)(4 / one));
+    const D v0 = (c0 - base) * step;
+    const D d0 = v0 * s - aw, d1 = (v0 + step) * s - aw;  // Eq. 2 with last bit 0 and 1
+    sse0 = sse0 + d0 * d0;
+    sse1 = sse1 + d1 * d1;
+  }
+  last = __builtin_convertvector(sse1 < sse0, Vec<int32_t, L>) & 1;  // a tie keeps 0
+}
+
+// The same from a = |w| * rs, rs = 1 / s in binary32, which is within 2^-22 of |w| / s of its own size.
+//   code: a times the inverse step is at most 16 where the code is not the largest, so it is off by 2^-18; it rounds to
+//     the same integer unless it lies within 2^-16 of a half.  (Where a is on the other side of 2 or 4 than the quotient, the
+//     pieces of the grid meet there and give the same code.)
+//   last bit: the difference of the squared errors, in units of s^2, is the sum of step * (2 (v0 - a) + step).  A term is off
+//     by step * (2^-21 a + 2^-22 step) at most, its sums' rounding by less than that: its sign holds beyond 2^-19 of the sum
+//     of step * (a + step).
+// The largest magnitude is 7.5 times the scale, so a above 16 means a scale that was rounded among the smallest binary16
+// numbers.
+template <int G, int L, int MBITS>
+AMS_INLINE void quantize_groups(const Vec<uint16_t, L> (&w)[G], double s, float rs, Vec<int32_t, L> (&upper)[G], Vec<int32_t, L>& last) {
+  typedef Vec<float, L> F;
+  constexpr float one = 1 << MBITS;
+  F diff = 0, size = 0, nearest = 0, largest = 0;
+#pragma unroll
+  for (int p = 0; p < G; p++) {
+    const Vec<uint16_t, L> mag = w[p] & (uint16_t)0x7FFF;
+    const F a = __builtin_convertvector(__builtin_bit_cast(Vec<_Float16, L>, mag), F) * rs;
+    const F scale = a < 2.0f ? (F)one : (a < 4.0f ? (F)(one * 0.5f) : (F)(one * 0.25f));
+    const F first = a < 2.0f ? (F)0.0f : (a < 4.0f ? (F)one : (F)(2 * one));
+    const F x = a * scale, r = __builtin_elementwise_roundeven(x);
+    nearest = __builtin_elementwise_max(nearest, __builtin_elementwise_abs(x - r));
+    largest = __builtin_elementwise_max(largest, a);
+    const F code = __builtin_elementwise_min(first + r, (F)(4 * one - 1));
+    upper[p] = __builtin_convertvector(code, Vec<int32_t, L>) & ~1;
+    const F c0 = __builtin_convertvector(upper[p], F);
+    const F base = c0 < 2 * one ? (F)0.0f : (c0 < 3 * one ? (F)one : (F)(2 * one));
+    const F step = c0 < 2 * one ? (F)(1 / one) : (c0 < 3 * one ? (F)(2 / one) : (F)(4 / one));
+    const F d0 = (c0 - base) * step - a;
+    diff = diff + step * (d0 + d0 + step);
+    size = size + step * (a + step);
+  }
+  last = (diff < 0.0f) & 1;
+  if (__builtin_reduce_or((nearest > 0.5f - 0x1p-16f) | (largest > 16.0f) | (__builtin_elementwise_abs(diff) <= size * 0x1p-19f)))
+    quantize_groups_exactly<G, L, MBITS>(w, s, upper, last);
+}
+
+// 1 where a weight is negative (not of -0)
+template <int L>
+AMS_INLINE Vec<int32_t, L> sign_of(const Vec<uint16_t, L>& w) {
+  return (__builtin_convertvector(w, Vec<int32_t, L>) > 0x8000) & 1;
+}
+
+// Whole vectors of L groups of a row (or run) from weight k on, as codes; returns where they end.
+template <int G, int L, int MBITS>
+AMS_INLINE int64_t wide_codes(const uint16_t* w, int64_t k, int64_t K, double s, float rs, uint8_t* codes) {
+  for (; k + L * G <= K; k += L * G) {
+    Vec<uint16_t, L> m[G];
+    Vec<int32_t, L> upper[G], last;
+    load_members<G, L>(w + k, m);
+    quantize_groups<G, L, MBITS>(m, s, rs, upper, last);
+    uint8_t c[G][L];
+#pragma unroll
+    for (int p = 0; p < G; p++) {
+      const Vec<uint8_t, L> v = __builtin_convertvector(upper[p] | last | sign_of<L>(m[p]) << (2 + MBITS), Vec<uint8_t, L>);
+      if constexpr (G == 1)
+        std::memcpy(codes + k, &v, L);
+      else
+        std::memcpy(c[p], &v, L);
+    }
+    if constexpr (G > 1) {
+      for (int g = 0; g < L; g++)
+        for (int p = 0; p < G; p++) codes[k + g * G + p] = c[p][g];
+    }
+  }
+  return k;
+}
+
+// Whole records of row r of strip t, straight into the packed matrix, for the two formats whose half-words are whole
+// sharing groups; w points at the row's record `rec`.
+template <int FMT, int L>
+AMS_INLINE void wide_records(const uint16_t* w, int64_t rec, int64_t rec_end, double s, uint8_t* packed, int64_t n_strips, int64_t t, int r) {
+  static_assert(FMT == ams::kFmtFp533 || FMT == ams::kFmtFp425, "half-words that are groups");
+  constexpr FormatInfo fi = ams::kFormats[FMT];
+  constexpr int G = fi.group, MBITS = fi.code_bits - 3;
+  const float rs = 1.0f / (float)s;
+  for (; rec < rec_end; rec++, w += fi.rec_k) {
+    const ams::RecordPlace rp = ams::record_place(fi, n_strips, t, rec);
+    for (int h0 = 0; h0 < 32; h0 += L) {  // half-words of the record: eight to a lane chunk
+      Vec<uint16_t, L> m[G];
+      Vec<int32_t, L> upper[G], last;
+      load_members<G, L>(w + h0 * G, m);
+      quantize_groups<G, L, MBITS>(m, s, rs, upper, last);
+      Vec<int32_t, L> hw = FMT == ams::kFmtFp533 ? last << 12 : (Vec<int32_t, L>)0;
+#pragma unroll
+      for (int p = 0; p < G; p++) {
+        constexpr int sign_at[2][4] = {{15, 12, 14, 13}, {15, 14, 13, 0}};
+        hw |= sign_of<L>(m[p]) << sign_at[FMT == ams::kFmtFp533][p] | (upper[p] >> 1) << (FMT == ams::kFmtFp533 ? 8 - 4 * p : 9 - 3 * p);
+      }
+      const Vec<uint16_t, L> out = __builtin_convertvector(hw, Vec<uint16_t, L>);
+      uint32_t bits = 0;  // FP4.25: the groups' last bits, one per half-word
+      if constexpr (FMT == ams::kFmtFp425) {
+        Vec<int32_t, L> at;
+#pragma unroll
+        for (int x = 0; x < L; x++) at[x] = x / 8 * 8 + 4 * (x & 1) + (x & 7) / 2;  // of half-word 2d + h: bit 4h + d of its chunk's byte
+        bits = (uint32_t)__builtin_reduce_or(last << at);
+      }
+#pragma unroll
+      for (int c = 0; c < L / 8; c++) {
+        const int lane = (h0 / 8 + c) * 16 + r;
+        std::memcpy(packed + rp.chunks + lane * 16, (const uint8_t*)&out + 16 * c, 16);
+        if constexpr (FMT == ams::kFmtFp425) packed[rp.side + 4 * lane + rp.side_shift / 8] = (uint8_t)(bits >> (8 * c));
+      }
+    }
+  }
+}
+
+// One row (or run) in one format, for one instruction set.
+struct WideRow {
+  int64_t (*codes)(int fmt, const uint16_t* w, int64_t K, double s, uint8_t* codes);
+  void (*records)(int fmt, const uint16_t* w, int64_t rec, int64_t rec_end, double s, uint8_t* packed, int64_t n_strips, int64_t t, int r);
+};
+template <int L>
+AMS_INLINE int64_t wide_codes_of(int fmt, const uint16_t* w, int64_t k, int64_t K, double s, uint8_t* codes) {
+  const float rs = 1.0f / (float)s;
+  switch (fmt) {
+    case ams::kFmtFp533: return wide_codes<3, L, 3>(w, k, K, s, rs, codes);
+    case ams::kFmtFp425: return wide_codes<4, L, 2>(w, k, K, s, rs, codes);
+    case ams::kFmtFp45: return wide_codes<2, L, 2>(w, k, K, s, rs, codes);
+    case ams::kFmtFp433: return wide_codes<3, L, 2>(w, k, K, s, rs, codes);
+    case ams::kFmtFp6: return wide_codes<1, L, 3>(w, k, K, s, rs, codes);
+    case ams::kFmtFp5: return wide_codes<1, L, 2>(w, k, K, s, rs, codes);
+    default: return wide_codes<1, L, 1>(w, k, K, s, rs, codes);
+  }
+}
+template <int L>
+AMS_INLINE void wide_records_of(int fmt, const uint16_t* w, int64_t rec, int64_t rec_end, double s, uint8_t* packed, int64_t n_strips, int64_t t, int r) {
+  if (fmt == ams::kFmtFp533)
+    wide_records<ams::kFmtFp533, L>(w, rec, rec_end, s, packed, n_strips, t, r);
+  else
+    wide_records<ams::kFmtFp425, L>(w, rec, rec_end, s, packed, n_strips, t, r);
+}
+#define AMS_AVX512 __attribute__((target("avx512f,avx512bw,avx512dq,avx512vl,f16c")))
+#define AMS_AVX2 __attribute__((target("avx2,f16c")))
+AMS_AVX512 int64_t codes_avx512(int fmt, const uint16_t* w, int64_t K, double s, uint8_t* codes) {
+  return wide_codes_of<8>(fmt, w, wide_codes_of<16>(fmt, w, 0, K, s, codes), K, s, codes);
+}
+AMS_AVX2 int64_t codes_avx2(int fmt, const uint16_t* w, int64_t K, double s, uint8_t* codes) { return wide_codes_of<8>(fmt, w, 0, K, s, codes); }
+AMS_AVX512 void records_avx512(int fmt, const uint16_t* w, int64_t rec, int64_t rec_end, double s, uint8_t* packed, int64_t n_strips, int64_t t, int r) {
+  wide_records_of<16>(fmt, w, rec, rec_end, s, packed, n_strips, t, r);
+}
+AMS_AVX2 void records_avx2(int fmt, const uint16_t* w, int64_t rec, int64_t rec_end, double s, uint8_t* packed, int64_t n_strips, int64_t t, int r) {
+  wide_records_of<8>(fmt, w, rec, rec_end, s, packed, n_strips, t, r);
+}
+// What this processor has of them (nullptr: neither; the codes are then looked up).
+const WideRow* wide_row() {
+  static const WideRow avx512 = {codes_avx512, records_avx512}, avx2 = {codes_avx2, records_avx2};
+  static const WideRow* const have = __builtin_cpu_supports("avx512f") && __builtin_cpu_supports("avx512bw") && __builtin_cpu_supports("avx512dq") &&
+                                             __builtin_cpu_supports("avx512vl") && __builtin_cpu_supports("f16c")
+                                         ? &avx512
+                                     : __builtin_cpu_supports("avx2") && __builtin_cpu_supports("f16c") ? &avx2 : nullptr;
+  return have;
+}
+
 // Quantize one row (or run): scale (Eq. 1), RTN, adaptive search of each group's shared bit.  Returns false on inf/NaN.
 // forced_scale: 0 = the row's own scale (Eq. 1 per output channel), else the fp16 bits to use.
-// 4096 x 4096 FP5.33, packing included, on 16 threads: 1.9 ms with the codes looked up, 36 ms when every weight was divided, rounded
-// and compared by itself with library calls; the squared errors are computed as before, in fp64 and member order.
+// 4096 x 4096 FP5.33, packing included, on 16 threads: 0.9 ms in vectors, 2.2 ms with the codes looked up (the re-rounding
+// search, processors without AVX2), 36 ms when every weight was divided, rounded and compared by itself with library calls.
 bool quantize_row(const RowQuant& q, const uint16_t* w, int64_t K, uint8_t* codes, uint16_t* scale_out, Steps& steps, uint16_t forced_scale = 0) {
   const uint16_t absmax = abs_max_bits(w, K);
   if (absmax >= 0x7C00) return false;
@@ -189,7 +415,8 @@ bool quantize_row(const RowQuant& q, const uint16_t* w, int64_t K, uint8_t* code
   const int sign_shift = 2 + q.mbits;
   // Looking codes up pays from about 200 weights per scale on (finding the intervals takes as long as evaluating that
   // many): 3971 x 400 FP5.33 3.3 -> 2.0 ms on 8 threads, 8000 x 200 3.5 -> 3.3, 16384 x 128 4.8 -> 5.9.
-  const bool lookup = K >= 192;
+  const WideRow* const wide = q.search == AMS_SEARCH_SET_BIT ? wide_row() : nullptr;
+  const bool lookup = !wide && K >= 192;
   if (lookup) steps.build(q, s, absmax);
   auto finish = [&](int64_t k, int mag_code) {
     const uint16_t wk = w[k];
@@ -198,6 +425,7 @@ bool quantize_row(const RowQuant& q, const uint16_t* w, int64_t K, uint8_t* code
   auto groups = [&](auto group_c) {
     constexpr int G = decltype(group_c)::value;
     int64_t k0 = 0;
+    if (wide) k0 = wide->codes(q.fmt, w, K, s, codes);
     if (lookup) {
       for (; k0 + G <= K; k0 += G) {
         int iv[G];
@@ -273,18 +501,19 @@ struct PlaceTable {
   }
 };
 
-// Writes the records of strip t of a packed matrix of n_strips strips.  codes: 16 rows of K bytes
-// (row pointer NULL = padding row).  Records beyond K that pad the last side group hold zero codes.
+// Writes the records of strip t of a packed matrix of n_strips strips, from record `first` on.  codes: 16 rows of their K - first *
+// rec_k codes (row pointer NULL = padding row).  Records beyond K that pad the last side group hold zero codes.
 template <int FMT>
-void pack_strip_of(const uint8_t* const rows[16], int64_t K, uint8_t* packed, int64_t n_strips, int64_t t) {
+void pack_strip_of(const uint8_t* const rows[16], int64_t K, uint8_t* packed, int64_t n_strips, int64_t t, int64_t first) {
   static const PlaceTable<FMT> table;
   constexpr FormatInfo fi = ams::kFormats[FMT];
   const int64_t n_rec = ams::round_up(ams::round_up(K, fi.rec_k) / fi.rec_k, ams::side_group(fi));
-  for (int64_t j = 0; j < n_rec; j++) {
+  K -= first * fi.rec_k;
+  for (int64_t j = first; j < n_rec; j++) {
     const ams::RecordPlace rp = ams::record_place(fi, n_strips, t, j);
     for (int l = 0; l < ams::kLanes; l++) {
       const uint8_t* row = rows[l & 15];
-      const int64_t kbase = j * fi.rec_k + (int64_t)(l >> 4) * fi.lane_k;
+      const int64_t kbase = (j - first) * fi.rec_k + (int64_t)(l >> 4) * fi.lane_k;
       uint64_t words[4] = {0, 0, 0, 0};
       if (row && kbase + fi.lane_k <= K) {
 #pragma unroll
@@ -302,16 +531,59 @@ void pack_strip_of(const uint8_t* const rows[16], int64_t K, uint8_t* packed, in
   }
 }
 
-void pack_strip(int fmt, const uint8_t* const rows[16], int64_t K, uint8_t* packed, int64_t n_strips, int64_t t) {
+void pack_strip(int fmt, const uint8_t* const rows[16], int64_t K, uint8_t* packed, int64_t n_strips, int64_t t, int64_t first = 0) {
   switch (fmt) {
-    case ams::kFmtFp533: return pack_strip_of<ams::kFmtFp533>(rows, K, packed, n_strips, t);
-    case ams::kFmtFp425: return pack_strip_of<ams::kFmtFp425>(rows, K, packed, n_strips, t);
-    case ams::kFmtFp45: return pack_strip_of<ams::kFmtFp45>(rows, K, packed, n_strips, t);
-    case ams::kFmtFp433: return pack_strip_of<ams::kFmtFp433>(rows, K, packed, n_strips, t);
-    case ams::kFmtFp6: return pack_strip_of<ams::kFmtFp6>(rows, K, packed, n_strips, t);
-    case ams::kFmtFp5: return pack_strip_of<ams::kFmtFp5>(rows, K, packed, n_strips, t);
-    default: return pack_strip_of<ams::kFmtFp4>(rows, K, packed, n_strips, t);
+    case ams::kFmtFp533: return pack_strip_of<ams::kFmtFp533>(rows, K, packed, n_strips, t, first);
+    case ams::kFmtFp425: return pack_strip_of<ams::kFmtFp425>(rows, K, packed, n_strips, t, first);
+    case ams::kFmtFp45: return pack_strip_of<ams::kFmtFp45>(rows, K, packed, n_strips, t, first);
+    case ams::kFmtFp433: return pack_strip_of<ams::kFmtFp433>(rows, K, packed, n_strips, t, first);
+    case ams::kFmtFp6: return pack_strip_of<ams::kFmtFp6>(rows, K, packed, n_strips, t, first);
+    case ams::kFmtFp5: return pack_strip_of<ams::kFmtFp5>(rows, K, packed, n_strips, t, first);
+    default: return pack_strip_of<ams::kFmtFp4>(rows, K, packed, n_strips, t, first);
   }
+}
+
+// Strip t quantized and packed in one pass over its weights, where the format's half-words are whole sharing groups: whole
+// records straight into the packed matrix, the rest of the rows and the padding as codes.  run: weights per scale (K, or a
+// multiple of the record).  scale_of(r, j): where run j of row r keeps its scale.  Returns false on inf/NaN.
+template <class ScaleOf>
+bool quantize_and_pack_strip(const RowQuant& q, const FormatInfo& fi, const WideRow& wide, const uint16_t* W, int64_t N, int64_t K, int64_t ldw, int64_t run,
+                             uint16_t forced_scale, uint8_t* packed, int64_t n_strips, int64_t t, Steps& steps, ScaleOf&& scale_of) {
+  const int64_t whole = K / fi.rec_k, rest = K - whole * fi.rec_k;
+  uint8_t rest_codes[16][128];
+  const uint8_t* rows[16];
+  bool finite = true;
+  for (int r = 0; r < 16; r++) {
+    const int64_t n = t * 16 + r;
+    rows[r] = n < N ? rest_codes[r] : nullptr;
+    if (n >= N) {  // a row of zero codes
+      for (int64_t j = 0; j < whole; j++) {
+        const ams::RecordPlace rp = ams::record_place(fi, n_strips, t, j);
+        for (int c = 0; c < 4; c++) {
+          std::memset(packed + rp.chunks + (c * 16 + r) * fi.chunk_bytes, 0, (size_t)fi.chunk_bytes);
+          std::memset(packed + rp.side + 4 * (c * 16 + r) + rp.side_shift / 8, 0, (size_t)fi.side_bytes);
+        }
+      }
+      continue;
+    }
+    const uint16_t* w = W + n * ldw;
+    for (int64_t a = 0, j = 0; a < K; a += run, j++) {
+      const int64_t end = std::min(K, a + run);
+      const uint16_t absmax = abs_max_bits(w + a, end - a);
+      if (absmax >= 0x7C00) {
+        finite = false;
+        continue;
+      }
+      const uint16_t sb = forced_scale ? forced_scale : scale_bits(absmax, q.fmax);
+      *scale_of(r, j) = sb;
+      const int64_t rec_end = std::min(end / fi.rec_k, whole);
+      wide.records(q.fmt, w + a, a / fi.rec_k, rec_end, half_to_double(sb), packed, n_strips, t, r);
+      uint16_t same;
+      if (end > whole * fi.rec_k) quantize_row(q, w + whole * fi.rec_k, rest, rest_codes[r], &same, steps, sb);
+    }
+  }
+  pack_strip(q.fmt, rows, K, packed, n_strips, t, whole);
+  return finite;
 }
 
 void unpack_strip(int fmt, const FormatInfo& fi, const uint8_t* packed, int64_t n_strips, int64_t t, int64_t K, uint8_t* const rows[16]) {
@@ -341,6 +613,19 @@ void unpack_strip(int fmt, const FormatInfo& fi, const uint8_t* packed, int64_t 
   }
 }
 
+// Whether strips are quantized and packed in one pass: nobody asks for the codes, and the format and the processor allow it.
+const WideRow* one_pass(const RowQuant& q, const uint8_t* codes_out) {
+  const bool fits = (q.fmt == ams::kFmtFp533 || q.fmt == ams::kFmtFp425) && q.search == AMS_SEARCH_SET_BIT && !codes_out;
+  return fits ? wide_row() : nullptr;
+}
+
+// Time of a weight in the packer, on one thread: in one pass, with the codes apart, one by one (long rows are looked up and
+// faster; on those all threads start anyway).
+double quantize_ns(const RowQuant& q, const WideRow* in_one_pass) {
+  if (q.search == AMS_SEARCH_REROUND) return 30;
+  return in_one_pass ? 0.4 : wide_row() ? 0.8 : 6;
+}
+
 int check_shape(int fmt, int64_t N, int64_t K) {
   if (!ams::format_info(fmt)) return AMS_ERR_FORMAT;
   if (N <= 0 || K <= 0 || N > (int64_t)1 << 24 || K > (int64_t)1 << 24) return AMS_ERR_SHAPE;
@@ -349,10 +634,14 @@ int check_shape(int fmt, int64_t N, int64_t K) {
 
 // Runs body(0 .. n-1) on up to 16 threads.  False when a body threw (the only thing these bodies can
 // throw is std::bad_alloc from their row buffers); a thread that cannot be started just means fewer workers.
+// ns: what the whole work takes one thread.  Starting a thread costs the starter about 12 us, so the sum of both is
+// least with the square root of work / 10 us: 256 x 4096 weights, 0.5 ms of work, 142 us on 7 or 8 threads, 229 on sixteen.
+// (Threads that start threads in turn: 168 and 273 us.)
 template <class F>
-bool parallel_for(int64_t n, F&& body) {
+bool parallel_for(int64_t n, double ns, F&& body) {
   unsigned hw = std::thread::hardware_concurrency();
-  int64_t nt = std::max<int64_t>(1, std::min<int64_t>({(int64_t)(hw ? hw : 1), (int64_t)16, n}));
+  const int64_t worth = (int64_t)std::ceil(std::sqrt(ns / 10e3));
+  int64_t nt = std::max<int64_t>(1, std::min<int64_t>({(int64_t)(hw ? hw : 1), (int64_t)16, n, worth}));
   std::atomic<int64_t> next{0};
   std::atomic<int> failed{0};
   auto work = [&] {
@@ -456,7 +745,7 @@ int pack_rows(int fmt, int search, bool per_tensor, const uint16_t* W, int64_t N
   if (!W || !packed || !scales) return AMS_ERR_NULL;
   if (ldw < K) return AMS_ERR_SHAPE;
   const FormatInfo& fi = *ams::format_info(fmt);
-  const RowQuant rq = {fi.code_bits - 3, fi.group, fi.fmax, search};
+  const RowQuant rq = {fmt, fi.code_bits - 3, fi.group, fi.fmax, search};
   const int64_t n_strips = ams::round_up(N, ams::kStripRows) / ams::kStripRows;
   uint16_t tensor_scale = 0;
   if (per_tensor) {  // Eq. 1 with the maximum over the whole matrix
@@ -466,9 +755,16 @@ int pack_rows(int fmt, int search, bool per_tensor, const uint16_t* W, int64_t N
     tensor_scale = scale_bits(absmax, fi.fmax);
   }
   std::atomic<int> bad{0};
-  const bool done = parallel_for(n_strips, [&](int64_t t) {
-    std::vector<uint8_t> buf((size_t)ams::kStripRows * K);
+  const WideRow* const wide = one_pass(rq, codes_out);
+  const bool done = parallel_for(n_strips, (double)N * K * quantize_ns(rq, wide), [&](int64_t t) {
     Steps steps;
+    if (wide) {
+      if (!quantize_and_pack_strip(rq, fi, *wide, W, N, K, ldw, K, tensor_scale, (uint8_t*)packed, n_strips, t, steps,
+                                   [&](int r, int64_t) { return scales + t * 16 + r; }))
+        bad.store(1);
+      return;
+    }
+    std::vector<uint8_t> buf((size_t)ams::kStripRows * K);
     const uint8_t* rows[16];
     for (int r = 0; r < 16; r++) {
       const int64_t n = t * 16 + r;
@@ -512,13 +808,21 @@ int ams_pack_grouped(int fmt, int search, int64_t scale_group, const uint16_t* W
   if (ldw < K) return AMS_ERR_SHAPE;
   const FormatInfo& fi = *ams::format_info(fmt);
   if (scale_group_shift(fi, scale_group) < 0) return AMS_ERR_SHAPE;
-  const RowQuant rq = {fi.code_bits - 3, fi.group, fi.fmax, search};
+  const RowQuant rq = {fmt, fi.code_bits - 3, fi.group, fi.fmax, search};
   const int64_t n_strips = ams::round_up(N, ams::kStripRows) / ams::kStripRows;
   const int64_t n_sg = (K + scale_group - 1) / scale_group;
   std::atomic<int> bad{0};
-  const bool done = parallel_for(n_strips, [&](int64_t t) {
-    std::vector<uint8_t> buf((size_t)ams::kStripRows * K);
+  const WideRow* const wide = one_pass(rq, codes_out);
+  const bool done = parallel_for(n_strips, (double)N * K * quantize_ns(rq, wide), [&](int64_t t) {
     Steps steps;
+    if (wide) {
+      auto scale_of = [&](int r, int64_t j) { return scales + ((size_t)t * n_sg + j) * 16 + r; };
+      for (int r = 0; r < 16; r++)
+        for (int64_t j = 0; j < n_sg && t * 16 + r >= N; j++) *scale_of(r, j) = 0x3C00;  // padding rows: 1.0
+      if (!quantize_and_pack_strip(rq, fi, *wide, W, N, K, ldw, scale_group, 0, (uint8_t*)packed, n_strips, t, steps, scale_of)) bad.store(1);
+      return;
+    }
+    std::vector<uint8_t> buf((size_t)ams::kStripRows * K);
     const uint8_t* rows[16];
     for (int r = 0; r < 16; r++) {
       const int64_t n = t * 16 + r;
@@ -548,7 +852,7 @@ int ams_pack_codes(int fmt, const uint8_t* codes, int64_t N, int64_t K, void* pa
   const FormatInfo& fi = *ams::format_info(fmt);
   const int64_t n_strips = ams::round_up(N, ams::kStripRows) / ams::kStripRows;
   std::atomic<int> bad{0};
-  parallel_for(n_strips, [&](int64_t t) {
+  parallel_for(n_strips, (double)N * K * 0.4, [&](int64_t t) {
     const uint8_t* rows[16];
     for (int r = 0; r < 16; r++) {
       const int64_t n = t * 16 + r;
@@ -570,7 +874,7 @@ int ams_unpack_host(int fmt, const void* packed, int64_t N, int64_t K, uint8_t* 
   if (!codes || !packed) return AMS_ERR_NULL;
   const FormatInfo& fi = *ams::format_info(fmt);
   const int64_t n_strips = ams::round_up(N, ams::kStripRows) / ams::kStripRows;
-  parallel_for(n_strips, [&](int64_t t) {
+  parallel_for(n_strips, (double)N * K * 0.4, [&](int64_t t) {
     uint8_t* rows[16];
     for (int r = 0; r < 16; r++) rows[r] = t * 16 + r < N ? codes + (t * 16 + r) * K : nullptr;
     unpack_strip(fmt, fi, (const uint8_t*)packed, n_strips, t, K, rows);

@@ -1,0 +1,68 @@
+"""The packer's vector paths: quantizing and packing in one pass (nobody asks for the codes) leaves the same bytes as
+packing the codes that the oracle finds, at the edges of vectors, lane chunks, records and strips, for every scale
+granularity; rows that make the first decision of a code or last bit unsure are decided exactly."""
+
+import numpy as np
+import pytest
+
+import paper_2510_16045_amd as ams
+from oracle import ams_oracle as O
+
+PAIRS = [(ams.FP533, O.FP533), (ams.FP425, O.FP425), (ams.FP45, O.FP45), (ams.FP433, O.FP433), (ams.FP6, O.FP6_E2M3), (ams.FP5, O.FP5_E2M2), (ams.FP4, O.FP4_E2M1)]
+
+
+def weights(N, K, seed):
+    rng = np.random.default_rng(seed)
+    W = (rng.standard_normal((N, K)) * np.exp2(rng.uniform(-18, 10, (N, 1)))).clip(-60000, 60000).astype(np.float16)
+    W[0] = 0
+    if K > 3:
+        W[-1, 1], W[-1, 2] = -0.0, 6e-8
+    return W
+
+
+@pytest.mark.parametrize("fmt,ofmt", PAIRS)
+@pytest.mark.parametrize("N,K", [(1, 1), (5, 23), (16, 24), (17, 32), (3, 47), (15, 48), (33, 63), (2, 64), (16, 95), (7, 96), (18, 97), (31, 128), (9, 129), (16, 511), (5, 515), (20, 1000)])
+def test_one_pass_leaves_the_codes_bytes(fmt, ofmt, N, K):
+    W = weights(N, K, 10 * K + fmt)
+    codes, scales, _ = O.ams_quantize(W, ofmt)
+    packed, got = ams.ams_pack(fmt, W)
+    assert np.array_equal(got.view(np.uint16), scales.view(np.uint16))
+    assert np.array_equal(packed, ams.ams_pack_codes(fmt, codes.astype(np.uint8)))
+    again, _, with_codes = ams.ams_pack(fmt, W, return_codes=True)
+    assert np.array_equal(with_codes, codes) and np.array_equal(again, packed)
+
+
+@pytest.mark.parametrize("fmt,ofmt", PAIRS)
+@pytest.mark.parametrize("runs", [1, 2, 3])
+def test_one_pass_with_other_scales(fmt, ofmt, runs):
+    rec = 96 if ofmt.code_bits == 6 or fmt == ams.FP433 else 128
+    W = weights(19, rec * 4 * runs - 8, runs)
+    packed, scales = ams.ams_pack_grouped(fmt, W, rec * 2)
+    codes, want = O.ams_quantize_grouped(W, ofmt, rec * 2)[:2]
+    assert np.array_equal(packed, ams.ams_pack_codes(fmt, codes.astype(np.uint8)))
+    rows = scales.transpose(0, 2, 1).reshape(-1, scales.shape[1])
+    assert np.array_equal(rows[:19].view(np.uint16), np.asarray(want).view(np.uint16)) and np.all(rows[19:] == 1)
+    packed, _ = ams.ams_pack_per_tensor(fmt, W)
+    codes = O.ams_quantize(W, ofmt, per_tensor=True)[0]
+    assert np.array_equal(packed, ams.ams_pack_codes(fmt, codes.astype(np.uint8)))
+
+
+@pytest.mark.parametrize("fmt,ofmt", PAIRS)
+def test_ties_of_codes_and_of_errors(fmt, ofmt):
+    # scale 1 and powers of two: the weights are multiples of a quarter of the smallest step, so that half of them lie on a tie
+    # of two codes and many groups' squared errors are equal; and scales among the smallest binary16 numbers
+    rng, fmax = np.random.default_rng(fmt), float(np.max(O.magnitude_table(ofmt)))
+    rows = []
+    for e in (-10, 0, 5):
+        w = rng.integers(-int(fmax * 32), int(fmax * 32) + 1, 700) / 32.0 * 2.0**e
+        w[0] = fmax * 2.0**e
+        rows.append(w)
+    for top in (1, 3, 11, 40):
+        rows.append(rng.integers(-top, top + 1, 700) * 2.0**-24)
+    W = np.stack(rows).astype(np.float16)
+    codes, _, _ = O.ams_quantize(W, ofmt)
+    assert np.array_equal(ams.ams_pack(fmt, W)[0], ams.ams_pack_codes(fmt, codes.astype(np.uint8)))
+    for bad in (np.inf, -np.inf, np.nan):
+        W[2, 699] = bad
+        with pytest.raises(ams.AmsError):
+            ams.ams_pack(fmt, W)
