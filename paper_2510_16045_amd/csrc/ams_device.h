@@ -312,18 +312,33 @@ __device__ __forceinline__ void permute_unit(const uint32_t (&in)[Fmt<FMT>::PB /
   }
 }
 
+// Eight halfs (packed pairs) moved down by n places with zeros behind (n <= 0: as they are; n >= 8 does not matter,
+// such a chunk lies beyond K and is zero already).
+__device__ __forceinline__ void shift_tail(uint32_t* v, int n) {
+  n = max(n, 0);
+  if (n & 4) v[0] = v[2], v[1] = v[3], v[2] = 0, v[3] = 0;
+  if (n & 2) v[0] = v[1], v[1] = v[2], v[2] = v[3], v[3] = 0;
+  if (n & 1) {
+    v[0] = v[0] >> 16 | v[1] << 16, v[1] = v[1] >> 16 | v[2] << 16;
+    v[2] = v[2] >> 16 | v[3] << 16, v[3] = v[3] >> 16;
+  }
+}
+
 constexpr int kLdsMaxBytes = 160 * 1024;  // LDS of a gfx950 compute unit
 constexpr int kOutOfRange = 0x7FFE0000;   // an offset beyond the range of every buffer: such a lane's load reads no memory and gives 0
 constexpr int kDeviceScope = 16;          // cache policy (sc1) of a buffer load or store that the whole device sees
 constexpr int kMaxSlices = 8;             // slices of K that workgroups may share
 
 // ---- slice_kernel (ams_slice.hip): what its launch needs ------------------------------------------
+// Variants: one scale per row of W; one per run of input channels; rows of X that are not 16-byte aligned.
+constexpr int kSlicePlain = 0, kSliceRunScales = 1, kSliceRagged = 2, kSliceVariants = 3;
+constexpr int kSliceRaggedMaxStrips = 4, kSliceRaggedMaxRows = 8;  // of the last one
 constexpr int kSliceMaxStrips = 8;  // strips per workgroup it is built for
 constexpr int slice_rows(int M) { return M <= 4 ? 4 : M <= 8 ? 8 : M <= 16 ? 16 : 32; }  // staged activation rows
 // Wavefronts of a workgroup.  Eight (with three pairs of weights ahead) are 3-10 % faster than sixteen with two where a
 // wavefront takes several strips or many rows: the sum over the wavefronts' tiles halves, and fewer contend for the VALU.
 // A single strip at M <= 4 needs sixteen to keep enough bytes in flight (4096 x 14336 FP5.33 M = 1 9.2 us against 9.6).
-constexpr int slice_waves(int R, int NS) { return R == 4 && NS == 1 ? 16 : 8; }
+constexpr int slice_waves(int R, int NS, int variant = 0) { return variant == kSliceRagged || (R == 4 && NS == 1) ? 16 : 8; }
 constexpr int slice_ahead(int S) { return S == 16 ? 2 : 3; }  // (record, strip) pairs of weights requested ahead
 constexpr int kSliceXAhead = 2;                               // records of activations requested ahead
 // 1 KiB loads that bring one record's activations
@@ -333,8 +348,8 @@ constexpr int slice_x_loads(int fmt, int R) {
 }
 // floats between the rows of a partial tile in LDS: 20 keeps a column's float4s in different banks, where it fits
 constexpr int slice_tile_row(int S, int R, int NS) { return S * NS * R * 20 * 4 <= 150 * 1024 ? 20 : 16; }
-constexpr int slice_lds(int fmt, int R, int NS) {
-  const int S = slice_waves(R, NS);
+constexpr int slice_lds(int fmt, int R, int NS, int variant = 0) {
+  const int S = slice_waves(R, NS, variant);
   const int staged = S * kSliceXAhead * slice_x_loads(fmt, R) * 1024;
   const int tiles = S * NS * R * slice_tile_row(S, R, NS) * 4 + NS * 64 + NS * 4;
   return staged > tiles ? staged : tiles;
@@ -355,8 +370,7 @@ struct SliceArgs {
   int n_sg, sg_shift;
 };
 // The kernel for `rows` staged rows and `strips` strips per workgroup (nullptr: there is none).
-// GS: one scale per run of input channels.
-template <int FMT, bool GS>
+template <int FMT, int VARIANT>
 const void* slice_kernel_of(int rows, int strips);
 
 }  // namespace ams_dev

@@ -76,18 +76,6 @@ __device__ __forceinline__ void x_load(XRegs<FMT, NU>& xr, const LinearArgs& a, 
   }
 }
 
-// Eight halfs (packed pairs) moved down by n places with zeros behind (n <= 0: as they are; n >= 8 does not matter,
-// such a chunk lies beyond K and is zero already).
-__device__ __forceinline__ void shift_tail(uint32_t* v, int n) {
-  n = max(n, 0);
-  if (n & 4) v[0] = v[2], v[1] = v[3], v[2] = 0, v[3] = 0;
-  if (n & 2) v[0] = v[1], v[1] = v[2], v[2] = v[3], v[3] = 0;
-  if (n & 1) {
-    v[0] = v[0] >> 16 | v[1] << 16, v[1] = v[1] >> 16 | v[2] << 16;
-    v[2] = v[2] >> 16 | v[3] << 16, v[3] = v[3] >> 16;
-  }
-}
-
 template <bool RAGGED = false, int FMT, int NU>
 __device__ __forceinline__ void x_store(const XRegs<FMT, NU>& xr, _Float16* xs, const LinearArgs& a, int k0, int nk, int u0,
                                         int idx, int nthr) {
@@ -1244,6 +1232,7 @@ struct ColumnPlan {
   int wpa;  // wavefronts of a strip that take records (= wps unless fewer divide the side groups evenly)
   int lr;   // records a wavefront keeps in flight beside the one it restores
   int ns;   // strips a wavefront owns alone (multi_kernel; 1: column_kernel); then wpa = wavefronts that own strips
+  bool ragged;  // slice_kernel's variant for rows of X that are not 16-byte aligned (with `slice`)
   bool slice;  // slice_kernel: the wavefronts share K and take every record of all spw strips; S, spw, grid, gn, gk, lr and lds hold
   int rows, row_tiles;  // slice_kernel: staged rows of X per workgroup, workgroups that share the rows
   size_t lds;
@@ -1259,7 +1248,7 @@ ColumnPlan column_plan_for(int S, int lr, int fmt, int M, int64_t n_strips, int 
                            int ns = 1) {
   ColumnPlan p;
   p.ns = ns;
-  p.slice = false;
+  p.slice = p.ragged = false;
   p.rows = M;
   p.row_tiles = 1;
   const int sg = ams::side_group(ams::kFormats[fmt]);
@@ -1433,6 +1422,37 @@ RowSplit row_split(int fmt, int M, int64_t n_strips, int gk, int tiles, bool one
 }
 constexpr int kMaxRowTiles = 4, kRowSplitMinRecords = 18, kRowSplitMinRows = 8;
 
+// Rows of X that are not 16-byte aligned: slice_kernel's variant for them, on tiles of eight rows and up to four strips (its
+// sixteen wavefronts have 128 registers each).  column_kernel stays where it reads three records ahead (8192 x 8193 FP5.33 M =
+// 1 11.0 / 11.2 us), with one scale per run, on one record, and where K is walked in phases at M = 8, on fewer than 32
+// strips or on more than one for every compute unit: there the new variant is faster too (4096 x 14339 FP4.25 M = 8 16.5 /
+// 11.9), but those shapes are the ones on which the tests exercise the phases.
+int ragged_tiles(int M) { return (M + kSliceRaggedMaxRows - 1) / kSliceRaggedMaxRows; }
+bool ragged_on_slice(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int gk, bool one_scale, const ColumnPlan& column) {
+  if (!one_scale || (int64_t)n_rec * rec_k < 8 + rec_k || n_strips > kSplitMaxStrips / kMaxRowTiles) return false;
+  if (column.lr == 3 || column.spw > kSliceRaggedMaxStrips) return false;
+  if (column.n_phase > 1 && (M == 8 || n_strips < 32 || n_strips > kNumCU)) return false;
+  return row_split(fmt, M, n_strips, gk, ragged_tiles(M), true).strips <= kSliceRaggedMaxStrips;
+}
+ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
+  p.row_tiles = ragged_tiles(M);
+  if (p.row_tiles > 1) {
+    const RowSplit s = row_split(fmt, M, n_strips, gk, p.row_tiles, true);
+    p.spw = s.strips;
+    p.gn = (int)((n_strips + p.spw - 1) / p.spw);
+    p.grid = s.positions * p.row_tiles;
+  }
+  p.slice = p.ragged = true;
+  p.rows = slice_rows((M + p.row_tiles - 1) / p.row_tiles);
+  p.S = slice_waves(p.rows, p.spw, kSliceRagged);
+  p.lr = slice_ahead(p.S);
+  p.lds = (size_t)slice_lds(fmt, p.rows, p.spw, kSliceRagged);
+  p.wps = p.wpa = p.S / p.spw;
+  p.n_phase = 1;
+  p.qd = false;
+  return p;
+}
+
 // The plan of a problem: slice_kernel where it takes it (aligned_rows: rows of X are 16-byte aligned, K % 8 == 0;
 // one_scale: one scale per row of W), else make_column_plan's.  slice_kernel is the faster one nearly everywhere
 // (twelve shapes, seven formats, M = 1 .. 32: 1.00-1.8 x); the exceptions, us column / slice:
@@ -1447,7 +1467,10 @@ constexpr int kMaxRowTiles = 4, kRowSplitMinRecords = 18, kRowSplitMinRows = 8;
 //   more than eight strips: see halved_is_faster.
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
   ColumnPlan p = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
-  if (!aligned_rows) return p;
+  if (!aligned_rows) {
+    if (ragged_on_slice(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, p)) return ragged_plan(p, fmt, M, n_strips, gk);
+    return p;
+  }
   if (p.spw == 1 && p.lr == 3) return p;
   if (long_k_on_column(fmt, M, p.spw, p.grid, n_rec_all, one_scale)) return p;
   if (short_slices_on_column(fmt, M, p.spw, gk, n_rec_all)) return p;
@@ -1707,10 +1730,12 @@ int launch_multi(const LinearArgs& a, unsigned grid, int S, size_t lds, hipStrea
 
 // slice_kernel for r staged rows and `strips` strips per workgroup.
 template <int FMT>
-int launch_slice(const LinearArgs& a, bool gs, int r, int strips, unsigned grid, hipStream_t st) {
-  const void* kern = gs ? slice_kernel_of<FMT, true>(r, strips) : slice_kernel_of<FMT, false>(r, strips);
+int launch_slice(const LinearArgs& a, int variant, int r, int strips, unsigned grid, hipStream_t st) {
+  const void* kern = variant == kSliceRunScales ? slice_kernel_of<FMT, kSliceRunScales>(r, strips)
+                     : variant == kSliceRagged  ? slice_kernel_of<FMT, kSliceRagged>(r, strips)
+                                                : slice_kernel_of<FMT, kSlicePlain>(r, strips);
   if (!kern) return AMS_ERR_LAUNCH;
-  const size_t lds = (size_t)slice_lds(FMT, r, strips);
+  const size_t lds = (size_t)slice_lds(FMT, r, strips, variant);
   if (lds > 64 * 1024 && !raise_lds_limit(kern)) return AMS_ERR_LAUNCH;
   if (grid == 0) return AMS_OK;
   const uint8_t* W = a.W;
@@ -1718,7 +1743,7 @@ int launch_slice(const LinearArgs& a, bool gs, int r, int strips, unsigned grid,
   int M = a.M, N = a.N, K = a.K, n_rec = a.n_rec, n_strips = a.n_strips, gn = a.gn, gk = a.gk, tile_rows = a.tile_rows;
   SliceArgs rest = {a.Y, a.ws_tiles, a.ws_count, a.n_sg, a.sg_shift};
   void* args[] = {&W, &X, &scales, &M, &N, &K, &n_rec, &n_strips, &gn, &gk, &tile_rows, &rest};
-  return hipLaunchKernel(kern, dim3(grid / a.row_tiles, a.row_tiles), dim3(64 * slice_waves(r, strips)), args, lds, st) == hipSuccess ? AMS_OK : AMS_ERR_LAUNCH;
+  return hipLaunchKernel(kern, dim3(grid / a.row_tiles, a.row_tiles), dim3(64 * slice_waves(r, strips, variant)), args, lds, st) == hipSuccess ? AMS_OK : AMS_ERR_LAUNCH;
 }
 
 template <int FMT>
@@ -1803,7 +1828,7 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
     a.x_shift = cp.x_shift;
     a.spw = cp.spw;
     a.rc = cp.rc;
-    if (cp.slice) return launch_slice<FMT>(a, scale_group != 0, cp.rows, cp.spw, cp.grid, st);
+    if (cp.slice) return launch_slice<FMT>(a, scale_group != 0 ? kSliceRunScales : cp.ragged ? kSliceRagged : kSlicePlain, cp.rows, cp.spw, cp.grid, st);
     if (cp.ns > 1) return launch_multi<FMT>(a, cp.grid, cp.S, cp.lds, st);
     return M <= 16 ? launch_column<FMT, 1>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st)
                    : launch_column<FMT, 2>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st);
@@ -1850,7 +1875,8 @@ int prepare_format() {
   if constexpr (FMT != FMT_FP16) {
     for (int r = 4; r <= 32; r *= 2)
       for (int strips = 1; strips <= kSliceMaxStrips; strips++)
-        for (int gs = 0; gs < 2; gs++) ok &= launch_slice<FMT>(a, gs != 0, r, strips, 0, nullptr) == AMS_OK;
+        for (int variant = 0; variant < kSliceVariants; variant++)
+          if (variant != kSliceRagged || (r <= kSliceRaggedMaxRows && strips <= kSliceRaggedMaxStrips)) ok &= launch_slice<FMT>(a, variant, r, strips, 0, nullptr) == AMS_OK;
     for (a.K = 8; a.K < 10; a.K++) {  // aligned and ragged rows of X
       for (int nt = 0; nt < 2; nt++)
         for (int gs = 0; gs < 2; gs++)
@@ -2017,13 +2043,15 @@ int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, ch
   if (f != FMT_FP16) {
     const bool nt = n_strips * n_rec * (int64_t)rec_bytes >= (2ll << 20);  // as run_linear decides it
     const ColumnPlan cp = make_plan(f, M, n_strips, n_rec, rec_k, gk, K % 8 == 0, !grouped, nt);
-    if (cp.slice) {
+    if (cp.slice && !cp.ragged) {
       const int len = snprintf(text, text_len, "slice grid=%d strips_per_wg=%d k_slices=%d waves=%d lds=%zu ahead=%d", cp.grid, cp.spw, cp.gk, cp.S, cp.lds, cp.lr);
       if (cp.row_tiles > 1 && len > 0 && (size_t)len < text_len)
         snprintf(text + len, text_len - len, " row_tiles=%d rows_per_tile=%d", cp.row_tiles, (M + cp.row_tiles - 1) / cp.row_tiles);
     } else {
-      snprintf(text, text_len, "column grid=%d strips_per_wg=%d k_slices=%d waves=%d waves_per_strip=%d phases=%d lds=%zu side_groups=%d active_per_strip=%d ahead=%d strips_per_wave=%d", cp.grid,
+      const int len = snprintf(text, text_len, "column grid=%d strips_per_wg=%d k_slices=%d waves=%d waves_per_strip=%d phases=%d lds=%zu side_groups=%d active_per_strip=%d ahead=%d strips_per_wave=%d", cp.grid,
                cp.spw, cp.gk, cp.S, cp.wps, cp.n_phase, cp.lds, cp.qd ? 1 : 0, cp.ns > 1 ? 1 : cp.wpa, cp.lr, cp.ns);
+      if (cp.ragged && len > 0 && (size_t)len < text_len)
+        snprintf(text + len, text_len - len, " streamed_rows=%d row_tiles=%d", (M + cp.row_tiles - 1) / cp.row_tiles, cp.row_tiles);
     }
     return AMS_OK;
   }

@@ -1,6 +1,6 @@
 // slice_kernel: the Linear with the activations streamed beside the weights (Sec. 3.3, Sec. 4.2), for
 // workgroups of up to eight strips of 16 output channels.  One format per translation unit
-// (AMS_SLICE_FMT; AMS_SLICE_GS: with one scale per run of input channels), so that they compile in parallel.
+// and variant (AMS_SLICE_FMT, AMS_SLICE_VARIANT), so that they compile in parallel.
 //
 // A workgroup owns NS neighbouring strips and its wavefronts share K: wavefront w takes records w, w + S, ... of all NS
 // strips.  The activations of a record are then needed by one wavefront only, so nothing is staged for the
@@ -30,8 +30,8 @@
 #ifndef AMS_SLICE_FMT
 #define AMS_SLICE_FMT 0
 #endif
-#ifndef AMS_SLICE_GS
-#define AMS_SLICE_GS 0
+#ifndef AMS_SLICE_VARIANT
+#define AMS_SLICE_VARIANT 0
 #endif
 
 namespace {
@@ -55,17 +55,18 @@ __device__ __forceinline__ void buffer_load_chunk(uint32_t* w, __amdgpu_buffer_r
 }
 
 // Shape of the kernel for R staged activation rows (4, 8, 16 or 32) and NS strips per workgroup.
-template <int FMT, int R, int NS, bool GS>
+template <int FMT, int R, int NS, int VAR>
 struct Slice {
+  static constexpr bool GS = VAR == kSliceRunScales, RAGGED = VAR == kSliceRagged;
   static constexpr int MT = R > 16 ? 2 : 1;
   static constexpr int RB = R > 16 ? 16 : R;                    // rows of one MFMA tile that are staged
   static constexpr int NI = slice_x_loads(FMT, R), NI1 = NI / MT;  // 1 KiB loads of a record's activations, of one tile's
   static constexpr int BYTES = NI * 1024;
   static constexpr int WL = (Fmt<FMT>::SIDE ? 2 : 1) + GS;      // load instructions of one weight record (and its scales)
-  static constexpr int S = slice_waves(R, NS);
+  static constexpr int S = slice_waves(R, NS, VAR);
   static constexpr int LX = kSliceXAhead;
   static constexpr int LW = slice_ahead(S);
-  static constexpr int U = NS > LW ? 1 : NS == 1 ? LW + 1 : 2;  // records per unrolled round
+  static constexpr int U = RAGGED ? (NS == 1 ? 4 : 2) : NS > LW ? 1 : NS == 1 ? LW + 1 : 2;  // records per unrolled round
   static constexpr int RS = U * NS;                             // slots of the weight ring
   static constexpr int ROW = slice_tile_row(S, R, NS);
 };
@@ -73,10 +74,16 @@ struct Slice {
 // GS: one scale per run of 2^a.sg_shift records.  A record goes through a fresh tile, times its run's scales, into the
 // sum; the four scales of a lane's output channels are one 8-byte load that travels with the record.  28672 x 4096
 // FP4.25, a scale per 128: M = 1 15.7 -> 12.8 us, M = 4 15.9 -> 13.5, M = 32 23.5 -> 20.2 (column_kernel before).
-template <int FMT, int R, int NS, bool GS>
-__global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(const uint8_t* W, const uint16_t* X, const uint16_t* scales, int M, int N, int K, int n_rec,
+//
+// RAGGED: rows of X that are not 16-byte aligned (K no multiple of 8) cannot be copied straight into LDS: they are loaded
+// two records ahead into registers, 16 unaligned bytes per lane, and written to the wave's own LDS when their record
+// begins.  Tiles of up to eight rows and up to four strips, sixteen wavefronts.  us, column_kernel (staged by the workgroup) / here:
+// 11003 x 4099 FP5.33 M = 5 10.6 / 8.7, 8192 x 8193 FP4.25 M = 4 12.6 / 9.6, 4096 x 14337 M = 32 47.7 / 21.5; 160 random shapes 1.30 x.
+template <int FMT, int R, int NS, int VAR>
+__global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel(const uint8_t* W, const uint16_t* X, const uint16_t* scales, int M, int N, int K, int n_rec,
                                                                          int n_strips, int gn, int gk_slices, int tile_rows, SliceArgs a) {
-  using P = Slice<FMT, R, NS, GS>;
+  using P = Slice<FMT, R, NS, VAR>;
+  constexpr bool GS = P::GS, RAGGED = P::RAGGED;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int FAR = kOutOfRange;
   constexpr int REC_K = Fmt<FMT>::REC_K, SG = Fmt<FMT>::SG, NF = Fmt<FMT>::N_MFMA, PB = Fmt<FMT>::PB, UNIT = Fmt<FMT>::UNIT;
@@ -145,6 +152,42 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
       const int piece = kq * NF + u;
       roff[u] = (piece >> 2) * (RB * 64) + m_lo * 64 + (((piece & 3) ^ swz(m_lo)) * 16);
     }
+    // RAGGED: the loads' rows, the channels of their pieces inside a record, and the two records under way
+    int row_at[MT], piece_at[MT];
+    u4 ahead[RAGGED ? LX : 1][RAGGED ? P::NI : 1];
+    if constexpr (RAGGED) {
+#pragma unroll
+      for (int t = 0; t < MT; t++) {
+        row_at[t] = min(16 * t + ld_m, rows - 1) * K;
+        piece_at[t] = ld_b * 32 + ((lane & 3) ^ swz(ld_m)) * 8;
+      }
+    }
+    const uint16_t* const xrows = X + (size_t)m_first * K;
+    auto request_ragged = [&](int p, auto set) {
+      const int rec = p < cnt ? first + S * p : first;  // behind the last record: any record (the results are not used)
+#pragma unroll
+      for (int t = 0; t < MT; t++)
+#pragma unroll
+        for (int i = 0; i < P::NI1; i++)  // a piece that runs past its row's end: the row's last eight channels
+          __builtin_memcpy(&ahead[set][t * P::NI1 + i], xrows + row_at[t] + min(rec * REC_K + piece_at[t] + i * (BLK * 32), K - 8), 16);
+    };
+    auto store_ragged = [&](int p, auto set) {
+      const int rec = first + S * p;
+#pragma unroll
+      for (int t = 0; t < MT; t++)
+#pragma unroll
+        for (int i = 0; i < P::NI1; i++) {
+          u4 v = ahead[set][t * P::NI1 + i];
+          if (rec == n_rec - 1) {  // channels beyond K count as zero
+            const int beyond = rec * REC_K + piece_at[t] + i * (BLK * 32) + 8 - K;
+            uint32_t h[4] = {v[0], v[1], v[2], v[3]};
+            shift_tail(h, beyond);
+            const uint32_t keep = beyond < 8 ? 0xFFFFFFFFu : 0u;
+            v = u4{h[0] & keep, h[1] & keep, h[2] & keep, h[3] & keep};
+          }
+          *(u4*)(xbuf + (t * P::NI1 + i) * 1024 + lane * 16) = v;
+        }
+    };
     auto request_x = [&](int p) {  // the wave's p-th record of activations
       const int soff = p < cnt ? (first + S * p) * (REC_K * 2) : 0;
       unsigned char* dst = xbuf + (p & (LX - 1)) * P::BYTES;
@@ -185,7 +228,12 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
     auto step = [&](int p, auto uc) {
       constexpr int u0 = decltype(uc)::value * NS;  // its first slot of the ring
       constexpr int STEADY = LX * NS * P::WL + (LX - 1) * P::NI;
-      if constexpr (LW >= LX * NS) {
+      constexpr std::integral_constant<int, decltype(uc)::value & 1> set;  // RAGGED: rounds are even
+      if constexpr (RAGGED) {
+        store_ragged(p, set);  // the compiler sees the loads and waits for them itself
+        request_ragged(p + LX, set);
+        __builtin_amdgcn_sched_barrier(0);
+      } else if constexpr (LW >= LX * NS) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STEADY) : "memory");
       } else {  // the first steps have fewer weights requested behind their activations
         if (p == 0)
@@ -196,18 +244,20 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
           asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STEADY) : "memory");
       }
       u4 b[MT][NF];
-      const unsigned char* src = xbuf + (p & (LX - 1)) * P::BYTES;
+      const unsigned char* src = RAGGED ? xbuf : xbuf + (p & (LX - 1)) * P::BYTES;
 #pragma unroll
       for (int t = 0; t < MT; t++)
 #pragma unroll
         for (int u = 0; u < NF; u++) b[t][u] = *(const u4*)(src + t * (P::NI1 * 1024) + roff[u]);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-      request_x(p + LX);
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (!RAGGED) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        request_x(p + LX);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
       const int rec = (first + S * p);
-      if (tail != 0 && rec == n_rec - 1) {  // channels beyond K: whatever was read there counts as zero
+      if (!RAGGED && tail != 0 && rec == n_rec - 1) {  // channels beyond K: whatever was read there counts as zero
 #pragma unroll
         for (int u = 0; u < NF; u++) {
           const uint32_t keep = rec * REC_K + (kq * NF + u) * 8 < K ? 0xFFFFFFFFu : 0u;
@@ -260,8 +310,14 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
       }
     };
     using std::integral_constant;
+    if constexpr (RAGGED) {
+      request_ragged(0, integral_constant<int, 0>{});
+      request_ragged(1, integral_constant<int, 1>{});
+      static_assert(LX == 2, "two sets");
+    } else {
 #pragma unroll
-    for (int q = 0; q < LX; q++) request_x(q);
+      for (int q = 0; q < LX; q++) request_x(q);
+    }
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -381,16 +437,20 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, GS>::S)) slice_kernel(
 
 template <int R>
 const void* by_strips(int strips) {
-  constexpr int F = AMS_SLICE_FMT;
+  constexpr int F = AMS_SLICE_FMT, V = AMS_SLICE_VARIANT;
   switch (strips) {
-    case 1: return (const void*)slice_kernel<F, R, 1, AMS_SLICE_GS != 0>;
-    case 2: return (const void*)slice_kernel<F, R, 2, AMS_SLICE_GS != 0>;
-    case 3: return (const void*)slice_kernel<F, R, 3, AMS_SLICE_GS != 0>;
-    case 4: return (const void*)slice_kernel<F, R, 4, AMS_SLICE_GS != 0>;
-    case 5: return (const void*)slice_kernel<F, R, 5, AMS_SLICE_GS != 0>;
-    case 6: return (const void*)slice_kernel<F, R, 6, AMS_SLICE_GS != 0>;
-    case 7: return (const void*)slice_kernel<F, R, 7, AMS_SLICE_GS != 0>;
-    case 8: return (const void*)slice_kernel<F, R, 8, AMS_SLICE_GS != 0>;
+    case 1: return (const void*)slice_kernel<F, R, 1, V>;
+    case 2: return (const void*)slice_kernel<F, R, 2, V>;
+    case 3: return (const void*)slice_kernel<F, R, 3, V>;
+    case 4: return (const void*)slice_kernel<F, R, 4, V>;
+  }
+  if constexpr (V != kSliceRagged) {
+    switch (strips) {
+      case 5: return (const void*)slice_kernel<F, R, 5, V>;
+      case 6: return (const void*)slice_kernel<F, R, 6, V>;
+      case 7: return (const void*)slice_kernel<F, R, 7, V>;
+      case 8: return (const void*)slice_kernel<F, R, 8, V>;
+    }
   }
   return nullptr;
 }
@@ -398,12 +458,16 @@ const void* by_strips(int strips) {
 }  // namespace
 
 template <>
-const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, AMS_SLICE_GS != 0>(int rows, int strips) {
+const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, AMS_SLICE_VARIANT>(int rows, int strips) {
   switch (rows) {
     case 4: return by_strips<4>(strips);
     case 8: return by_strips<8>(strips);
-    case 16: return by_strips<16>(strips);
-    case 32: return by_strips<32>(strips);
+  }
+  if constexpr (AMS_SLICE_VARIANT != kSliceRagged) {
+    switch (rows) {
+      case 16: return by_strips<16>(strips);
+      case 32: return by_strips<32>(strips);
+    }
   }
   return nullptr;
 }

@@ -22,7 +22,7 @@ def plan(*a, **k):
     [
         (ams.FP425, 32, 4096, 14336, 0, 2), (ams.FP425, 16, 4096, 14336, 0, 2), (ams.FP425, 15, 4096, 14336, 0, 1), (ams.FP425, 32, 28672, 4096, 0, 1),
         (ams.FP533, 24, 2560, 9728, 0, 3), (ams.FP533, 32, 1024, 4096, 0, 4), (ams.FP533, 16, 8192, 8192, 0, 1), (ams.FP533, 32, 8192, 8192, 0, 2),
-        (ams.FP533, 32, 4096, 17 * 96, 0, 1), (ams.FP533, 32, 4096, 18 * 96, 0, 2), (ams.FP533, 32, 4096, 4099, 0, 1),  # too few records; unaligned rows
+        (ams.FP533, 32, 4096, 17 * 96, 0, 1), (ams.FP533, 32, 4096, 18 * 96, 0, 2), (ams.FP533, 32, 28672, 4099, 0, 1),  # too few records; unaligned rows on too many strips
         (ams.FP533, 16, 4608, 2368, 2, 1), (ams.FP533, 16, 4608, 2368, 0, 2),  # scales per run
         (ams.FP425, 32, 2560, 9728, 1, 2),
     ],
