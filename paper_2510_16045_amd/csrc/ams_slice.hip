@@ -363,37 +363,59 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
   }
   if (tid < NS * 16) scale_of[tid] = (float)__builtin_bit_cast(_Float16, (uint16_t)scale_bits) * kTwo14;
   __syncthreads();
-  // One output per thread, the wavefronts' sums added in wave order.
   uint16_t* const Y = a.Y + (size_t)m_first * N;
-  const int n = tid & 15;
-  auto finish = [&](int i, int m, float sum) {
-    const int row = (s_first + i) * 16 + n;
-    if (row < N) Y[(size_t)m * N + row] = __builtin_bit_cast(uint16_t, (_Float16)(sum * scale_of[i * 16 + n]));
-  };
-  auto tile_sum = [&](int i, int m) {
-    float sum = 0;
+  const int pairs = rows * NS;
+  // Four neighbouring channels of an output row: the wavefronts' sums added in wave order; what leaves for Y.
+  auto quad_sum = [&](int i, int m, int c) {
+    f4 sum = f4{0, 0, 0, 0};
 #pragma unroll
-    for (int w = 0; w < S; w++) sum += parts[((w * NS + i) * R + m) * P::ROW + n];
+    for (int w = 0; w < S; w++) sum += *(const f4*)(parts + ((w * NS + i) * R + m) * P::ROW + c);
     return sum;
   };
-  const int pairs = rows * NS;
+  auto finish_quad = [&](int i, int m, int c, const f4 sum) {
+    const int row = (s_first + i) * 16 + c;
+    us4 h;
+#pragma unroll
+    for (int r = 0; r < 4; r++) h[r] = __builtin_bit_cast(uint16_t, (_Float16)(sum[r] * scale_of[i * 16 + c + r]));
+    if ((N & 3) == 0) {  // whole quads of channels, eight aligned bytes of Y's row
+      if (row < N) *(us4*)(Y + (size_t)m * N + row) = h;
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; r++)
+        if (row + r < N) Y[(size_t)m * N + row + r] = h[r];
+    }
+  };
   if (gk_slices == 1) {
-    for (int r = tid >> 4; r < pairs; r += 4 * S) finish(r % NS, r / NS, tile_sum(r % NS, r / NS));
+    // With many outputs a quad per thread: 28672 x 4096 FP5.33 M = 32 20.4 -> 19.9 us, 20000 x 2048 FP4.25 M = 24 9.2 -> 8.9.  With few,
+    // more threads share them: 4096 x 4096 M = 9 5.33, as quads 5.51.
+    if constexpr (R >= 16 && NS >= 3) {
+      for (int u = tid; u < pairs * 4; u += 64 * S) {
+        const int c = 4 * (u & 3), i = (u >> 2) % NS, m = (u >> 2) / NS;
+        finish_quad(i, m, c, quad_sum(i, m, c));
+      }
+    } else {  // one output per thread
+      const int n = tid & 15;
+      for (int p = tid >> 4; p < pairs; p += 4 * S) {
+        const int i = p % NS, m = p / NS, row = (s_first + i) * 16 + n;
+        float sum = 0;
+#pragma unroll
+        for (int w = 0; w < S; w++) sum += parts[((w * NS + i) * R + m) * P::ROW + n];
+        if (row < N) Y[(size_t)m * N + row] = __builtin_bit_cast(uint16_t, (_Float16)(sum * scale_of[i * 16 + n]));
+      }
+    }
     return;
   }
   // K is split over gk workgroups: the same exchange as exchange_tile's, with the workgroup's barriers around the count
-  // (every wave's stores are acknowledged before any strip is counted in).  Four channels per thread, and the slices' tiles
-  // are all asked for before the first is added: one by one they were a trip to
-  // memory each (5120 x 25600 FP5.33 M = 16, four slices, 22.9 -> 19.4 us; 4096 x 14336 FP4.25 M = 32 18.0 -> 13.6).
+  // (every wave's stores are acknowledged before any strip is counted in).  Quads of channels, and the slices' tiles are all
+  // asked for before the first is added: one by one they were a trip to memory each (5120 x 25600 FP5.33 M = 16, four slices,
+  // 22.9 -> 19.4 us; 4096 x 14336 FP4.25 M = 32 18.0 -> 13.6).
   const int tile = M > 16 ? 512 : 256;  // floats of a strip's tile: the rows of all row tiles
   unsigned* const counts = a.ws_count + s_first * (int)gridDim.y + blockIdx.y;  // of this row tile: one per strip
   const __amdgpu_buffer_rsrc_t tiles = __builtin_amdgcn_make_buffer_rsrc((void*)a.ws_tiles, 0, gk_slices * n_strips * tile * 4, 0x00020000);
   auto tile_offset = [&](int slice, int i, int m, int c) { return (((slice * n_strips + s_first + i) * tile) + (m_first + m) * 16 + c) * 4; };
   for (int u = tid; u < pairs * 4; u += 64 * S) {
     const int c = 4 * (u & 3), i = (u >> 2) % NS, m = (u >> 2) / NS;
-    f4 sum = f4{0, 0, 0, 0};
-#pragma unroll
-    for (int w = 0; w < S; w++) sum += *(const f4*)(parts + ((w * NS + i) * R + m) * P::ROW + c);
+    const f4 sum = quad_sum(i, m, c);
     if (i < ns) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, sum), tiles, tile_offset(gk, i, m, c), 0, kDeviceScope);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -421,17 +443,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
     f4 sum = f4{0, 0, 0, 0};
 #pragma unroll
     for (int q = 0; q < kMaxSlices; q++) sum += part[q];
-    const int row = (s_first + i) * 16 + c;
-    us4 h;
-#pragma unroll
-    for (int r = 0; r < 4; r++) h[r] = __builtin_bit_cast(uint16_t, (_Float16)(sum[r] * scale_of[i * 16 + c + r]));
-    if ((N & 3) == 0) {  // whole quads of channels, eight aligned bytes of Y's row
-      if (row < N) *(us4*)(Y + (size_t)m * N + row) = h;
-    } else {
-#pragma unroll
-      for (int r = 0; r < 4; r++)
-        if (row + r < N) Y[(size_t)m * N + row + r] = h[r];
-    }
+    finish_quad(i, m, c, sum);
   }
 }
 
