@@ -348,9 +348,10 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the requests past the end are done with LDS
   }
   asm volatile("" : "+v"(scale_bits));
-  __syncthreads();
+  constexpr bool APART = slice_tiles_apart(FMT, R, NS, VAR);
+  if constexpr (!APART) __syncthreads();  // every wave is done with its activations
   // Partial tiles [wave][strip][activation row][16 channels, padded], then the scales, then who was last.
-  float* const parts = (float*)smem;
+  float* const parts = (float*)(smem + (APART ? S * LX * P::BYTES : 0));
   float* const scale_of = parts + S * NS * R * P::ROW;
   int* const last = (int*)(scale_of + NS * 16);
   {
