@@ -367,14 +367,16 @@ constexpr int slice_lds(int fmt, int R, int NS, int variant = 0) {
 constexpr bool slice_two_fit(int fmt, int strips) {
   return ams::kFormats[fmt].rec_k == 96 || strips <= (fmt == FMT_FP4 ? 7 : 6);
 }
-// Its arguments but for those that are needed before the first request: those are plain parameters, 14 dwords in all, which
-// the build has preloaded into scalar registers (with the address of one struct instead, every wavefront of a launch starts
-// with a trip to memory: 4096 x 4096 at M = 12 5.84 us, preloaded 5.69; 256 x 768 2.84, 2.78).
+// Its arguments but for those that are needed before the first request: those are 14 plain dwords, which the build has
+// preloaded into scalar registers (with the address of one struct instead, every wavefront of a launch starts with a trip
+// to memory: 4096 x 4096 at M = 12 5.84 us, preloaded 5.69; 256 x 768 2.84, 2.78).  Four vector parameters rather than eleven
+// scalars and pointers: the host pays for every parameter of a launch.
 struct SliceArgs {
   uint16_t* Y;
   f4* ws_tiles;
   unsigned* ws_count;
   int n_sg, sg_shift;
+  int row_tiles;  // = gridDim.y, which would bring the runtime's hidden arguments into every launch
 };
 // The kernel for `rows` staged rows and `strips` strips per workgroup (nullptr: there is none).
 template <int FMT, int VARIANT>

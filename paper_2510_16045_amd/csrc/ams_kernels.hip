@@ -1738,11 +1738,11 @@ int launch_slice(const LinearArgs& a, int variant, int r, int strips, unsigned g
   const size_t lds = (size_t)slice_lds(FMT, r, strips, variant);
   if (lds > 64 * 1024 && !raise_lds_limit(kern)) return AMS_ERR_LAUNCH;
   if (grid == 0) return AMS_OK;
-  const uint8_t* W = a.W;
-  const uint16_t *X = a.X, *scales = a.scales;
-  int M = a.M, N = a.N, K = a.K, n_rec = a.n_rec, n_strips = a.n_strips, gn = a.gn, gk = a.gk, tile_rows = a.tile_rows;
-  SliceArgs rest = {a.Y, a.ws_tiles, a.ws_count, a.n_sg, a.sg_shift};
-  void* args[] = {&W, &X, &scales, &M, &N, &K, &n_rec, &n_strips, &gn, &gk, &tile_rows, &rest};
+  const uint64_t w = (uint64_t)a.W, x = (uint64_t)a.X, sc = (uint64_t)a.scales;
+  uint32_t head[14] = {(uint32_t)w, (uint32_t)(w >> 32), (uint32_t)x, (uint32_t)(x >> 32), (uint32_t)sc, (uint32_t)(sc >> 32), (uint32_t)a.M, (uint32_t)a.N,
+                       (uint32_t)a.K, (uint32_t)a.n_rec, (uint32_t)a.n_strips, (uint32_t)a.gn, (uint32_t)a.gk, (uint32_t)a.tile_rows};
+  SliceArgs rest = {a.Y, a.ws_tiles, a.ws_count, a.n_sg, a.sg_shift, a.row_tiles};
+  void* args[] = {head, head + 4, head + 8, head + 12, &rest};
   return hipLaunchKernel(kern, dim3(grid / a.row_tiles, a.row_tiles), dim3(64 * slice_waves(r, strips, variant)), args, lds, st) == hipSuccess ? AMS_OK : AMS_ERR_LAUNCH;
 }
 

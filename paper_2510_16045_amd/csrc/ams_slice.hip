@@ -1,6 +1,6 @@
 // slice_kernel: the Linear with the activations streamed beside the weights (Sec. 3.3, Sec. 4.2), for
 // workgroups of up to eight strips of 16 output channels.  One format per translation unit
-// and variant (AMS_SLICE_FMT, AMS_SLICE_VARIANT), so that they compile in parallel.
+// and variant (AMS_SLICE_FMT, AMS_SLICE_RUN_SCALES), so that they compile in parallel.
 //
 // A workgroup owns NS neighbouring strips and its wavefronts share K: wavefront w takes records w, w + S, ... of all NS
 // strips.  The activations of a record are then needed by one wavefront only, so nothing is staged for the
@@ -30,12 +30,14 @@
 #ifndef AMS_SLICE_FMT
 #define AMS_SLICE_FMT 0
 #endif
-#ifndef AMS_SLICE_VARIANT
-#define AMS_SLICE_VARIANT 0
+#ifndef AMS_SLICE_RUN_SCALES
+#define AMS_SLICE_RUN_SCALES 0
 #endif
 
 namespace {
 using namespace ams_dev;
+
+__device__ __forceinline__ const void* pointer_of(uint32_t low, uint32_t high) { return (const void*)((uint64_t)high << 32 | low); }
 
 // CHUNK bytes per lane through a buffer descriptor; NT = 2: non-temporal.
 template <int CHUNK, int NT = 2>
@@ -80,8 +82,11 @@ struct Slice {
 // begins.  Tiles of up to eight rows and up to four strips, sixteen wavefronts.  us, column_kernel (staged by the workgroup) / here:
 // 11003 x 4099 FP5.33 M = 5 10.6 / 8.7, 8192 x 8193 FP4.25 M = 4 12.6 / 9.6, 4096 x 14337 M = 32 47.7 / 21.5; 160 random shapes 1.30 x.
 template <int FMT, int R, int NS, int VAR>
-__global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel(const uint8_t* W, const uint16_t* X, const uint16_t* scales, int M, int N, int K, int n_rec,
-                                                                         int n_strips, int gn, int gk_slices, int tile_rows, SliceArgs a) {
+__global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel(u4 head0, u4 head1, u4 head2, u2 head3, SliceArgs a) {
+  const uint8_t* const W = (const uint8_t*)pointer_of(head0[0], head0[1]);
+  const uint16_t* const X = (const uint16_t*)pointer_of(head0[2], head0[3]);
+  const uint16_t* const scales = (const uint16_t*)pointer_of(head1[0], head1[1]);
+  const int M = head1[2], N = head1[3], K = head2[0], n_rec = head2[1], n_strips = head2[2], gn = head2[3], gk_slices = head3[0], tile_rows = head3[1];
   using P = Slice<FMT, R, NS, VAR>;
   constexpr bool GS = P::GS, RAGGED = P::RAGGED;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -411,7 +416,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
   // asked for before the first is added: one by one they were a trip to memory each (5120 x 25600 FP5.33 M = 16, four slices,
   // 22.9 -> 19.4 us; 4096 x 14336 FP4.25 M = 32 18.0 -> 13.6).
   const int tile = M > 16 ? 512 : 256;  // floats of a strip's tile: the rows of all row tiles
-  unsigned* const counts = a.ws_count + s_first * (int)gridDim.y + blockIdx.y;  // of this row tile: one per strip
+  unsigned* const counts = a.ws_count + s_first * a.row_tiles + blockIdx.y;  // of this row tile: one per strip
   const __amdgpu_buffer_rsrc_t tiles = __builtin_amdgcn_make_buffer_rsrc((void*)a.ws_tiles, 0, gk_slices * n_strips * tile * 4, 0x00020000);
   auto tile_offset = [&](int slice, int i, int m, int c) { return (((slice * n_strips + s_first + i) * tile) + (m_first + m) * 16 + c) * 4; };
   for (int u = tid; u < pairs * 4; u += 64 * S) {
@@ -422,9 +427,9 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid < ns) {
-    const unsigned before = __hip_atomic_fetch_add(counts + tid * gridDim.y, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned before = __hip_atomic_fetch_add(counts + tid * a.row_tiles, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const bool is_last = before == (unsigned)gk_slices - 1;
-    if (is_last) __hip_atomic_store(counts + tid * gridDim.y, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (is_last) __hip_atomic_store(counts + tid * a.row_tiles, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     last[tid] = is_last;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -448,9 +453,9 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
   }
 }
 
-template <int R>
+template <int V, int R>
 const void* by_strips(int strips) {
-  constexpr int F = AMS_SLICE_FMT, V = AMS_SLICE_VARIANT;
+  constexpr int F = AMS_SLICE_FMT;
   switch (strips) {
     case 1: return (const void*)slice_kernel<F, R, 1, V>;
     case 2: return (const void*)slice_kernel<F, R, 2, V>;
@@ -467,20 +472,35 @@ const void* by_strips(int strips) {
   }
   return nullptr;
 }
-
-}  // namespace
-
-template <>
-const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, AMS_SLICE_VARIANT>(int rows, int strips) {
+template <int V>
+const void* by_rows(int rows, int strips) {
   switch (rows) {
-    case 4: return by_strips<4>(strips);
-    case 8: return by_strips<8>(strips);
+    case 4: return by_strips<V, 4>(strips);
+    case 8: return by_strips<V, 8>(strips);
   }
-  if constexpr (AMS_SLICE_VARIANT != kSliceRagged) {
+  if constexpr (V != kSliceRagged) {
     switch (rows) {
-      case 16: return by_strips<16>(strips);
-      case 32: return by_strips<32>(strips);
+      case 16: return by_strips<V, 16>(strips);
+      case 32: return by_strips<V, 32>(strips);
     }
   }
   return nullptr;
 }
+
+}  // namespace
+
+#if AMS_SLICE_RUN_SCALES
+template <>
+const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, ams_dev::kSliceRunScales>(int rows, int strips) {
+  return by_rows<kSliceRunScales>(rows, strips);
+}
+#else
+template <>
+const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, ams_dev::kSlicePlain>(int rows, int strips) {
+  return by_rows<kSlicePlain>(rows, strips);
+}
+template <>
+const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, ams_dev::kSliceRagged>(int rows, int strips) {
+  return by_rows<kSliceRagged>(rows, strips);
+}
+#endif
