@@ -71,7 +71,7 @@ const char* ams_strerror(int code);
  * is only REQUIRED before the first call of an entry point happens inside a HIP stream
  * capture (function attributes should not be changed while capturing).  Allocates nothing,
  * enqueues nothing; may be called any number of times, once per device that is used (the first call
- * takes about 20 ms: the HIP runtime loads every kernel of the library).
+ * takes about 25 ms: the HIP runtime loads every kernel of the library).
  */
 int ams_init(void);
 

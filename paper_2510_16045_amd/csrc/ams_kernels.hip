@@ -1403,7 +1403,8 @@ bool short_slices_on_column(int fmt, int M, int spw, int gk, int n_rec_all) {
 // bytes' worth (4608 x 2368 FP5.33 M = 16 5.47 / 5.71, FP4.25 5888 x 22656 26.7 / 27.9).  us, one / two tiles: 4096 x 14336 FP4.25 M = 32
 // 20.3 / 16.4, M = 24 17.8 / 16.3, M = 16 13.9 / 13.2, M = 12 12.5 / 12.7; FP5.33 M = 32 22.6 / 18.3; 8192 x 8192 M = 32 15.7 / 14.5,
 // M = 16 11.7 / 12.9; 14336 x 4096 M = 32 12.9 / 13.1; 2560 x 9728 M = 24 12.8 / 11.1, three tiles 9.6.  Tiles of fewer than eight rows never
-// pay (2419 x 20352 FP5.33 M = 12 16.9, three tiles 19.2).  The bound on the records keeps a third record for some wavefront.
+// pay (2419 x 20352 FP5.33 M = 12 16.9, three tiles 19.2).  With fewer
+// than 18 records, two for a wavefront, the plans stay as they were (not measured).
 constexpr int64_t kSplitMaxStrips = 16384;  // strips that the counters of a split of K have room for
 struct RowSplit {
   int strips, positions;  // strips per workgroup; workgroups of one tile: whole groups of eight, so that the tiles of a position meet on one XCD

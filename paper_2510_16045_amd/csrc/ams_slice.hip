@@ -11,10 +11,10 @@
 // all NS strips.  What it replaces staged the activations of all of K (or of a phase of it) for the workgroup, through
 // registers, between barriers, and sat in front of the weight stream.
 //
-// Bound: at M <= 8 by the weight stream and the restoration's VALU work, as before; at M = 32 with one strip per workgroup
-// by what a compute unit does per record (64 KiB of activations through LDS in and out, restoration, permutation): with
-// neither weights nor activations coming from memory 4096 x 14336 still takes 12 us.  L2 is not the bound: 256 workgroups
-// that read 896 KiB each do so in 7 us.
+// Bound: at M <= 8 by the weight stream and the restoration's VALU work; at larger batches by the one in-order path through
+// which a compute unit draws weights (from memory) and activations (from L2), 32 KiB of both in flight: without the activations 4096 x
+// 14336 FP4.25 at M = 32 took 9.7 us of 20.2, without weights from memory 14.9, without either 9.0, without the restoration
+// 20.1.  So the rows are dealt to several workgroups there (20.2 -> 16.0).
 //
 // Measured against what it replaces (us, M = 1 / 4 / 16 / 32): 4096 x 4096 FP4.25 5.2 -> 4.3, 6.0 -> 4.5, 7.6 -> 6.1, 13.4 -> 8.0;
 // 4096 x 14336 8.7 -> 8.5, 10.3 -> 9.3, 18.3 -> 13.7, 30.9 -> 19.7; 8192 x 8192 FP5.33 10.5 -> 10.0, 11.2 -> 10.3, 15.6 -> 14.2,
