@@ -187,17 +187,26 @@ __device__ __forceinline__ bool exchange_tile(const LinearArgs& a, int gk, int s
   before = __builtin_amdgcn_readfirstlane(before);
   if (before != (unsigned)a.gk - 1) return false;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the count has returned; the tile loads below are issued after it
-  f4 part[kMaxSlices][MT];
+  // With two row tiles four slices are in registers at a time, the second four only where they exist:
+  // all eight would be 64 registers, which workgroups of 1024 threads have only with spills (10 column
+  // kernels spilled, now 5).  8192 x 14337 FP6 M = 32 in four slices 33.1 -> 32.6 us, 5120 x 10008 FP4.33
+  // M = 24 15.1 -> 14.9; with eight slices one trip more, 1000 x 14337 FP5.33 M = 24 12.7 -> 12.9.
+  constexpr int AT_ONCE = kMaxSlices / MT;
 #pragma unroll
-  for (int q = 0; q < kMaxSlices; q++)
+  for (int t = 0; t < MT; t++) sum[t] = f4{0, 0, 0, 0};
 #pragma unroll
-    for (int t = 0; t < MT; t++)  // slices that do not exist read nothing and add 0
-      part[q][t] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(tiles, q < a.gk ? offset(q, t) : kOutOfRange, 0, kDeviceScope));
+  for (int q0 = 0; q0 < kMaxSlices; q0 += AT_ONCE) {
+    if (q0 > 0 && q0 >= a.gk) break;
+    f4 part[AT_ONCE][MT];
 #pragma unroll
-  for (int t = 0; t < MT; t++) {
-    sum[t] = f4{0, 0, 0, 0};
+    for (int q = 0; q < AT_ONCE; q++)
 #pragma unroll
-    for (int q = 0; q < kMaxSlices; q++) sum[t] += part[q][t];
+      for (int t = 0; t < MT; t++)  // slices that do not exist read nothing and add 0
+        part[q][t] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(tiles, q0 + q < a.gk ? offset(q0 + q, t) : kOutOfRange, 0, kDeviceScope));
+#pragma unroll
+    for (int t = 0; t < MT; t++)
+#pragma unroll
+      for (int q = 0; q < AT_ONCE; q++) sum[t] += part[q][t];
   }
   if (lane == 0) __hip_atomic_store(a.ws_count + strip, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return true;
