@@ -545,39 +545,43 @@ void pack_strip(int fmt, const uint8_t* const rows[16], int64_t K, uint8_t* pack
 
 // Strip t quantized and packed in one pass over its weights, where the format's half-words are whole sharing groups: whole
 // records straight into the packed matrix, the rest of the rows and the padding as codes.  run: weights per scale (K, or a
-// multiple of the record).  scale_of(r, j): where run j of row r keeps its scale.  Returns false on inf/NaN.
+// multiple of the record).  scale_of(r, j): where run j of row r keeps its scale.  Returns false on inf/NaN; a run that holds one
+// gets zero codes and its scale is left alone, as where the codes are made first.
 template <class ScaleOf>
 bool quantize_and_pack_strip(const RowQuant& q, const FormatInfo& fi, const WideRow& wide, const uint16_t* W, int64_t N, int64_t K, int64_t ldw, int64_t run,
                              uint16_t forced_scale, uint8_t* packed, int64_t n_strips, int64_t t, Steps& steps, ScaleOf&& scale_of) {
   const int64_t whole = K / fi.rec_k, rest = K - whole * fi.rec_k;
-  uint8_t rest_codes[16][128];
+  uint8_t rest_codes[16][128] = {};
   const uint8_t* rows[16];
   bool finite = true;
   for (int r = 0; r < 16; r++) {
     const int64_t n = t * 16 + r;
     rows[r] = n < N ? rest_codes[r] : nullptr;
-    if (n >= N) {  // a row of zero codes
-      for (int64_t j = 0; j < whole; j++) {
-        const ams::RecordPlace rp = ams::record_place(fi, n_strips, t, j);
+    auto zero_codes = [&](int64_t rec, int64_t rec_end) {  // whole records of this row
+      for (; rec < rec_end; rec++) {
+        const ams::RecordPlace rp = ams::record_place(fi, n_strips, t, rec);
         for (int c = 0; c < 4; c++) {
           std::memset(packed + rp.chunks + (c * 16 + r) * fi.chunk_bytes, 0, (size_t)fi.chunk_bytes);
           std::memset(packed + rp.side + 4 * (c * 16 + r) + rp.side_shift / 8, 0, (size_t)fi.side_bytes);
         }
       }
+    };
+    if (n >= N) {
+      zero_codes(0, whole);
       continue;
     }
     const uint16_t* w = W + n * ldw;
     for (int64_t a = 0, j = 0; a < K; a += run, j++) {
-      const int64_t end = std::min(K, a + run);
+      const int64_t end = std::min(K, a + run), rec = a / fi.rec_k, rec_end = std::min(end / fi.rec_k, whole);
       const uint16_t absmax = abs_max_bits(w + a, end - a);
       if (absmax >= 0x7C00) {
         finite = false;
+        zero_codes(rec, rec_end);
         continue;
       }
       const uint16_t sb = forced_scale ? forced_scale : scale_bits(absmax, q.fmax);
       *scale_of(r, j) = sb;
-      const int64_t rec_end = std::min(end / fi.rec_k, whole);
-      wide.records(q.fmt, w + a, a / fi.rec_k, rec_end, half_to_double(sb), packed, n_strips, t, r);
+      wide.records(q.fmt, w + a, rec, rec_end, half_to_double(sb), packed, n_strips, t, r);
       uint16_t same;
       if (end > whole * fi.rec_k) quantize_row(q, w + whole * fi.rec_k, rest, rest_codes[r], &same, steps, sb);
     }

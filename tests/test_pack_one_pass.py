@@ -66,3 +66,32 @@ def test_ties_of_codes_and_of_errors(fmt, ofmt):
         W[2, 699] = bad
         with pytest.raises(ams.AmsError):
             ams.ams_pack(fmt, W)
+
+
+@pytest.mark.parametrize("fmt,ofmt", PAIRS)
+@pytest.mark.parametrize("scale_group", [0, 1, 2])
+@pytest.mark.parametrize("N,K,bad", [(3, 70, ((1, 69),)), (17, 300, ((0, 5), (16, 299))), (20, 1000, ((4, 999), (5, 400), (5, 600), (18, 0)))])
+def test_rows_with_infinities_are_zero_codes(fmt, ofmt, scale_group, N, K, bad):
+    # refused, with every byte of the matrix written all the same: the row or run with an inf or NaN as zero codes, its scale
+    # left alone, and the others as ever, whether anybody asks for the codes (made first then) or not (one pass)
+    rec = 96 if ofmt.code_bits == 6 or fmt == ams.FP433 else 128
+    W = weights(N, K, K + fmt)
+    lib, out = ams.load_library(), []
+    codes = (O.ams_quantize_grouped(W, ofmt, rec * scale_group) if scale_group else O.ams_quantize(W, ofmt))[0]
+    want = codes.astype(np.uint8)
+    run = rec * scale_group or K
+    for i, (n, k) in enumerate(bad):
+        W[n, k] = (np.inf, -np.inf, np.nan)[i % 3]
+        want[n, k // run * run : (k // run + 1) * run] = 0
+    for codes_out in (None, np.empty((N, K), np.uint8)):
+        packed = np.full(ams.ams_packed_bytes(fmt, N, K), 0xA5, np.uint8)
+        got = np.full((N + 15) // 16 * 16 * -(-K // run), 0x1234, np.uint16)
+        ptr = codes_out.ctypes.data if codes_out is not None else None
+        if scale_group:
+            rc = lib.ams_pack_grouped(fmt, 0, run, W.ctypes.data, N, K, K, packed.ctypes.data, got.ctypes.data, ptr)
+        else:
+            rc = lib.ams_pack_ex(fmt, 0, W.ctypes.data, N, K, K, packed.ctypes.data, got.ctypes.data, ptr)
+        assert rc == -5  # AMS_ERR_NONFINITE
+        assert np.array_equal(packed, ams.ams_pack_codes(fmt, want))
+        out.append(got)
+    assert np.array_equal(*out) and np.count_nonzero(out[0] == 0x1234) >= len({(n, k // run) for n, k in bad})
