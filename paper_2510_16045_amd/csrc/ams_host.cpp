@@ -84,7 +84,8 @@ inline int reround_magnitude_code(double a, int mbits, int m0) {
   double best_d = std::fabs(a - magnitude(m0, mbits));
   for (int j = 1; j < n_upper; j++) {
     const double d = std::fabs(a - magnitude(2 * j + m0, mbits));
-    if (d < best_d || (d == best_d && (j & 1) == 0)) best = j, best_d = d;
+    if (d > best_d) break;  // the magnitudes ascend: from here on they are further and further away
+    if (d < best_d || (j & 1) == 0) best = j, best_d = d;
   }
   return 2 * best + m0;
 }

@@ -95,3 +95,15 @@ def test_rows_with_infinities_are_zero_codes(fmt, ofmt, scale_group, N, K, bad):
         assert np.array_equal(packed, ams.ams_pack_codes(fmt, want))
         out.append(got)
     assert np.array_equal(*out) and np.count_nonzero(out[0] == 0x1234) >= len({(n, k // run) for n, k in bad})
+
+
+@pytest.mark.parametrize("fmt,ofmt", PAIRS)
+@pytest.mark.parametrize("K", [5, 150, 700])  # candidates found one by one, and by intervals
+def test_ties_of_the_rerounding_search(fmt, ofmt, K):
+    # multiples of a quarter of the smallest step: midpoints between neighbouring candidates
+    rng, fmax = np.random.default_rng(fmt + K), float(np.max(O.magnitude_table(ofmt)))
+    W = (rng.integers(-int(fmax * 32), int(fmax * 32) + 1, (6, K)) / 32.0 * 2.0 ** rng.integers(-10, 6, (6, 1))).astype(np.float16)
+    W[1:4, 0] = fmax * np.array([0.25, 1, 4])
+    codes, scales, _ = O.ams_quantize(W, ofmt, search="reround")
+    packed, got = ams.ams_pack_ex(fmt, ams.SEARCH_REROUND, W)
+    assert np.array_equal(got.view(np.uint16), scales.view(np.uint16)) and np.array_equal(packed, ams.ams_pack_codes(fmt, codes.astype(np.uint8)))
