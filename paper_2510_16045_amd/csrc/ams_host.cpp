@@ -404,20 +404,21 @@ const WideRow* wide_row() {
 }
 
 // Quantize one row (or run): scale (Eq. 1), RTN, adaptive search of each group's shared bit.  Returns false on inf/NaN.
-// forced_scale: 0 = the row's own scale (Eq. 1 per output channel), else the fp16 bits to use.
+// forced_scale: 0 = the row's own scale (Eq. 1 per output channel), else the fp16 bits to use (whoever gives them has seen
+// that the weights are finite).
 // 4096 x 4096 FP5.33, packing included, on 16 threads: 0.9 ms in vectors, 2.2 ms with the codes looked up (the re-rounding
 // search, processors without AVX2), 36 ms when every weight was divided, rounded and compared by itself with library calls.
 bool quantize_row(const RowQuant& q, const uint16_t* w, int64_t K, uint8_t* codes, uint16_t* scale_out, Steps& steps, uint16_t forced_scale = 0) {
-  const uint16_t absmax = abs_max_bits(w, K);
+  const int sign_shift = 2 + q.mbits;
+  // Looking codes up pays from about 200 weights per scale on (finding the intervals takes as long as evaluating that
+  // many): 3971 x 400 FP5.33 3.3 -> 2.0 ms on 8 threads, 8000 x 200 3.5 -> 3.3, 16384 x 128 4.8 -> 5.9.
+  const WideRow* const wide = q.search == AMS_SEARCH_SET_BIT && K >= 8 * q.group ? wide_row() : nullptr;  // not for less than a vector
+  const bool lookup = !wide && K >= 192;
+  const uint16_t absmax = !forced_scale || lookup ? abs_max_bits(w, K) : 0;
   if (absmax >= 0x7C00) return false;
   const uint16_t sb = forced_scale ? forced_scale : scale_bits(absmax, q.fmax);
   *scale_out = sb;
   const double s = half_to_double(sb);
-  const int sign_shift = 2 + q.mbits;
-  // Looking codes up pays from about 200 weights per scale on (finding the intervals takes as long as evaluating that
-  // many): 3971 x 400 FP5.33 3.3 -> 2.0 ms on 8 threads, 8000 x 200 3.5 -> 3.3, 16384 x 128 4.8 -> 5.9.
-  const WideRow* const wide = q.search == AMS_SEARCH_SET_BIT ? wide_row() : nullptr;
-  const bool lookup = !wide && K >= 192;
   if (lookup) steps.build(q, s, absmax);
   auto finish = [&](int64_t k, int mag_code) {
     const uint16_t wk = w[k];
@@ -618,18 +619,24 @@ void unpack_strip(int fmt, const FormatInfo& fi, const uint8_t* packed, int64_t 
   }
 }
 
-// Whether strips are quantized and packed in one pass: nobody asks for the codes, and the format and the processor allow it.
-const WideRow* one_pass(const RowQuant& q, const uint8_t* codes_out) {
-  const bool fits = (q.fmt == ams::kFmtFp533 || q.fmt == ams::kFmtFp425) && q.search == AMS_SEARCH_SET_BIT && !codes_out;
+// Whether strips are quantized and packed in one pass: nobody asks for the codes, the rows have whole records, and the format
+// and the processor allow it.
+const WideRow* one_pass(const RowQuant& q, const FormatInfo& fi, int64_t K, const uint8_t* codes_out) {
+  const bool fits = (q.fmt == ams::kFmtFp533 || q.fmt == ams::kFmtFp425) && q.search == AMS_SEARCH_SET_BIT && !codes_out && K >= fi.rec_k;
   return fits ? wide_row() : nullptr;
 }
 
-// Time of a weight in the packer, on one thread: in one pass, with the codes apart, one by one (long rows are looked up and
-// faster; on those all threads start anyway).
-double quantize_ns(const RowQuant& q, const WideRow* in_one_pass) {
-  if (q.search == AMS_SEARCH_REROUND) return 30;
-  return in_one_pass ? 0.4 : wide_row() ? 0.8 : 6;
+// Time of N rows of K weights in the packer with `run` weights per scale, on one thread: every scale, and a weight in one pass,
+// with the codes apart, looked up (long runs), one by one.  (Long rows are faster; on those all threads start anyway.)
+double quantize_ns(const RowQuant& q, const WideRow* in_one_pass, int64_t N, int64_t K, int64_t run) {
+  run = std::min(run, K);
+  const bool wide = q.search == AMS_SEARCH_SET_BIT && run >= 8 * q.group && wide_row();
+  const double weight = q.search == AMS_SEARCH_REROUND ? 30 : in_one_pass ? 0.4 : wide ? 0.8 : run >= 192 ? 6 : 15;
+  return N * ((K + run - 1) / run * 100.0 + K * weight);
 }
+// The same of codes that are given: placed by table, and read back bit by bit (at a twentieth of this, four threads
+// where eight pay, 256 x 768 took 620 us instead of 410).
+constexpr double kPackCodesNs = 1.5, kUnpackNs = 8;
 
 int check_shape(int fmt, int64_t N, int64_t K) {
   if (!ams::format_info(fmt)) return AMS_ERR_FORMAT;
@@ -760,8 +767,8 @@ int pack_rows(int fmt, int search, bool per_tensor, const uint16_t* W, int64_t N
     tensor_scale = scale_bits(absmax, fi.fmax);
   }
   std::atomic<int> bad{0};
-  const WideRow* const wide = one_pass(rq, codes_out);
-  const bool done = parallel_for(n_strips, (double)N * K * quantize_ns(rq, wide), [&](int64_t t) {
+  const WideRow* const wide = one_pass(rq, fi, K, codes_out);
+  const bool done = parallel_for(n_strips, quantize_ns(rq, wide, N, K, K), [&](int64_t t) {
     Steps steps;
     if (wide) {
       if (!quantize_and_pack_strip(rq, fi, *wide, W, N, K, ldw, K, tensor_scale, (uint8_t*)packed, n_strips, t, steps,
@@ -817,8 +824,8 @@ int ams_pack_grouped(int fmt, int search, int64_t scale_group, const uint16_t* W
   const int64_t n_strips = ams::round_up(N, ams::kStripRows) / ams::kStripRows;
   const int64_t n_sg = (K + scale_group - 1) / scale_group;
   std::atomic<int> bad{0};
-  const WideRow* const wide = one_pass(rq, codes_out);
-  const bool done = parallel_for(n_strips, (double)N * K * quantize_ns(rq, wide), [&](int64_t t) {
+  const WideRow* const wide = one_pass(rq, fi, K, codes_out);
+  const bool done = parallel_for(n_strips, quantize_ns(rq, wide, N, K, scale_group), [&](int64_t t) {
     Steps steps;
     if (wide) {
       auto scale_of = [&](int r, int64_t j) { return scales + ((size_t)t * n_sg + j) * 16 + r; };
@@ -857,7 +864,7 @@ int ams_pack_codes(int fmt, const uint8_t* codes, int64_t N, int64_t K, void* pa
   const FormatInfo& fi = *ams::format_info(fmt);
   const int64_t n_strips = ams::round_up(N, ams::kStripRows) / ams::kStripRows;
   std::atomic<int> bad{0};
-  parallel_for(n_strips, (double)N * K * 0.4, [&](int64_t t) {
+  parallel_for(n_strips, (double)N * K * kPackCodesNs, [&](int64_t t) {
     const uint8_t* rows[16];
     for (int r = 0; r < 16; r++) {
       const int64_t n = t * 16 + r;
@@ -879,7 +886,7 @@ int ams_unpack_host(int fmt, const void* packed, int64_t N, int64_t K, uint8_t* 
   if (!codes || !packed) return AMS_ERR_NULL;
   const FormatInfo& fi = *ams::format_info(fmt);
   const int64_t n_strips = ams::round_up(N, ams::kStripRows) / ams::kStripRows;
-  parallel_for(n_strips, (double)N * K * 0.4, [&](int64_t t) {
+  parallel_for(n_strips, (double)N * K * kUnpackNs, [&](int64_t t) {
     uint8_t* rows[16];
     for (int r = 0; r < 16; r++) rows[r] = t * 16 + r < N ? codes + (t * 16 + r) * K : nullptr;
     unpack_strip(fmt, fi, (const uint8_t*)packed, n_strips, t, K, rows);
