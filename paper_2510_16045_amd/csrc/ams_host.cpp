@@ -90,10 +90,12 @@ inline int reround_magnitude_code(double a, int mbits, int m0) {
   return 2 * best + m0;
 }
 
+struct WideRow;
 struct RowQuant {
   int fmt, mbits, group;
   double fmax;
   int search;  // AMS_SEARCH_*
+  const WideRow* vectors;  // the instruction set's vector path (nullptr: none)
 };
 
 // Largest magnitude of a run of weights as binary16 bits (they order like the magnitudes); 0x7C00 or more when one of
@@ -358,6 +360,7 @@ AMS_INLINE void wide_records(const uint16_t* w, int64_t rec, int64_t rec_end, do
 
 // One row (or run) in one format, for one instruction set.
 struct WideRow {
+  int lanes;
   int64_t (*codes)(int fmt, const uint16_t* w, int64_t K, double s, uint8_t* codes);
   void (*records)(int fmt, const uint16_t* w, int64_t rec, int64_t rec_end, double s, uint8_t* packed, int64_t n_strips, int64_t t, int r);
 };
@@ -393,14 +396,14 @@ AMS_AVX512 void records_avx512(int fmt, const uint16_t* w, int64_t rec, int64_t 
 AMS_AVX2 void records_avx2(int fmt, const uint16_t* w, int64_t rec, int64_t rec_end, double s, uint8_t* packed, int64_t n_strips, int64_t t, int r) {
   wide_records_of<8>(fmt, w, rec, rec_end, s, packed, n_strips, t, r);
 }
-// What this processor has of them (nullptr: neither; the codes are then looked up).
-const WideRow* wide_row() {
-  static const WideRow avx512 = {codes_avx512, records_avx512}, avx2 = {codes_avx2, records_avx2};
-  static const WideRow* const have = __builtin_cpu_supports("avx512f") && __builtin_cpu_supports("avx512bw") && __builtin_cpu_supports("avx512dq") &&
-                                             __builtin_cpu_supports("avx512vl") && __builtin_cpu_supports("f16c")
-                                         ? &avx512
-                                     : __builtin_cpu_supports("avx2") && __builtin_cpu_supports("f16c") ? &avx2 : nullptr;
-  return have;
+// Vectors of at most `lanes` groups: the widest that this processor has (nullptr: none; the codes are then looked up).
+constexpr int kWidest = 16;
+const WideRow* wide_row(int lanes) {
+  static const WideRow avx512 = {16, codes_avx512, records_avx512}, avx2 = {8, codes_avx2, records_avx2};
+  static const bool has512 = __builtin_cpu_supports("avx512f") && __builtin_cpu_supports("avx512bw") && __builtin_cpu_supports("avx512dq") &&
+                             __builtin_cpu_supports("avx512vl") && __builtin_cpu_supports("f16c");
+  static const bool has2 = __builtin_cpu_supports("avx2") && __builtin_cpu_supports("f16c");
+  return lanes >= 16 && has512 ? &avx512 : lanes >= 8 && has2 ? &avx2 : nullptr;
 }
 
 // Quantize one row (or run): scale (Eq. 1), RTN, adaptive search of each group's shared bit.  Returns false on inf/NaN.
@@ -412,7 +415,7 @@ bool quantize_row(const RowQuant& q, const uint16_t* w, int64_t K, uint8_t* code
   const int sign_shift = 2 + q.mbits;
   // Looking codes up pays from about 200 weights per scale on (finding the intervals takes as long as evaluating that
   // many): 3971 x 400 FP5.33 3.3 -> 2.0 ms on 8 threads, 8000 x 200 3.5 -> 3.3, 16384 x 128 4.8 -> 5.9.
-  const WideRow* const wide = q.search == AMS_SEARCH_SET_BIT && K >= 8 * q.group ? wide_row() : nullptr;  // not for less than a vector
+  const WideRow* const wide = q.search == AMS_SEARCH_SET_BIT && K >= 8 * q.group ? q.vectors : nullptr;  // not for less than a vector
   const bool lookup = !wide && K >= 192;
   const uint16_t absmax = !forced_scale || lookup ? abs_max_bits(w, K) : 0;
   if (absmax >= 0x7C00) return false;
@@ -623,14 +626,14 @@ void unpack_strip(int fmt, const FormatInfo& fi, const uint8_t* packed, int64_t 
 // and the processor allow it.
 const WideRow* one_pass(const RowQuant& q, const FormatInfo& fi, int64_t K, const uint8_t* codes_out) {
   const bool fits = (q.fmt == ams::kFmtFp533 || q.fmt == ams::kFmtFp425) && q.search == AMS_SEARCH_SET_BIT && !codes_out && K >= fi.rec_k;
-  return fits ? wide_row() : nullptr;
+  return fits ? q.vectors : nullptr;
 }
 
 // Time of N rows of K weights in the packer with `run` weights per scale, on one thread: every scale, and a weight in one pass,
 // with the codes apart, looked up (long runs), one by one.  (Long rows are faster; on those all threads start anyway.)
 double quantize_ns(const RowQuant& q, const WideRow* in_one_pass, int64_t N, int64_t K, int64_t run) {
   run = std::min(run, K);
-  const bool wide = q.search == AMS_SEARCH_SET_BIT && run >= 8 * q.group && wide_row();
+  const bool wide = q.search == AMS_SEARCH_SET_BIT && run >= 8 * q.group && q.vectors;
   const double weight = q.search == AMS_SEARCH_REROUND ? 30 : in_one_pass ? 0.4 : wide ? 0.8 : run >= 192 ? 6 : 15;
   return N * ((K + run - 1) / run * 100.0 + K * weight);
 }
@@ -735,29 +738,29 @@ int ams_pack(int fmt, const uint16_t* W, int64_t N, int64_t K, int64_t ldw, void
 }
 
 namespace {
-int pack_rows(int fmt, int search, bool per_tensor, const uint16_t* W, int64_t N, int64_t K, int64_t ldw, void* packed,
+int pack_rows(int lanes, int fmt, int search, bool per_tensor, const uint16_t* W, int64_t N, int64_t K, int64_t ldw, void* packed,
               uint16_t* scales, uint8_t* codes_out);
 }
 
 int ams_pack_ex(int fmt, int search, const uint16_t* W, int64_t N, int64_t K, int64_t ldw, void* packed, uint16_t* scales,
                 uint8_t* codes_out) {
-  return pack_rows(fmt, search, false, W, N, K, ldw, packed, scales, codes_out);
+  return pack_rows(kWidest, fmt, search, false, W, N, K, ldw, packed, scales, codes_out);
 }
 
 int ams_pack_per_tensor(int fmt, int search, const uint16_t* W, int64_t N, int64_t K, int64_t ldw, void* packed,
                         uint16_t* scales, uint8_t* codes_out) {
-  return pack_rows(fmt, search, true, W, N, K, ldw, packed, scales, codes_out);
+  return pack_rows(kWidest, fmt, search, true, W, N, K, ldw, packed, scales, codes_out);
 }
 
 namespace {
-int pack_rows(int fmt, int search, bool per_tensor, const uint16_t* W, int64_t N, int64_t K, int64_t ldw, void* packed,
+int pack_rows(int lanes, int fmt, int search, bool per_tensor, const uint16_t* W, int64_t N, int64_t K, int64_t ldw, void* packed,
               uint16_t* scales, uint8_t* codes_out) {
   if (int rc = check_shape(fmt, N, K)) return rc;
   if (search != AMS_SEARCH_SET_BIT && search != AMS_SEARCH_REROUND) return AMS_ERR_SHAPE;
   if (!W || !packed || !scales) return AMS_ERR_NULL;
   if (ldw < K) return AMS_ERR_SHAPE;
   const FormatInfo& fi = *ams::format_info(fmt);
-  const RowQuant rq = {fmt, fi.code_bits - 3, fi.group, fi.fmax, search};
+  const RowQuant rq = {fmt, fi.code_bits - 3, fi.group, fi.fmax, search, wide_row(lanes)};
   const int64_t n_strips = ams::round_up(N, ams::kStripRows) / ams::kStripRows;
   uint16_t tensor_scale = 0;
   if (per_tensor) {  // Eq. 1 with the maximum over the whole matrix
@@ -812,15 +815,16 @@ int ams_group_scales_count(int fmt, int64_t N, int64_t K, int64_t scale_group, s
   return AMS_OK;
 }
 
-int ams_pack_grouped(int fmt, int search, int64_t scale_group, const uint16_t* W, int64_t N, int64_t K, int64_t ldw,
-                     void* packed, uint16_t* scales, uint8_t* codes_out) {
+namespace {
+int pack_runs(int lanes, int fmt, int search, int64_t scale_group, const uint16_t* W, int64_t N, int64_t K, int64_t ldw,
+              void* packed, uint16_t* scales, uint8_t* codes_out) {
   if (int rc = check_shape(fmt, N, K)) return rc;
   if (search != AMS_SEARCH_SET_BIT && search != AMS_SEARCH_REROUND) return AMS_ERR_SHAPE;
   if (!W || !packed || !scales) return AMS_ERR_NULL;
   if (ldw < K) return AMS_ERR_SHAPE;
   const FormatInfo& fi = *ams::format_info(fmt);
   if (scale_group_shift(fi, scale_group) < 0) return AMS_ERR_SHAPE;
-  const RowQuant rq = {fmt, fi.code_bits - 3, fi.group, fi.fmax, search};
+  const RowQuant rq = {fmt, fi.code_bits - 3, fi.group, fi.fmax, search, wide_row(lanes)};
   const int64_t n_strips = ams::round_up(N, ams::kStripRows) / ams::kStripRows;
   const int64_t n_sg = (K + scale_group - 1) / scale_group;
   std::atomic<int> bad{0};
@@ -856,6 +860,24 @@ int ams_pack_grouped(int fmt, int search, int64_t scale_group, const uint16_t* W
   });
   if (!done) return AMS_ERR_NOMEM;
   return bad.load() ? AMS_ERR_NONFINITE : AMS_OK;
+}
+
+}  // namespace
+
+int ams_pack_grouped(int fmt, int search, int64_t scale_group, const uint16_t* W, int64_t N, int64_t K, int64_t ldw,
+                     void* packed, uint16_t* scales, uint8_t* codes_out) {
+  return pack_runs(kWidest, fmt, search, scale_group, W, N, K, ldw, packed, scales, codes_out);
+}
+
+// Not in the header, for the tests: the packer as a processor with vectors of at most `lanes` groups (16, 8 or 0) runs it.
+// scale_group: weights per scale, 0: a scale per row, -1: one for the matrix.  AMS_ERR_DEVICE: this processor's vectors
+// are shorter.
+int ams_pack_lanes(int lanes, int fmt, int search, int64_t scale_group, const uint16_t* W, int64_t N, int64_t K, int64_t ldw,
+                   void* packed, uint16_t* scales, uint8_t* codes_out) {
+  const WideRow* const vectors = wide_row(lanes);
+  if (lanes != (vectors ? vectors->lanes : 0)) return AMS_ERR_DEVICE;
+  if (scale_group > 0) return pack_runs(lanes, fmt, search, scale_group, W, N, K, ldw, packed, scales, codes_out);
+  return pack_rows(lanes, fmt, search, scale_group < 0, W, N, K, ldw, packed, scales, codes_out);
 }
 
 int ams_pack_codes(int fmt, const uint8_t* codes, int64_t N, int64_t K, void* packed) {

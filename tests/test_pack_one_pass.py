@@ -2,6 +2,8 @@
 packing the codes that the oracle finds, at the edges of vectors, lane chunks, records and strips, for every scale
 granularity; rows that make the first decision of a code or last bit unsure are decided exactly."""
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -107,3 +109,45 @@ def test_ties_of_the_rerounding_search(fmt, ofmt, K):
     codes, scales, _ = O.ams_quantize(W, ofmt, search="reround")
     packed, got = ams.ams_pack_ex(fmt, ams.SEARCH_REROUND, W)
     assert np.array_equal(got.view(np.uint16), scales.view(np.uint16)) and np.array_equal(packed, ams.ams_pack_codes(fmt, codes.astype(np.uint8)))
+
+
+def pack_lanes(lanes, fmt, W, scale_group, codes_out=False):
+    """ams_pack* as a processor with vectors of `lanes` groups runs it; skips where this one has none so long."""
+    N, K = W.shape
+    fn = ams.load_library().ams_pack_lanes
+    fn.argtypes = [ctypes.c_int] * 3 + [ctypes.c_int64, ctypes.c_void_p] + [ctypes.c_int64] * 3 + [ctypes.c_void_p] * 3
+    packed = np.full(ams.ams_packed_bytes(fmt, N, K), 0xA5, np.uint8)
+    n_scales = -(-N // 16) * 16 * -(-K // scale_group) if scale_group > 0 else N
+    scales, codes = np.zeros(n_scales, np.float16), np.full((N, K), 0xA5, np.uint8)
+    rc = fn(lanes, fmt, ams.SEARCH_SET_BIT, scale_group, W.ctypes.data, N, K, K, packed.ctypes.data, scales.ctypes.data, codes.ctypes.data if codes_out else None)
+    if rc == -7:  # AMS_ERR_DEVICE
+        pytest.skip(f"no vectors of {lanes} groups on this processor")
+    assert rc == 0
+    return packed, scales, codes
+
+
+def tied_weights(fmt, ofmt, K):
+    rng, fmax = np.random.default_rng(fmt), float(np.max(O.magnitude_table(ofmt)))
+    rows = [rng.integers(-int(fmax * 32), int(fmax * 32) + 1, K) / 32.0 * 2.0**e for e in (-10, 0, 5)]
+    for w, e in zip(rows, (-10, 0, 5)):
+        w[0] = fmax * 2.0**e
+    return np.stack(rows + [rng.integers(-top, top + 1, K) * 2.0**-24 for top in (1, 3, 11, 40)]).astype(np.float16)
+
+
+@pytest.mark.parametrize("lanes", [16, 8, 0])
+@pytest.mark.parametrize("fmt,ofmt", PAIRS)
+def test_every_vector_length_leaves_the_codes_bytes(fmt, ofmt, lanes):
+    # every instruction set's path, whatever this processor would take: with 16 groups at a time, with 8, looked up
+    rec = 96 if ofmt.code_bits == 6 or fmt == ams.FP433 else 128
+    for N, K in ((1, 1), (5, 23), (16, 24), (17, 32), (3, 47), (15, 48), (33, 63), (2, 64), (7, 96), (18, 97), (31, 128), (9, 129), (16, 511), (5, 515), (20, 1000), (7, 700)):
+        W = tied_weights(fmt, ofmt, K) if K == 700 else weights(N, K, 10 * K + fmt)
+        codes, scales, _ = O.ams_quantize(W, ofmt)
+        want = ams.ams_pack_codes(fmt, codes.astype(np.uint8))
+        for codes_out in (False, True):
+            packed, got, out = pack_lanes(lanes, fmt, W, 0, codes_out)
+            assert np.array_equal(packed, want) and np.array_equal(got.view(np.uint16), scales.view(np.uint16)), (N, K)
+            assert not codes_out or np.array_equal(out, codes), (N, K)
+        packed, _, _ = pack_lanes(lanes, fmt, W, -1)
+        assert np.array_equal(packed, ams.ams_pack_codes(fmt, O.ams_quantize(W, ofmt, per_tensor=True)[0].astype(np.uint8))), (N, K)
+        packed, _, _ = pack_lanes(lanes, fmt, W, 2 * rec)
+        assert np.array_equal(packed, ams.ams_pack_codes(fmt, O.ams_quantize_grouped(W, ofmt, 2 * rec)[0].astype(np.uint8))), (N, K)
