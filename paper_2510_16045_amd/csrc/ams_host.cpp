@@ -635,7 +635,7 @@ double quantize_ns(const RowQuant& q, const WideRow* in_one_pass, int64_t N, int
   run = std::min(run, K);
   const bool wide = q.search == AMS_SEARCH_SET_BIT && run >= 8 * q.group && q.vectors;
   const double weight = q.search == AMS_SEARCH_REROUND ? 30 : in_one_pass ? 0.4 : wide ? 0.8 : run >= 192 ? 6 : 15;
-  return N * ((K + run - 1) / run * 100.0 + K * weight);
+  return N * ((K + run - 1) / run * (wide ? 30.0 : 100.0) + K * weight);
 }
 // The same of codes that are given: placed by table, and read back bit by bit (at a twentieth of this, four threads
 // where eight pay, 256 x 768 took 620 us instead of 410).
