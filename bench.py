@@ -248,7 +248,7 @@ def dominant_kernel(ams, layer, fmt_name, M):
     """The kernel the library's plan gives this Linear."""
     fmt = next(f for f, name in FMT_NAMES.items() if name == fmt_name)
     plan = ams.ams_linear_plan(fmt, M, layer.N, layer.K)
-    return "slice_kernel" if plan.startswith("slice ") or "streamed_rows=" in plan else "multi_kernel" if "strips_per_wave=2" in plan else "column_kernel"
+    return "slice_kernel" if plan.startswith("slice ") else "multi_kernel" if "strips_per_wave=2" in plan else "column_kernel"
 
 
 def measured_traffic(ams, layer, fmt_name, M, kernel):

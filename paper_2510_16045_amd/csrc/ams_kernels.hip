@@ -1457,9 +1457,6 @@ ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
   p.S = slice_waves(p.rows, p.spw, kSliceRagged);
   p.lr = slice_ahead(p.S);
   p.lds = (size_t)slice_lds(fmt, p.rows, p.spw, kSliceRagged);
-  p.wps = p.wpa = p.S / p.spw;
-  p.n_phase = 1;
-  p.qd = false;
   return p;
 }
 
@@ -2053,15 +2050,18 @@ int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, ch
   if (f != FMT_FP16) {
     const bool nt = n_strips * n_rec * (int64_t)rec_bytes >= (2ll << 20);  // as run_linear decides it
     const ColumnPlan cp = make_plan(f, M, n_strips, n_rec, rec_k, gk, K % 8 == 0, !grouped, nt);
-    if (cp.slice && !cp.ragged) {
+    if (cp.slice) {
+      const int rows = (M + cp.row_tiles - 1) / cp.row_tiles;
       const int len = snprintf(text, text_len, "slice grid=%d strips_per_wg=%d k_slices=%d waves=%d lds=%zu ahead=%d", cp.grid, cp.spw, cp.gk, cp.S, cp.lds, cp.lr);
-      if (cp.row_tiles > 1 && len > 0 && (size_t)len < text_len)
-        snprintf(text + len, text_len - len, " row_tiles=%d rows_per_tile=%d", cp.row_tiles, (M + cp.row_tiles - 1) / cp.row_tiles);
+      if (len > 0 && (size_t)len < text_len) {
+        if (cp.ragged)
+          snprintf(text + len, text_len - len, " streamed_rows=%d row_tiles=%d", rows, cp.row_tiles);
+        else if (cp.row_tiles > 1)
+          snprintf(text + len, text_len - len, " row_tiles=%d rows_per_tile=%d", cp.row_tiles, rows);
+      }
     } else {
-      const int len = snprintf(text, text_len, "column grid=%d strips_per_wg=%d k_slices=%d waves=%d waves_per_strip=%d phases=%d lds=%zu side_groups=%d active_per_strip=%d ahead=%d strips_per_wave=%d", cp.grid,
+      snprintf(text, text_len, "column grid=%d strips_per_wg=%d k_slices=%d waves=%d waves_per_strip=%d phases=%d lds=%zu side_groups=%d active_per_strip=%d ahead=%d strips_per_wave=%d", cp.grid,
                cp.spw, cp.gk, cp.S, cp.wps, cp.n_phase, cp.lds, cp.qd ? 1 : 0, cp.ns > 1 ? 1 : cp.wpa, cp.lr, cp.ns);
-      if (cp.ragged && len > 0 && (size_t)len < text_len)
-        snprintf(text + len, text_len - len, " streamed_rows=%d row_tiles=%d", (M + cp.row_tiles - 1) / cp.row_tiles, cp.row_tiles);
     }
     return AMS_OK;
   }

@@ -41,3 +41,10 @@ def test_printed_record_fits_where_8000_characters_are_kept():
     assert len(back["batch_sweep"]) == 24 and len(back["qwen_down"]["rows"]) == 24 and len(back["llama70b"]["rows"]) == 18
     none = dict(line, batch_sweep=None, llama70b=None, lm_head=None, qwen_down=None, cpu_baseline=None)
     assert all(bench.printed_record(none)[k] is None for k in ("batch_sweep", "llama70b", "lm_head", "qwen_down", "cpu_baseline"))
+
+
+def test_the_kernel_of_a_launch_is_the_one_its_plan_starts_with():
+    from types import SimpleNamespace
+
+    for N, K, M, kernel in ((28672, 4096, 1, "slice_kernel"), (11003, 4099, 5, "slice_kernel"), (28672, 4099, 5, "column_kernel"), (57344, 8192, 1, "multi_kernel")):
+        assert bench.dominant_kernel(ams, SimpleNamespace(N=N, K=K), "fp5.33-e2m3", M) == kernel

@@ -279,10 +279,14 @@ def test_launch_plans_cover_the_kernels_and_the_split():
     assert plan(ams.FP533, 32, 28672, 4099)["waves"] == "16" and plan(ams.FP533, 8, 28672, 4099)["waves"] == "8"
     assert plan(ams.FP425, 1, 4096, 14339)["waves"] == "16"  # one strip per workgroup: sixteen wavefronts share it
     assert plan(ams.FP533, 1, 4096, 14336)["waves"] == "8" and plan(ams.FP533, 4, 4096, 14339)["waves"] == "16"
-    assert plan(ams.FP533, 1, 4096, 4099)["waves"] == "16"  # 43 records for 8 wavefronts: too short a stream
-    assert plan(ams.FP533, 1, 6144, 4099)["waves"] == "16"  # 192 workgroups do not fill the chip
-    p = plan(ams.FP425, 1, 4096, 14339)  # one strip per workgroup: all 16 wavefronts on it
+    assert plan(ams.FP533, 1, 4096, 4099)["waves"] == "16" and plan(ams.FP533, 1, 6144, 4099)["waves"] == "16"
+    for N, K in ((28672, 15 * 96 - 1), (24640, 4099)):  # fifteen records: too short a stream for 8 wavefronts; 220 workgroups do not fill the chip
+        assert kind(ams.FP533, 1, N, K) == "column" and plan(ams.FP533, 1, N, K)["waves"] == "16"
+    assert plan(ams.FP533, 1, 28672, 16 * 96 - 1)["waves"] == plan(ams.FP533, 1, 25088, 4099)["waves"] == "8"
+    p = plan(ams.FP425, 1, 4096, 14339, with_workspace=2)  # one strip per workgroup: all 16 wavefronts on it (one scale per run)
     assert (p["grid"], p["strips_per_wg"], p["waves_per_strip"], p["phases"]) == ("256", "1", "16", "1")
+    p = plan(ams.FP425, 1, 4096, 14339)  # one scale per row: slice_kernel, which streams unaligned rows on up to four strips
+    assert kind(ams.FP425, 1, 4096, 14339) == "slice" and set(p) == {"grid", "strips_per_wg", "k_slices", "waves", "lds", "ahead", "streamed_rows", "row_tiles"}
     p = plan(ams.FP533, 1, 57344, 8192)  # fourteen strips per workgroup: eight wavefronts (seven busy) with two strips each
     assert (p["grid"], p["strips_per_wg"], p["waves"], p["waves_per_strip"], p["strips_per_wave"], p["ahead"]) == ("256", "14", "8", "1", "2", "3")
     p = plan(ams.FP425, 1, 57344, 8192)  # with side groups: sixteen wavefronts, fourteen of them alone on a strip
@@ -382,7 +386,7 @@ def test_launch_plans_random_shapes_stay_inside_the_machine():
             if kind == "sweep":
                 assert 16 % int(kv["waves_per_strip"]) == 0 or int(kv["waves_per_strip"]) == int(kv["waves"]), text
             if kind == "slice":
-                assert K % 8 == 0 and 1 <= int(kv["strips_per_wg"]) <= 8 and (kv["waves"], kv["ahead"]) in (("16", "2"), ("8", "3")), text
+                assert (K % 8 == 0) == ("streamed_rows" not in kv) and 1 <= int(kv["strips_per_wg"]) <= 8 and (kv["waves"], kv["ahead"]) in (("16", "2"), ("8", "3")), text
             if kind == "column":
                 if kv["strips_per_wave"] == "1":
                     assert int(kv["strips_per_wg"]) <= 16 and int(kv["waves_per_strip"]) == int(kv["waves"]) // int(kv["strips_per_wg"]) >= 1, text
