@@ -393,8 +393,10 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
   };
   if (gk_slices == 1) {
     // With many outputs a quad per thread: 28672 x 4096 FP5.33 M = 32 20.4 -> 19.9 us, 20000 x 2048 FP4.25 M = 24 9.2 -> 8.9.  With few,
-    // more threads share them: 4096 x 4096 M = 9 5.33, as quads 5.51.
-    if constexpr (R >= 16 && NS >= 3) {
+    // more threads share them: 4096 x 4096 M = 9 5.33, as quads 5.51; three strips as quads 1-4 % slower up to 12 rows (10569 x
+    // 264 FP5.33 M = 9 3.46 / 3.65), equal at 13.
+    constexpr bool QUADS = R >= 16 && NS >= 3;
+    if (QUADS && (R > 16 || NS > 3 || pairs >= 40)) {
       for (int u = tid; u < pairs * 4; u += 64 * S) {
         const int c = 4 * (u & 3), i = (u >> 2) % NS, m = (u >> 2) / NS;
         finish_quad(i, m, c, quad_sum(i, m, c));
