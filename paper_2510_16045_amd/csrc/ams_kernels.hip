@@ -1412,8 +1412,10 @@ bool short_slices_on_column(int fmt, int M, int spw, int gk, int n_rec_all) {
 // bytes' worth (4608 x 2368 FP5.33 M = 16 5.47 / 5.71, FP4.25 5888 x 22656 26.7 / 27.9).  us, one / two tiles: 4096 x 14336 FP4.25 M = 32
 // 20.3 / 16.4, M = 24 17.8 / 16.3, M = 16 13.9 / 13.2, M = 12 12.5 / 12.7; FP5.33 M = 32 22.6 / 18.3; 8192 x 8192 M = 32 15.7 / 14.5,
 // M = 16 11.7 / 12.9; 14336 x 4096 M = 32 12.9 / 13.1; 2560 x 9728 M = 24 12.8 / 11.1, three tiles 9.6.  Tiles of fewer than eight rows never
-// pay (2419 x 20352 FP5.33 M = 12 16.9, three tiles 19.2).  With fewer
-// than 18 records, two for a wavefront, the plans stay as they were (not measured).
+// pay (2419 x 20352 FP5.33 M = 12 16.9, three tiles 19.2).  At 16 rows
+// a second strip costs FP6, and FP4.33 up to 32 records (with a scale per run 96), what the rows save (one / two tiles: 2739 x 1920
+// FP6 4.2 / 4.5, 2155 x 2776 FP4.33 with a scale per run 5.1 / 5.5; 129 to 256 strips 0.90-0.98 x); on up to 128 strips they
+// take none and are dealt.  With fewer than 18 records, two for a wavefront, the plans stay as they were (not measured).
 constexpr int64_t kSplitMaxStrips = 16384;  // strips that the counters of a split of K have room for
 struct RowSplit {
   int strips, positions;  // strips per workgroup; workgroups of one tile: whole groups of eight, so that the tiles of a position meet on one XCD
@@ -1489,10 +1491,11 @@ ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k,
     p.grid = p.gn = (int)((n_strips + p.spw - 1) / p.spw);
   }
   if (M >= 2 * kRowSplitMinRows && n_rec_all / gk >= kRowSplitMinRecords && n_strips <= kSplitMaxStrips / kMaxRowTiles) {
+    const bool costly_strip = gk == 1 && ((one_scale && fmt == FMT_FP6) || (fmt == FMT_FP433 && n_rec_all <= (one_scale ? 32 : 96)));
     double best = 0.97 * row_split_cost(fmt, p.spw, M, one_scale);
     for (int t = 2; t <= kMaxRowTiles && t * kRowSplitMinRows <= M; t++) {
       const RowSplit s = row_split(fmt, M, n_strips, gk, t, one_scale);
-      if (s.strips > kSliceMaxStrips || s.cost >= best) continue;
+      if (s.strips > kSliceMaxStrips || s.cost >= best || (M <= 16 && s.strips > p.spw && costly_strip)) continue;
       best = s.cost;
       p.row_tiles = t;
       p.spw = s.strips;
