@@ -157,13 +157,16 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
       const int piece = kq * NF + u;
       roff[u] = (piece >> 2) * (RB * 64) + m_lo * 64 + (((piece & 3) ^ swz(m_lo)) * 16);
     }
-    // RAGGED: the loads' rows, the channels of their pieces inside a record, and the two records under way
+    // RAGGED: the loads' rows, the channels of their pieces inside a record, and the two records under way.  Lanes whose row does
+    // not exist ask for nothing on tiles of eight rows, and for row 0 on tiles of four, where the branch costs one and three
+    // rows 2-3 %.  (With the last row again for all of them its lines were asked for by lanes in several pairs of rows,
+    // which takes longer the more there are: 2544 x 6015 FP4.33, 2 / 6 / 10 rows 6.6 / 8.8 / 10.1 us, now 5.4 / 7.7 / 8.5.)
     int row_at[MT], piece_at[MT];
-    u4 ahead[RAGGED ? LX : 1][RAGGED ? P::NI : 1];
+    u4 ahead[RAGGED ? LX : 1][RAGGED ? P::NI : 1] = {};
     if constexpr (RAGGED) {
 #pragma unroll
       for (int t = 0; t < MT; t++) {
-        row_at[t] = min(16 * t + ld_m, rows - 1) * K;
+        row_at[t] = (16 * t + ld_m < rows ? 16 * t + ld_m : 0) * K;
         piece_at[t] = ld_b * 32 + ((lane & 3) ^ swz(ld_m)) * 8;
       }
     }
@@ -174,7 +177,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
       for (int t = 0; t < MT; t++)
 #pragma unroll
         for (int i = 0; i < P::NI1; i++)  // a piece that runs past its row's end: the row's last eight channels
-          __builtin_memcpy(&ahead[set][t * P::NI1 + i], xrows + row_at[t] + min(rec * REC_K + piece_at[t] + i * (BLK * 32), K - 8), 16);
+          if (RB == 4 || 16 * t + ld_m < rows) __builtin_memcpy(&ahead[set][t * P::NI1 + i], xrows + row_at[t] + min(rec * REC_K + piece_at[t] + i * (BLK * 32), K - 8), 16);
     };
     auto store_ragged = [&](int p, auto set) {
       const int rec = first + S * p;
