@@ -1434,17 +1434,33 @@ RowSplit row_split(int fmt, int M, int64_t n_strips, int gk, int tiles, bool one
 }
 constexpr int kMaxRowTiles = 4, kRowSplitMinRecords = 18, kRowSplitMinRows = 8;
 
-// Rows of X that are not 16-byte aligned: slice_kernel's variant for them, on tiles of eight rows and up to four strips (its
-// sixteen wavefronts have 128 registers each).  column_kernel stays where it reads three records ahead (8192 x 8193 FP5.33 M =
-// 1 11.0 / 11.2 us), with one scale per run, on one record, and where K is walked in phases at M = 8, on fewer than 32
-// strips or on more than one for every compute unit: there the new variant is faster too (4096 x 14339 FP4.25 M = 8 16.5 /
-// 11.9), but those shapes are the ones on which the tests exercise the phases.
+// Rows of X that are not 16-byte aligned: slice_kernel's variant for them, on tiles of up to eight rows and up to four strips
+// (its sixteen wavefronts have 128 registers each).  21000 shapes against column_kernel, which stages the rows for the workgroup
+// (in phases of K where all of it does not fit): 1.7 x in the mean (32 rows 2-4 x: 4096 x 14337 FP4.25 47.7 / 21.5 us; 8 rows in
+// phases 4096 x 14339 FP4.25 16.5 / 11.9, 13 strips 1.5 x, 400 strips 1.2 x).  column_kernel stays with one scale per run, on
+// one record, where it reads three records ahead (8192 x 8193 FP5.33 M = 1 11.0 / 11.2), and:
+//   at one row on long K, where staging it is nothing and the wavefronts live on the records in flight: from where the two meet, by
+//     format (5.33 bits from 230 records on 0.98 x, from 800 on 0.91 x; FP4.5 0.95 and 0.94 x);
+//   two tiles of four strips, which wavefronts walk one after the other: see four_strips_on_column.
 int ragged_tiles(int M) { return (M + kSliceRaggedMaxRows - 1) / kSliceRaggedMaxRows; }
+// Two tiles of unaligned rows (9 to 16) on four strips, n records; column / streamed over 7800 shapes:
+//   29 to 32 records, which column_kernel's eight wavefronts of a strip share evenly: 0.89-1.0 x (6285 x 2727 FP5.33 M = 12 8.2 / 9.0; 25
+//     to 28 records 1.0-1.2 x, 33 to 36 1.0-1.3 x);
+//   57 to 64 likewise, up to 12 rows (0.84-0.97 x; FP4.5 and FP4 1.1 x); FP6 there from 49 on (0.85-0.94 x; 13 to 15 rows 0.91-1.1 x, left);
+//   nine rows, a tile of five and one of four, from 29 on (FP5 0.81-0.93 x, FP4.25 0.86-0.98, FP5.33 0.96-1.13); ten of FP5 (0.86-0.91 x).
+bool four_strips_on_column(int fmt, int M, int n) {
+  if (n <= 28) return false;
+  if (n <= 32 || M == 9 || (M == 10 && fmt == FMT_FP5)) return true;
+  return M <= 12 && ((n > 56 && n <= 64) || (fmt == FMT_FP6 && n > 48));
+}
+constexpr int kRaggedLongK[ams::kNumFormats] = {230, 220, 155, 190, 160, 240, 280};
 bool ragged_on_slice(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int gk, bool one_scale, const ColumnPlan& column) {
   if (!one_scale || (int64_t)n_rec * rec_k < 8 + rec_k || n_strips > kSplitMaxStrips / kMaxRowTiles) return false;
   if (column.lr == 3 || column.spw > kSliceRaggedMaxStrips) return false;
-  if (column.n_phase > 1 && (M == 8 || n_strips < 32 || n_strips > kNumCU)) return false;
-  return row_split(fmt, M, n_strips, gk, ragged_tiles(M), true).strips <= kSliceRaggedMaxStrips;
+  if (M == 1 && n_rec > kRaggedLongK[fmt]) return false;
+  const int tiles = ragged_tiles(M), strips = row_split(fmt, M, n_strips, gk, tiles, true).strips;
+  if (tiles == 2 && strips == kSliceRaggedMaxStrips && gk <= 2 && four_strips_on_column(fmt, M, (n_rec + gk - 1) / gk)) return false;
+  return strips <= kSliceRaggedMaxStrips;
 }
 ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
   p.row_tiles = ragged_tiles(M);

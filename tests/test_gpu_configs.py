@@ -127,8 +127,7 @@ def test_qwen_down_projections(model, Ms):
 @pytest.mark.parametrize("N,K,Ms", [(1_000_003, 100, (1, 5)), (20, 1_000_000, (1, 5, 32)), (20, 1_000_003, (5,))])
 def test_extreme_aspect_ratios(N, K, Ms):
     # a million rows of two records each (62501 strips: thousands of workgroups in many rounds), and two strips
-    # of ten thousand records (split over workgroups when a workspace is given; on rows that are not 16-byte aligned K is
-    # walked in phases from M = 5 on)
+    # of ten thousand records (split over workgroups when a workspace is given)
     W = synth.gaussian_weights(N, K, 750 + (N % 7))
     check_shape_against_oracle(N, K, W, Ms, 4999, with_workspace=N < 100, with_static=N < 100)
 

@@ -247,10 +247,10 @@ def test_linear_large_shapes_sampled_rows(fmt, ofmt, N, K, Ms):
     "N,K,Ms",
     [
         (200, 6000, (16, 17, 32)),  # one strip per workgroup; slice_kernel
-        (200, 6003, (16, 17, 32)),  # the same in column_kernel: many phases
-        (90, 6004, (32,)),  # activation rows not 16-byte aligned
+        (200, 6003, (16, 17, 32)),  # activation rows not 16-byte aligned; slice_kernel, which streams them
+        (90, 6004, (32,)),
         (4400, 3000, (24, 32)),  # two strips per workgroup, the last workgroup has one; slice_kernel
-        (4400, 3001, (24, 32)),  # the same in column_kernel
+        (4400, 3001, (24, 32)),  # unaligned rows: slice_kernel in three row tiles; column_kernel in two phases (four row tiles would take five strips)
         (33000, 5120, (16, 32)),  # nine strips per workgroup, aligned rows: column_kernel, with side groups dealt whole where there are any
     ],
 )
@@ -264,8 +264,8 @@ def test_linear_activations_in_several_phases(fmt, ofmt, N, K, Ms):
     codes, o_scales, _ = O.ams_quantize(W[rows], ofmt)
     for M in Ms:
         plan = ams.ams_linear_plan(fmt, M, N, K)
-        if K % 8 == 0 and N < 33000:
-            assert plan.startswith("slice "), plan
+        if N < 33000 and (K, M) != (3001, 32):
+            assert plan.startswith("slice ") and ("streamed_rows" in plan) == (K % 8 != 0), plan
         else:
             assert plan.startswith("column ") and "phases=1 " not in plan, plan
             assert N < 33000 or ("side_groups=1" in plan) == (fmt in (ams.FP425, ams.FP45, ams.FP433, ams.FP6)), plan

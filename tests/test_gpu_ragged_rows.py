@@ -58,7 +58,7 @@ def test_every_remainder(fmt, ofmt, K):
         (ams.FP533, O.FP533, 16 * 11 * 230, 1003, 3, "strips_per_wave=2"),
         (ams.FP6, O.FP6_E2M3, 20496, 96 * 12 - 5, 5, "side_groups=1"),
         (ams.FP433, O.FP433, 20496, 96 * 24 - 3, 1, "side_groups=1"),
-        (ams.FP45, O.FP45, 48, 9001, 32, "phases=5 "),  # K in several phases
+        (ams.FP45, O.FP45, 20500, 4501, 32, "phases=3 "),  # K in several phases
     ],
 )
 def test_every_launch_variant(fmt, ofmt, N, K, M, want):
@@ -70,3 +70,20 @@ def test_every_launch_variant(fmt, ofmt, N, K, M, want):
     X = synth.activations(M, K, 63)
     y = ams.ams_linear(dev(packed), dev(scales), dev(X), N, fmt)[:, torch.from_numpy(rows).cuda()].contiguous()
     check(y, O.linear(codes, o_scales, X, ofmt), slice(None), f"{ofmt.name} N={N} K={K} M={M}")
+
+
+@pytest.mark.parametrize("fmt,ofmt,K", [(ams.FP533, O.FP533, 25601), (ams.FP425, O.FP425, 25603), (ams.FP6, O.FP6_E2M3, 25607)])
+def test_slices_of_k_in_phases(fmt, ofmt, K):
+    # more strips than the tiles of a split take: column_kernel, each of eight slices of K in two phases
+    N, M = 600, 32
+    plan = ams.ams_linear_plan(fmt, M, N, K, with_workspace=True)
+    assert plan.startswith("column ") and "k_slices=8 " in plan and "phases=2 " in plan, plan
+    W = synth.gaussian_weights(N, K, 64)
+    packed, scales = ams.ams_pack(fmt, W)
+    codes, o_scales, _ = O.ams_quantize(W, ofmt)
+    X, ws = synth.activations(M, K, 65), torch.zeros(16 << 20, dtype=torch.uint8, device="cuda")
+    wp, sc, x = dev(packed), dev(scales), dev(X)
+    first, ref = ams.ams_linear_ws(wp, sc, x, N, fmt, ws), O.linear(codes, o_scales, X, ofmt)
+    check(first, ref, slice(None), plan)
+    assert torch.equal(ams.ams_linear_ws(wp, sc, x, N, fmt, ws), first) and torch.equal(ams.ams_linear_static_ws(wp, sc, x, N, fmt), first)
+    assert not ws[: 4 * 16384].any()

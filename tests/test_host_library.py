@@ -295,7 +295,7 @@ def test_launch_plans_cover_the_kernels_and_the_split():
     assert plan(ams.FP533, 1, 128256, 4096)["strips_per_wg"] == "16"  # more strips than 16 x 256: more workgroups
     assert int(plan(ams.FP533, 1, 128256, 4096)["grid"]) == -(-(-(-128256 // 16)) // 16)
     assert kind(ams.FP533, 32, 57344, 8195) == "column" and int(plan(ams.FP533, 32, 57344, 8195)["phases"]) > 1
-    assert int(plan(ams.FP425, 8, 4096, 14339)["phases"]) > 1
+    assert int(plan(ams.FP425, 8, 4096, 14339, with_workspace=2)["phases"]) > 1 and kind(ams.FP425, 8, 4096, 14339) == "slice"
     assert plan(ams.FP425, 8, 4096, 14339, with_workspace=True)["k_slices"] == "4"
     assert kind(-1, 1, 4096, 4096) == "gemv" and kind(-1, 4, 28672, 4096) == "gemv"  # small batches: rows dealt to wavefronts
     assert kind(-1, 4, 8192, 28672) == "sweep"  # four rows of 28672 activations do not fit in LDS

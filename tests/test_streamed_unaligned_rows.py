@@ -23,8 +23,12 @@ def plan(*a, **k):
     [
         (ams.FP533, 5, 11003, 4099, 0, 1), (ams.FP425, 8, 4096, 4099, 0, 1), (ams.FP425, 9, 4096, 4099, 0, 2), (ams.FP425, 32, 4096, 14337, 0, 4),
         (ams.FP425, 32, 4112, 14337, 0, 0), (ams.FP425, 16, 8192, 4099, 0, 2), (ams.FP425, 16, 8208, 4099, 0, 0), (ams.FP425, 4, 16384, 4099, 0, 1), (ams.FP425, 4, 16400, 4099, 0, 0),
-        (ams.FP425, 8, 4096, 14339, 0, 0), (ams.FP425, 7, 4096, 14339, 0, 1), (ams.FP425, 4, 256, 129, 0, 1), (ams.FP425, 4, 256, 127, 0, 0), (ams.FP533, 4, 256, 97, 2, 0),
+        (ams.FP425, 8, 4096, 14339, 0, 1), (ams.FP425, 8, 4112, 14339, 0, 1), (ams.FP425, 8, 200, 14339, 0, 1), (ams.FP425, 7, 4096, 14339, 0, 1), (ams.FP425, 4, 256, 129, 0, 1), (ams.FP425, 4, 256, 127, 0, 0), (ams.FP533, 4, 256, 97, 2, 0),
         (ams.FP533, 1, 8192, 8193, 0, 0), (ams.FP533, 3, 8192, 8193, 0, 1),
+        (ams.FP45, 1, 355, 24567, 0, 0), (ams.FP425, 1, 355, 28159, 0, 1), (ams.FP425, 1, 355, 28161, 0, 0), (ams.FP533, 1, 355, 105783, 0, 0), (ams.FP533, 2, 355, 105783, 0, 1),  # long K
+        (ams.FP533, 12, 6285, 2727, 0, 0), (ams.FP533, 12, 6285, 2687, 0, 2), (ams.FP533, 12, 6140, 2727, 0, 2), (ams.FP533, 12, 6285, 4099, 0, 2),  # two tiles of four strips
+        (ams.FP533, 13, 6285, 3071, 0, 0), (ams.FP533, 13, 6285, 3073, 0, 2), (ams.FP6, 15, 6552, 2857, 0, 0), (ams.FP533, 12, 6285, 5999, 0, 0), (ams.FP533, 13, 6285, 5999, 0, 2),
+        (ams.FP425, 9, 6285, 4099, 0, 0), (ams.FP425, 10, 6285, 4099, 0, 2), (ams.FP5, 10, 6285, 4099, 0, 0), (ams.FP5, 11, 6285, 4099, 0, 2), (ams.FP6, 12, 6285, 29179, 0, 0), (ams.FP6, 13, 6285, 29179, 0, 2),
     ],
 )
 def test_where_unaligned_rows_are_streamed(fmt, M, N, K, entry, tiles):
