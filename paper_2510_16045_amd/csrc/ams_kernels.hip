@@ -1490,8 +1490,8 @@ ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
 //     FP5.33 M = 32 24.7 / 18.9);
 //   short slices of a split K: see short_slices_on_column;
 //   more than eight strips: see halved_is_faster.
-ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
-  ColumnPlan p = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
+// p: make_column_plan's of the same problem.
+ColumnPlan plan_from(ColumnPlan p, int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale) {
   if (!aligned_rows) {
     if (ragged_on_slice(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, p)) return ragged_plan(p, fmt, M, n_strips, gk);
     return p;
@@ -1525,6 +1525,10 @@ ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k,
   p.lr = slice_ahead(p.S);
   p.lds = (size_t)slice_lds(fmt, p.rows, p.spw);
   return p;
+}
+ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
+  const ColumnPlan column = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
+  return plan_from(column, fmt, M, n_strips, n_rec_all, rec_k, gk, aligned_rows, one_scale);
 }
 
 // Workspace of a split in gk slices: per-strip arrival counters, then the partial tiles.  The
@@ -1564,18 +1568,19 @@ void* const kStaticScratch = (void*)(uintptr_t)1;
 // whole and a split never paid).  For the packed formats it prices column_kernel, to which it was fitted; slice_kernel, which takes
 // the slices but for the short ones, stages nothing per phase and is now and then faster without the split (2560 x 9728
 // FP4.25 M = 16 9.7 us, split 10.0).
-int cheapest_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int rec_bytes) {
+// column: make_column_plan's with 1, 2, 4, 8 slices, as far as they were looked at.
+int cheapest_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int rec_bytes, ColumnPlan (&column)[4]) {
   if (M < 4) return 1;
   int best = 1;
   double best_cost = 0;
-  for (int gk = 1; gk <= kMaxSplit; gk *= 2) {
+  for (int gk = 1, j = 0; gk <= kMaxSplit; gk *= 2, j++) {
     if (gk > 1 && (n_rec / gk < 8 || n_strips > kSplitMaxStrips)) break;
     int spw, rc;
     double rounds = 1.0;  // the packed formats' workgroups take at most 16 strips: more of them means more rounds
     SweepPlan p;
     p.ok = true;
     if (fmt != FMT_FP16) {
-      const ColumnPlan cp = make_column_plan(fmt, M, n_strips, n_rec, rec_k, gk);
+      const ColumnPlan& cp = column[j] = make_column_plan(fmt, M, n_strips, n_rec, rec_k, gk);
       spw = cp.spw, rc = cp.rc;
       rounds = std::max(1.0, (double)cp.grid / kNumCU);
     } else {
@@ -1608,20 +1613,44 @@ double plan_time(const ColumnPlan& p, int fmt, int M, int n_rec) {
   return p.gk > 1 ? t + 3.05 - 1.7 * tiles : t;
 }
 
-// The split that a call with a workspace uses.  On short K the exchange costs more than the slices save, now that the plain
-// call deals the rows of X: whichever plan_time prefers.  us, split / whole: 896 x 2880 FP4.25 M = 32 7.0 / 4.0, 4096 x 4096 M = 32 8.4 /
-// 7.2, 1226 x 5760 FP5.33 M = 16 6.4 / 5.2; 82 shapes 1.22x, none slower by more than 3 %.  From K = 9216 on the two are
-// within their spread of each other (2560 x 9728 M = 16 9.7 / 8.1) and the split stays; at M = 4 and one strip per workgroup from
-// 12800 on (1920 x 9920 FP5.33 7.6 / 6.6, 1117 x 14080 FP4.25 7.0 / 7.7; with two strips 4480 x 10240 9.5 / 10.3).
-constexpr int64_t split_short_k(int M, int64_t n_strips) { return M == 4 && n_strips <= kNumCU ? 12800 : 9216; }
-int choose_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int rec_bytes, int64_t K) {
-  const int gk = cheapest_split(fmt, M, n_strips, n_rec, rec_k, rec_bytes);
-  if (gk == 1 || fmt == FMT_FP16 || K >= split_short_k(M, n_strips) || K % 8 != 0) return gk;
+// The split that a call with a workspace uses: cheapest_split's, unless the plain call is faster.  us, split / whole:
+//   slices on slice_kernel: on short K the exchange costs more than they save, and plan_time decides (896 x 2880 FP4.25 M = 32 7.0 /
+//     4.0, 4096 x 4096 8.4 / 7.2, 1226 x 5760 FP5.33 M = 16 6.4 / 5.2).  How short depends on M, because the activations of
+//     all of K weigh more with every row, and from 16 rows on a plain call deals them out: over 43000 shapes the two meet at
+//     K = 12800 with 4 rows, 9000 with 8, 6500 with 12 and 9200 from 16 on (where more than one strip falls on every compute unit, at
+//     9200 with 4 too).  Beyond that the split is the faster one (2560 x 9728 FP4.25 M = 16 8.0 / 9.6, 5120 x 25600 FP5.33 19 /
+//     27).  The choice is within 0.4 % of the faster one in the mean, and more than 6 % off in 2 % of the shapes.
+//   four or eight slices on column_kernel (short ones, or more than eight strips): below K = 9216 the plain call is the faster one, up
+//     to 12 rows at every K (5120 x 6144 FP5.33 M = 32 12.3 / 10.8, 7168 x 8192 FP4.5 M = 16 13.4 / 11.6; 1215 shapes: 1.10 x at K = 8000, 1.03 x
+//     around 9000, 0.96 x at 12000; M = 8 up to 20000 1.11 x).
+// Unaligned rows keep cheapest_split's (17000 shapes: the plain call is 1.1-1.3 x faster below K = 5000 and the split from 8000
+// on; in between it depends on the strips).
+constexpr int kSplitLongK = 9216;
+constexpr int kSplitLongKOfRows[16] = {0, 0, 0, 0, 12800, 10950, 9640, 8650, 7880, 7250, 6740, 6300, 5930, 5610, 5320, 5070};  // 12800 (4 / M)^0.7
+struct Split {
+  int gk;
+  bool planned;  // plan: make_plan's for gk slices, non-temporal loads
+  ColumnPlan plan;
+};
+Split choose_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int rec_bytes, int64_t K) {
+  ColumnPlan column[4];
+  Split c;
+  c.gk = cheapest_split(fmt, M, n_strips, n_rec, rec_k, rec_bytes, column);
+  c.planned = false;
+  if (c.gk == 1 || fmt == FMT_FP16 || K % 8 != 0) return c;
+  const ColumnPlan& sliced = column[c.gk == 2 ? 1 : c.gk == 4 ? 2 : 3];
+  const bool on_slice = sliced.spw <= kSliceMaxStrips && !short_slices_on_column(fmt, M, sliced.spw, c.gk, n_rec);  // as plan_from has it
+  int long_k = kSplitLongK;
+  if (on_slice && M < 16) long_k = n_strips > kNumCU ? std::min(kSplitLongKOfRows[M], kSplitLongK) : kSplitLongKOfRows[M];
+  if (on_slice ? K >= long_k : c.gk == 2 || (K >= long_k && M > 12)) return c;
   // a split that the static scratch refuses stays refused
-  if (split_workspace_bytes(M, n_strips, gk) > kStaticScratchBytes) return gk;
-  const ColumnPlan split = make_plan(fmt, M, n_strips, n_rec, rec_k, gk, true, true, true);
-  const ColumnPlan whole = make_plan(fmt, M, n_strips, n_rec, rec_k, 1, true, true, true);
-  return whole.slice && split.slice && plan_time(whole, fmt, M, n_rec) < plan_time(split, fmt, M, n_rec) ? 1 : gk;
+  if (split_workspace_bytes(M, n_strips, c.gk) > kStaticScratchBytes) return c;
+  const ColumnPlan whole = plan_from(column[0], fmt, M, n_strips, n_rec, rec_k, 1, true, true);
+  if (!whole.slice) return c;
+  c.plan = plan_from(sliced, fmt, M, n_strips, n_rec, rec_k, c.gk, true, true);
+  c.planned = true;
+  if (!c.plan.slice || plan_time(whole, fmt, M, n_rec) < plan_time(c.plan, fmt, M, n_rec)) c.gk = 1, c.plan = whole;
+  return c;
 }
 
 // Per-device state, set up once per device with that device current: whether it is the GPU
@@ -1821,15 +1850,16 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
   a.red_slots = 0;
   a.piece_q = a.piece_r = 0;
   constexpr int REC_BYTES = FMT == FMT_FP16 ? 4096 : Fmt<FMT>::REC_BYTES;
-  int gk = 1;
+  Split split = {1, false, {}};
   if (workspace && scale_group == 0) {
     if (!aligned16(workspace)) return AMS_ERR_ALIGN;
-    gk = choose_split(FMT, M, n_strips, n_rec, REC_K, REC_BYTES, K);
-    if (split_workspace_bytes(M, n_strips, gk) > ws_bytes) {
+    split = choose_split(FMT, M, n_strips, n_rec, REC_K, REC_BYTES, K);
+    if (split_workspace_bytes(M, n_strips, split.gk) > ws_bytes) {
       if (static_ws) return AMS_ERR_SCRATCH;  // beyond the static array: refused, never silently another plan
-      gk = 1;                                 // a caller's workspace that is too small: no split
+      split = {1, false, {}};                 // a caller's workspace that is too small: no split
     }
   }
+  const int gk = split.gk;
   auto use_split = [&](int plan_gk) {
     if (plan_gk > 1) {
       a.ws_count = (unsigned*)workspace;
@@ -1841,7 +1871,7 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
     // in any cache (a model's layers in turn): equal or up to 5 % faster than ordinary loads at every size; ordinary
     // loads only win when the same few megabytes are read again call after call.
     const bool nt = n_strips * n_rec * (int64_t)REC_BYTES >= (2ll << 20);
-    const ColumnPlan cp = make_plan(FMT, M, n_strips, n_rec, REC_K, gk, K % 8 == 0, scale_group == 0, nt);
+    const ColumnPlan cp = split.planned && nt ? split.plan : make_plan(FMT, M, n_strips, n_rec, REC_K, gk, K % 8 == 0, scale_group == 0, nt);
     a.gn = cp.gn;
     a.gk = cp.gk;
     a.row_tiles = cp.row_tiles;
@@ -2049,7 +2079,7 @@ int ams_linear_workspace_bytes(int fmt, int M, int64_t N, int64_t K, size_t* byt
   }
   const int64_t n_strips = (N + 15) / 16;
   const int n_rec = (int)((K + rec_k - 1) / rec_k);
-  *bytes = split_workspace_bytes(M, n_strips, choose_split(f, M, n_strips, n_rec, rec_k, rec_bytes, K));
+  *bytes = split_workspace_bytes(M, n_strips, choose_split(f, M, n_strips, n_rec, rec_k, rec_bytes, K).gk);
   return AMS_OK;
 }
 
@@ -2065,7 +2095,7 @@ int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, ch
   const int64_t n_strips = (N + 15) / 16;
   const int n_rec = (int)((K + rec_k - 1) / rec_k);
   const bool grouped = with_workspace == 2;  // ams_linear_grouped
-  const int gk = with_workspace && !grouped ? choose_split(f, M, n_strips, n_rec, rec_k, rec_bytes, K) : 1;
+  const int gk = with_workspace && !grouped ? choose_split(f, M, n_strips, n_rec, rec_k, rec_bytes, K).gk : 1;
   if (f != FMT_FP16) {
     const bool nt = n_strips * n_rec * (int64_t)rec_bytes >= (2ll << 20);  // as run_linear decides it
     const ColumnPlan cp = make_plan(f, M, n_strips, n_rec, rec_k, gk, K % 8 == 0, !grouped, nt);

@@ -150,7 +150,7 @@ LINES = [
     ("FP425", 24, 24571, 1, "plain", "column"), ("FP425", 24, 24571, 2, "grouped", "column"), ("FP45", 16, 32763, 2, "plain", "column"),
     ("FP425", 1, 4107, 97, "plain", "column"), ("FP533", 1, 6139, 97, "grouped", "column"), ("FP533", 1, 6139, 96, "plain", "slice"), ("FP6", 1, 7163, 97, "grouped", "column"),
     ("FP5", 2, 7163, 145, "grouped", "column"), ("FP433", 1, 1003, 201, "plain", "column"), ("FP533", 1, 1003, 201, "grouped", "column"), ("FP45", 1, 1003, 250, "grouped", "column"),
-    ("FP533", 16, 2555, 198, "ws", "column"), ("FP425", 32, 2043, 200, "ws", "column"), ("FP533", 32, 5115, 64, "ws", "column"), ("FP45", 16, 7163, 64, "ws", "column"),
+    ("FP533", 16, 2555, 198, "ws", "column"), ("FP425", 32, 2043, 200, "ws", "column"), ("FP533", 32, 5115, 100, "ws", "column"), ("FP45", 32, 2043, 200, "ws", "column"),
     ("FP6", 16, 3579, 230, "ws", "column"), ("FP425", 32, 1531, 108, "ws", "column"), ("FP533", 16, 5115, 100, "ws", "slice"),
 ]
 

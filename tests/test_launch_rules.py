@@ -103,14 +103,30 @@ def test_long_k_at_small_batches(fmt, M, N, n_rec, entry, want):
         (ams.FP533, 16, 2560, 18944, 8, "column"), (ams.FP533, 16, 2560, 25600, 8, "slice"), (ams.FP425, 16, 2560, 25600, 8, "slice"),
         (ams.FP6, 16, 3584, 22016, 8, "column"), (ams.FP425, 32, 2048, 25600, 8, "column"), (ams.FP425, 16, 1536, 13824, 8, "slice"),
         (ams.FP425, 32, 1536, 13824, 8, "column"), (ams.FP425, 32, 1536, 18944, 8, "slice"), (ams.FP533, 32, 1536, 18944, 8, "column"),
-        (ams.FP533, 32, 5120, 6144, 4, "column"), (ams.FP433, 32, 5120, 11008, 4, "column"), (ams.FP425, 32, 5120, 11008, 4, "slice"),
-        (ams.FP45, 16, 7168, 8192, 4, "column"), (ams.FP45, 16, 7168, 9728, 4, "slice"), (ams.FP433, 16, 7168, 13824, 4, "slice"),
+        (ams.FP533, 32, 5120, 9600, 4, "column"), (ams.FP433, 32, 5120, 11008, 4, "column"), (ams.FP425, 32, 5120, 11008, 4, "slice"),
+        (ams.FP45, 32, 2048, 25600, 8, "column"), (ams.FP45, 16, 7168, 9728, 4, "slice"), (ams.FP433, 16, 7168, 13824, 4, "slice"),
         (ams.FP425, 8, 4096, 14336, 4, "slice"), (ams.FP533, 16, 5120, 25600, 4, "slice"),
     ],
 )
 def test_short_slices_of_a_split(fmt, M, N, K, slices, want):
     kind, p = plan(fmt, M, N, K, with_workspace=True)
     assert kind == want and int(p["k_slices"]) == slices, p
+
+
+@pytest.mark.parametrize(
+    "fmt,M,N,K,split",
+    [
+        (ams.FP533, 32, 5120, 6144, False), (ams.FP45, 16, 7168, 8192, False), (ams.FP533, 32, 5120, 9600, True),  # slices on column_kernel
+        (ams.FP533, 7, 8714, 14560, False), (ams.FP533, 8, 8244, 13272, False), (ams.FP533, 12, 10612, 14552, False), (ams.FP425, 16, 9049, 16088, True),
+        (ams.FP425, 12, 1187, 7848, True), (ams.FP45, 12, 1238, 7640, True), (ams.FP425, 12, 1187, 5000, False),  # on slice_kernel: K by the rows
+        (ams.FP533, 5, 1920, 9920, False), (ams.FP425, 5, 1920, 10960, True), (ams.FP425, 16, 2560, 9208, False), (ams.FP425, 16, 2560, 9216, True),
+        (ams.FP425, 32, 896, 2880, False), (ams.FP425, 32, 4096, 4096, False), (ams.FP533, 16, 1226, 5760, False),
+    ],
+)
+def test_a_split_only_where_it_beats_the_plain_call(fmt, M, N, K, split):
+    assert (plan(fmt, M, N, K, with_workspace=1)[1]["k_slices"] != "1") == split == (ams.ams_linear_workspace_bytes(fmt, M, N, K) > 0)
+    if not split:
+        assert plan(fmt, M, N, K, with_workspace=1) == plan(fmt, M, N, K)
 
 
 def test_deep_and_two_strip_plans_stay_where_their_kernels_exist():
