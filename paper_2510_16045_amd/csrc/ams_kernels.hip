@@ -1618,8 +1618,8 @@ double plan_time(const ColumnPlan& p, int fmt, int M, int n_rec) {
 //     4.0, 4096 x 4096 8.4 / 7.2, 1226 x 5760 FP5.33 M = 16 6.4 / 5.2).  How short depends on M, because the activations of
 //     all of K weigh more with every row, and from 16 rows on a plain call deals them out: over 43000 shapes the two meet at
 //     K = 12800 with 4 rows, 9000 with 8, 6500 with 12 and 9200 from 16 on (where more than one strip falls on every compute unit, at
-//     9200 with 4 too).  Beyond that the split is the faster one (2560 x 9728 FP4.25 M = 16 8.0 / 9.6, 5120 x 25600 FP5.33 19 /
-//     27).  The choice is within 0.4 % of the faster one in the mean, and more than 6 % off in 2 % of the shapes.
+//     9200 with 4 too); the bounds lie a little below, where the choice errs least.  Beyond them the split is the faster one (2560 x
+//     9728 FP4.25 M = 16 7.8 / 9.1, 5120 x 25600 FP5.33 19 / 29).  The choice is within 0.4 % of the faster one in the mean, and more than 6 % off in 2 % of the shapes.
 //   four or eight slices on column_kernel (short ones, or more than eight strips): below K = 9216 the plain call is the faster one, up
 //     to 12 rows at every K (5120 x 6144 FP5.33 M = 32 12.3 / 10.8, 7168 x 8192 FP4.5 M = 16 13.4 / 11.6; 1215 shapes: 1.10 x at K = 8000, 1.03 x
 //     around 9000, 0.96 x at 12000; M = 8 up to 20000 1.11 x).

@@ -14,11 +14,11 @@
 // Bound: at M <= 8 by the weight stream and the restoration's VALU work; at larger batches by the one in-order path through
 // which a compute unit draws weights (from memory) and activations (from L2), 32 KiB of both in flight: without the activations 4096 x
 // 14336 FP4.25 at M = 32 took 9.7 us of 20.2, without weights from memory 14.9, without either 9.0, without the restoration
-// 20.1.  So the rows are dealt to several workgroups there (20.2 -> 16.0).
+// 20.1.  So the rows are dealt to several workgroups there (20.3 -> 16.4).
 //
-// Measured against what it replaces (us, M = 1 / 4 / 16 / 32): 4096 x 4096 FP4.25 5.2 -> 4.3, 6.0 -> 4.5, 7.6 -> 6.1, 13.4 -> 8.0;
-// 4096 x 14336 8.7 -> 8.5, 10.3 -> 9.3, 18.3 -> 13.7, 30.9 -> 19.7; 8192 x 8192 FP5.33 10.5 -> 10.0, 11.2 -> 10.3, 15.6 -> 14.2,
-// 25.4 -> 17.8; 28672 x 4096 FP4.25 12.8 -> 12.4, 13.8 -> 12.6, 15.3 -> 14.8, 21.7 -> 18.7; 256 x 768 4.1 -> 2.6 at every M <= 16.
+// Measured against what it replaces (us, M = 1 / 4 / 16 / 32): 4096 x 4096 FP4.25 5.2 -> 4.3, 6.0 -> 4.5, 7.6 -> 5.7, 13.4 -> 6.6;
+// 4096 x 14336 8.7 -> 8.5, 10.3 -> 9.1, 18.3 -> 12.9, 30.9 -> 16.0; 8192 x 8192 FP5.33 10.5 -> 9.9, 11.2 -> 10.0, 15.6 -> 12.9,
+// 25.4 -> 15.5; 28672 x 4096 FP4.25 12.8 -> 11.8, 13.8 -> 12.4, 15.3 -> 13.9, 21.7 -> 17.9; 256 x 768 4.1 -> 2.7 up to M = 4, 3.1 at 16.
 //
 // The counted waits need every step to make the same requests in the same order: requests past a wavefront's last record
 // are made too, out of the buffers' range (they read no memory), the scheduler may not move requests across the
