@@ -556,7 +556,7 @@ template <class ScaleOf>
 bool quantize_and_pack_strip(const RowQuant& q, const FormatInfo& fi, const WideRow& wide, const uint16_t* W, int64_t N, int64_t K, int64_t ldw, int64_t run,
                              uint16_t forced_scale, uint8_t* packed, int64_t n_strips, int64_t t, Steps& steps, ScaleOf&& scale_of) {
   const int64_t whole = K / fi.rec_k, rest = K - whole * fi.rec_k;
-  uint8_t rest_codes[16][128] = {};
+  uint8_t rest_codes[16][128];
   const uint8_t* rows[16];
   bool finite = true;
   for (int r = 0; r < 16; r++) {
@@ -582,6 +582,7 @@ bool quantize_and_pack_strip(const RowQuant& q, const FormatInfo& fi, const Wide
       if (absmax >= 0x7C00) {
         finite = false;
         zero_codes(rec, rec_end);
+        if (end > whole * fi.rec_k) std::memset(rest_codes[r], 0, (size_t)rest);
         continue;
       }
       const uint16_t sb = forced_scale ? forced_scale : scale_bits(absmax, q.fmax);
@@ -657,9 +658,16 @@ bool parallel_for(int64_t n, double ns, F&& body) {
   unsigned hw = std::thread::hardware_concurrency();
   const int64_t worth = (int64_t)std::ceil(std::sqrt(ns / 10e3));
   int64_t nt = std::max<int64_t>(1, std::min<int64_t>({(int64_t)(hw ? hw : 1), (int64_t)16, n, worth}));
-  std::atomic<int64_t> next{0};
-  std::atomic<int> failed{0};
-  auto work = [&] {
+  struct alignas(64) Shared {  // alone on its cache line: every claim of an index takes the line away from all threads
+    std::atomic<int64_t> next{0};
+    std::atomic<int> failed{0};
+  } shared;
+  std::atomic<int64_t>& next = shared.next;
+  std::atomic<int>& failed = shared.failed;
+  // Every thread has a copy of the body and, the bodies capturing by value, of what it reads: on the stack of the calling thread,
+  // which works on it too, the same lines were taken from one thread by another for every row (4096 x 4096 FP4.25 on 16 threads
+  // 667 us, by reference 675 to 807, as the compiler happened to place things).
+  auto work = [&, body] {
     try {
       for (int64_t i; !failed.load() && (i = next.fetch_add(1)) < n;) body(i);
     } catch (...) {
@@ -771,7 +779,7 @@ int pack_rows(int lanes, int fmt, int search, bool per_tensor, const uint16_t* W
   }
   std::atomic<int> bad{0};
   const WideRow* const wide = one_pass(rq, fi, K, codes_out);
-  const bool done = parallel_for(n_strips, quantize_ns(rq, wide, N, K, K), [&](int64_t t) {
+  const bool done = parallel_for(n_strips, quantize_ns(rq, wide, N, K, K), [=, &fi, &bad](int64_t t) {
     Steps steps;
     if (wide) {
       if (!quantize_and_pack_strip(rq, fi, *wide, W, N, K, ldw, K, tensor_scale, (uint8_t*)packed, n_strips, t, steps,
@@ -829,7 +837,7 @@ int pack_runs(int lanes, int fmt, int search, int64_t scale_group, const uint16_
   const int64_t n_sg = (K + scale_group - 1) / scale_group;
   std::atomic<int> bad{0};
   const WideRow* const wide = one_pass(rq, fi, K, codes_out);
-  const bool done = parallel_for(n_strips, quantize_ns(rq, wide, N, K, scale_group), [&](int64_t t) {
+  const bool done = parallel_for(n_strips, quantize_ns(rq, wide, N, K, scale_group), [=, &fi, &bad](int64_t t) {
     Steps steps;
     if (wide) {
       auto scale_of = [&](int r, int64_t j) { return scales + ((size_t)t * n_sg + j) * 16 + r; };
@@ -886,7 +894,7 @@ int ams_pack_codes(int fmt, const uint8_t* codes, int64_t N, int64_t K, void* pa
   const FormatInfo& fi = *ams::format_info(fmt);
   const int64_t n_strips = ams::round_up(N, ams::kStripRows) / ams::kStripRows;
   std::atomic<int> bad{0};
-  parallel_for(n_strips, (double)N * K * kPackCodesNs, [&](int64_t t) {
+  parallel_for(n_strips, (double)N * K * kPackCodesNs, [=, &fi, &bad](int64_t t) {
     const uint8_t* rows[16];
     for (int r = 0; r < 16; r++) {
       const int64_t n = t * 16 + r;
@@ -908,7 +916,7 @@ int ams_unpack_host(int fmt, const void* packed, int64_t N, int64_t K, uint8_t* 
   if (!codes || !packed) return AMS_ERR_NULL;
   const FormatInfo& fi = *ams::format_info(fmt);
   const int64_t n_strips = ams::round_up(N, ams::kStripRows) / ams::kStripRows;
-  parallel_for(n_strips, (double)N * K * kUnpackNs, [&](int64_t t) {
+  parallel_for(n_strips, (double)N * K * kUnpackNs, [=, &fi](int64_t t) {
     uint8_t* rows[16];
     for (int r = 0; r < 16; r++) rows[r] = t * 16 + r < N ? codes + (t * 16 + r) * K : nullptr;
     unpack_strip(fmt, fi, (const uint8_t*)packed, n_strips, t, K, rows);
