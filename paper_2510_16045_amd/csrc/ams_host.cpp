@@ -640,7 +640,7 @@ double quantize_ns(const RowQuant& q, const WideRow* in_one_pass, int64_t N, int
 }
 // The same of codes that are given: placed by table, and read back bit by bit (at a twentieth of this, four threads
 // where eight pay, 256 x 768 took 620 us instead of 410).
-constexpr double kPackCodesNs = 1.5, kUnpackNs = 8;
+constexpr double kPackCodesNs = 0.5, kUnpackNs = 8;
 
 int check_shape(int fmt, int64_t N, int64_t K) {
   if (!ams::format_info(fmt)) return AMS_ERR_FORMAT;
@@ -652,12 +652,12 @@ int check_shape(int fmt, int64_t N, int64_t K) {
 // throw is std::bad_alloc from their row buffers); a thread that cannot be started just means fewer workers.
 // ns: what the whole work takes one thread.  Starting a thread costs the starter about 12 us, so the sum of both is
 // least with the square root of work / 10 us: 256 x 4096 weights, 0.5 ms of work, 142 us on 7 or 8 threads, 229 on sixteen.
-// (Threads that start threads in turn: 168 and 273 us.)  Below 100 us a thread comes too late to help (64 x 512 FP5.33 75 us on two
+// (Threads that start threads in turn: 168 and 273 us.)  Below 60 us a thread comes too late to help (64 x 512 FP5.33 75 us on two
 // threads, 44 on one).
 template <class F>
 bool parallel_for(int64_t n, double ns, F&& body) {
   unsigned hw = std::thread::hardware_concurrency();
-  const int64_t worth = ns < 100e3 ? 1 : (int64_t)std::ceil(std::sqrt(ns / 10e3));
+  const int64_t worth = ns < 60e3 ? 1 : (int64_t)std::ceil(std::sqrt(ns / 10e3));
   int64_t nt = std::max<int64_t>(1, std::min<int64_t>({(int64_t)(hw ? hw : 1), (int64_t)16, n, worth}));
   struct alignas(64) Shared {  // alone on its cache line: every claim of an index takes the line away from all threads
     std::atomic<int64_t> next{0};
