@@ -1415,7 +1415,9 @@ bool short_slices_on_column(int fmt, int M, int spw, int gk, int n_rec_all) {
 // pay (2419 x 20352 FP5.33 M = 12 16.9, three tiles 19.2).  At 16 rows
 // a second strip costs FP6, and FP4.33 up to 32 records (with a scale per run 96), what the rows save (one / two tiles: 2739 x 1920
 // FP6 4.2 / 4.5, 2155 x 2776 FP4.33 with a scale per run 5.1 / 5.5; 129 to 256 strips 0.90-0.98 x); on up to 128 strips they
-// take none and are dealt.  With fewer than 18 records, two for a wavefront, the plans stay as they were (not measured).
+// take none and are dealt.  With fewer than 18 records, two for a wavefront, the plans stay as they were before the rows were dealt;
+// the line is not where the two meet: over 15500 such shapes dealing is 1.03-1.07 x at 16 rows and 1.12-1.17 x beyond on 5 to 17
+// records, 0.99-1.06 x on 2 to 4.
 constexpr int64_t kSplitMaxStrips = 16384;  // strips that the counters of a split of K have room for
 struct RowSplit {
   int strips, positions;  // strips per workgroup; workgroups of one tile: whole groups of eight, so that the tiles of a position meet on one XCD
