@@ -348,19 +348,16 @@ constexpr int slice_x_loads(int fmt, int R) {
 }
 // floats between the rows of a partial tile in LDS: 20 keeps a column's float4s in different banks, where it fits
 constexpr int slice_tile_row(int S, int R, int NS) { return S * NS * R * 20 * 4 <= 150 * 1024 ? 20 : 16; }
-constexpr int slice_staged(int fmt, int R, int NS, int variant) { return slice_waves(R, NS, variant) * kSliceXAhead * slice_x_loads(fmt, R) * 1024; }
-constexpr int slice_tiles(int R, int NS, int variant) {
-  const int S = slice_waves(R, NS, variant);
-  return S * NS * R * slice_tile_row(S, R, NS) * 4 + NS * 64 + NS * 4;
+// Floats between the tiles of neighbouring strips.  The final sum reads four strips at a time, 64 bytes of each: from 16 rows on
+// they would all lie in the same banks (28672 x 4096 FP5.33 M = 32 19.2 -> 18.9 us; up to eight rows two at a time, no gain).
+constexpr int slice_tile_strip(int S, int R, int NS) { return R * slice_tile_row(S, R, NS) + (NS > 1 && R >= 16 ? 16 : 0); }
+// LDS of one wavefront: its records of activations and, when its stream has ended, its partial tiles in the same place.  It
+// leaves them as soon as it is done itself, without a barrier (28672 x 4096 FP4.25 M = 16 14.0 -> 13.7, M = 32 17.8 -> 17.5).
+constexpr int slice_wave_lds(int fmt, int R, int NS, int variant) {
+  const int staged = kSliceXAhead * slice_x_loads(fmt, R) * 1024, tiles = NS * slice_tile_strip(slice_waves(R, NS, variant), R, NS) * 4;
+  return staged > tiles ? staged : tiles;
 }
-// The tiles of the final sum lie behind the staged activations where both fit in the 64 KiB that any launch may have: a
-// wavefront then leaves its tiles as soon as it is done, without waiting for the others to be done with theirs (14
-// shapes at M <= 8 0.05-0.1 us less: 4096 x 4096 FP4.25 M = 4 4.56 -> 4.48, 28672 x 4096 12.20 -> 12.06).
-constexpr bool slice_tiles_apart(int fmt, int R, int NS, int variant) { return slice_staged(fmt, R, NS, variant) + slice_tiles(R, NS, variant) <= 64 * 1024; }
-constexpr int slice_lds(int fmt, int R, int NS, int variant = 0) {
-  const int staged = slice_staged(fmt, R, NS, variant), tiles = slice_tiles(R, NS, variant);
-  return slice_tiles_apart(fmt, R, NS, variant) ? staged + tiles : staged > tiles ? staged : tiles;
-}
+constexpr int slice_lds(int fmt, int R, int NS, int variant = 0) { return slice_waves(R, NS, variant) * slice_wave_lds(fmt, R, NS, variant) + NS * 64 + NS * 4; }
 // Whether two workgroups of `strips` strips fit on a compute unit at M <= 4 with one scale per run of input channels: at
 // most 128 registers (as the compiler reports them; the formats of 96 weights per record take 126 at most, FP4.25, FP4.5
 // and FP5 124 with six strips and 134 with seven, FP4 126 with seven and 130 with eight).

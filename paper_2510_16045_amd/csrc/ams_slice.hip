@@ -70,7 +70,8 @@ struct Slice {
   static constexpr int LW = slice_ahead(S);
   static constexpr int U = RAGGED ? (NS == 1 ? 4 : 2) : NS > LW ? 1 : NS == 1 ? LW + 1 : 2;  // records per unrolled round
   static constexpr int RS = U * NS;                             // slots of the weight ring
-  static constexpr int ROW = slice_tile_row(S, R, NS);
+  static constexpr int ROW = slice_tile_row(S, R, NS), STRIP = slice_tile_strip(S, R, NS);  // floats
+  static constexpr int WAVE = slice_wave_lds(FMT, R, NS, VAR);                             // bytes
 };
 
 // GS: one scale per run of 2^a.sg_shift records.  A record goes through a fresh tile, times its run's scales, into the
@@ -127,7 +128,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
     for (int t = 0; t < MT; t++) acc[i][t] = f4{0, 0, 0, 0};
 
   if (cnt > 0) {
-    unsigned char* const xbuf = smem + wave * (LX * P::BYTES);
+    unsigned char* const xbuf = smem + wave * P::WAVE;
     // A load brings 16 (8, 4) rows x 4 (8, 16) pieces of 16 bytes: four neighbouring lanes read 64 neighbouring bytes of a
     // row (with neighbouring lanes in different rows the same bytes take three times as long).  The pieces of four lanes
     // are swapped by a function of the row that makes the reads of an operand, 8 or 16 rows at one piece, free of bank
@@ -356,11 +357,10 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the requests past the end are done with LDS
   }
   asm volatile("" : "+v"(scale_bits));
-  constexpr bool APART = slice_tiles_apart(FMT, R, NS, VAR);
-  if constexpr (!APART) __syncthreads();  // every wave is done with its activations
-  // Partial tiles [wave][strip][activation row][16 channels, padded], then the scales, then who was last.
-  float* const parts = (float*)(smem + (APART ? S * LX * P::BYTES : 0));
-  float* const scale_of = parts + S * NS * R * P::ROW;
+  // Partial tiles [wave][strip][activation row][16 channels, padded], each wavefront's where its own activations were, then
+  // the scales, then who was last.
+  float* const parts = (float*)smem;
+  float* const scale_of = (float*)(smem + S * P::WAVE);
   int* const last = (int*)(scale_of + NS * 16);
   {
     const int m_lo = lane & 15, kq = lane >> 4;
@@ -368,7 +368,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
 #pragma unroll
       for (int i = 0; i < NS; i++)
 #pragma unroll
-        for (int t = 0; t < MT; t++) *(f4*)(parts + ((wave * NS + i) * R + 16 * t + m_lo) * P::ROW + 4 * kq) = acc[i][t];
+        for (int t = 0; t < MT; t++) *(f4*)(parts + wave * (P::WAVE / 4) + i * P::STRIP + (16 * t + m_lo) * P::ROW + 4 * kq) = acc[i][t];
   }
   if (tid < NS * 16) scale_of[tid] = (float)__builtin_bit_cast(_Float16, (uint16_t)scale_bits) * kTwo14;
   __syncthreads();
@@ -378,7 +378,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
   auto quad_sum = [&](int i, int m, int c) {
     f4 sum = f4{0, 0, 0, 0};
 #pragma unroll
-    for (int w = 0; w < S; w++) sum += *(const f4*)(parts + ((w * NS + i) * R + m) * P::ROW + c);
+    for (int w = 0; w < S; w++) sum += *(const f4*)(parts + w * (P::WAVE / 4) + i * P::STRIP + m * P::ROW + c);
     return sum;
   };
   auto finish_quad = [&](int i, int m, int c, const f4 sum) {
@@ -410,7 +410,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
         const int i = p % NS, m = p / NS, row = (s_first + i) * 16 + n;
         float sum = 0;
 #pragma unroll
-        for (int w = 0; w < S; w++) sum += parts[((w * NS + i) * R + m) * P::ROW + n];
+        for (int w = 0; w < S; w++) sum += parts[w * (P::WAVE / 4) + i * P::STRIP + m * P::ROW + n];
         if (row < N) Y[(size_t)m * N + row] = __builtin_bit_cast(uint16_t, (_Float16)(sum * scale_of[i * 16 + n]));
       }
     }
