@@ -224,7 +224,7 @@ int ams_linear_workspace_bytes(int fmt, int M, int64_t N, int64_t K, size_t* byt
  * workgroup, slices of K, wavefronts, LDS bytes; of the kernels that have them: wavefronts per strip or strips per
  * wavefront, phases of K, whether side groups are dealt whole, records ahead).  In a "slice" plan every wavefront takes
  * its records of K from all strips of the workgroup, so it has no wavefronts per strip, phases or side groups, and
- * `ahead` counts (record, strip) pairs; row_tiles workgroups share the rows of X where it names them.  A slice plan for rows
+ * `ahead` counts (record, strip) pairs, the most that any kernel of as many wavefronts requests ahead; row_tiles workgroups share the rows of X where it names them.  A slice plan for rows
  * of X that are not 16-byte aligned (K % 8 != 0) names streamed_rows, the rows of a workgroup, and row_tiles.
  * Host only, launches nothing. */
 int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, char* text, size_t text_len);

@@ -335,12 +335,45 @@ constexpr int kSlicePlain = 0, kSliceRunScales = 1, kSliceRagged = 2, kSliceVari
 constexpr int kSliceRaggedMaxStrips = 4, kSliceRaggedMaxRows = 8;  // of the last one
 constexpr int kSliceMaxStrips = 8;  // strips per workgroup it is built for
 constexpr int slice_rows(int M) { return M <= 4 ? 4 : M <= 8 ? 8 : M <= 16 ? 16 : 32; }  // staged activation rows
-// Wavefronts of a workgroup.  Eight (with three pairs of weights ahead) are 3-10 % faster than sixteen with two where a
-// wavefront takes several strips or many rows: the sum over the wavefronts' tiles halves, and fewer contend for the VALU.
-// A single strip at M <= 4 needs sixteen to keep enough bytes in flight (4096 x 14336 FP5.33 M = 1 9.2 us against 9.6).
-constexpr int slice_waves(int R, int NS, int variant = 0) { return variant == kSliceRagged || (R == 4 && NS == 1) ? 16 : 8; }
-constexpr int slice_ahead(int S) { return S == 16 ? 2 : 3; }  // (record, strip) pairs of weights requested ahead
-constexpr int kSliceXAhead = 2;                               // records of activations requested ahead
+// Wavefronts of a workgroup and what each of them asks for ahead of its work.  A compute unit keeps about 32 KiB of
+// requests in flight, in order: what is asked for beyond that does not come sooner, it only stands before another
+// wavefront's next record, activations before weights and the other way round.  So a wavefront asks for little: one record of
+// activations ahead (not two), and weights one to three (record, strip) pairs ahead.  us, two records of activations and two or
+// three pairs of weights ahead (before) / here: 4096 x 14336 FP4.25 M = 4 8.9 / 8.0, M = 16 12.7 / 11.5, M = 32 15.8 / 14.5; 8192 x
+// 28672 FP5.33 M = 8 29.4 / 28.4, M = 16 37.2 / 34.9; 6144 x 4096 FP4.25 M = 8 5.9 / 5.4; 28672 x 4096 FP4.25 M = 32 17.0 /
+// 15.9; four records of activations ahead instead of two 0.93-1.0 x, six pairs of weights 0.89-1.02 x.
+struct SliceAsk {
+  int waves;    // wavefronts of the workgroup
+  int streams;  // of them, those that take records; the others help with the sum at the end
+  int weights;  // (record, strip) pairs of weights asked for ahead
+  int acts;     // records of activations asked for ahead
+  int behind;   // strips of a record whose weights are asked for before the next record's activations
+};
+constexpr SliceAsk slice_ask(int fmt, int R, int NS, int variant) {
+  if (variant == kSliceRagged) return {16, 16, 2, 2, 0};  // activations through registers: two sets of them
+  const bool rec96 = ams::kFormats[fmt].rec_k == 96, runs = variant == kSliceRunScales;
+  if (NS == 1) {
+    // One strip: many wavefronts that each wait for one record (4096 x 9728 FP4.25 M = 1, sixteen with two records ahead / with
+    // one / twelve / eight with two: 1.00 / 1.10 / 1.02 / 1.03 x; only FP5.33 and FP4 at M = 1 on fewer than 224 strips, from 180
+    // records on, would like two of both, 0.98 x).  Up to eight rows eight stay, two ahead of both (one ahead
+    // 0.88-1.0 x of it); up to sixteen rows twelve stream (FP4.25 1.05-1.16 x, FP5.33 M = 9 to 15 1.02-1.07 x but 0.98 x on
+    // 16 to 28 records), but for 96-weight records with a scale per run (11 to 28 records 1.01-1.08 x, twelve 0.96-1.01 x).
+    if (R == 4) return {16, 16, 1, 1, 0};
+    if (R == 8) return {8, 8, 2, 2, 0};
+    if (R == 16) return rec96 && runs ? SliceAsk{8, 8, 1, 2, 0} : SliceAsk{16, 12, 1, 1, 0};
+    return {8, 8, 1, 1, 0};
+  }
+  // Two strips: the next record's.  At M <= 4 sixteen wavefronts, of which twelve stream where a record takes more than one load
+  // (its side dword, its scales): 6144 x 4096 FP4.25 M = 1 eight / twelve / sixteen 1.02 / 1.09 / 1.04 x the time before, 8192 x
+  // 28672 FP5.33 M = 1 0.98 (twelve) / 1.03 x (sixteen), 6144 x 4096 1.05 / 1.05.
+  if (NS == 2) return R == 4 ? SliceAsk{16, ams::kFormats[fmt].side_bytes != 0 || runs ? 12 : 16, 2, 1, 0} : SliceAsk{8, 8, 2, 1, 0};
+  // More strips keep a wavefront busy for longer than a trip to the L2: the next activations are asked for shortly before the
+  // record ends (28672 x 4096 M = 32 FP4.25 at its start / before the last strip but one: 15.9 / 15.5; 20480 x 4096 M = 16 1.04 /
+  // 1.07 x).  Up to eight rows earlier: at the end of a short stream the last request is one for nothing and waited for (K = 1024
+  // and less, M <= 8: 0.99 x before the last strip but one, 1.02 x behind the first).
+  return {8, 8, 3, 1, R > 8 ? NS - 2 : NS >= 5 ? 1 : 0};
+}
+constexpr int slice_most_ahead(int waves) { return waves == 16 ? 2 : 3; }  // what a plan names: the most pairs of any kernel with as many wavefronts
 // 1 KiB loads that bring one record's activations
 constexpr int slice_x_loads(int fmt, int R) {
   const int rb = R > 16 ? 16 : R, pieces = (ams::kFormats[fmt].rec_k / 8 + 3) / 4 * 4;
@@ -354,10 +387,11 @@ constexpr int slice_tile_strip(int S, int R, int NS) { return R * slice_tile_row
 // LDS of one wavefront: its records of activations and, when its stream has ended, its partial tiles in the same place.  It
 // leaves them as soon as it is done itself, without a barrier (28672 x 4096 FP4.25 M = 16 14.0 -> 13.7, M = 32 17.8 -> 17.5).
 constexpr int slice_wave_lds(int fmt, int R, int NS, int variant) {
-  const int staged = kSliceXAhead * slice_x_loads(fmt, R) * 1024, tiles = NS * slice_tile_strip(slice_waves(R, NS, variant), R, NS) * 4;
+  const SliceAsk a = slice_ask(fmt, R, NS, variant);
+  const int staged = a.acts * slice_x_loads(fmt, R) * 1024, tiles = NS * slice_tile_strip(a.streams, R, NS) * 4;
   return staged > tiles ? staged : tiles;
 }
-constexpr int slice_lds(int fmt, int R, int NS, int variant = 0) { return slice_waves(R, NS, variant) * slice_wave_lds(fmt, R, NS, variant) + NS * 64 + NS * 4; }
+constexpr int slice_lds(int fmt, int R, int NS, int variant) { return slice_ask(fmt, R, NS, variant).streams * slice_wave_lds(fmt, R, NS, variant) + NS * 64 + NS * 4; }
 // Whether two workgroups of `strips` strips fit on a compute unit at M <= 4 with one scale per run of input channels: at
 // most 128 registers (as the compiler reports them; the formats of 96 weights per record take 126 at most, FP4.25, FP4.5
 // and FP5 124 with six strips and 134 with seven, FP4 126 with seven and 130 with eight).

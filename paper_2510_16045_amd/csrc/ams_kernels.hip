@@ -1474,8 +1474,8 @@ ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
   }
   p.slice = p.ragged = true;
   p.rows = slice_rows((M + p.row_tiles - 1) / p.row_tiles);
-  p.S = slice_waves(p.rows, p.spw, kSliceRagged);
-  p.lr = slice_ahead(p.S);
+  p.S = slice_ask(fmt, p.rows, p.spw, kSliceRagged).waves;
+  p.lr = slice_most_ahead(p.S);
   p.lds = (size_t)slice_lds(fmt, p.rows, p.spw, kSliceRagged);
   return p;
 }
@@ -1523,9 +1523,10 @@ ColumnPlan plan_from(ColumnPlan p, int fmt, int M, int64_t n_strips, int n_rec_a
   }
   p.slice = true;
   p.rows = slice_rows((M + p.row_tiles - 1) / p.row_tiles);
-  p.S = slice_waves(p.rows, p.spw);
-  p.lr = slice_ahead(p.S);
-  p.lds = (size_t)slice_lds(fmt, p.rows, p.spw);
+  const int variant = one_scale ? kSlicePlain : kSliceRunScales;
+  p.S = slice_ask(fmt, p.rows, p.spw, variant).waves;
+  p.lr = slice_most_ahead(p.S);
+  p.lds = (size_t)slice_lds(fmt, p.rows, p.spw, variant);
   return p;
 }
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
@@ -1800,7 +1801,7 @@ int launch_slice(const LinearArgs& a, int variant, int r, int strips, unsigned g
                        (uint32_t)a.K, (uint32_t)a.n_rec, (uint32_t)a.n_strips, (uint32_t)a.gn, (uint32_t)a.gk, (uint32_t)a.tile_rows};
   SliceArgs rest = {a.Y, a.ws_tiles, a.ws_count, a.n_sg, a.sg_shift, a.row_tiles};
   void* args[] = {head, head + 4, head + 8, head + 12, &rest};
-  return hipLaunchKernel(kern, dim3(grid / a.row_tiles, a.row_tiles), dim3(64 * slice_waves(r, strips, variant)), args, lds, st) == hipSuccess ? AMS_OK : AMS_ERR_LAUNCH;
+  return hipLaunchKernel(kern, dim3(grid / a.row_tiles, a.row_tiles), dim3(64 * slice_ask(FMT, r, strips, variant).waves), args, lds, st) == hipSuccess ? AMS_OK : AMS_ERR_LAUNCH;
 }
 
 template <int FMT>

@@ -5,20 +5,22 @@
 // A workgroup owns NS neighbouring strips and its wavefronts share K: wavefront w takes records w, w + S, ... of all NS
 // strips.  The activations of a record are then needed by one wavefront only, so nothing is staged for the
 // workgroup and there is no barrier before the sums at the end: a wavefront copies the M x REC_K activations of its
-// next records straight into LDS of its own (16 bytes per lane and load, no registers) in the same in-order stream of
+// next record straight into LDS of its own (16 bytes per lane and load, no registers) in the same in-order stream of
 // requests as the weights, and one s_waitcnt that counts the younger requests lets a record start as soon as its own
-// loads are there.  They arrive in input-channel order; the operand registers are permuted once per record and serve
+// loads are there (how far ahead it asks: slice_ask).  They arrive in input-channel order; the operand registers are permuted once per record and serve
 // all NS strips.  What it replaces staged the activations of all of K (or of a phase of it) for the workgroup, through
 // registers, between barriers, and sat in front of the weight stream.
 //
 // Bound: at M <= 8 by the weight stream and the restoration's VALU work; at larger batches by the one in-order path through
 // which a compute unit draws weights (from memory) and activations (from L2), 32 KiB of both in flight: without the activations 4096 x
 // 14336 FP4.25 at M = 32 took 9.7 us of 20.2, without weights from memory 14.9, without either 9.0, without the restoration
-// 20.1.  So the rows are dealt to several workgroups there (20.3 -> 16.4).
+// 20.1.  So the rows are dealt to several workgroups there (20.3 -> 16.4), and a wavefront asks for one record of activations
+// ahead, not two (-> 14.5; the same requests without any work between them take 13.7).
 //
-// Measured against what it replaces (us, M = 1 / 4 / 16 / 32): 4096 x 4096 FP4.25 5.2 -> 4.3, 6.0 -> 4.5, 7.6 -> 5.7, 13.4 -> 6.6;
-// 4096 x 14336 8.7 -> 8.5, 10.3 -> 9.1, 18.3 -> 12.9, 30.9 -> 16.0; 8192 x 8192 FP5.33 10.5 -> 9.9, 11.2 -> 10.0, 15.6 -> 12.9,
-// 25.4 -> 15.5; 28672 x 4096 FP4.25 12.8 -> 11.8, 13.8 -> 12.4, 15.3 -> 13.9, 21.7 -> 17.9; 256 x 768 4.1 -> 2.7 up to M = 4, 3.1 at 16.
+// Measured against what it replaced, and with two records of activations ahead / now (us, M = 1 / 4 / 16 / 32): 4096 x 4096 FP4.25
+// 5.2 -> 4.3 / 4.1, 6.0 -> 4.5 / 4.2, 7.6 -> 5.8 / 5.3, 13.4 -> 6.8 / 6.1; 4096 x 14336 8.7 -> 8.2 / 7.7, 10.3 -> 8.9 / 8.0, 18.3 -> 12.9 /
+// 11.7, 30.9 -> 15.8 / 14.6; 8192 x 8192 FP5.33 10.5 -> 9.8 / 9.6, 11.2 -> 10.0 / 9.8, 15.6 -> 12.9 / 12.0, 25.4 -> 15.5 / 15.1; 28672 x 4096
+// FP4.25 12.8 -> 11.7 / 11.5, 13.8 -> 11.9 / 11.8, 15.3 -> 13.6 / 12.8, 21.7 -> 17.0 / 15.5; 256 x 768 4.1 -> 2.4 / 2.3 up to M = 4, 2.8 / 2.4 at 16.
 //
 // The counted waits need every step to make the same requests in the same order: requests past a wavefront's last record
 // are made too, out of the buffers' range (they read no memory), the scheduler may not move requests across the
@@ -65,10 +67,14 @@ struct Slice {
   static constexpr int NI = slice_x_loads(FMT, R), NI1 = NI / MT;  // 1 KiB loads of a record's activations, of one tile's
   static constexpr int BYTES = NI * 1024;
   static constexpr int WL = (Fmt<FMT>::SIDE ? 2 : 1) + GS;      // load instructions of one weight record (and its scales)
-  static constexpr int S = slice_waves(R, NS, VAR);
-  static constexpr int LX = kSliceXAhead;
-  static constexpr int LW = slice_ahead(S);
-  static constexpr int U = RAGGED ? (NS == 1 ? 4 : 2) : NS > LW ? 1 : NS == 1 ? LW + 1 : 2;  // records per unrolled round
+  static constexpr SliceAsk ASK = slice_ask(FMT, R, NS, VAR);
+  static constexpr int S = ASK.streams, THREADS = 64 * ASK.waves;
+  static constexpr bool IDLE = S < ASK.waves;  // some wavefronts only help with the sum at the end
+  static constexpr int LX = ASK.acts, LW = ASK.weights, BEHIND = ASK.behind;
+  static constexpr int U = RAGGED ? (NS == 1 ? 4 : 2) : NS > LW ? 1 : NS == 1 ? (LW == 1 ? 2 : 4) : 2;  // records per unrolled round
+  // Side dwords that several records share are read by as many wavefronts and stay in the caches (FP4.25, four readers: 4096 x
+  // 14336 M = 16 12.7 -> 12.3 us), but for M <= 4 on three strips and more, where they take the weights' place (28672 x 4096 M = 1 11.7, cached 11.9).
+  static constexpr int SIDE_NT = Fmt<FMT>::SG == 1 || (R == 4 && NS >= 3) ? 2 : 0;
   static constexpr int RS = U * NS;                             // slots of the weight ring
   static constexpr int ROW = slice_tile_row(S, R, NS), STRIP = slice_tile_strip(S, R, NS);  // floats
   static constexpr int WAVE = slice_wave_lds(FMT, R, NS, VAR);                             // bytes
@@ -83,7 +89,7 @@ struct Slice {
 // begins.  Tiles of up to eight rows and up to four strips, sixteen wavefronts.  us, column_kernel (staged by the workgroup) / here:
 // 11003 x 4099 FP5.33 M = 5 10.6 / 8.7, 8192 x 8193 FP4.25 M = 4 12.6 / 9.6, 4096 x 14337 M = 32 47.7 / 21.5; 160 random shapes 1.30 x.
 template <int FMT, int R, int NS, int VAR>
-__global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel(u4 head0, u4 head1, u4 head2, u2 head3, SliceArgs a) {
+__global__ void __launch_bounds__((Slice<FMT, R, NS, VAR>::THREADS)) slice_kernel(u4 head0, u4 head1, u4 head2, u2 head3, SliceArgs a) {
   const uint8_t* const W = (const uint8_t*)pointer_of(head0[0], head0[1]);
   const uint16_t* const X = (const uint16_t*)pointer_of(head0[2], head0[3]);
   const uint16_t* const scales = (const uint16_t*)pointer_of(head1[0], head1[1]);
@@ -110,7 +116,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
   const int rec_lo = gk_slices > 1 ? (int)((unsigned)(gk * n_rec) / (unsigned)gk_slices) : 0;
   const int rec_hi = gk_slices > 1 ? (int)((unsigned)((gk + 1) * n_rec) / (unsigned)gk_slices) : n_rec;
   const int first = rec_lo + wave;  // this wave's records: first, first + S, ...
-  const int cnt = first < rec_hi ? (rec_hi - first + S - 1) / S : 0;
+  const int cnt = (!P::IDLE || wave < S) && first < rec_hi ? (rec_hi - first + S - 1) / S : 0;
   // The scales of the workgroup's channels are asked for ahead of the stream and not touched before its end.  (Behind a
   // branch, the compiler moved their conversion up to the load: the first wavefront then waited for memory before its
   // first record.)  Threads beyond them, and channels beyond N, ask for nothing and get 0.
@@ -221,7 +227,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
       buffer_load_chunk<Fmt<FMT>::CHUNK>(slot.w, w, vo, (int)(rec % SG) * Fmt<FMT>::CB);
       if constexpr (Fmt<FMT>::SIDE != 0) {
         const int vs = p < cnt ? lane * 4 : FAR;
-        buffer_load_chunk<4>(&slot.t, w, vs, SG * Fmt<FMT>::CB);
+        buffer_load_chunk<4, P::SIDE_NT>(&slot.t, w, vs, SG * Fmt<FMT>::CB);
       }
       if constexpr (GS) {  // cached: a run spans many records and rows of lanes
         const uint16_t* run = scales + ((size_t)(s_first + min(i, ns - 1)) * a.n_sg + (rec >> a.sg_shift)) * 16;
@@ -236,19 +242,21 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
     // after this record's activations: every step makes the same requests, those past the end out of range.
     auto step = [&](int p, auto uc) {
       constexpr int u0 = decltype(uc)::value * NS;  // its first slot of the ring
-      constexpr int STEADY = LX * NS * P::WL + (LX - 1) * P::NI;
+      // younger than record p's activations when step p begins: the weights requested since, and the records behind it
+      constexpr int STEADY = (LX * NS - P::BEHIND) * P::WL + (LX - 1) * P::NI;
+      constexpr auto at_start = [](int q) { return (LW + q * NS < LX * NS - P::BEHIND ? LW + q * NS : LX * NS - P::BEHIND) * P::WL + (LX - 1) * P::NI; };
       constexpr std::integral_constant<int, decltype(uc)::value & 1> set;  // RAGGED: rounds are even
       if constexpr (RAGGED) {
         store_ragged(p, set);  // the compiler sees the loads and waits for them itself
         request_ragged(p + LX, set);
         __builtin_amdgcn_sched_barrier(0);
-      } else if constexpr (LW >= LX * NS) {
+      } else if constexpr (LW >= LX * NS - P::BEHIND) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STEADY) : "memory");
       } else {  // the first steps have fewer weights requested behind their activations
         if (p == 0)
-          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LW * P::WL + (LX - 1) * P::NI) : "memory");
-        else if (p == 1)
-          asm volatile("s_waitcnt vmcnt(%0)" ::"n"((LW < NS ? LW + NS : 2 * NS) * P::WL + (LX - 1) * P::NI) : "memory");
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(at_start(0)) : "memory");
+        else if (LX > 1 && p == 1)
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(at_start(1)) : "memory");
         else
           asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STEADY) : "memory");
       }
@@ -261,7 +269,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
       if constexpr (!RAGGED) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        request_x(p + LX);
+        if constexpr (P::BEHIND == 0) request_x(p + LX);
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -290,6 +298,12 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
 #pragma unroll
       for (int i = 0; i < NS; i++) {
         request_w(p + (i + LW) / NS, (i + LW) % NS, ring[(u0 + i + LW) % RS], ring_sc[GS ? (u0 + i + LW) % RS : 0]);
+        if (!RAGGED && i == P::BEHIND - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          asm volatile("" ::: "memory");
+          request_x(p + LX);
+          asm volatile("" ::: "memory");
+        }
         __builtin_amdgcn_sched_barrier(0);
         uint32_t o[4 * NF];
         restore_rec<FMT>(ring[u0 + i], side_shift, o);
@@ -364,7 +378,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
   int* const last = (int*)(scale_of + NS * 16);
   {
     const int m_lo = lane & 15, kq = lane >> 4;
-    if (m_lo < RB)
+    if (m_lo < RB && (!P::IDLE || wave < S))
 #pragma unroll
       for (int i = 0; i < NS; i++)
 #pragma unroll
@@ -400,13 +414,13 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
     // 264 FP5.33 M = 9 3.46 / 3.65), equal at 13.
     constexpr bool QUADS = R >= 16 && NS >= 3;
     if (QUADS && (R > 16 || NS > 3 || pairs >= 40)) {
-      for (int u = tid; u < pairs * 4; u += 64 * S) {
+      for (int u = tid; u < pairs * 4; u += P::THREADS) {
         const int c = 4 * (u & 3), i = (u >> 2) % NS, m = (u >> 2) / NS;
         finish_quad(i, m, c, quad_sum(i, m, c));
       }
     } else {  // one output per thread
       const int n = tid & 15;
-      for (int p = tid >> 4; p < pairs; p += 4 * S) {
+      for (int p = tid >> 4; p < pairs; p += P::THREADS / 16) {
         const int i = p % NS, m = p / NS, row = (s_first + i) * 16 + n;
         float sum = 0;
 #pragma unroll
@@ -424,7 +438,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
   unsigned* const counts = a.ws_count + s_first * a.row_tiles + blockIdx.y;  // of this row tile: one per strip
   const __amdgpu_buffer_rsrc_t tiles = __builtin_amdgcn_make_buffer_rsrc((void*)a.ws_tiles, 0, gk_slices * n_strips * tile * 4, 0x00020000);
   auto tile_offset = [&](int slice, int i, int m, int c) { return (((slice * n_strips + s_first + i) * tile) + (m_first + m) * 16 + c) * 4; };
-  for (int u = tid; u < pairs * 4; u += 64 * S) {
+  for (int u = tid; u < pairs * 4; u += P::THREADS) {
     const int c = 4 * (u & 3), i = (u >> 2) % NS, m = (u >> 2) / NS;
     const f4 sum = quad_sum(i, m, c);
     if (i < ns) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, sum), tiles, tile_offset(gk, i, m, c), 0, kDeviceScope);
@@ -439,7 +453,7 @@ __global__ void __launch_bounds__(64 * (Slice<FMT, R, NS, VAR>::S)) slice_kernel
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  for (int u = tid; u < pairs * 4; u += 64 * S) {
+  for (int u = tid; u < pairs * 4; u += P::THREADS) {
     const int c = 4 * (u & 3), i = (u >> 2) % NS, m = (u >> 2) / NS;
     if (i >= ns || !last[i]) continue;
     f4 part[kMaxSlices];

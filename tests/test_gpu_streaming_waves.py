@@ -1,0 +1,45 @@
+"""slice_kernel where only twelve of a workgroup's sixteen wavefronts take records (two strips at M <= 4, one strip at 9 to
+16 rows): as many records as streaming wavefronts, one fewer, one more and two rounds of them, and a wavefront's last
+record short; one scale per row, per run, and K split over workgroups; sampled rows against the oracle."""
+
+import numpy as np
+import pytest
+
+import paper_2510_16045_amd as ams
+from oracle import ams_oracle as O
+from paper_2510_16045_amd import synth
+from test_gpu_slice_kernel import PAIRS, REC_K, check, dev, problem, scales_per_run
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("fmt,ofmt", PAIRS)
+@pytest.mark.parametrize("strips,N,Ms", [(2, 16 * 300 - 5, (1, 4)), (1, 16 * 40 - 5, (9, 15))])
+def test_records_around_the_streaming_wavefronts(fmt, ofmt, strips, N, Ms):
+    for n_rec in (11, 12, 13, 24, 25):
+        K = REC_K[fmt] * n_rec - 8 * (n_rec % 3)
+        codes, scales, rows = problem(fmt, ofmt, N, K, n_rec)
+        packed = dev(ams.ams_pack_codes(fmt, codes))
+        run_scales, run_packed = scales_per_run(N, K, 2 * REC_K[fmt], 4)
+        for M in Ms:
+            plan = ams.ams_linear_plan(fmt, M, N, K)
+            assert plan.startswith("slice ") and f"strips_per_wg={strips} " in plan and " waves=16 " in plan, plan
+            X = synth.activations(M, K, 50 + M)
+            what = f"{ofmt.name} N={N} K={K} M={M}: {plan}"
+            check(ams.ams_linear(packed, dev(scales), dev(X), N, fmt), O.linear(codes[rows], scales[rows], X, ofmt), rows, what)
+            y = ams.ams_linear_grouped(packed, dev(run_packed), 2 * REC_K[fmt], dev(X), N, fmt)
+            check(y, O.linear(codes[rows], run_scales[rows], X, ofmt, 2 * REC_K[fmt]), rows, "scales per run, " + what)
+
+
+@pytest.mark.parametrize("fmt,ofmt", PAIRS)
+def test_streaming_wavefronts_and_slices_of_k(fmt, ofmt):
+    N, K, M = 507, 14344, 15
+    plan = ams.ams_linear_plan(fmt, M, N, K, with_workspace=True)
+    assert plan.startswith("slice ") and " strips_per_wg=1 " in plan and "k_slices=1 " not in plan and " waves=16 " in plan, plan
+    codes, scales, rows = problem(fmt, ofmt, N, K, 6)
+    X = synth.activations(M, K, 61)
+    packed, sc, x, ws = dev(ams.ams_pack_codes(fmt, codes)), dev(scales), dev(X), torch.zeros(16 << 20, dtype=torch.uint8, device="cuda")
+    first = ams.ams_linear_ws(packed, sc, x, N, fmt, ws)
+    check(first, O.linear(codes[rows], scales[rows], X, ofmt), rows, plan)
+    assert torch.equal(ams.ams_linear_ws(packed, sc, x, N, fmt, ws), first) and not ws[: 4 * 16384].any(), plan
