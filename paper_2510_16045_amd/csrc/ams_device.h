@@ -350,8 +350,11 @@ struct SliceAsk {
   int behind;   // strips of a record whose weights are asked for before the next record's activations
 };
 constexpr SliceAsk slice_ask(int fmt, int R, int NS, int variant) {
-  if (variant == kSliceRagged) return {16, 16, 2, 2, 0};  // activations through registers: two sets of them
-  const bool rec96 = ams::kFormats[fmt].rec_k == 96, runs = variant == kSliceRunScales;
+  const bool rec96 = ams::kFormats[fmt].rec_k == 96, runs = variant == kSliceRunScales, loads2 = ams::kFormats[fmt].side_bytes != 0 || runs;
+  // Unaligned rows come through registers, one record ahead and one pair of weights on one strip.  Against two records and two pairs,
+  // seven formats: 5 to 8 rows 1.18 x on one strip, 1.12 on two, 1.08 on three and four (11003 x 4099 FP5.33 M = 5 8.8 / 8.1 us, 4096 x 14339
+  // M = 8 14.9 / 12.7); up to four rows 1.07, 1.03, 1.02, 1.01 (twelve streams of 96-weight records 0.94-0.97 x on two strips).
+  if (variant == kSliceRagged) return {16, R == 4 && NS == 2 && loads2 && !rec96 ? 12 : 16, NS == 1 ? 1 : 2, 1, 0};
   if (NS == 1) {
     // One strip: many wavefronts that each wait for one record (4096 x 9728 FP4.25 M = 1, sixteen with two records ahead / with
     // one / twelve / eight with two: 1.00 / 1.10 / 1.02 / 1.03 x; only FP5.33 and FP4 at M = 1 on fewer than 224 strips, from 180
@@ -366,7 +369,7 @@ constexpr SliceAsk slice_ask(int fmt, int R, int NS, int variant) {
   // Two strips: the next record's.  At M <= 4 sixteen wavefronts, of which twelve stream where a record takes more than one load
   // (its side dword, its scales): 6144 x 4096 FP4.25 M = 1 eight / twelve / sixteen 1.02 / 1.09 / 1.04 x the time before, 8192 x
   // 28672 FP5.33 M = 1 0.98 (twelve) / 1.03 x (sixteen), 6144 x 4096 1.05 / 1.05.
-  if (NS == 2) return R == 4 ? SliceAsk{16, ams::kFormats[fmt].side_bytes != 0 || runs ? 12 : 16, 2, 1, 0} : SliceAsk{8, 8, 2, 1, 0};
+  if (NS == 2) return R == 4 ? SliceAsk{16, loads2 ? 12 : 16, 2, 1, 0} : SliceAsk{8, 8, 2, 1, 0};
   // More strips keep a wavefront busy for longer than a trip to the L2: the next activations are asked for shortly before the
   // record ends (28672 x 4096 M = 32 FP4.25 at its start / before the last strip but one: 15.9 / 15.5; 20480 x 4096 M = 16 1.04 /
   // 1.07 x).  Up to eight rows earlier: at the end of a short stream the last request is one for nothing and waited for (K = 1024

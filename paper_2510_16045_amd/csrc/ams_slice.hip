@@ -71,7 +71,7 @@ struct Slice {
   static constexpr int S = ASK.streams, THREADS = 64 * ASK.waves;
   static constexpr bool IDLE = S < ASK.waves;  // some wavefronts only help with the sum at the end
   static constexpr int LX = ASK.acts, LW = ASK.weights, BEHIND = ASK.behind;
-  static constexpr int U = RAGGED ? (NS == 1 ? 4 : 2) : NS > LW ? 1 : NS == 1 ? (LW == 1 ? 2 : 4) : 2;  // records per unrolled round
+  static constexpr int U = NS > LW && !RAGGED ? 1 : NS == 1 ? (LW == 1 ? 2 : 4) : 2;  // records per unrolled round
   // Side dwords that several records share are read by as many wavefronts and stay in the caches (FP4.25, four readers: 4096 x
   // 14336 M = 16 12.7 -> 12.3 us), but for M <= 4 on three strips and more, where they take the weights' place (28672 x 4096 M = 1 11.7, cached 11.9).
   static constexpr int SIDE_NT = Fmt<FMT>::SG == 1 || (R == 4 && NS >= 3) ? 2 : 0;
@@ -85,9 +85,9 @@ struct Slice {
 // FP4.25, a scale per 128: M = 1 15.7 -> 12.8 us, M = 4 15.9 -> 13.5, M = 32 23.5 -> 20.2 (column_kernel before).
 //
 // RAGGED: rows of X that are not 16-byte aligned (K no multiple of 8) cannot be copied straight into LDS: they are loaded
-// two records ahead into registers, 16 unaligned bytes per lane, and written to the wave's own LDS when their record
+// one record ahead into registers, 16 unaligned bytes per lane, and written to the wave's own LDS when their record
 // begins.  Tiles of up to eight rows and up to four strips, sixteen wavefronts.  us, column_kernel (staged by the workgroup) / here:
-// 11003 x 4099 FP5.33 M = 5 10.6 / 8.7, 8192 x 8193 FP4.25 M = 4 12.6 / 9.6, 4096 x 14337 M = 32 47.7 / 21.5; 160 random shapes 1.30 x.
+// 11003 x 4099 FP5.33 M = 5 10.6 / 8.1, 8192 x 8193 FP4.25 M = 4 12.6 / 9.3, 4096 x 14337 M = 32 47.7 / 20.2.
 template <int FMT, int R, int NS, int VAR>
 __global__ void __launch_bounds__((Slice<FMT, R, NS, VAR>::THREADS)) slice_kernel(u4 head0, u4 head1, u4 head2, u2 head3, SliceArgs a) {
   const uint8_t* const W = (const uint8_t*)pointer_of(head0[0], head0[1]);
@@ -164,12 +164,12 @@ __global__ void __launch_bounds__((Slice<FMT, R, NS, VAR>::THREADS)) slice_kerne
       const int piece = kq * NF + u;
       roff[u] = (piece >> 2) * (RB * 64) + m_lo * 64 + (((piece & 3) ^ swz(m_lo)) * 16);
     }
-    // RAGGED: the loads' rows, the channels of their pieces inside a record, and the two records under way.  Lanes whose row does
+    // RAGGED: the loads' rows, the channels of their pieces inside a record, and the record under way.  Lanes whose row does
     // not exist ask for nothing on tiles of eight rows, and for row 0 on tiles of four, where the branch costs one and three
     // rows 2-3 %.  (With the last row again for all of them its lines were asked for by lanes in several pairs of rows,
     // which takes longer the more there are: 2544 x 6015 FP4.33, 2 / 6 / 10 rows 6.6 / 8.8 / 10.1 us, now 5.4 / 7.7 / 8.5.)
     int row_at[MT], piece_at[MT];
-    u4 ahead[RAGGED ? LX : 1][RAGGED ? P::NI : 1] = {};
+    u4 ahead[RAGGED ? P::NI : 1] = {};
     if constexpr (RAGGED) {
 #pragma unroll
       for (int t = 0; t < MT; t++) {
@@ -178,21 +178,21 @@ __global__ void __launch_bounds__((Slice<FMT, R, NS, VAR>::THREADS)) slice_kerne
       }
     }
     const uint16_t* const xrows = X + (size_t)m_first * K;
-    auto request_ragged = [&](int p, auto set) {
+    auto request_ragged = [&](int p) {
       const int rec = p < cnt ? first + S * p : first;  // behind the last record: any record (the results are not used)
 #pragma unroll
       for (int t = 0; t < MT; t++)
 #pragma unroll
         for (int i = 0; i < P::NI1; i++)  // a piece that runs past its row's end: the row's last eight channels
-          if (RB == 4 || 16 * t + ld_m < rows) __builtin_memcpy(&ahead[set][t * P::NI1 + i], xrows + row_at[t] + min(rec * REC_K + piece_at[t] + i * (BLK * 32), K - 8), 16);
+          if (RB == 4 || 16 * t + ld_m < rows) __builtin_memcpy(&ahead[t * P::NI1 + i], xrows + row_at[t] + min(rec * REC_K + piece_at[t] + i * (BLK * 32), K - 8), 16);
     };
-    auto store_ragged = [&](int p, auto set) {
+    auto store_ragged = [&](int p) {
       const int rec = first + S * p;
 #pragma unroll
       for (int t = 0; t < MT; t++)
 #pragma unroll
         for (int i = 0; i < P::NI1; i++) {
-          u4 v = ahead[set][t * P::NI1 + i];
+          u4 v = ahead[t * P::NI1 + i];
           if (rec == n_rec - 1) {  // channels beyond K count as zero
             const int beyond = rec * REC_K + piece_at[t] + i * (BLK * 32) + 8 - K;
             uint32_t h[4] = {v[0], v[1], v[2], v[3]};
@@ -245,10 +245,9 @@ __global__ void __launch_bounds__((Slice<FMT, R, NS, VAR>::THREADS)) slice_kerne
       // younger than record p's activations when step p begins: the weights requested since, and the records behind it
       constexpr int STEADY = (LX * NS - P::BEHIND) * P::WL + (LX - 1) * P::NI;
       constexpr auto at_start = [](int q) { return (LW + q * NS < LX * NS - P::BEHIND ? LW + q * NS : LX * NS - P::BEHIND) * P::WL + (LX - 1) * P::NI; };
-      constexpr std::integral_constant<int, decltype(uc)::value & 1> set;  // RAGGED: rounds are even
       if constexpr (RAGGED) {
-        store_ragged(p, set);  // the compiler sees the loads and waits for them itself
-        request_ragged(p + LX, set);
+        store_ragged(p);  // the compiler sees the loads and waits for them itself
+        request_ragged(p + 1);
         __builtin_amdgcn_sched_barrier(0);
       } else if constexpr (LW >= LX * NS - P::BEHIND) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STEADY) : "memory");
@@ -334,9 +333,8 @@ __global__ void __launch_bounds__((Slice<FMT, R, NS, VAR>::THREADS)) slice_kerne
     };
     using std::integral_constant;
     if constexpr (RAGGED) {
-      request_ragged(0, integral_constant<int, 0>{});
-      request_ragged(1, integral_constant<int, 1>{});
-      static_assert(LX == 2, "two sets");
+      static_assert(LX == 1, "one record under way");
+      request_ragged(0);
     } else {
 #pragma unroll
       for (int q = 0; q < LX; q++) request_x(q);
