@@ -1341,26 +1341,41 @@ ColumnPlan make_column_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int
 }
 
 // More than eight strips for every compute unit (spw of them): whether two workgroups of slice_kernel with half the strips
-// each beat the one of column_kernel / multi_kernel.  Formats without side groups and one scale per row from M = 9 on,
-// the others from M = 3 on.  Bounds, us column / slice; 1500 shapes per class, in one round of workgroups unless said:
-//   M > 4: long K, where the staging of the activations starts to cost (128256 x 4096 FP4.25 M = 8 49.6 / 50.2, 45000 x 4096
-//     M = 16 21.1 / 23.3; 64 to 80 records at M > 16 0.92-1.0 x);
-//   M <= 4, one scale per row: everything but two records per side group with a count that is even but no multiple of
-//     four, which column_kernel deals without a rest while most of the eight wavefronts idle (65536 x 256 FP4.5 0.87 x,
-//     x 768 0.90 x, x 1792 0.93 x; from 24 records on +- 3 %);
-//   M <= 4, one scale per run: a wavefront's strips follow each other and the sum over eight wavefronts' tiles is the same
-//     for one record as for a hundred, so a few records do not pay (65536 x 96 FP5.33 0.83 x, x 1152 0.96 x), and where
+// each beat the one of column_kernel / multi_kernel.  us column / slice; 2600 shapes of M = 1 to 16 since a wavefront asks for one
+// record of activations ahead, 1500 per class before.
+//   One scale per row, M <= 8, side groups: everywhere (128256 x 4096 FP4.25 M = 8 1.12 x, 90000 x 4096 1.38 x; 1.11-1.21 x in the mean, no
+//     format below 1.02) but for two records per side group with a count that is even but no multiple of four, which
+//     column_kernel deals without a rest while most of the eight wavefronts idle (65536 x 256 FP4.5 0.87 x, x 768 0.90 x,
+//     from 24 records on +- 3 %).  At M = 1 in one round from 64 records on left where it was (57344 x 8192; 1.05-1.14 x).
+//   One scale per row, M <= 8, no side groups: up to ten strips, where three of multi_kernel's eight wavefronts, two strips each, have none
+//     (33000 x 4096 FP5.33 M = 1 1.35 x, 40000 x 4096 1.28 x; one and two records 0.87-0.96 x; eleven to thirteen strips, left with
+//     multi_kernel, 1.05-1.2 x, 65536 x 4096 0.92 x), and where at most half of the compute units
+//     have a workgroup in the last round (90000 x 4096 1.17 x, 128256 x 4096 0.96 x).
+//   M > 8: long K, where the staging of the activations starts to cost (45000 x 4096 M = 16 21.1 / 23.3; 64 to 80
+//     records at M > 16 0.92-1.0 x).  Left: from 32 or 43 records on at M = 10 to 16, one scale per row, 1.06-1.14 x.
+//   One scale per run: a wavefront's strips follow each other and the sum over eight wavefronts' tiles is the same
+//     for one record as for a hundred, so a few records do not pay (65536 x 96 FP5.33 M = 4 0.83 x, x 1152 0.96 x), and where
 //     the scales push the kernel beyond 128 registers the two workgroups take turns (65536 x 128 FP4.25 0.61 x, x 1024
 //     0.87 x; FP4 0.57 x, 0.80 x); with more than one round of workgroups the turns fill each other's gaps earlier.
+//     M <= 2 and 5 to 8 where it is taken: 96-weight records 1.06-1.13 x, FP4.25 1.10 x, 0.96 x at worst.
 bool halved_is_faster(int fmt, int M, int64_t n_strips, int spw, int n_rec, bool one_scale) {
-  const int sg = ams::side_group(ams::kFormats[fmt]);
-  const bool one_round = n_strips <= 16 * kNumCU;
-  if (M <= (one_scale && sg == 1 ? 8 : 2)) return false;
-  if (M > 4) return n_rec >= (M > 16 && one_round ? 80 : 64);
-  if (one_scale) return sg != 2 || (one_round ? n_rec % 4 != 2 || n_rec >= 24 : n_rec > 2);
-  const int half = (spw + 1) / 2;
-  if (slice_two_fit(fmt, half)) return n_rec >= (one_round && half > 5 ? 16 : 3);
-  return n_rec >= (!one_round ? 32 : half == kSliceMaxStrips && fmt != FMT_FP425 ? 64 : 24);
+  const int sg = ams::side_group(ams::kFormats[fmt]), half = (spw + 1) / 2;
+  const bool one_round = n_strips <= 16 * kNumCU, rec96 = ams::kFormats[fmt].rec_k == 96;
+  if (M > 8) return n_rec >= (M > 16 && one_round ? 80 : 64);
+  if (one_scale && sg == 1) {
+    const int last = (int)((n_strips + spw - 1) / spw % kNumCU);  // workgroups of the last round
+    return n_rec >= 3 && (one_round ? spw <= 10 : last > 0 && last <= kNumCU / 2);
+  }
+  if (one_scale) {
+    if (sg == 2 && (one_round ? n_rec % 4 == 2 && n_rec < 24 : n_rec <= 2)) return false;
+    return M > 1 || !one_round || n_rec < 64;
+  }
+  if (M == 3 || M == 4) {
+    if (slice_two_fit(fmt, half)) return n_rec >= (one_round && half > 5 ? 16 : 3);
+    return n_rec >= (!one_round ? 32 : half == kSliceMaxStrips && fmt != FMT_FP425 ? 64 : 24);
+  }
+  if (rec96 || half <= 6) return n_rec >= (one_round && half > 5 ? 24 : M > 4 ? 8 : 3);
+  return half < kSliceMaxStrips ? n_rec >= 24 : fmt == FMT_FP425 && n_rec >= 64;
 }
 
 // Long K at M <= 2, where both kernels live on the bytes in flight: column_kernel has sixteen wavefronts on one, two and
