@@ -1426,13 +1426,17 @@ bool short_slices_on_column(int fmt, int M, int spw, int gk, int n_rec_all) {
 // line out of L2 comes quicker than one out of memory); fitted to 108 shapes.  One scale per run costs every strip another 384
 // bytes' worth (4608 x 2368 FP5.33 M = 16 5.47 / 5.71, FP4.25 5888 x 22656 26.7 / 27.9).  us, one / two tiles: 4096 x 14336 FP4.25 M = 32
 // 20.3 / 16.4, M = 24 17.8 / 16.3, M = 16 13.9 / 13.2, M = 12 12.5 / 12.7; FP5.33 M = 32 22.6 / 18.3; 8192 x 8192 M = 32 15.7 / 14.5,
-// M = 16 11.7 / 12.9; 14336 x 4096 M = 32 12.9 / 13.1; 2560 x 9728 M = 24 12.8 / 11.1, three tiles 9.6.  Tiles of fewer than eight rows never
-// pay (2419 x 20352 FP5.33 M = 12 16.9, three tiles 19.2).  At 16 rows
+// M = 16 11.7 / 12.9; 14336 x 4096 M = 32 12.9 / 13.1; 2560 x 9728 M = 24 12.8 / 11.1, three tiles 9.6.  Tiles of fewer than eight rows
+// do not pay where they cost strips (2419 x 20352 FP5.33 M = 12 16.9, three tiles 19.2).  At 16 rows
 // a second strip costs FP6, and FP4.33 up to 32 records (with a scale per run 96), what the rows save (one / two tiles: 2739 x 1920
 // FP6 4.2 / 4.5, 2155 x 2776 FP4.33 with a scale per run 5.1 / 5.5; 129 to 256 strips 0.90-0.98 x); on up to 128 strips they
-// take none and are dealt.  With fewer than 18 records, two for a wavefront, the plans stay as they were before the rows were dealt;
-// the line is not where the two meet: over 15500 such shapes dealing is 1.03-1.07 x at 16 rows and 1.12-1.17 x beyond on 5 to 17
-// records, 0.99-1.06 x on 2 to 4.
+// take none and are dealt.  With fewer than 18 records, two for a wavefront, plans with 129 strips and more stay as they were before the
+// rows were dealt; the line is not where the two meet: over 15500 such shapes dealing is 1.03-1.07 x at 16 rows and 1.12-1.17 x beyond on
+// 5 to 17 records, 0.99-1.06 x on 2 to 4.
+// Up to 128 strips (two tiles, 80 three, 64 four) the tiles go to compute units that have nothing to do otherwise: from five rows
+// on, tiles of four rows and more (us, undealt / dealt: 1024 x 14336 FP4.25 M = 8 8.3 / 7.0, M = 12 10.3 / 7.3, M = 16 two tiles 8.2 / four
+// 7.4; 2048 x 9728 FP5.33 M = 12 8.6 / 7.1; 2048 x 1024 FP4.25 M = 32 3.8 / 3.1; 32000 shapes of M = 5 to 32 1.08 x, 1.1-1.5 x beyond 64
+// records), but for tiles of five to eight rows on up to eight records at M <= 16 (0.96-0.99 x).
 constexpr int64_t kSplitMaxStrips = 16384;  // strips that the counters of a split of K have room for
 struct RowSplit {
   int strips, positions;  // strips per workgroup; workgroups of one tile: whole groups of eight, so that the tiles of a position meet on one XCD
@@ -1526,14 +1530,21 @@ ColumnPlan plan_from(ColumnPlan p, int fmt, int M, int64_t n_strips, int n_rec_a
   if (M >= 2 * kRowSplitMinRows && n_rec_all / gk >= kRowSplitMinRecords && n_strips <= kSplitMaxStrips / kMaxRowTiles) {
     const bool costly_strip = gk == 1 && ((one_scale && fmt == FMT_FP6) || (fmt == FMT_FP433 && n_rec_all <= (one_scale ? 32 : 96)));
     double best = 0.97 * row_split_cost(fmt, p.spw, M, one_scale);
-    for (int t = 2; t <= kMaxRowTiles && t * kRowSplitMinRows <= M; t++) {
+    const int one_strip = gk == 1 ? p.spw : 0;
+    for (int t = 2; t <= kMaxRowTiles; t++) {
       const RowSplit s = row_split(fmt, M, n_strips, gk, t, one_scale);
       if (s.strips > kSliceMaxStrips || s.cost >= best || (M <= 16 && s.strips > p.spw && costly_strip)) continue;
+      if (t * kRowSplitMinRows > M && (s.strips > 1 || one_strip != 1)) continue;
       best = s.cost;
       p.row_tiles = t;
       p.spw = s.strips;
       p.gn = (int)((n_strips + s.strips - 1) / s.strips);
       p.grid = s.positions * t;
+    }
+  } else if (gk == 1 && p.spw == 1) {
+    for (int t = std::min(kMaxRowTiles, (M + 3) / 4); t > 1 && p.row_tiles == 1; t--) {
+      const RowSplit s = row_split(fmt, M, n_strips, gk, t, one_scale);
+      if (s.strips == 1 && (M > 16 || (M + t - 1) / t <= 4 || n_rec_all > 8)) p.row_tiles = t, p.grid = s.positions * t;
     }
   }
   p.slice = true;
@@ -1623,9 +1634,10 @@ int cheapest_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int r
 }
 
 // Time of a plan in us, slices with aligned rows: the bytes of row_split_cost at 47 KB a microsecond, the sum over the
-// wavefronts' tiles, and for a split the exchange.  Fitted to 197 shapes with and without their split (9 % r.m.s.).
+// wavefronts' tiles, and for a split the exchange.  Fitted to 197 shapes with and without their split (9 % r.m.s.), none of them
+// with tiles of fewer than eight rows, which count as undealt.
 double plan_time(const ColumnPlan& p, int fmt, int M, int n_rec) {
-  const int rows = (M + p.row_tiles - 1) / p.row_tiles;
+  const int row_tiles = std::min(p.row_tiles, std::max(1, M / kRowSplitMinRows)), rows = (M + row_tiles - 1) / row_tiles;
   const double tiles = p.spw * rows / 100.0;
   const double t = 2.1 + (n_rec + p.gk - 1) / p.gk * row_split_cost(fmt, p.spw, rows, true) / 46500.0 + 3.25 * tiles;
   return p.gk > 1 ? t + 3.05 - 1.7 * tiles : t;

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("fmt,ofmt", PAIRS)
-@pytest.mark.parametrize("strips,N,Ms", [(2, 16 * 300 - 5, (1, 4)), (1, 16 * 40 - 5, (9, 15))])
+@pytest.mark.parametrize("strips,N,Ms", [(2, 16 * 300 - 5, (1, 4)), (1, 16 * 140 - 5, (9, 15))])
 def test_records_around_the_streaming_wavefronts(fmt, ofmt, strips, N, Ms):
     for n_rec in (11, 12, 13, 24, 25):
         K = REC_K[fmt] * n_rec - 8 * (n_rec % 3)
