@@ -1,0 +1,81 @@
+// The calls of the Linear from Python in one native function: what `ams_linear` and its variants in __init__.py check of their
+// tensors, the current stream and the call of libams.so, with the interpreter left out.  An eager call of 256 x 768 is bound
+// by this (the kernel takes 2.3 us).  It takes plain tensors and integers and answers None to everything else, and to a call that the library
+// refuses: the caller then goes the long way, which raises what there is to raise.
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPStream.h>
+
+#include "../../include/ams.h"
+
+namespace {
+
+// A plain strided tensor on the GPU: no subclass, no wrapper of a transformation, no view that needs resolving.
+const at::Tensor* plain(PyObject* o, c10::ScalarType type) {
+  if (!THPVariable_CheckExact(o)) return nullptr;
+  const at::Tensor& t = THPVariable_Unpack(o);
+  if (!t.defined()) return nullptr;
+  constexpr auto ordinary =
+      c10::DispatchKeySet({c10::DispatchKey::CUDA, c10::DispatchKey::ADInplaceOrView, c10::DispatchKey::AutogradCUDA, c10::DispatchKey::AutocastCUDA});
+  if ((t.key_set().raw_repr() & ~ordinary.raw_repr()) != 0 || !t.is_cuda() || t.scalar_type() != type || !t.is_contiguous()) return nullptr;
+  return &t;
+}
+
+bool whole(PyObject* o, int64_t* v) {
+  if (!PyLong_CheckExact(o)) return false;
+  int overflow = 0;
+  *v = PyLong_AsLongLongAndOverflow(o, &overflow);
+  return !overflow;
+}
+
+enum Entry { kPlain, kWorkspace, kStatic, kGrouped };
+
+// linear(entry, W_packed, scales, X, N, fmt, out, workspace or scale_group): out, or None.
+PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) try {
+  int64_t entry = 0, N = 0, fmt = 0, group = 0;
+  if (n != 8 || !whole(a[0], &entry) || !whole(a[4], &N) || !whole(a[5], &fmt)) Py_RETURN_NONE;
+  if (at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set()) Py_RETURN_NONE;
+  const at::Tensor *W = plain(a[1], at::kByte), *scales = plain(a[2], at::kHalf), *X = plain(a[3], at::kHalf), *out = plain(a[6], at::kHalf);
+  if (!W || !scales || !X || !out || X->dim() != 2 || fmt < 0 || fmt > 0x7FFF) Py_RETURN_NONE;
+  const int64_t M = X->size(0), K = X->size(1);
+  if (M > AMS_MAX_M) Py_RETURN_NONE;
+  size_t bytes = 0, count = 0;
+  if (ams_packed_bytes((int)fmt, N, K, &bytes) != AMS_OK || (size_t)W->numel() != bytes) Py_RETURN_NONE;
+  const at::Tensor* workspace = nullptr;
+  if (entry == kGrouped) {
+    if (!whole(a[7], &group) || ams_group_scales_count((int)fmt, N, K, group, &count) != AMS_OK || (size_t)scales->numel() != count) Py_RETURN_NONE;
+  } else {
+    if (scales->numel() != N) Py_RETURN_NONE;
+    if (entry == kWorkspace && a[7] != Py_None && !(workspace = plain(a[7], at::kByte))) Py_RETURN_NONE;
+  }
+  const void* const w = W->const_data_ptr();
+  const auto* const s = (const uint16_t*)scales->const_data_ptr();
+  const auto* const x = (const uint16_t*)X->const_data_ptr();
+  auto* const y = (uint16_t*)out->data_ptr();
+  void* const ws = workspace ? workspace->data_ptr() : nullptr;
+  const size_t ws_bytes = workspace ? (size_t)workspace->numel() : 0;
+  void* const stream = (void*)c10::hip::getCurrentHIPStream().stream();  // of the current device
+  int rc = -1;
+  Py_BEGIN_ALLOW_THREADS;
+  switch (entry) {
+    case kPlain: rc = ams_linear(w, s, x, y, (int)M, N, K, (int)fmt, stream); break;
+    case kWorkspace: rc = ams_linear_ws(w, s, x, y, (int)M, N, K, (int)fmt, ws, ws_bytes, stream); break;
+    case kStatic: rc = ams_linear_static_ws(w, s, x, y, (int)M, N, K, (int)fmt, stream); break;
+    case kGrouped: rc = ams_linear_grouped(w, s, group, x, y, (int)M, N, K, (int)fmt, stream); break;
+  }
+  Py_END_ALLOW_THREADS;
+  if (rc != AMS_OK) Py_RETURN_NONE;
+  Py_INCREF(a[6]);
+  return a[6];
+} catch (...) {  // torch's own checks; the long way meets them again
+  Py_RETURN_NONE;
+}
+
+PyMethodDef methods[] = {{"linear", (PyCFunction)(void (*)(void))linear, METH_FASTCALL, nullptr}, {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&module); }

@@ -1,0 +1,136 @@
+"""The eager calls of the Linear in native code (csrc/ams_binding.cpp) against the same calls in Python: results, the stream they
+go to, and everything that is not a plain tensor or an int or that is wrong, which takes the long way and raises there."""
+
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2510_16045_amd as ams
+
+torch = pytest.importorskip("torch")
+
+
+def native(*a):
+    from paper_2510_16045_amd import _binding
+
+    return _binding.linear(*a)
+
+
+def long_way(monkeypatch):
+    monkeypatch.setattr(ams, "_call", lambda *a: None)
+
+
+def test_what_is_not_on_the_gpu_or_no_tensor_is_left_alone():
+    u8, f16 = torch.zeros(ams.ams_packed_bytes(ams.FP425, 16, 128), dtype=torch.uint8), torch.zeros(16, dtype=torch.float16)
+    x, y = torch.zeros((2, 128), dtype=torch.float16), torch.zeros((2, 16), dtype=torch.float16)
+    for entry in range(4):
+        assert native(entry, u8, f16, x, 16, ams.FP425, y, 128) is None
+        assert native(entry, None, f16, x, 16, ams.FP425, y, None) is None
+        assert native(entry, u8, f16, x, 16.0, ams.FP425, y, None) is None
+    assert native() is None and native(0, u8) is None and native("0", u8, f16, x, 16, ams.FP425, y, None) is None
+    with pytest.raises(ValueError):
+        ams.ams_linear(u8, f16, x, 16, ams.FP425, out=y)
+
+
+@pytest.fixture
+def problem():
+    def make(M=3, N=300, K=520, fmt=ams.FP425, group=128):
+        rng = np.random.default_rng(4)
+        codes = (rng.integers(0, 32, size=(N, K), dtype=np.uint8) & 0xFE) | 1
+        W = torch.from_numpy(ams.ams_pack_codes(fmt, codes)).cuda()
+        gen = torch.Generator(device="cuda").manual_seed(5)
+        X = torch.randn((M, K), generator=gen, device="cuda").half()
+        run = torch.rand(ams.ams_group_scales_count(fmt, N, K, group), generator=gen, device="cuda").half()
+        ws = torch.zeros(max(16, ams.ams_linear_workspace_bytes(fmt, M, N, K)), dtype=torch.uint8, device="cuda")
+        scales = torch.rand(N, generator=gen, device="cuda").half()
+        return W, scales, run, X, N, fmt, ws, group
+
+    return make
+
+
+def calls(p):
+    W, scales, run, X, N, fmt, ws, group = p
+    return {
+        "plain": lambda out: ams.ams_linear(W, scales, X, N, fmt, out=out),
+        "ws": lambda out: ams.ams_linear_ws(W, scales, X, N, fmt, ws, out=out),
+        "no ws": lambda out: ams.ams_linear_ws(W, scales, X, N, fmt, None, out=out),
+        "static": lambda out: ams.ams_linear_static_ws(W, scales, X, N, fmt, out=out),
+        "grouped": lambda out: ams.ams_linear_grouped(W, run, group, X, N, fmt, out=out),
+    }
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [dict(), dict(M=32, N=256, K=14336), dict(M=1, N=5, K=7), dict(M=8, N=4096, K=12808)])
+def test_results_are_the_long_ways(monkeypatch, problem, shape):
+    p = problem(**shape)
+    M, N = p[3].shape[0], p[4]
+    got = {}
+    for name, call in calls(p).items():
+        out = torch.full((M, N), 9.0, dtype=torch.float16, device="cuda")
+        assert call(out) is out
+        got[name] = out
+    assert native(0, p[0], p[1], p[3], p[4], p[5], got["plain"], None) is got["plain"]  # the native way is the one taken
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        on_side = calls(p)["plain"](torch.empty_like(got["plain"]))
+    side.synchronize()
+    graph, captured = torch.cuda.CUDAGraph(), torch.zeros_like(got["plain"])
+    with torch.cuda.graph(graph):
+        calls(p)["plain"](captured)
+    for _ in range(3):
+        captured.zero_()
+        graph.replay()
+        assert torch.equal(captured, got["plain"])
+    long_way(monkeypatch)
+    for name, call in calls(p).items():
+        assert torch.equal(call(torch.empty_like(got[name])), got[name]), name
+        assert torch.equal(call(None), got[name]), name
+    assert torch.equal(on_side, got["plain"])
+
+
+@pytest.mark.gpu
+def test_what_is_wrong_raises_as_before(monkeypatch, problem):
+    W, scales, run, X, N, fmt, ws, group = problem()
+    out = torch.empty((X.shape[0], N), dtype=torch.float16, device="cuda")
+    wrong = [
+        (W[:-1], scales, X, N, fmt, out), (W.view(torch.int8), scales, X, N, fmt, out), (W, scales[:-1], X, N, fmt, out), (W, scales.float(), X, N, fmt, out),
+        (W, scales, X.float(), N, fmt, out), (W, scales, X.t().contiguous().t(), N, fmt, out), (W, scales, X[0], N, fmt, out), (W, scales, X.cpu(), N, fmt, out),
+        (W, scales, X, float(N), fmt, out), (W, scales, X, N, 99, out), (W, scales, X, -N, fmt, out), (W, scales, X, N, fmt, out.t()), (W, scales, X, N, fmt, out.float()),
+        (W, scales, X.repeat(20, 1), N, fmt, out), (W, scales, X, 1 << 70, fmt, out), (None, scales, X, N, fmt, out), (W, scales, X, N, fmt, "out"),
+    ]
+
+    def outcome(args):
+        try:
+            ams.ams_linear(*args[:5], out=args[5])
+        except (Exception, ctypes.ArgumentError) as e:
+            return type(e), str(e)
+        return None
+
+    first = [outcome(a) for a in wrong]
+    assert all(first), first
+    long_way(monkeypatch)
+    assert [outcome(a) for a in wrong] == first
+
+
+@pytest.mark.gpu
+def test_other_tensors_take_the_long_way(problem):
+    W, scales, run, X, N, fmt, ws, group = problem()
+    out = torch.empty((X.shape[0], N), dtype=torch.float16, device="cuda")
+
+    class Sub(torch.Tensor):
+        pass
+
+    assert native(0, W, scales, X.as_subclass(Sub), N, fmt, out, None) is None
+    assert torch.equal(ams.ams_linear(W, scales, X.as_subclass(Sub), N, fmt, out=out), ams.ams_linear(W, scales, X, N, fmt))
+    assert native(0, W, torch.nn.Parameter(scales), X, N, fmt, out, None) is out
+    seen = []
+
+    def wrapped(x):
+        seen.append(native(0, W, scales, x, N, fmt, out, None))
+        return x
+
+    torch.vmap(wrapped)(X.expand(2, *X.shape).contiguous())
+    torch.func.jvp(wrapped, (X,), (X,))
+    assert seen == [None, None]
