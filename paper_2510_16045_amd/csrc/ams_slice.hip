@@ -87,7 +87,7 @@ struct Slice {
 // RAGGED: rows of X that are not 16-byte aligned (K no multiple of 8) cannot be copied straight into LDS: they are loaded
 // one record ahead into registers, 16 unaligned bytes per lane, and written to the wave's own LDS when their record
 // begins.  Tiles of up to eight rows and up to four strips, sixteen wavefronts.  us, column_kernel (staged by the workgroup) / here:
-// 11003 x 4099 FP5.33 M = 5 10.6 / 8.1, 8192 x 8193 FP4.25 M = 4 12.6 / 9.3, 4096 x 14337 M = 32 47.7 / 20.2.
+// 11003 x 4099 FP5.33 M = 5 10.6 / 8.1, 8192 x 8193 FP4.25 M = 4 12.6 / 9.3, 4096 x 14337 M = 32 47.7 / 22.5.
 template <int FMT, int R, int NS, int VAR>
 __global__ void __launch_bounds__((Slice<FMT, R, NS, VAR>::THREADS)) slice_kernel(u4 head0, u4 head1, u4 head2, u2 head3, SliceArgs a) {
   const uint8_t* const W = (const uint8_t*)pointer_of(head0[0], head0[1]);
