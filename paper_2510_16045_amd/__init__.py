@@ -197,13 +197,14 @@ def _bind_call():
     try:
         import torch  # noqa: F401  (its libraries first)
 
-        from ._binding import linear
+        from . import _binding
     except ImportError:
 
-        def linear(*args):
-            return None
-
-    _call = linear
+        _call = lambda *args: None
+        return
+    lib = load_library()
+    _binding.bind(*(ctypes.cast(f, _vp).value for f in (lib.ams_packed_bytes, lib.ams_group_scales_count, lib.ams_linear, lib.ams_linear_ws, lib.ams_linear_static_ws, lib.ams_linear_grouped)))
+    _call = _binding.linear
 
 
 _PLAIN, _WORKSPACE, _STATIC, _GROUPED = range(4)  # of csrc/ams_binding.cpp

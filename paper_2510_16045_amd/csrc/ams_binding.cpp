@@ -2,11 +2,16 @@
 // tensors, the current stream and the call of libams.so, with the interpreter left out.  An eager call of 256 x 768 is bound
 // by this (the kernel takes 2.3 us).  It takes plain tensors and integers and answers None to everything else, and to a call that the library
 // refuses: the caller then goes the long way, which raises what there is to raise.
+//
+// It is not linked to libams.so but given the addresses of the entry points of the one that the package has loaded: a path or a
+// name in the dynamic section could find another tree's.
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
+
+#include <string.h>
 
 #include "../../include/ams.h"
 
@@ -32,20 +37,46 @@ bool whole(PyObject* o, int64_t* v) {
 
 enum Entry { kPlain, kWorkspace, kStatic, kGrouped };
 
+// The entry points that are called, in the order in which bind() takes them.
+struct Library {
+  decltype(&ams_packed_bytes) packed_bytes;
+  decltype(&ams_group_scales_count) group_scales_count;
+  decltype(&ams_linear) linear;
+  decltype(&ams_linear_ws) linear_ws;
+  decltype(&ams_linear_static_ws) linear_static_ws;
+  decltype(&ams_linear_grouped) linear_grouped;
+} lib;
+
+// bind(address of each entry point of Library)
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  void* at[6];
+  if (n != 6) return PyErr_Format(PyExc_TypeError, "bind takes 6 addresses");
+  for (int i = 0; i < 6; i++)
+    if (!(at[i] = PyLong_AsVoidPtr(a[i]))) return PyErr_Occurred() ? nullptr : PyErr_Format(PyExc_ValueError, "no address");
+  static_assert(sizeof lib == sizeof at, "one address for each");
+  memcpy(&lib, at, sizeof lib);
+  Py_RETURN_NONE;
+}
+
+struct WithoutInterpreterLock {  // taken again on every way out
+  PyThreadState* const state = PyEval_SaveThread();
+  ~WithoutInterpreterLock() { PyEval_RestoreThread(state); }
+};
+
 // linear(entry, W_packed, scales, X, N, fmt, out, workspace or scale_group): out, or None.
 PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) try {
   int64_t entry = 0, N = 0, fmt = 0, group = 0;
-  if (n != 8 || !whole(a[0], &entry) || !whole(a[4], &N) || !whole(a[5], &fmt)) Py_RETURN_NONE;
+  if (!lib.linear || n != 8 || !whole(a[0], &entry) || !whole(a[4], &N) || !whole(a[5], &fmt)) Py_RETURN_NONE;
   if (at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set()) Py_RETURN_NONE;
   const at::Tensor *W = plain(a[1], at::kByte), *scales = plain(a[2], at::kHalf), *X = plain(a[3], at::kHalf), *out = plain(a[6], at::kHalf);
   if (!W || !scales || !X || !out || X->dim() != 2 || fmt < 0 || fmt > 0x7FFF) Py_RETURN_NONE;
   const int64_t M = X->size(0), K = X->size(1);
   if (M > AMS_MAX_M) Py_RETURN_NONE;
   size_t bytes = 0, count = 0;
-  if (ams_packed_bytes((int)fmt, N, K, &bytes) != AMS_OK || (size_t)W->numel() != bytes) Py_RETURN_NONE;
+  if (lib.packed_bytes((int)fmt, N, K, &bytes) != AMS_OK || (size_t)W->numel() != bytes) Py_RETURN_NONE;
   const at::Tensor* workspace = nullptr;
   if (entry == kGrouped) {
-    if (!whole(a[7], &group) || ams_group_scales_count((int)fmt, N, K, group, &count) != AMS_OK || (size_t)scales->numel() != count) Py_RETURN_NONE;
+    if (!whole(a[7], &group) || lib.group_scales_count((int)fmt, N, K, group, &count) != AMS_OK || (size_t)scales->numel() != count) Py_RETURN_NONE;
   } else {
     if (scales->numel() != N) Py_RETURN_NONE;
     if (entry == kWorkspace && a[7] != Py_None && !(workspace = plain(a[7], at::kByte))) Py_RETURN_NONE;
@@ -58,14 +89,15 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) try {
   const size_t ws_bytes = workspace ? (size_t)workspace->numel() : 0;
   void* const stream = (void*)c10::hip::getCurrentHIPStream().stream();  // of the current device
   int rc = -1;
-  Py_BEGIN_ALLOW_THREADS;
-  switch (entry) {
-    case kPlain: rc = ams_linear(w, s, x, y, (int)M, N, K, (int)fmt, stream); break;
-    case kWorkspace: rc = ams_linear_ws(w, s, x, y, (int)M, N, K, (int)fmt, ws, ws_bytes, stream); break;
-    case kStatic: rc = ams_linear_static_ws(w, s, x, y, (int)M, N, K, (int)fmt, stream); break;
-    case kGrouped: rc = ams_linear_grouped(w, s, group, x, y, (int)M, N, K, (int)fmt, stream); break;
+  {
+    const WithoutInterpreterLock unlocked;
+    switch (entry) {
+      case kPlain: rc = lib.linear(w, s, x, y, (int)M, N, K, (int)fmt, stream); break;
+      case kWorkspace: rc = lib.linear_ws(w, s, x, y, (int)M, N, K, (int)fmt, ws, ws_bytes, stream); break;
+      case kStatic: rc = lib.linear_static_ws(w, s, x, y, (int)M, N, K, (int)fmt, stream); break;
+      case kGrouped: rc = lib.linear_grouped(w, s, group, x, y, (int)M, N, K, (int)fmt, stream); break;
+    }
   }
-  Py_END_ALLOW_THREADS;
   if (rc != AMS_OK) Py_RETURN_NONE;
   Py_INCREF(a[6]);
   return a[6];
@@ -73,7 +105,9 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) try {
   Py_RETURN_NONE;
 }
 
-PyMethodDef methods[] = {{"linear", (PyCFunction)(void (*)(void))linear, METH_FASTCALL, nullptr}, {nullptr, nullptr, 0, nullptr}};
+PyMethodDef methods[] = {{"bind", (PyCFunction)(void (*)(void))bind, METH_FASTCALL, nullptr},
+                         {"linear", (PyCFunction)(void (*)(void))linear, METH_FASTCALL, nullptr},
+                         {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

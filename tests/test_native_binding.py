@@ -2,6 +2,10 @@
 go to, and everything that is not a plain tensor or an int or that is wrong, which takes the long way and raises there."""
 
 import ctypes
+import os
+import shutil
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -31,6 +35,28 @@ def test_what_is_not_on_the_gpu_or_no_tensor_is_left_alone():
     assert native() is None and native(0, u8) is None and native("0", u8, f16, x, 16, ams.FP425, y, None) is None
     with pytest.raises(ValueError):
         ams.ams_linear(u8, f16, x, 16, ams.FP425, out=y)
+
+
+def in_a_copy(tmp_path, code, spoil=None):
+    """Runs code in a process of its own with a copy of the built package, from which `spoil` may take or change something."""
+    package = tmp_path / "paper_2510_16045_amd"
+    shutil.copytree(os.path.dirname(ams.__file__), package, ignore=shutil.ignore_patterns("__pycache__"))
+    if spoil:
+        spoil(package)
+    run = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, env={**os.environ, "PYTHONPATH": str(tmp_path)}, capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, run.stderr
+    return run.stdout
+
+
+def test_a_copy_of_the_package_calls_its_own_library(tmp_path):
+    code = """
+import paper_2510_16045_amd as ams
+ams._bind_call()
+from paper_2510_16045_amd import _binding
+assert ams._call is _binding.linear
+print(*sorted({line.split()[-1] for line in open("/proc/self/maps") if "libams" in line}))
+"""
+    assert in_a_copy(tmp_path, code).split() == [str(tmp_path / "paper_2510_16045_amd" / "libams.so")]
 
 
 @pytest.fixture
