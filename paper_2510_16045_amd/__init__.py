@@ -2,8 +2,8 @@
 
 Argument marshalling only (of the Linear's eager calls in native code, csrc/ams_binding.cpp): every step of the path
 (quantize, pack, restore, multiply) runs inside the C-ABI library declared in include/ams.h.  PyTorch is used for device
-memory and streams.  There is no fallback: if the library has not been built
-(``python __graft_entry__.py``) every call raises.
+memory and streams.  If the library has not been built (``python __graft_entry__.py``) every call raises; without the
+native binding, which needs torch's headers, the same calls go through ctypes.
 """
 
 from __future__ import annotations
@@ -12,6 +12,7 @@ import ctypes
 import functools
 import os
 import sys
+import warnings
 
 import numpy as np
 
@@ -90,7 +91,7 @@ def ams_version() -> int:
 def ams_init() -> None:
     """Check the current device and raise the kernels' LDS limits (needed only before a first call under stream capture)."""
     _check(load_library().ams_init(), "ams_init")
-    if "torch" in sys.modules:
+    if "torch" in sys.modules and _call is _first_call:
         _bind_call()
 
 
@@ -184,23 +185,31 @@ def _stream():
     return _current_stream()
 
 
-def _call(*args):
+def _first_call(*args):
     """One of the calls of the Linear below in native code (csrc/ams_binding.cpp): the same checks, stream and library.  None, and nothing
     done, for arguments that are not plain tensors and ints or that something is wrong with: those go the long way, which raises.
-    A whole call of ams_linear takes 3.1 us with it and 5.3 without.  This one stands in until ams_init or the first call."""
+    A whole call of ams_linear(..., out=...) takes 3.1 us with it and 5.3 without; calls that allocate their output don't ask it.
+    This one stands in until ams_init or the first call."""
     _bind_call()
     return _call(*args)
 
 
+_call = _first_call
+
+
 def _bind_call():
     global _call
+    _call = lambda *args: None  # the long way
     try:
         import torch  # noqa: F401  (its libraries first)
-
-        from . import _binding
     except ImportError:
-
-        _call = lambda *args: None
+        return
+    if not any(name.startswith("_binding.") and name.endswith(".so") for name in os.listdir(os.path.dirname(_LIB_PATH))):
+        return  # a package without it is whole
+    try:
+        from . import _binding
+    except ImportError as e:
+        warnings.warn(f"calls of the Linear are slower than they need be: {e} (build again with `python __graft_entry__.py`)", RuntimeWarning, stacklevel=3)
         return
     lib = load_library()
     _binding.bind(*(ctypes.cast(f, _vp).value for f in (lib.ams_packed_bytes, lib.ams_group_scales_count, lib.ams_linear, lib.ams_linear_ws, lib.ams_linear_static_ws, lib.ams_linear_grouped)))

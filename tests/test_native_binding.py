@@ -59,6 +59,33 @@ print(*sorted({line.split()[-1] for line in open("/proc/self/maps") if "libams" 
     assert in_a_copy(tmp_path, code).split() == [str(tmp_path / "paper_2510_16045_amd" / "libams.so")]
 
 
+BIND_TWICE = """
+import warnings
+import paper_2510_16045_amd as ams
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    ams._call()
+    ams._call()
+print(len(seen), *{w.category.__name__ for w in seen}, ams._call(), *{str(w.message) for w in seen})
+"""
+
+
+def native_files(package):
+    return [f for f in package.iterdir() if f.name.startswith("_binding.") and f.suffix == ".so"]
+
+
+def test_a_binding_that_does_not_load_is_said_once(tmp_path):
+    def spoil(package):
+        for f in native_files(package):
+            f.write_bytes(b"no library")
+
+    assert in_a_copy(tmp_path, BIND_TWICE, spoil).startswith("1 RuntimeWarning None ")
+
+
+def test_a_package_without_the_binding_is_whole(tmp_path):
+    assert in_a_copy(tmp_path, BIND_TWICE, lambda package: [f.unlink() for f in native_files(package)]).split() == ["0", "None"]
+
+
 @pytest.fixture
 def problem():
     def make(M=3, N=300, K=520, fmt=ams.FP425, group=128):
