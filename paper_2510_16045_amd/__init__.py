@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import importlib.machinery
 import os
 import sys
 import warnings
@@ -201,13 +202,17 @@ def _bind_call():
     global _call
     _call = lambda *args: None  # the long way
     try:
-        import torch  # noqa: F401  (its libraries first)
+        import torch  # its libraries first
     except ImportError:
         return
-    if not any(name.startswith("_binding.") and name.endswith(".so") for name in os.listdir(os.path.dirname(_LIB_PATH))):
-        return  # a package without it is whole
+    here = f"{torch.__version__} {torch.version.git_version}"
+    if not any(os.path.exists(os.path.join(os.path.dirname(_LIB_PATH), "_binding" + s)) for s in importlib.machinery.EXTENSION_SUFFIXES):
+        return  # a package without it, or with another Python's, is whole
     try:
         from . import _binding
+
+        if getattr(_binding, "BUILT_FOR", None) != here:  # it reads tensors as that torch lays them out
+            raise ImportError(f"{_binding.__file__} was not built for torch {here}")
     except ImportError as e:
         warnings.warn(f"calls of the Linear are slower than they need be: {e} (build again with `python __graft_entry__.py`)", RuntimeWarning, stacklevel=3)
         return

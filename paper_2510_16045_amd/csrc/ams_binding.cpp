@@ -112,4 +112,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__binding() {
+  PyObject* const m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "BUILT_FOR", AMS_TORCH) != 0) {  // whose tensors it reads
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -82,6 +82,11 @@ def test_a_binding_that_does_not_load_is_said_once(tmp_path):
     assert in_a_copy(tmp_path, BIND_TWICE, spoil).startswith("1 RuntimeWarning None ")
 
 
+def test_a_binding_for_another_torch_is_declined(tmp_path):
+    other = "import torch; torch.version.git_version = 'f' * 40" + BIND_TWICE
+    assert in_a_copy(tmp_path, other).startswith("1 RuntimeWarning None ")
+
+
 def test_a_package_without_the_binding_is_whole(tmp_path):
     assert in_a_copy(tmp_path, BIND_TWICE, lambda package: [f.unlink() for f in native_files(package)]).split() == ["0", "None"]
 
