@@ -91,6 +91,16 @@ def test_a_package_without_the_binding_is_whole(tmp_path):
     assert in_a_copy(tmp_path, BIND_TWICE, lambda package: [f.unlink() for f in native_files(package)]).split() == ["0", "None"]
 
 
+def test_the_library_is_built_where_torch_has_no_headers(monkeypatch):
+    import __graft_entry__ as entry
+
+    ran = []
+    monkeypatch.setattr(entry, "_run", ran.append)
+    monkeypatch.setitem(sys.modules, "torch.utils", None)
+    entry.build()
+    assert any(entry.LIB in cmd for cmd in ran) and not any("ams_binding" in word for cmd in ran for word in cmd)
+
+
 @pytest.fixture
 def problem():
     def make(M=3, N=300, K=520, fmt=ams.FP425, group=128):
