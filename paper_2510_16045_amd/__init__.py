@@ -232,6 +232,12 @@ def _dev_ptr(t, dtype=None):
     return t.data_ptr()
 
 
+def _check_out(out, rows, columns):
+    # the kernels write that many values (a buffer for a larger batch may be given)
+    if out.numel() < rows * columns:
+        raise ValueError(f"out must hold {rows} x {columns} values, it has {out.numel()}")
+
+
 def ams_dequant(fmt: int, W_packed, scales, N: int, K: int, scaled: bool = True, out=None):
     """Restore a packed matrix (uint8 CUDA tensor) to fp16 [N,K] on the GPU."""
     import torch
@@ -240,6 +246,8 @@ def ams_dequant(fmt: int, W_packed, scales, N: int, K: int, scaled: bool = True,
         raise ValueError("packed buffer has the wrong size")
     if out is None:
         out = torch.empty((N, K), dtype=torch.float16, device=W_packed.device)
+    else:
+        _check_out(out, N, K)
     sp = _dev_ptr(scales, torch.float16) if scales is not None else None
     if scales is not None and scales.numel() != N:
         raise ValueError("scales must have N entries")
@@ -261,6 +269,8 @@ def ams_linear(W_packed, scales, X, N: int, fmt: int, out=None):
         raise ValueError("scales must have N entries")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
+    else:
+        _check_out(out, M, N)
     rc = load_library().ams_linear(
         _dev_ptr(W_packed, torch.uint8), _dev_ptr(scales, torch.float16), _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K, fmt, _stream()
     )
@@ -278,6 +288,8 @@ def ams_fp16_linear(W, X, out=None):
         raise ValueError("X and W disagree in K")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
+    else:
+        _check_out(out, M, N)
     rc = load_library().ams_fp16_linear(_dev_ptr(W, torch.float16), _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K, _stream())
     _check(rc, "ams_fp16_linear")
     return out
@@ -323,6 +335,8 @@ def ams_dequant_grouped(fmt: int, W_packed, scales, scale_group: int, N: int, K:
         raise ValueError("scale buffer has the wrong size")
     if out is None:
         out = torch.empty((N, K), dtype=torch.float16, device=W_packed.device)
+    else:
+        _check_out(out, N, K)
     rc = load_library().ams_dequant_grouped(fmt, _dev_ptr(W_packed, torch.uint8), _dev_ptr(scales, torch.float16), scale_group, _dev_ptr(out, torch.float16), N, K, int(scaled), _stream())
     _check(rc, "ams_dequant_grouped")
     return out
@@ -340,6 +354,8 @@ def ams_linear_grouped(W_packed, scales, scale_group: int, X, N: int, fmt: int, 
         raise ValueError("scale buffer has the wrong size")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
+    else:
+        _check_out(out, M, N)
     rc = load_library().ams_linear_grouped(
         _dev_ptr(W_packed, torch.uint8), _dev_ptr(scales, torch.float16), scale_group, _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K, fmt, _stream()
     )
@@ -367,6 +383,8 @@ def ams_linear_ws(W_packed, scales, X, N: int, fmt: int, workspace, out=None):
         raise ValueError("scales must have N entries")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
+    else:
+        _check_out(out, M, N)
     rc = load_library().ams_linear_ws(
         _dev_ptr(W_packed, torch.uint8), _dev_ptr(scales, torch.float16), _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K, fmt,
         _dev_ptr(workspace, torch.uint8) if workspace is not None else None, workspace.numel() if workspace is not None else 0, _stream()
@@ -388,6 +406,8 @@ def ams_linear_static_ws(W_packed, scales, X, N: int, fmt: int, out=None):
         raise ValueError("scales must have N entries")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
+    else:
+        _check_out(out, M, N)
     rc = load_library().ams_linear_static_ws(
         _dev_ptr(W_packed, torch.uint8), _dev_ptr(scales, torch.float16), _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K, fmt, _stream()
     )
@@ -404,6 +424,8 @@ def ams_fp16_linear_ws(W, X, workspace, out=None):
         raise ValueError("X and W disagree in K")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
+    else:
+        _check_out(out, M, N)
     rc = load_library().ams_fp16_linear_ws(
         _dev_ptr(W, torch.float16), _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K,
         _dev_ptr(workspace, torch.uint8) if workspace is not None else None, workspace.numel() if workspace is not None else 0, _stream()

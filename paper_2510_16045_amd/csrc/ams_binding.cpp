@@ -71,7 +71,7 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) try {
   const at::Tensor *W = plain(a[1], at::kByte), *scales = plain(a[2], at::kHalf), *X = plain(a[3], at::kHalf), *out = plain(a[6], at::kHalf);
   if (!W || !scales || !X || !out || X->dim() != 2 || fmt < 0 || fmt > 0x7FFF) Py_RETURN_NONE;
   const int64_t M = X->size(0), K = X->size(1);
-  if (M > AMS_MAX_M) Py_RETURN_NONE;
+  if (M > AMS_MAX_M || N <= 0 || N > (1 << 24) || out->numel() < M * N) Py_RETURN_NONE;
   size_t bytes = 0, count = 0;
   if (lib.packed_bytes((int)fmt, N, K, &bytes) != AMS_OK || (size_t)W->numel() != bytes) Py_RETURN_NONE;
   const at::Tensor* workspace = nullptr;

@@ -101,6 +101,19 @@ def test_the_library_is_built_where_torch_has_no_headers(monkeypatch):
     assert any(entry.LIB in cmd for cmd in ran) and not any("ams_binding" in word for cmd in ran for word in cmd)
 
 
+def test_an_output_that_is_too_small_is_refused():
+    W, scales, x = torch.zeros(ams.ams_packed_bytes(ams.FP425, 16, 128), dtype=torch.uint8), torch.zeros(16, dtype=torch.float16), torch.zeros((2, 128), dtype=torch.float16)
+    small, small_w, w = torch.zeros(31, dtype=torch.float16), torch.zeros((15, 128), dtype=torch.float16), torch.zeros((16, 128), dtype=torch.float16)
+    for call in (
+        lambda: ams.ams_linear(W, scales, x, 16, ams.FP425, out=small), lambda: ams.ams_linear_ws(W, scales, x, 16, ams.FP425, None, out=small),
+        lambda: ams.ams_linear_static_ws(W, scales, x, 16, ams.FP425, out=small), lambda: ams.ams_linear_grouped(W, scales, 128, x, 16, ams.FP425, out=small),
+        lambda: ams.ams_fp16_linear(w, x, out=small), lambda: ams.ams_fp16_linear_ws(w, x, None, out=small),
+        lambda: ams.ams_dequant(ams.FP425, W, scales, 16, 128, out=small_w), lambda: ams.ams_dequant_grouped(ams.FP425, W, scales, 128, 16, 128, out=small_w),
+    ):
+        with pytest.raises(ValueError, match="out must hold"):
+            call()
+
+
 @pytest.fixture
 def problem():
     def make(M=3, N=300, K=520, fmt=ams.FP425, group=128):
@@ -167,6 +180,7 @@ def test_what_is_wrong_raises_as_before(monkeypatch, problem):
         (W, scales, X.float(), N, fmt, out), (W, scales, X.t().contiguous().t(), N, fmt, out), (W, scales, X[0], N, fmt, out), (W, scales, X.cpu(), N, fmt, out),
         (W, scales, X, float(N), fmt, out), (W, scales, X, N, 99, out), (W, scales, X, -N, fmt, out), (W, scales, X, N, fmt, out.t()), (W, scales, X, N, fmt, out.float()),
         (W, scales, X.repeat(20, 1), N, fmt, out), (W, scales, X, 1 << 70, fmt, out), (None, scales, X, N, fmt, out), (W, scales, X, N, fmt, "out"),
+        (W, scales, X, N, fmt, out[:-1]), (W, scales, X, N, fmt, out.flatten()[:-1]),
     ]
 
     def outcome(args):
@@ -176,8 +190,12 @@ def test_what_is_wrong_raises_as_before(monkeypatch, problem):
             return type(e), str(e)
         return None
 
+    assert native(0, W, scales, X, N, fmt, out[:-1], None) is None
     first = [outcome(a) for a in wrong]
     assert all(first), first
+    larger = torch.full((X.shape[0] + 1, N), 9.0, dtype=torch.float16, device="cuda")  # a buffer for a larger batch
+    assert ams.ams_linear(W, scales, X, N, fmt, out=larger) is larger
+    assert torch.equal(larger[:-1], ams.ams_linear(W, scales, X, N, fmt)) and (larger[-1] == 9.0).all()
     long_way(monkeypatch)
     assert [outcome(a) for a in wrong] == first
 
