@@ -224,11 +224,25 @@ def _bind_call():
 _PLAIN, _WORKSPACE, _STATIC, _GROUPED = range(4)  # of csrc/ams_binding.cpp
 
 
+_current_device = None
+
+
+def _device():
+    global _current_device
+    if _current_device is None:
+        import torch
+
+        _current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+    return _current_device()
+
+
 def _dev_ptr(t, dtype=None):
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("expected a contiguous CUDA tensor")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"expected {dtype}, got {t.dtype}")
+    if t.get_device() != _device():  # the kernels run on the current device and in the order of its stream
+        raise ValueError(f"expected a tensor on the current device, cuda:{_device()}, got one on cuda:{t.get_device()}")
     return t.data_ptr()
 
 

@@ -17,14 +17,15 @@
 
 namespace {
 
-// A plain strided tensor on the GPU: no subclass, no wrapper of a transformation, no view that needs resolving.
-const at::Tensor* plain(PyObject* o, c10::ScalarType type) {
+// A plain strided tensor on the current GPU (the kernels run there, in the order of its stream): no subclass, no wrapper of a
+// transformation, no view that needs resolving.
+const at::Tensor* plain(PyObject* o, c10::ScalarType type, c10::DeviceIndex device) {
   if (!THPVariable_CheckExact(o)) return nullptr;
   const at::Tensor& t = THPVariable_Unpack(o);
   if (!t.defined()) return nullptr;
   constexpr auto ordinary =
       c10::DispatchKeySet({c10::DispatchKey::CUDA, c10::DispatchKey::ADInplaceOrView, c10::DispatchKey::AutogradCUDA, c10::DispatchKey::AutocastCUDA});
-  if ((t.key_set().raw_repr() & ~ordinary.raw_repr()) != 0 || !t.is_cuda() || t.scalar_type() != type || !t.is_contiguous()) return nullptr;
+  if ((t.key_set().raw_repr() & ~ordinary.raw_repr()) != 0 || !t.is_cuda() || t.get_device() != device || t.scalar_type() != type || !t.is_contiguous()) return nullptr;
   return &t;
 }
 
@@ -68,7 +69,9 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) try {
   int64_t entry = 0, N = 0, fmt = 0, group = 0;
   if (!lib.linear || n != 8 || !whole(a[0], &entry) || !whole(a[4], &N) || !whole(a[5], &fmt)) Py_RETURN_NONE;
   if (at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set()) Py_RETURN_NONE;
-  const at::Tensor *W = plain(a[1], at::kByte), *scales = plain(a[2], at::kHalf), *X = plain(a[3], at::kHalf), *out = plain(a[6], at::kHalf);
+  const auto stream = c10::hip::getCurrentHIPStream();  // of the current device
+  const c10::DeviceIndex dev = stream.device_index();
+  const at::Tensor *W = plain(a[1], at::kByte, dev), *scales = plain(a[2], at::kHalf, dev), *X = plain(a[3], at::kHalf, dev), *out = plain(a[6], at::kHalf, dev);
   if (!W || !scales || !X || !out || X->dim() != 2 || fmt < 0 || fmt > 0x7FFF) Py_RETURN_NONE;
   const int64_t M = X->size(0), K = X->size(1);
   if (M > AMS_MAX_M || N <= 0 || N > (1 << 24) || out->numel() < M * N) Py_RETURN_NONE;
@@ -79,7 +82,7 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) try {
     if (!whole(a[7], &group) || lib.group_scales_count((int)fmt, N, K, group, &count) != AMS_OK || (size_t)scales->numel() != count) Py_RETURN_NONE;
   } else {
     if (scales->numel() != N) Py_RETURN_NONE;
-    if (entry == kWorkspace && a[7] != Py_None && !(workspace = plain(a[7], at::kByte))) Py_RETURN_NONE;
+    if (entry == kWorkspace && a[7] != Py_None && !(workspace = plain(a[7], at::kByte, dev))) Py_RETURN_NONE;
   }
   const void* const w = W->const_data_ptr();
   const auto* const s = (const uint16_t*)scales->const_data_ptr();
@@ -87,15 +90,15 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) try {
   auto* const y = (uint16_t*)out->data_ptr();
   void* const ws = workspace ? workspace->data_ptr() : nullptr;
   const size_t ws_bytes = workspace ? (size_t)workspace->numel() : 0;
-  void* const stream = (void*)c10::hip::getCurrentHIPStream().stream();  // of the current device
+  void* const st = (void*)stream.stream();
   int rc = -1;
   {
     const WithoutInterpreterLock unlocked;
     switch (entry) {
-      case kPlain: rc = lib.linear(w, s, x, y, (int)M, N, K, (int)fmt, stream); break;
-      case kWorkspace: rc = lib.linear_ws(w, s, x, y, (int)M, N, K, (int)fmt, ws, ws_bytes, stream); break;
-      case kStatic: rc = lib.linear_static_ws(w, s, x, y, (int)M, N, K, (int)fmt, stream); break;
-      case kGrouped: rc = lib.linear_grouped(w, s, group, x, y, (int)M, N, K, (int)fmt, stream); break;
+      case kPlain: rc = lib.linear(w, s, x, y, (int)M, N, K, (int)fmt, st); break;
+      case kWorkspace: rc = lib.linear_ws(w, s, x, y, (int)M, N, K, (int)fmt, ws, ws_bytes, st); break;
+      case kStatic: rc = lib.linear_static_ws(w, s, x, y, (int)M, N, K, (int)fmt, st); break;
+      case kGrouped: rc = lib.linear_grouped(w, s, group, x, y, (int)M, N, K, (int)fmt, st); break;
     }
   }
   if (rc != AMS_OK) Py_RETURN_NONE;

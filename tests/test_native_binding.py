@@ -114,6 +114,20 @@ def test_an_output_that_is_too_small_is_refused():
             call()
 
 
+def test_a_tensor_on_another_device_is_refused(monkeypatch):
+    class There:
+        is_cuda = True
+        is_contiguous = lambda self: True
+        get_device = lambda self: 1
+        data_ptr = lambda self: 4096
+
+    monkeypatch.setattr(ams, "_current_device", lambda: 1, raising=False)
+    assert ams._dev_ptr(There()) == 4096
+    monkeypatch.setattr(ams, "_current_device", lambda: 0, raising=False)
+    with pytest.raises(ValueError, match="current device"):
+        ams._dev_ptr(There())
+
+
 @pytest.fixture
 def problem():
     def make(M=3, N=300, K=520, fmt=ams.FP425, group=128):
