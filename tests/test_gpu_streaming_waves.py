@@ -34,7 +34,7 @@ def test_records_around_the_streaming_wavefronts(fmt, ofmt, strips, N, Ms):
 
 @pytest.mark.parametrize("fmt,ofmt", PAIRS)
 def test_streaming_wavefronts_and_slices_of_k(fmt, ofmt):
-    N, K, M = 507, 14344, 15
+    N, K, M = 507, 16392, 15
     plan = ams.ams_linear_plan(fmt, M, N, K, with_workspace=True)
     assert plan.startswith("slice ") and " strips_per_wg=1 " in plan and "k_slices=1 " not in plan and " waves=16 " in plan, plan
     codes, scales, rows = problem(fmt, ofmt, N, K, 6)
