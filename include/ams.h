@@ -224,8 +224,10 @@ int ams_linear_workspace_bytes(int fmt, int M, int64_t N, int64_t K, size_t* byt
  * workgroup, slices of K, wavefronts, LDS bytes; of the kernels that have them: wavefronts per strip or strips per
  * wavefront, phases of K, whether side groups are dealt whole, records ahead).  In a "slice" plan every wavefront takes
  * its records of K from all strips of the workgroup, so it has no wavefronts per strip, phases or side groups, and
- * `ahead` counts (record, strip) pairs, the most that any kernel of as many wavefronts requests ahead; row_tiles workgroups share the rows of X where it names them.  A slice plan for rows
- * of X that are not 16-byte aligned (K % 8 != 0) names streamed_rows, the rows of a workgroup, and row_tiles.
+ * `ahead` counts the (record, strip) pairs of weights that a wavefront requests ahead.  It names streams where fewer of the
+ * wavefronts than all take records, x_ahead where more than one record of activations is requested ahead, and row_tiles
+ * where as many workgroups share the rows of X.  A slice plan for rows of X that are not 16-byte aligned (K % 8 != 0) names
+ * streamed_rows, the rows of a workgroup, and row_tiles.
  * Host only, launches nothing. */
 int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, char* text, size_t text_len);
 int ams_linear_ws(const void* W_packed, const uint16_t* scales, const uint16_t* X, uint16_t* Y, int M, int64_t N,

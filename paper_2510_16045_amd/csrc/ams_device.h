@@ -376,7 +376,6 @@ constexpr SliceAsk slice_ask(int fmt, int R, int NS, int variant) {
   // and less, M <= 8: 0.99 x before the last strip but one, 1.02 x behind the first).
   return {8, 8, 3, 1, R > 8 ? NS - 2 : NS >= 5 ? 1 : 0};
 }
-constexpr int slice_most_ahead(int waves) { return waves == 16 ? 2 : 3; }  // what a plan names: the most pairs of any kernel with as many wavefronts
 // 1 KiB loads that bring one record's activations
 constexpr int slice_x_loads(int fmt, int R) {
   const int rb = R > 16 ? 16 : R, pieces = (ams::kFormats[fmt].rec_k / 8 + 3) / 4 * 4;

@@ -1241,8 +1241,8 @@ struct ColumnPlan {
   int wpa;  // wavefronts of a strip that take records (= wps unless fewer divide the side groups evenly)
   int lr;   // records a wavefront keeps in flight beside the one it restores
   int ns;   // strips a wavefront owns alone (multi_kernel; 1: column_kernel); then wpa = wavefronts that own strips
-  bool ragged;  // slice_kernel's variant for rows of X that are not 16-byte aligned (with `slice`)
   bool slice;  // slice_kernel: the wavefronts share K and take every record of all spw strips; S, spw, grid, gn, gk, lr and lds hold
+  int variant;  // slice_kernel's
   int rows, row_tiles;  // slice_kernel: staged rows of X per workgroup, workgroups that share the rows
   size_t lds;
 };
@@ -1257,7 +1257,8 @@ ColumnPlan column_plan_for(int S, int lr, int fmt, int M, int64_t n_strips, int 
                            int ns = 1) {
   ColumnPlan p;
   p.ns = ns;
-  p.slice = p.ragged = false;
+  p.slice = false;
+  p.variant = kSlicePlain;
   p.rows = M;
   p.row_tiles = 1;
   const int sg = ams::side_group(ams::kFormats[fmt]);
@@ -1483,6 +1484,17 @@ bool ragged_on_slice(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int
   if (tiles == 2 && strips == kSliceRaggedMaxStrips && gk <= 2 && four_strips_on_column(fmt, M, (n_rec + gk - 1) / gk)) return false;
   return strips <= kSliceRaggedMaxStrips;
 }
+// p on slice_kernel: what its variant of p's strips and row tiles is launched with.
+ColumnPlan slice_plan(ColumnPlan p, int fmt, int M, int variant) {
+  p.slice = true;
+  p.variant = variant;
+  p.rows = slice_rows((M + p.row_tiles - 1) / p.row_tiles);
+  const SliceAsk ask = slice_ask(fmt, p.rows, p.spw, variant);
+  p.S = ask.waves;
+  p.lr = ask.weights;
+  p.lds = (size_t)slice_lds(fmt, p.rows, p.spw, variant);
+  return p;
+}
 ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
   p.row_tiles = ragged_tiles(M);
   if (p.row_tiles > 1) {
@@ -1491,12 +1503,7 @@ ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
     p.gn = (int)((n_strips + p.spw - 1) / p.spw);
     p.grid = s.positions * p.row_tiles;
   }
-  p.slice = p.ragged = true;
-  p.rows = slice_rows((M + p.row_tiles - 1) / p.row_tiles);
-  p.S = slice_ask(fmt, p.rows, p.spw, kSliceRagged).waves;
-  p.lr = slice_most_ahead(p.S);
-  p.lds = (size_t)slice_lds(fmt, p.rows, p.spw, kSliceRagged);
-  return p;
+  return slice_plan(p, fmt, M, kSliceRagged);
 }
 
 // The plan of a problem: slice_kernel where it takes it (aligned_rows: rows of X are 16-byte aligned, K % 8 == 0;
@@ -1547,13 +1554,7 @@ ColumnPlan plan_from(ColumnPlan p, int fmt, int M, int64_t n_strips, int n_rec_a
       if (s.strips == 1 && (M > 16 || (M + t - 1) / t <= 4 || n_rec_all > 8)) p.row_tiles = t, p.grid = s.positions * t;
     }
   }
-  p.slice = true;
-  p.rows = slice_rows((M + p.row_tiles - 1) / p.row_tiles);
-  const int variant = one_scale ? kSlicePlain : kSliceRunScales;
-  p.S = slice_ask(fmt, p.rows, p.spw, variant).waves;
-  p.lr = slice_most_ahead(p.S);
-  p.lds = (size_t)slice_lds(fmt, p.rows, p.spw, variant);
-  return p;
+  return slice_plan(p, fmt, M, one_scale ? kSlicePlain : kSliceRunScales);
 }
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
   const ColumnPlan column = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
@@ -1927,7 +1928,7 @@ int run_linear(const void* W, const uint16_t* scales, const uint16_t* X, uint16_
     a.x_shift = cp.x_shift;
     a.spw = cp.spw;
     a.rc = cp.rc;
-    if (cp.slice) return launch_slice<FMT>(a, scale_group != 0 ? kSliceRunScales : cp.ragged ? kSliceRagged : kSlicePlain, cp.rows, cp.spw, cp.grid, st);
+    if (cp.slice) return launch_slice<FMT>(a, cp.variant, cp.rows, cp.spw, cp.grid, st);
     if (cp.ns > 1) return launch_multi<FMT>(a, cp.grid, cp.S, cp.lds, st);
     return M <= 16 ? launch_column<FMT, 1>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st)
                    : launch_column<FMT, 2>(nt, scale_group != 0, cp.qd, cp.lr, a, cp.grid, cp.S, cp.lds, st);
@@ -2144,13 +2145,19 @@ int ams_linear_plan(int fmt, int M, int64_t N, int64_t K, int with_workspace, ch
     const ColumnPlan cp = make_plan(f, M, n_strips, n_rec, rec_k, gk, K % 8 == 0, !grouped, nt);
     if (cp.slice) {
       const int rows = (M + cp.row_tiles - 1) / cp.row_tiles;
-      const int len = snprintf(text, text_len, "slice grid=%d strips_per_wg=%d k_slices=%d waves=%d lds=%zu ahead=%d", cp.grid, cp.spw, cp.gk, cp.S, cp.lds, cp.lr);
-      if (len > 0 && (size_t)len < text_len) {
-        if (cp.ragged)
-          snprintf(text + len, text_len - len, " streamed_rows=%d row_tiles=%d", rows, cp.row_tiles);
-        else if (cp.row_tiles > 1)
-          snprintf(text + len, text_len - len, " row_tiles=%d rows_per_tile=%d", cp.row_tiles, rows);
-      }
+      const SliceAsk ask = slice_ask(f, cp.rows, cp.spw, cp.variant);
+      size_t len = 0;
+      const auto say = [&](const char* format, auto... v) {
+        const int n = len < text_len ? snprintf(text + len, text_len - len, format, v...) : 0;
+        len += n > 0 ? n : 0;
+      };
+      say("slice grid=%d strips_per_wg=%d k_slices=%d waves=%d lds=%zu ahead=%d", cp.grid, cp.spw, cp.gk, ask.waves, cp.lds, ask.weights);
+      if (ask.streams < ask.waves) say(" streams=%d", ask.streams);
+      if (ask.acts > 1) say(" x_ahead=%d", ask.acts);
+      if (cp.variant == kSliceRagged)
+        say(" streamed_rows=%d row_tiles=%d", rows, cp.row_tiles);
+      else if (cp.row_tiles > 1)
+        say(" row_tiles=%d rows_per_tile=%d", cp.row_tiles, rows);
     } else {
       snprintf(text, text_len, "column grid=%d strips_per_wg=%d k_slices=%d waves=%d waves_per_strip=%d phases=%d lds=%zu side_groups=%d active_per_strip=%d ahead=%d strips_per_wave=%d", cp.grid,
                cp.spw, cp.gk, cp.S, cp.wps, cp.n_phase, cp.lds, cp.qd ? 1 : 0, cp.ns > 1 ? 1 : cp.wpa, cp.lr, cp.ns);

@@ -152,3 +152,22 @@ def test_deep_and_two_strip_plans_stay_where_their_kernels_exist():
             deep += 1
             assert M <= 16 and (fmt in (ams.FP533, ams.FP5, ams.FP4) or (fmt == ams.FP425 and K % 8 and p["side_groups"] == "1")), (fmt, M, N, K, p)
     assert deep > 50 and two > 50
+
+
+@pytest.mark.parametrize(
+    "fmt,M,N,K,asks",
+    [
+        (ams.FP425, 1, 4096, 14336, dict(waves="16", ahead="1")),  # one strip: one record ahead
+        (ams.FP425, 8, 4096, 14336, dict(waves="8", ahead="2", x_ahead="2")),
+        (ams.FP425, 12, 4096, 4096, dict(waves="16", ahead="1", streams="12")),
+        (ams.FP425, 1, 6144, 4096, dict(waves="16", ahead="2", streams="12")),  # two strips
+        (ams.FP533, 1, 6144, 4096, dict(waves="16", ahead="2")),
+        (ams.FP425, 8, 6144, 4096, dict(waves="8", ahead="2")),
+        (ams.FP425, 1, 28672, 4096, dict(waves="8", ahead="3")),
+        (ams.FP425, 3, 6144, 4099, dict(waves="16", ahead="2", streams="12", streamed_rows="3")),  # unaligned rows
+        (ams.FP533, 5, 4096, 4099, dict(waves="16", ahead="1", streamed_rows="5")),
+    ],
+)
+def test_a_slice_plan_says_what_its_kernel_asks_for(fmt, M, N, K, asks):
+    kind, p = plan(fmt, M, N, K)
+    assert kind == "slice" and {k: v for k, v in p.items() if k in ("waves", "ahead", "streams", "x_ahead", "streamed_rows")} == asks, p
