@@ -11,6 +11,7 @@
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 
+#include <cxxabi.h>
 #include <string.h>
 
 #include "../../include/ams.h"
@@ -59,53 +60,77 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Py_RETURN_NONE;
 }
 
-struct WithoutInterpreterLock {  // taken again on every way out
-  PyThreadState* const state = PyEval_SaveThread();
-  ~WithoutInterpreterLock() { PyEval_RestoreThread(state); }
+// What a call of the library takes.
+struct Call {
+  int64_t entry, M, N, K, group;
+  int fmt;
+  const void* w;
+  const uint16_t *s, *x;
+  uint16_t* y;
+  void* ws;
+  size_t ws_bytes;
+  void* st;
 };
 
-// linear(entry, W_packed, scales, X, N, fmt, out, workspace or scale_group): out, or None.
-PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) try {
+// linear's arguments, checked; false for those that are not taken.
+bool arguments(PyObject* const* a, Py_ssize_t n, Call* c) try {
   int64_t entry = 0, N = 0, fmt = 0, group = 0;
-  if (!lib.linear || n != 8 || !whole(a[0], &entry) || !whole(a[4], &N) || !whole(a[5], &fmt)) Py_RETURN_NONE;
-  if (at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set()) Py_RETURN_NONE;
+  if (!lib.linear || n != 8 || !whole(a[0], &entry) || !whole(a[4], &N) || !whole(a[5], &fmt)) return false;
+  if (at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set()) return false;
   const auto stream = c10::hip::getCurrentHIPStream();  // of the current device
   const c10::DeviceIndex dev = stream.device_index();
   const at::Tensor *W = plain(a[1], at::kByte, dev), *scales = plain(a[2], at::kHalf, dev), *X = plain(a[3], at::kHalf, dev), *out = plain(a[6], at::kHalf, dev);
-  if (!W || !scales || !X || !out || X->dim() != 2 || fmt < 0 || fmt > 0x7FFF) Py_RETURN_NONE;
+  if (!W || !scales || !X || !out || X->dim() != 2 || fmt < 0 || fmt > 0x7FFF) return false;
   const int64_t M = X->size(0), K = X->size(1);
-  if (M > AMS_MAX_M || N <= 0 || N > (1 << 24) || out->numel() < M * N) Py_RETURN_NONE;
+  if (M > AMS_MAX_M || N <= 0 || N > (1 << 24) || out->numel() < M * N) return false;
   size_t bytes = 0, count = 0;
-  if (lib.packed_bytes((int)fmt, N, K, &bytes) != AMS_OK || (size_t)W->numel() != bytes) Py_RETURN_NONE;
+  if (lib.packed_bytes((int)fmt, N, K, &bytes) != AMS_OK || (size_t)W->numel() != bytes) return false;
   const at::Tensor* workspace = nullptr;
   if (entry == kGrouped) {
-    if (!whole(a[7], &group) || lib.group_scales_count((int)fmt, N, K, group, &count) != AMS_OK || (size_t)scales->numel() != count) Py_RETURN_NONE;
+    if (!whole(a[7], &group) || lib.group_scales_count((int)fmt, N, K, group, &count) != AMS_OK || (size_t)scales->numel() != count) return false;
   } else {
-    if (scales->numel() != N) Py_RETURN_NONE;
-    if (entry == kWorkspace && a[7] != Py_None && !(workspace = plain(a[7], at::kByte, dev))) Py_RETURN_NONE;
+    if (scales->numel() != N) return false;
+    if (entry == kWorkspace && a[7] != Py_None && !(workspace = plain(a[7], at::kByte, dev))) return false;
   }
-  const void* const w = W->const_data_ptr();
-  const auto* const s = (const uint16_t*)scales->const_data_ptr();
-  const auto* const x = (const uint16_t*)X->const_data_ptr();
-  auto* const y = (uint16_t*)out->data_ptr();
-  void* const ws = workspace ? workspace->data_ptr() : nullptr;
-  const size_t ws_bytes = workspace ? (size_t)workspace->numel() : 0;
-  void* const st = (void*)stream.stream();
+  *c = {entry, M, N, K, group, (int)fmt, W->const_data_ptr(), (const uint16_t*)scales->const_data_ptr(), (const uint16_t*)X->const_data_ptr(), (uint16_t*)out->data_ptr(),
+        workspace ? workspace->data_ptr() : nullptr, workspace ? (size_t)workspace->numel() : 0, (void*)stream.stream()};
+  return true;
+} catch (...) {  // torch's own checks; the long way meets them again
+  return false;
+}
+
+int call(const Call& c) {
+  switch (c.entry) {
+    case kPlain: return lib.linear(c.w, c.s, c.x, c.y, (int)c.M, c.N, c.K, c.fmt, c.st);
+    case kWorkspace: return lib.linear_ws(c.w, c.s, c.x, c.y, (int)c.M, c.N, c.K, c.fmt, c.ws, c.ws_bytes, c.st);
+    case kStatic: return lib.linear_static_ws(c.w, c.s, c.x, c.y, (int)c.M, c.N, c.K, c.fmt, c.st);
+    case kGrouped: return lib.linear_grouped(c.w, c.s, c.group, c.x, c.y, (int)c.M, c.N, c.K, c.fmt, c.st);
+  }
+  return -1;
+}
+
+// The call, with the interpreter's lock given up for it.  It is taken again outside of every try block and destructor: where the
+// interpreter ends meanwhile, pthread_exit ends a daemon thread there by unwinding its stack, and a handler that stops that, or
+// a destructor that it would leave, aborts the process.
+int call_unlocked(const Call& c) {
+  PyThreadState* const state = PyEval_SaveThread();
   int rc = -1;
-  {
-    const WithoutInterpreterLock unlocked;
-    switch (entry) {
-      case kPlain: rc = lib.linear(w, s, x, y, (int)M, N, K, (int)fmt, st); break;
-      case kWorkspace: rc = lib.linear_ws(w, s, x, y, (int)M, N, K, (int)fmt, ws, ws_bytes, st); break;
-      case kStatic: rc = lib.linear_static_ws(w, s, x, y, (int)M, N, K, (int)fmt, st); break;
-      case kGrouped: rc = lib.linear_grouped(w, s, group, x, y, (int)M, N, K, (int)fmt, st); break;
-    }
+  try {
+    rc = call(c);
+  } catch (const abi::__forced_unwind&) {
+    throw;
+  } catch (...) {
   }
-  if (rc != AMS_OK) Py_RETURN_NONE;
+  PyEval_RestoreThread(state);
+  return rc;
+}
+
+// linear(entry, W_packed, scales, X, N, fmt, out, workspace or scale_group): out, or None.
+PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Call c;
+  if (!arguments(a, n, &c) || call_unlocked(c) != AMS_OK) Py_RETURN_NONE;
   Py_INCREF(a[6]);
   return a[6];
-} catch (...) {  // torch's own checks; the long way meets them again
-  Py_RETURN_NONE;
 }
 
 PyMethodDef methods[] = {{"bind", (PyCFunction)(void (*)(void))bind, METH_FASTCALL, nullptr},

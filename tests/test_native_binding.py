@@ -128,6 +128,41 @@ def test_a_tensor_on_another_device_is_refused(monkeypatch):
         ams._dev_ptr(There())
 
 
+def test_a_daemon_thread_in_a_call_ends_with_the_interpreter(tmp_path):
+    # the binding's own code around a library that takes 2 ms for a call: when the interpreter ends, the thread is in one
+    (tmp_path / "in_call.cpp").write_text(f"""
+#include "{os.path.dirname(ams.__file__)}/csrc/ams_binding.cpp"
+#include <unistd.h>
+static PyObject* run(PyObject*, PyObject*) {{
+  lib.linear = [](const void*, const uint16_t*, const uint16_t*, uint16_t*, int, int64_t, int64_t, int, void*) {{ return usleep(2000), (int)AMS_OK; }};
+  return PyLong_FromLong(call_unlocked(Call{{}}));
+}}
+static PyMethodDef only[] = {{{{"run", run, METH_NOARGS, nullptr}}, {{nullptr, nullptr, 0, nullptr}}}};
+static PyModuleDef here = {{PyModuleDef_HEAD_INIT, "in_call", nullptr, -1, only, nullptr, nullptr, nullptr, nullptr}};
+PyMODINIT_FUNC PyInit_in_call() {{ return PyModule_Create(&here); }}
+""")
+    import __graft_entry__ as g
+
+    subprocess.run(g.binding_command(g._hipcc(), g.binding_includes(), str(tmp_path / "in_call.cpp"), str(tmp_path / "in_call.so")), check=True, timeout=300)
+    code = """
+import threading, time, torch, in_call
+
+class Last:  # gone when the interpreter has begun to end
+    def __del__(self, sleep=time.sleep):
+        sleep(0.1)
+
+def calls():
+    while True:
+        assert in_call.run() == 0
+
+last = Last()
+threading.Thread(target=calls, daemon=True).start()
+time.sleep(0.05)
+"""
+    end = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, timeout=300)
+    assert (end.returncode, end.stderr) == (0, "")
+
+
 @pytest.fixture
 def problem():
     def make(M=3, N=300, K=520, fmt=ams.FP425, group=128):
