@@ -1506,6 +1506,18 @@ ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
   return slice_plan(p, fmt, M, kSliceRagged);
 }
 
+// One strip, one scale per row: whether to ask for two records of both ahead (kSliceDeep), not one.
+//   M <= 2, no side groups, fewer workgroups than 7/8 of the compute units, and a stream that is long against its start: the
+//     memory is not what limits them there, every compute unit waits for its own requests.  1500 shapes of 1 to 223 strips 1.035 x
+//     (FP5.33 M = 1 2560 x 24960 11.64 / 11.04 us, 1024 x 18432 8.89 / 8.59; FP4 3520 x 38400 13.70 / 12.76; M = 2 12.24 / 11.83 on
+//     3520 x 24960), at the first percentile 0.988 x; at the lines 1.00-1.01 x.  From 224 strips on 0.90-0.98 x below 128 records;
+//     the longer ones are column_kernel's.  Formats with side groups 0.95-1.03 x.
+bool more_ahead_is_faster(int fmt, int M, int rows, int strips, int grid, int n_rec) {
+  if (!slice_has_deep(fmt, rows, strips)) return false;
+  if (rows == 4) return M <= 2 && grid < kNumCU * 7 / 8 && n_rec >= (fmt == FMT_FP5 ? (M == 1 ? 128 : 240) : (M == 1 ? 96 : 160));
+  return false;
+}
+
 // The plan of a problem: slice_kernel where it takes it (aligned_rows: rows of X are 16-byte aligned, K % 8 == 0;
 // one_scale: one scale per row of W), else make_column_plan's.  slice_kernel is the faster one nearly everywhere
 // (twelve shapes, seven formats, M = 1 .. 32: 1.00-1.8 x); the exceptions, us column / slice:
@@ -1554,7 +1566,8 @@ ColumnPlan plan_from(ColumnPlan p, int fmt, int M, int64_t n_strips, int n_rec_a
       if (s.strips == 1 && (M > 16 || (M + t - 1) / t <= 4 || n_rec_all > 8)) p.row_tiles = t, p.grid = s.positions * t;
     }
   }
-  return slice_plan(p, fmt, M, one_scale ? kSlicePlain : kSliceRunScales);
+  const bool deep = one_scale && gk == 1 && more_ahead_is_faster(fmt, M, slice_rows((M + p.row_tiles - 1) / p.row_tiles), p.spw, p.grid, n_rec_all);
+  return slice_plan(p, fmt, M, deep ? kSliceDeep : one_scale ? kSlicePlain : kSliceRunScales);
 }
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
   const ColumnPlan column = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
@@ -1832,6 +1845,7 @@ template <int FMT>
 int launch_slice(const LinearArgs& a, int variant, int r, int strips, unsigned grid, hipStream_t st) {
   const void* kern = variant == kSliceRunScales ? slice_kernel_of<FMT, kSliceRunScales>(r, strips)
                      : variant == kSliceRagged  ? slice_kernel_of<FMT, kSliceRagged>(r, strips)
+                     : variant == kSliceDeep    ? slice_kernel_of<FMT, kSliceDeep>(r, strips)
                                                 : slice_kernel_of<FMT, kSlicePlain>(r, strips);
   if (!kern) return AMS_ERR_LAUNCH;
   const size_t lds = (size_t)slice_lds(FMT, r, strips, variant);
@@ -1976,7 +1990,7 @@ int prepare_format() {
     for (int r = 4; r <= 32; r *= 2)
       for (int strips = 1; strips <= kSliceMaxStrips; strips++)
         for (int variant = 0; variant < kSliceVariants; variant++)
-          if (variant != kSliceRagged || (r <= kSliceRaggedMaxRows && strips <= kSliceRaggedMaxStrips)) ok &= launch_slice<FMT>(a, variant, r, strips, 0, nullptr) == AMS_OK;
+          if (variant == kSliceDeep ? slice_has_deep(FMT, r, strips) : variant != kSliceRagged || (r <= kSliceRaggedMaxRows && strips <= kSliceRaggedMaxStrips)) ok &= launch_slice<FMT>(a, variant, r, strips, 0, nullptr) == AMS_OK;
     for (a.K = 8; a.K < 10; a.K++) {  // aligned and ragged rows of X
       for (int nt = 0; nt < 2; nt++)
         for (int gs = 0; gs < 2; gs++)

@@ -1,4 +1,4 @@
-"""slice_kernel where only twelve of a workgroup's sixteen wavefronts take records (two strips at M <= 4, one strip at 9 to
+"""slice_kernel where a wavefront asks for more ahead on one strip, and where only twelve of a workgroup's sixteen wavefronts take records (two strips at M <= 4, one strip at 9 to
 16 rows): as many records as streaming wavefronts, one fewer, one more and two rounds of them, and a wavefront's last
 record short; one scale per row, per run, and K split over workgroups; sampled rows against the oracle."""
 
@@ -43,3 +43,18 @@ def test_streaming_wavefronts_and_slices_of_k(fmt, ofmt):
     first = ams.ams_linear_ws(packed, sc, x, N, fmt, ws)
     check(first, O.linear(codes[rows], scales[rows], X, ofmt), rows, plan)
     assert torch.equal(ams.ams_linear_ws(packed, sc, x, N, fmt, ws), first) and not ws[: 4 * 16384].any(), plan
+
+
+@pytest.mark.parametrize("fmt,ofmt,n_recs", [(ams.FP533, O.FP533, (96, 97, 161)), (ams.FP5, O.FP5_E2M2, (128, 129, 241)), (ams.FP4, O.FP4_E2M1, (96, 111, 161))])
+def test_two_records_ahead_on_one_strip(fmt, ofmt, n_recs):
+    # whole rounds of sixteen wavefronts and one record more, one row and two, a last record that ends after 8 channels
+    for n_rec, Ms, N in zip(n_recs, ((1,), (1,), (1, 2)), (16 * 7, 16 * 219 - 5, 16 * 30 - 5)):
+        K = REC_K[fmt] * (n_rec - 1) + (REC_K[fmt] if n_rec == n_recs[0] else 8)
+        codes, scales, rows = problem(fmt, ofmt, N, K, n_rec)
+        packed = dev(ams.ams_pack_codes(fmt, codes))
+        for M in Ms:
+            plan = ams.ams_linear_plan(fmt, M, N, K)
+            assert plan.startswith("slice ") and " x_ahead=2" in plan and " waves=16 " in plan, plan
+            X = synth.activations(M, K, 80 + M)
+            X[M - 1, K - 1] = 3  # the last channel counts
+            check(ams.ams_linear(packed, dev(scales), dev(X), N, fmt), O.linear(codes[rows], scales[rows], X, ofmt), rows, f"{ofmt.name} N={N} K={K} M={M}: {plan}")

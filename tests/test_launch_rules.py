@@ -171,3 +171,18 @@ def test_deep_and_two_strip_plans_stay_where_their_kernels_exist():
 def test_a_slice_plan_says_what_its_kernel_asks_for(fmt, M, N, K, asks):
     kind, p = plan(fmt, M, N, K)
     assert kind == "slice" and {k: v for k, v in p.items() if k in ("waves", "ahead", "streams", "x_ahead", "streamed_rows")} == asks, p
+
+
+@pytest.mark.parametrize(
+    "fmt,M,strips,n_rec,deep",
+    [
+        (ams.FP533, 1, 160, 95, False), (ams.FP533, 1, 160, 96, True), (ams.FP533, 1, 223, 96, True), (ams.FP533, 1, 224, 96, False), (ams.FP533, 1, 1, 300, True),
+        (ams.FP4, 2, 160, 159, False), (ams.FP4, 2, 160, 160, True), (ams.FP4, 3, 160, 300, False), (ams.FP5, 1, 160, 127, False), (ams.FP5, 1, 160, 128, True),
+        (ams.FP5, 2, 160, 239, False), (ams.FP5, 2, 160, 240, True), (ams.FP425, 1, 160, 180, False), (ams.FP433, 1, 160, 180, False),
+    ],
+)
+def test_one_strip_asks_for_two_records_ahead_where_that_is_faster(fmt, M, strips, n_rec, deep):
+    K = n_rec * (96 if fmt in (ams.FP533, ams.FP433, ams.FP6) else 128)
+    kind, p = plan(fmt, M, 16 * strips - 3, K - 8)
+    assert kind == "slice" and (p["ahead"], p.get("x_ahead", "1")) == (("2", "2") if deep else ("1", "1")), p
+    assert "x_ahead" not in plan(fmt, M, 16 * strips, K, with_workspace=2)[1]  # one scale per run
