@@ -1506,16 +1506,20 @@ ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
   return slice_plan(p, fmt, M, kSliceRagged);
 }
 
-// One strip, one scale per row: whether to ask for two records of both ahead (kSliceDeep), not one.
+// One strip, one scale per row: whether to ask for two records of both ahead (kSliceDeep), not one.  us, one / two:
 //   M <= 2, no side groups, fewer workgroups than 7/8 of the compute units, and a stream that is long against its start: the
 //     memory is not what limits them there, every compute unit waits for its own requests.  1500 shapes of 1 to 223 strips 1.035 x
 //     (FP5.33 M = 1 2560 x 24960 11.64 / 11.04 us, 1024 x 18432 8.89 / 8.59; FP4 3520 x 38400 13.70 / 12.76; M = 2 12.24 / 11.83 on
 //     3520 x 24960), at the first percentile 0.988 x; at the lines 1.00-1.01 x.  From 224 strips on 0.90-0.98 x below 128 records;
 //     the longer ones are column_kernel's.  Formats with side groups 0.95-1.03 x.
+//   Tiles of 9 to 16 rows of 96-weight records, where the records are two to four for each of eight wavefronts: twelve that
+//     stream leave a round half empty and write half as many tiles again.  900 shapes FP4.33 1.04 x (4096 x 2688 M = 15 4.69 / 4.42,
+//     4096 x 1536 3.78 / 3.53), FP6 1.025 x (4.93 / 4.77), FP5.33 1.012 x; from 29 records on FP4.33 1.03 x up to 36, the others 0.99-1.0 x;
+//     below 16 0.98-1.01 x.
 bool more_ahead_is_faster(int fmt, int M, int rows, int strips, int grid, int n_rec) {
   if (!slice_has_deep(fmt, rows, strips)) return false;
   if (rows == 4) return M <= 2 && grid < kNumCU * 7 / 8 && n_rec >= (fmt == FMT_FP5 ? (M == 1 ? 128 : 240) : (M == 1 ? 96 : 160));
-  return false;
+  return n_rec >= 16 && n_rec <= (fmt == FMT_FP433 ? 36 : 28);
 }
 
 // The plan of a problem: slice_kernel where it takes it (aligned_rows: rows of X are 16-byte aligned, K % 8 == 0;

@@ -524,6 +524,8 @@ template <>
 const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, ams_dev::kSliceDeep>(int rows, int strips) {
   if constexpr (slice_has_deep(AMS_SLICE_FMT, 4, 1))
     if (rows == 4 && strips == 1) return (const void*)slice_kernel<AMS_SLICE_FMT, 4, 1, kSliceDeep>;
+  if constexpr (slice_has_deep(AMS_SLICE_FMT, 16, 1))
+    if (rows == 16 && strips == 1) return (const void*)slice_kernel<AMS_SLICE_FMT, 16, 1, kSliceDeep>;
   return nullptr;
 }
 #endif

@@ -45,6 +45,19 @@ def test_streaming_wavefronts_and_slices_of_k(fmt, ofmt):
     assert torch.equal(ams.ams_linear_ws(packed, sc, x, N, fmt, ws), first) and not ws[: 4 * 16384].any(), plan
 
 
+@pytest.mark.parametrize("fmt,ofmt", [p for p in PAIRS if REC_K[p[0]] == 96])
+def test_two_records_ahead_on_tiles_of_sixteen_rows(fmt, ofmt):
+    # two and three records for a wavefront, one more and one fewer; whole rows of X and rows dealt to two workgroups
+    for n_rec, N, M in ((16, 2300, 9), (17, 4096, 16), (23, 16 * 130 - 5, 12), (24, 2000, 26), (25, 16 * 125, 19), (28, 2064, 15)):
+        K = 96 * n_rec - 8 * (n_rec % 12)
+        plan = ams.ams_linear_plan(fmt, M, N, K)
+        assert plan.startswith("slice ") and " x_ahead=2" in plan and " waves=8 " in plan, plan
+        codes, scales, rows = problem(fmt, ofmt, N, K, n_rec)
+        X = synth.activations(M, K, 90 + M)
+        y = ams.ams_linear(dev(ams.ams_pack_codes(fmt, codes)), dev(scales), dev(X), N, fmt)
+        check(y, O.linear(codes[rows], scales[rows], X, ofmt), rows, f"{ofmt.name} N={N} K={K} M={M}: {plan}")
+
+
 @pytest.mark.parametrize("fmt,ofmt,n_recs", [(ams.FP533, O.FP533, (96, 97, 161)), (ams.FP5, O.FP5_E2M2, (128, 129, 241)), (ams.FP4, O.FP4_E2M1, (96, 111, 161))])
 def test_two_records_ahead_on_one_strip(fmt, ofmt, n_recs):
     # whole rounds of sixteen wavefronts and one record more, one row and two, a last record that ends after 8 channels

@@ -186,3 +186,14 @@ def test_one_strip_asks_for_two_records_ahead_where_that_is_faster(fmt, M, strip
     kind, p = plan(fmt, M, 16 * strips - 3, K - 8)
     assert kind == "slice" and (p["ahead"], p.get("x_ahead", "1")) == (("2", "2") if deep else ("1", "1")), p
     assert "x_ahead" not in plan(fmt, M, 16 * strips, K, with_workspace=2)[1]  # one scale per run
+
+
+@pytest.mark.parametrize("M,N", [(9, 2300), (15, 4096), (20, 2000), (26, 2000)])  # 20 and 26 rows: two tiles
+@pytest.mark.parametrize("fmt,last", [(ams.FP533, 28), (ams.FP433, 36), (ams.FP6, 28)])
+def test_tiles_of_sixteen_rows_have_eight_wavefronts_where_twelve_leave_a_round_half_empty(fmt, last, M, N):
+    for n_rec, deep in ((15, False), (16, True), (last, True), (last + 1, False)):
+        kind, p = plan(fmt, M, N, 96 * n_rec - 8)
+        assert kind == "slice" and p.get("row_tiles", "1") == ("2" if M > 16 else "1"), p
+        want = ("8", "8", "2", "2") if deep else ("16", "12", "1", "1")
+        assert (p["waves"], p.get("streams", p["waves"]), p["ahead"], p.get("x_ahead", "1")) == want, p
+    assert plan(ams.FP425, M, N, 128 * 16)[1]["streams"] == "12"
