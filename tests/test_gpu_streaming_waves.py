@@ -1,5 +1,5 @@
 """slice_kernel where a wavefront asks for more ahead on one strip, and where only twelve of a workgroup's sixteen wavefronts take records (two strips at M <= 4, one strip at 9 to
-16 rows): as many records as streaming wavefronts, one fewer, one more and two rounds of them, and a wavefront's last
+16 rows): as many records as streaming wavefronts, one fewer, one more, two and four rounds of them, and a wavefront's last
 record short; one scale per row, per run, and K split over workgroups; sampled rows against the oracle."""
 
 import numpy as np
@@ -17,14 +17,15 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("fmt,ofmt", PAIRS)
 @pytest.mark.parametrize("strips,N,Ms", [(2, 16 * 300 - 5, (1, 4)), (1, 16 * 140 - 5, (9, 15))])
 def test_records_around_the_streaming_wavefronts(fmt, ofmt, strips, N, Ms):
-    for n_rec in (11, 12, 13, 24, 25):
+    for n_rec in (11, 12, 13, 24, 25, 48, 49):
+        eight = strips == 1 and REC_K[fmt] == 96 and n_rec in (24, 25)  # wavefronts, which are the faster there
         K = REC_K[fmt] * n_rec - 8 * (n_rec % 3)
         codes, scales, rows = problem(fmt, ofmt, N, K, n_rec)
         packed = dev(ams.ams_pack_codes(fmt, codes))
         run_scales, run_packed = scales_per_run(N, K, 2 * REC_K[fmt], 4)
         for M in Ms:
             plan = ams.ams_linear_plan(fmt, M, N, K)
-            assert plan.startswith("slice ") and f"strips_per_wg={strips} " in plan and " waves=16 " in plan, plan
+            assert plan.startswith("slice ") and f"strips_per_wg={strips} " in plan and (" waves=8 " if eight else " waves=16 ") in plan, plan
             X = synth.activations(M, K, 50 + M)
             what = f"{ofmt.name} N={N} K={K} M={M}: {plan}"
             check(ams.ams_linear(packed, dev(scales), dev(X), N, fmt), O.linear(codes[rows], scales[rows], X, ofmt), rows, what)
