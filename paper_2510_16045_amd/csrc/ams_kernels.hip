@@ -1672,14 +1672,20 @@ double plan_time(const ColumnPlan& p, int fmt, int M, int n_rec) {
 //     to 12 rows at every K (5120 x 6144 FP5.33 M = 32 12.3 / 10.8, 7168 x 8192 FP4.5 M = 16 13.4 / 11.6; 1215 shapes: 1.10 x at K = 8000, 1.03 x
 //     around 9000, 0.96 x at 12000; M = 8 up to 20000 1.11 x).
 //   up to 128 strips, from five rows on: the plain call deals its rows to the compute units that the strips leave idle (plan_from), and
-//     where such a compute unit moves less than kSplitMoved bytes (of row_split_cost: 4.4 us) the exchange costs more than the slices
-//     save: 1187 x 7848 FP4.25 M = 12 6.4 / 5.2, 1024 x 14336 M = 12 7.6 / 7.1, 2048 x 9728 FP5.33 M = 12 7.05 / 7.05, 2048 x 14336 8.4 / 9.2.
-//     Over 21000 shapes the choice is 0.25 % off the faster one in the mean (1.7 % without this line; below K = 6000 10-25 %).
+//     where such a compute unit moves less than split_moved the exchange costs more than the slices save.  Counted are its records, a
+//     side dword's load as 224 bytes (320 where no other record shares it), and 90 bytes for a row of activations; the line lies
+//     lower on a few strips, whose slices hardly meet in the exchange (69 x 11016 FP6 M = 9 5.3 / 7.0), and higher where four slices
+//     are 224 to 256 workgroups.  1187 x 7848 FP4.25 M = 12 6.3 / 5.2, 1024 x 14336 M = 12 7.5 / 7.0, 2048 x 9728 FP5.33 M = 12 6.8 /
+//     7.0, 2048 x 14336 8.1 / 9.0.
+//     Over 4000 such shapes that would split without this line the choice is 0.10 % off the faster one in the mean, 3.4 % at
+//     the last percentile (4.5 and 36 % without it).
 // Unaligned rows keep cheapest_split's (17000 shapes: the plain call is 1.1-1.3 x faster below K = 5000 and the split from 8000
 // on; in between it depends on the strips).
 constexpr int kSplitLongK = 9216;
 constexpr int kSplitLongKOfRows[16] = {0, 0, 0, 0, 12800, 10950, 9640, 8650, 7880, 7250, 6740, 6300, 5930, 5610, 5320, 5070};  // 12800 (4 / M)^0.7
-constexpr double kSplitMoved = 205e3;
+double split_moved(int64_t n_strips) {
+  return std::min(172e3, 124e3 + 6e3 * std::max<double>(0, n_strips - 7)) + (n_strips >= 56 && n_strips <= 64 ? 20e3 : 0);
+}
 struct Split {
   int gk;
   bool planned;  // plan: make_plan's for gk slices, non-temporal loads
@@ -1695,8 +1701,9 @@ Split choose_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int r
   const bool on_slice = sliced.spw <= kSliceMaxStrips && !short_slices_on_column(fmt, M, sliced.spw, c.gk, n_rec);  // as plan_from has it
   if (on_slice && n_strips <= kNumCU / 2 && M > 4) {  // the plain call deals its rows out
     const ColumnPlan whole = plan_from(column[0], fmt, M, n_strips, n_rec, rec_k, 1, true, true);
-    const double moved = n_rec * row_split_cost(fmt, whole.spw, (M + whole.row_tiles - 1) / whole.row_tiles, true);
-    if (whole.slice && moved < kSplitMoved) {
+    const ams::FormatInfo& fi = ams::kFormats[fmt];
+    const double moved = n_rec * (whole.spw * (fi.rec_bytes + (fi.side_bytes == 4 ? 320.0 : fi.side_bytes ? 224.0 : 0.0)) + 90.0 * ((M + whole.row_tiles - 1) / whole.row_tiles));
+    if (whole.slice && moved < split_moved(n_strips)) {
       c.gk = 1, c.plan = whole, c.planned = true;
       return c;
     }

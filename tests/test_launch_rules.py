@@ -120,9 +120,10 @@ def test_short_slices_of_a_split(fmt, M, N, K, slices, want):
         (ams.FP533, 7, 8714, 14560, False), (ams.FP533, 8, 8244, 13272, False), (ams.FP533, 12, 10612, 14552, False), (ams.FP425, 16, 9049, 16088, True),
         (ams.FP425, 12, 2187, 7848, True), (ams.FP45, 12, 2238, 7640, True), (ams.FP425, 12, 2187, 5000, False),  # on slice_kernel: K by the rows
         # up to 128 strips, where a plain call deals its rows: by the bytes a compute unit moves (1187 x 7848 split 6.4 us, whole 5.2)
-        (ams.FP425, 12, 1187, 7848, False), (ams.FP45, 12, 1238, 7640, False), (ams.FP425, 12, 1187, 5000, False), (ams.FP425, 12, 1024, 14336, False), (ams.FP425, 12, 1024, 14472, True),
-        (ams.FP425, 8, 2048, 14336, False), (ams.FP425, 8, 2048, 14472, True), (ams.FP533, 12, 2048, 9216, False), (ams.FP533, 12, 2048, 9728, True), (ams.FP425, 32, 1024, 9984, False), (ams.FP425, 32, 1024, 10368, True),
+        (ams.FP425, 12, 1187, 7848, False), (ams.FP45, 12, 1238, 7640, False), (ams.FP425, 12, 1187, 5000, False), (ams.FP425, 12, 1024, 14592, False), (ams.FP425, 12, 1024, 14600, True),
+        (ams.FP425, 8, 2048, 13056, False), (ams.FP425, 8, 2048, 13064, True), (ams.FP533, 12, 2048, 10464, False), (ams.FP533, 12, 2048, 10472, True), (ams.FP425, 32, 1024, 12032, False), (ams.FP425, 32, 1024, 12040, True),
         (ams.FP533, 5, 1920, 9920, False), (ams.FP425, 5, 1920, 10960, False), (ams.FP425, 5, 1920, 16000, True), (ams.FP425, 16, 2560, 9208, False), (ams.FP425, 16, 2560, 9216, True),
+        (ams.FP6, 9, 69, 7200, False), (ams.FP6, 9, 69, 7208, True), (ams.FP425, 12, 160, 10752, False), (ams.FP425, 12, 160, 10760, True),  # a few strips: less
         (ams.FP425, 32, 896, 2880, False), (ams.FP425, 32, 4096, 4096, False), (ams.FP533, 16, 1226, 5760, False),
     ],
 )
