@@ -1673,7 +1673,7 @@ double plan_time(const ColumnPlan& p, int fmt, int M, int n_rec) {
 //     around 9000, 0.96 x at 12000; M = 8 up to 20000 1.11 x).
 //   up to 128 strips, from five rows on: the plain call deals its rows to the compute units that the strips leave idle (plan_from), and
 //     where such a compute unit moves less than split_moved the exchange costs more than the slices save.  Counted are its records, a
-//     side dword's load as 224 bytes (320 where no other record shares it), and 90 bytes for a row of activations; the line lies
+//     side dword's load as 224 bytes (320 where no other record shares it), and 90 bytes for a row of activations (190 from the ninth on); it lies
 //     lower on a few strips, whose slices hardly meet in the exchange (69 x 11016 FP6 M = 9 5.3 / 7.0), and higher where four slices
 //     are 224 to 256 workgroups.  1187 x 7848 FP4.25 M = 12 6.3 / 5.2, 1024 x 14336 M = 12 7.5 / 7.0, 2048 x 9728 FP5.33 M = 12 6.8 /
 //     7.0, 2048 x 14336 8.1 / 9.0.
@@ -1702,7 +1702,8 @@ Split choose_split(int fmt, int M, int64_t n_strips, int n_rec, int rec_k, int r
   if (on_slice && n_strips <= kNumCU / 2 && M > 4) {  // the plain call deals its rows out
     const ColumnPlan whole = plan_from(column[0], fmt, M, n_strips, n_rec, rec_k, 1, true, true);
     const ams::FormatInfo& fi = ams::kFormats[fmt];
-    const double moved = n_rec * (whole.spw * (fi.rec_bytes + (fi.side_bytes == 4 ? 320.0 : fi.side_bytes ? 224.0 : 0.0)) + 90.0 * ((M + whole.row_tiles - 1) / whole.row_tiles));
+    const int rows = (M + whole.row_tiles - 1) / whole.row_tiles;
+    const double moved = n_rec * (whole.spw * (fi.rec_bytes + (fi.side_bytes == 4 ? 320.0 : fi.side_bytes ? 224.0 : 0.0)) + 90.0 * rows + 100.0 * std::max(0, rows - 8));
     if (whole.slice && moved < split_moved(n_strips)) {
       c.gk = 1, c.plan = whole, c.planned = true;
       return c;
