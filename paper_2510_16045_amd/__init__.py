@@ -224,16 +224,17 @@ def _bind_call():
 _PLAIN, _WORKSPACE, _STATIC, _GROUPED = range(4)  # of csrc/ams_binding.cpp
 
 
-_current_device = None
+_devices = 0  # of this machine, once asked: with one of them no tensor is on another
 
 
-def _device():
-    global _current_device
-    if _current_device is None:
-        import torch
+def _check_device(t):
+    # the kernels run on the current device and in the order of its stream
+    global _devices
+    import torch
 
-        _current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
-    return _current_device()
+    _devices = torch.cuda.device_count()
+    if t.get_device() != torch.cuda.current_device():
+        raise ValueError(f"expected a tensor on the current device, cuda:{torch.cuda.current_device()}, got one on cuda:{t.get_device()}")
 
 
 def _dev_ptr(t, dtype=None):
@@ -241,15 +242,14 @@ def _dev_ptr(t, dtype=None):
         raise ValueError("expected a contiguous CUDA tensor")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"expected {dtype}, got {t.dtype}")
-    if t.get_device() != _device():  # the kernels run on the current device and in the order of its stream
-        raise ValueError(f"expected a tensor on the current device, cuda:{_device()}, got one on cuda:{t.get_device()}")
+    if _devices != 1:
+        _check_device(t)
     return t.data_ptr()
 
 
-def _check_out(out, rows, columns):
+def _too_small(out, rows, columns):
     # the kernels write that many values (a buffer for a larger batch may be given)
-    if out.numel() < rows * columns:
-        raise ValueError(f"out must hold {rows} x {columns} values, it has {out.numel()}")
+    return ValueError(f"out must hold {rows} x {columns} values, it has {out.numel()}")
 
 
 def ams_dequant(fmt: int, W_packed, scales, N: int, K: int, scaled: bool = True, out=None):
@@ -260,8 +260,8 @@ def ams_dequant(fmt: int, W_packed, scales, N: int, K: int, scaled: bool = True,
         raise ValueError("packed buffer has the wrong size")
     if out is None:
         out = torch.empty((N, K), dtype=torch.float16, device=W_packed.device)
-    else:
-        _check_out(out, N, K)
+    elif out.numel() < N * K:
+        raise _too_small(out, N, K)
     sp = _dev_ptr(scales, torch.float16) if scales is not None else None
     if scales is not None and scales.numel() != N:
         raise ValueError("scales must have N entries")
@@ -283,8 +283,8 @@ def ams_linear(W_packed, scales, X, N: int, fmt: int, out=None):
         raise ValueError("scales must have N entries")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
-    else:
-        _check_out(out, M, N)
+    elif out.numel() < M * N:
+        raise _too_small(out, M, N)
     rc = load_library().ams_linear(
         _dev_ptr(W_packed, torch.uint8), _dev_ptr(scales, torch.float16), _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K, fmt, _stream()
     )
@@ -302,8 +302,8 @@ def ams_fp16_linear(W, X, out=None):
         raise ValueError("X and W disagree in K")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
-    else:
-        _check_out(out, M, N)
+    elif out.numel() < M * N:
+        raise _too_small(out, M, N)
     rc = load_library().ams_fp16_linear(_dev_ptr(W, torch.float16), _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K, _stream())
     _check(rc, "ams_fp16_linear")
     return out
@@ -349,8 +349,8 @@ def ams_dequant_grouped(fmt: int, W_packed, scales, scale_group: int, N: int, K:
         raise ValueError("scale buffer has the wrong size")
     if out is None:
         out = torch.empty((N, K), dtype=torch.float16, device=W_packed.device)
-    else:
-        _check_out(out, N, K)
+    elif out.numel() < N * K:
+        raise _too_small(out, N, K)
     rc = load_library().ams_dequant_grouped(fmt, _dev_ptr(W_packed, torch.uint8), _dev_ptr(scales, torch.float16), scale_group, _dev_ptr(out, torch.float16), N, K, int(scaled), _stream())
     _check(rc, "ams_dequant_grouped")
     return out
@@ -368,8 +368,8 @@ def ams_linear_grouped(W_packed, scales, scale_group: int, X, N: int, fmt: int, 
         raise ValueError("scale buffer has the wrong size")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
-    else:
-        _check_out(out, M, N)
+    elif out.numel() < M * N:
+        raise _too_small(out, M, N)
     rc = load_library().ams_linear_grouped(
         _dev_ptr(W_packed, torch.uint8), _dev_ptr(scales, torch.float16), scale_group, _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K, fmt, _stream()
     )
@@ -397,8 +397,8 @@ def ams_linear_ws(W_packed, scales, X, N: int, fmt: int, workspace, out=None):
         raise ValueError("scales must have N entries")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
-    else:
-        _check_out(out, M, N)
+    elif out.numel() < M * N:
+        raise _too_small(out, M, N)
     rc = load_library().ams_linear_ws(
         _dev_ptr(W_packed, torch.uint8), _dev_ptr(scales, torch.float16), _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K, fmt,
         _dev_ptr(workspace, torch.uint8) if workspace is not None else None, workspace.numel() if workspace is not None else 0, _stream()
@@ -420,8 +420,8 @@ def ams_linear_static_ws(W_packed, scales, X, N: int, fmt: int, out=None):
         raise ValueError("scales must have N entries")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
-    else:
-        _check_out(out, M, N)
+    elif out.numel() < M * N:
+        raise _too_small(out, M, N)
     rc = load_library().ams_linear_static_ws(
         _dev_ptr(W_packed, torch.uint8), _dev_ptr(scales, torch.float16), _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K, fmt, _stream()
     )
@@ -438,8 +438,8 @@ def ams_fp16_linear_ws(W, X, workspace, out=None):
         raise ValueError("X and W disagree in K")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=X.device)
-    else:
-        _check_out(out, M, N)
+    elif out.numel() < M * N:
+        raise _too_small(out, M, N)
     rc = load_library().ams_fp16_linear_ws(
         _dev_ptr(W, torch.float16), _dev_ptr(X, torch.float16), _dev_ptr(out, torch.float16), M, N, K,
         _dev_ptr(workspace, torch.uint8) if workspace is not None else None, workspace.numel() if workspace is not None else 0, _stream()

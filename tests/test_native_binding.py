@@ -121,11 +121,14 @@ def test_a_tensor_on_another_device_is_refused(monkeypatch):
         get_device = lambda self: 1
         data_ptr = lambda self: 4096
 
-    monkeypatch.setattr(ams, "_current_device", lambda: 1, raising=False)
+    monkeypatch.setattr(ams, "_devices", 0)
+    monkeypatch.setattr(torch.cuda, "device_count", lambda: 2)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 1)
     assert ams._dev_ptr(There()) == 4096
-    monkeypatch.setattr(ams, "_current_device", lambda: 0, raising=False)
-    with pytest.raises(ValueError, match="current device"):
-        ams._dev_ptr(There())
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    for _ in range(2):
+        with pytest.raises(ValueError, match="current device"):
+            ams._dev_ptr(There())
 
 
 def test_a_daemon_thread_in_a_call_ends_with_the_interpreter(tmp_path):
