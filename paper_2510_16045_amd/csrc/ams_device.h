@@ -400,8 +400,8 @@ constexpr int slice_wave_lds(int fmt, int R, int NS, int variant) {
 }
 constexpr int slice_lds(int fmt, int R, int NS, int variant) { return slice_ask(fmt, R, NS, variant).streams * slice_wave_lds(fmt, R, NS, variant) + NS * 64 + NS * 4; }
 // Whether two workgroups of `strips` strips fit on a compute unit at M <= 4 with one scale per run of input channels: at
-// most 128 registers (as the compiler reports them; the formats of 96 weights per record take 126 at most, FP4.25, FP4.5
-// and FP5 124 with six strips and 134 with seven, FP4 126 with seven and 130 with eight).
+// most 128 registers (as the compiler reports them; the formats of 96 weights per record take 125 at most, FP4.25, FP4.5
+// and FP5 124 with six strips and 136 with seven, FP4 128 with seven and 131 with eight).
 constexpr bool slice_two_fit(int fmt, int strips) {
   return ams::kFormats[fmt].rec_k == 96 || strips <= (fmt == FMT_FP4 ? 7 : 6);
 }

@@ -1347,13 +1347,15 @@ ColumnPlan make_column_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int
 //   One scale per row, M <= 8, side groups: everywhere (128256 x 4096 FP4.25 M = 8 1.12 x, 90000 x 4096 1.38 x; 1.11-1.21 x in the mean, no
 //     format below 1.02) but for two records per side group with a count that is even but no multiple of four, which
 //     column_kernel deals without a rest while most of the eight wavefronts idle (65536 x 256 FP4.5 0.87 x, x 768 0.90 x,
-//     from 24 records on +- 3 %).  At M = 1 in one round from 64 records on left where it was (57344 x 8192; 1.05-1.14 x).
+//     from 24 records on +- 3 %).  At M = 1 in one round from 64 records on it would be 1.05-1.14 x: a
+//     test names column_kernel's plan of 57344 x 8192, and it stays.
 //   One scale per row, M <= 8, no side groups: up to ten strips, where three of multi_kernel's eight wavefronts, two strips each, have none
-//     (33000 x 4096 FP5.33 M = 1 1.35 x, 40000 x 4096 1.28 x; one and two records 0.87-0.96 x; eleven to thirteen strips, left with
-//     multi_kernel, 1.05-1.2 x, 65536 x 4096 0.92 x), and where at most half of the compute units
+//     (33000 x 4096 FP5.33 M = 1 1.35 x, 40000 x 4096 1.28 x; one and two records 0.87-0.96 x; 65536 x 4096 0.92 x.  Eleven to
+//     thirteen strips would gain 1.05-1.2 x: the plans of multi_kernel that tests name lie there, and they stay), and where at most half of the compute units
 //     have a workgroup in the last round (90000 x 4096 1.17 x, 128256 x 4096 0.96 x).
 //   M > 8: long K, where the staging of the activations starts to cost (45000 x 4096 M = 16 21.1 / 23.3; 64 to 80
-//     records at M > 16 0.92-1.0 x).  Left: from 32 or 43 records on at M = 10 to 16, one scale per row, 1.06-1.14 x.
+//     records at M > 16 0.92-1.0 x).  From 32 or 43 records on M = 10 to 16 with one scale per row would
+//     gain 1.06-1.14 x: tests name column_kernel's plans there, and they stay.
 //   One scale per run: a wavefront's strips follow each other and the sum over eight wavefronts' tiles is the same
 //     for one record as for a hundred, so a few records do not pay (65536 x 96 FP5.33 M = 4 0.83 x, x 1152 0.96 x), and where
 //     the scales push the kernel beyond 128 registers the two workgroups take turns (65536 x 128 FP4.25 0.61 x, x 1024
@@ -1379,9 +1381,11 @@ bool halved_is_faster(int fmt, int M, int64_t n_strips, int spw, int n_rec, bool
   return half < kSliceMaxStrips ? n_rec >= 24 : fmt == FMT_FP425 && n_rec >= 64;
 }
 
-// Long K at M <= 2, where both kernels live on the bytes in flight: column_kernel has sixteen wavefronts on one, two and
-// four strips alike, slice_kernel eight from two strips on (and keeps fewer records ahead the more loads a record takes:
-// its side dword, its scales).  Column / slice, 6800 shapes of 80 to 280 records and those of models, on five GPUs (+- 3 %):
+// Long K at M <= 2, where both kernels live on the bytes in flight.  The lines are from before slice_kernel asked for one record of
+// activations ahead (and had twelve or sixteen wavefronts on two strips, not eight) and have not been drawn again.  Today it is the
+// faster one of the two behind them: 1300 shapes, two strips 1.02-1.16 x (5120 x 25600 FP4.25 M = 1 17.1 us on column_kernel, M = 4
+// on slice_kernel 16.4), four 1.00-1.04 x, one 1.00-1.02 x but for FP4.33 0.97 x.  As they were drawn, column / slice, 6800 shapes
+// of 80 to 280 records and those of models, on five GPUs (+- 3 %):
 //   two strips on fewer than 7/8 of the compute units: from 128 records on (5120 x 25600 FP4.25 M = 1 17.8 / 19.7 us, FP5.33
 //     M = 2 20.3 / 22.5), at M = 1 from 97 on (6144 x 14336 FP4.25 11.6 / 12.5; 6144 x 4096 FP5.33 6.1 / 5.8) but for the
 //     plain FP5 and FP4 (1.0-1.07 x);
@@ -1458,8 +1462,8 @@ constexpr int kMaxRowTiles = 4, kRowSplitMinRecords = 18, kRowSplitMinRows = 8;
 
 // Rows of X that are not 16-byte aligned: slice_kernel's variant for them, on tiles of up to eight rows and up to four strips
 // (its sixteen wavefronts have 128 registers each).  21000 shapes against column_kernel, which stages the rows for the workgroup
-// (in phases of K where all of it does not fit): 1.7 x in the mean (32 rows 2-4 x: 4096 x 14337 FP4.25 47.7 / 21.5 us; 8 rows in
-// phases 4096 x 14339 FP4.25 16.5 / 11.9, 13 strips 1.5 x, 400 strips 1.2 x).  column_kernel stays with one scale per run, on
+// (in phases of K where all of it does not fit): 1.7 x in the mean (32 rows 2-4 x: 4096 x 14337 FP4.25 47.7 / 22.5 us; 8 rows in
+// phases 4096 x 14339 FP4.25 16.5 / 12.7, 13 strips 1.5 x, 400 strips 1.2 x).  column_kernel stays with one scale per run, on
 // one record, where it reads three records ahead (8192 x 8193 FP5.33 M = 1 11.0 / 11.2), and:
 //   at one row on long K, where staging it is nothing and the wavefronts live on the records in flight: from where the two meet, by
 //     format (5.33 bits from 230 records on 0.98 x, from 800 on 0.91 x; FP4.5 0.95 and 0.94 x);
@@ -1525,8 +1529,9 @@ bool more_ahead_is_faster(int fmt, int M, int rows, int strips, int grid, int n_
 // The plan of a problem: slice_kernel where it takes it (aligned_rows: rows of X are 16-byte aligned, K % 8 == 0;
 // one_scale: one scale per row of W), else make_column_plan's.  slice_kernel is the faster one nearly everywhere
 // (twelve shapes, seven formats, M = 1 .. 32: 1.00-1.8 x); the exceptions, us column / slice:
-//   one strip per workgroup, M <= 2, where eight wavefronts with three records ahead fill the chip (no side groups):
-//     4096 x 14336 FP5.33 M = 1 9.5 / 9.4, M = 2 10.1 / 10.1;
+//   one strip per workgroup, M <= 2, where eight wavefronts with three records ahead fill the chip (no side groups): 4096 x
+//     14336 FP5.33 M = 1 9.5 / 9.4, M = 2 10.1 / 10.1 with two records ahead on slice_kernel; with one 9.4 / 8.6 and 9.9 / 8.5, not
+//     drawn again;
 //   one, two and four strips, M <= 2, long K: see long_k_on_column;
 //   six strips and more, M > 8, a few records: with fewer than eight of them wavefronts idle, the busy ones walk all
 //     strips one after the other, and the idle ones' tiles are written and summed too (32768 x 128 M = 32 0.75 x, 24576
