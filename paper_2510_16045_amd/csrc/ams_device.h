@@ -330,13 +330,15 @@ constexpr int kDeviceScope = 16;          // cache policy (sc1) of a buffer load
 constexpr int kMaxSlices = 8;             // slices of K that workgroups may share
 
 // ---- slice_kernel (ams_slice.hip): what its launch needs ------------------------------------------
-// Variants: one scale per row of W; one per run of input channels; rows of X that are not 16-byte aligned; one scale per row and
-// more asked for ahead.
-constexpr int kSlicePlain = 0, kSliceRunScales = 1, kSliceRagged = 2, kSliceDeep = 3, kSliceVariants = 4;
+// Variants: one scale per row of W; one per run of input channels; rows of X that are not 16-byte aligned; one scale per row, or per
+// run, and more asked for ahead.
+constexpr int kSlicePlain = 0, kSliceRunScales = 1, kSliceRagged = 2, kSliceDeep = 3, kSliceDeepRuns = 4, kSliceVariants = 5;
 constexpr int kSliceRaggedMaxStrips = 4, kSliceRaggedMaxRows = 8;  // of kSliceRagged
-// Whether there is a kSliceDeep kernel for `rows` staged rows and `strips` strips (where it is taken: more_ahead_is_faster).
-constexpr bool slice_has_deep(int fmt, int rows, int strips) {
-  return strips == 1 && ((rows == 4 && ams::side_group(ams::kFormats[fmt]) == 1) || (rows == 16 && ams::kFormats[fmt].rec_k == 96));
+// Whether there is a kernel of the last two for `rows` staged rows and `strips` strips (where they are taken: more_ahead_is_faster).
+constexpr bool slice_has_deep(int fmt, int variant, int rows, int strips) {
+  const bool rec96 = ams::kFormats[fmt].rec_k == 96;
+  if (strips != 1) return false;
+  return variant == kSliceDeepRuns ? rows == 16 && !rec96 : (rows == 4 && ams::side_group(ams::kFormats[fmt]) == 1) || (rows == 16 && rec96);
 }
 constexpr int kSliceMaxStrips = 8;  // strips per workgroup it is built for
 constexpr int slice_rows(int M) { return M <= 4 ? 4 : M <= 8 ? 8 : M <= 16 ? 16 : 32; }  // staged activation rows
@@ -360,12 +362,14 @@ constexpr SliceAsk slice_ask(int fmt, int R, int NS, int variant) {
   // seven formats: 5 to 8 rows 1.18 x on one strip, 1.12 on two, 1.08 on three and four (11003 x 4099 FP5.33 M = 5 8.8 / 8.1 us, 4096 x 14339
   // M = 8 14.9 / 12.7); up to four rows 1.07, 1.03, 1.02, 1.01 (twelve streams of 96-weight records 0.94-0.97 x on two strips).
   if (variant == kSliceRagged) return {16, R == 4 && NS == 2 && loads2 && !rec96 ? 12 : 16, NS == 1 ? 1 : 2, 1, 0};
+  if (variant == kSliceDeepRuns) return {8, 8, 1, 2, 0};
   if (variant == kSliceDeep) return R == 4 ? SliceAsk{16, 16, 2, 2, 0} : SliceAsk{8, 8, 2, 2, 0};
   if (NS == 1) {
     // One strip: many wavefronts that each wait for one record (4096 x 9728 FP4.25 M = 1, sixteen with two records ahead / with
     // one / twelve / eight with two: 1.00 / 1.10 / 1.02 / 1.03 x; two of both only as kSliceDeep).  Up to eight rows eight stay, two ahead of both (one ahead
     // 0.88-1.0 x of it); up to sixteen rows twelve stream (FP4.25 1.05-1.16 x, FP5.33 M = 9 to 15 1.02-1.07 x but for
-    // kSliceDeep's 16 to 36 records), but for 96-weight records with a scale per run (11 to 28 records 1.01-1.08 x, twelve 0.96-1.01 x).
+    // kSliceDeep's 16 to 36 records), but for 96-weight records with a scale per run (11 to 28 records 1.01-1.08 x, twelve 0.96-1.01 x;
+    // those of 128 as kSliceDeepRuns).
     if (R == 4) return {16, 16, 1, 1, 0};
     if (R == 8) return {8, 8, 2, 2, 0};
     if (R == 16) return rec96 && runs ? SliceAsk{8, 8, 1, 2, 0} : SliceAsk{16, 12, 1, 1, 0};

@@ -1510,7 +1510,7 @@ ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
   return slice_plan(p, fmt, M, kSliceRagged);
 }
 
-// One strip, one scale per row: whether to ask for two records of both ahead (kSliceDeep), not one.  us, one / two:
+// One strip: whether to ask for two records ahead (kSliceDeep; kSliceDeepRuns: of activations), not one.  us, one / two:
 //   M <= 2, no side groups, fewer workgroups than 7/8 of the compute units, and a stream that is long against its start: the
 //     memory is not what limits them there, every compute unit waits for its own requests.  1500 shapes of 1 to 223 strips 1.035 x
 //     (FP5.33 M = 1 2560 x 24960 11.64 / 11.04 us, 1024 x 18432 8.89 / 8.59; FP4 3520 x 38400 13.70 / 12.76; M = 2 12.24 / 11.83 on
@@ -1520,8 +1520,11 @@ ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
 //     stream leave a round half empty and write half as many tiles again.  900 shapes FP4.33 1.04 x (4096 x 2688 M = 15 4.69 / 4.42,
 //     4096 x 1536 3.78 / 3.53), FP6 1.025 x (4.93 / 4.77), FP5.33 1.012 x; from 29 records on FP4.33 1.03 x up to 36, the others 0.99-1.0 x;
 //     below 16 0.98-1.01 x.
-bool more_ahead_is_faster(int fmt, int M, int rows, int strips, int grid, int n_rec) {
-  if (!slice_has_deep(fmt, rows, strips)) return false;
+//   One scale per run, 13 to 16 rows of 128-weight records, from 18 of them on: eight wavefronts instead of twelve streams 1.03 x over
+//     340 shapes (4096 x 3072 FP4.25 M = 16 5.34 / 4.91, x 14336 13.92 / 13.54); 9 rows 0.98 x, 12 rows 1.01 x; 6 to 17 records 0.98-1.02 x.
+bool more_ahead_is_faster(int fmt, int variant, int M, int rows, int strips, int grid, int n_rec) {
+  if (!slice_has_deep(fmt, variant, rows, strips)) return false;
+  if (variant == kSliceDeepRuns) return M >= 13 && M <= 16 && n_rec >= 18;
   if (rows == 4) return M <= 2 && grid < kNumCU * 7 / 8 && n_rec >= (fmt == FMT_FP5 ? (M == 1 ? 128 : 240) : (M == 1 ? 96 : 160));
   return n_rec >= 16 && n_rec <= (fmt == FMT_FP433 ? 36 : 28);
 }
@@ -1575,8 +1578,9 @@ ColumnPlan plan_from(ColumnPlan p, int fmt, int M, int64_t n_strips, int n_rec_a
       if (s.strips == 1 && (M > 16 || (M + t - 1) / t <= 4 || n_rec_all > 8)) p.row_tiles = t, p.grid = s.positions * t;
     }
   }
-  const bool deep = one_scale && gk == 1 && more_ahead_is_faster(fmt, M, slice_rows((M + p.row_tiles - 1) / p.row_tiles), p.spw, p.grid, n_rec_all);
-  return slice_plan(p, fmt, M, deep ? kSliceDeep : one_scale ? kSlicePlain : kSliceRunScales);
+  const int deep = one_scale ? kSliceDeep : kSliceDeepRuns;
+  if (gk == 1 && more_ahead_is_faster(fmt, deep, M, slice_rows((M + p.row_tiles - 1) / p.row_tiles), p.spw, p.grid, n_rec_all)) return slice_plan(p, fmt, M, deep);
+  return slice_plan(p, fmt, M, one_scale ? kSlicePlain : kSliceRunScales);
 }
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {
   const ColumnPlan column = make_column_plan(fmt, M, n_strips, n_rec_all, rec_k, gk, one_scale, one_scale && nt);
@@ -1863,7 +1867,8 @@ int launch_slice(const LinearArgs& a, int variant, int r, int strips, unsigned g
   const void* kern = variant == kSliceRunScales ? slice_kernel_of<FMT, kSliceRunScales>(r, strips)
                      : variant == kSliceRagged  ? slice_kernel_of<FMT, kSliceRagged>(r, strips)
                      : variant == kSliceDeep    ? slice_kernel_of<FMT, kSliceDeep>(r, strips)
-                                                : slice_kernel_of<FMT, kSlicePlain>(r, strips);
+                     : variant == kSliceDeepRuns ? slice_kernel_of<FMT, kSliceDeepRuns>(r, strips)
+                                                 : slice_kernel_of<FMT, kSlicePlain>(r, strips);
   if (!kern) return AMS_ERR_LAUNCH;
   const size_t lds = (size_t)slice_lds(FMT, r, strips, variant);
   if (lds > 64 * 1024 && !raise_lds_limit(kern)) return AMS_ERR_LAUNCH;
@@ -2007,7 +2012,7 @@ int prepare_format() {
     for (int r = 4; r <= 32; r *= 2)
       for (int strips = 1; strips <= kSliceMaxStrips; strips++)
         for (int variant = 0; variant < kSliceVariants; variant++)
-          if (variant == kSliceDeep ? slice_has_deep(FMT, r, strips) : variant != kSliceRagged || (r <= kSliceRaggedMaxRows && strips <= kSliceRaggedMaxStrips)) ok &= launch_slice<FMT>(a, variant, r, strips, 0, nullptr) == AMS_OK;
+          if (variant >= kSliceDeep ? slice_has_deep(FMT, variant, r, strips) : variant != kSliceRagged || (r <= kSliceRaggedMaxRows && strips <= kSliceRaggedMaxStrips)) ok &= launch_slice<FMT>(a, variant, r, strips, 0, nullptr) == AMS_OK;
     for (a.K = 8; a.K < 10; a.K++) {  // aligned and ragged rows of X
       for (int nt = 0; nt < 2; nt++)
         for (int gs = 0; gs < 2; gs++)

@@ -61,7 +61,7 @@ __device__ __forceinline__ void buffer_load_chunk(uint32_t* w, __amdgpu_buffer_r
 // Shape of the kernel for R staged activation rows (4, 8, 16 or 32) and NS strips per workgroup.
 template <int FMT, int R, int NS, int VAR>
 struct Slice {
-  static constexpr bool GS = VAR == kSliceRunScales, RAGGED = VAR == kSliceRagged;
+  static constexpr bool GS = VAR == kSliceRunScales || VAR == kSliceDeepRuns, RAGGED = VAR == kSliceRagged;
   static constexpr int MT = R > 16 ? 2 : 1;
   static constexpr int RB = R > 16 ? 16 : R;                    // rows of one MFMA tile that are staged
   static constexpr int NI = slice_x_loads(FMT, R), NI1 = NI / MT;  // 1 KiB loads of a record's activations, of one tile's
@@ -504,12 +504,26 @@ const void* by_rows(int rows, int strips) {
   return nullptr;
 }
 
+template <int V>
+const void* by_rows_deep(int rows, int strips) {
+  constexpr int F = AMS_SLICE_FMT;
+  if constexpr (slice_has_deep(F, V, 4, 1))
+    if (rows == 4 && strips == 1) return (const void*)slice_kernel<F, 4, 1, V>;
+  if constexpr (slice_has_deep(F, V, 16, 1))
+    if (rows == 16 && strips == 1) return (const void*)slice_kernel<F, 16, 1, V>;
+  return nullptr;
+}
+
 }  // namespace
 
 #if AMS_SLICE_RUN_SCALES
 template <>
 const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, ams_dev::kSliceRunScales>(int rows, int strips) {
   return by_rows<kSliceRunScales>(rows, strips);
+}
+template <>
+const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, ams_dev::kSliceDeepRuns>(int rows, int strips) {
+  return by_rows_deep<kSliceDeepRuns>(rows, strips);
 }
 #else
 template <>
@@ -522,10 +536,6 @@ const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, ams_dev::kSliceRagged>(int r
 }
 template <>
 const void* ams_dev::slice_kernel_of<AMS_SLICE_FMT, ams_dev::kSliceDeep>(int rows, int strips) {
-  if constexpr (slice_has_deep(AMS_SLICE_FMT, 4, 1))
-    if (rows == 4 && strips == 1) return (const void*)slice_kernel<AMS_SLICE_FMT, 4, 1, kSliceDeep>;
-  if constexpr (slice_has_deep(AMS_SLICE_FMT, 16, 1))
-    if (rows == 16 && strips == 1) return (const void*)slice_kernel<AMS_SLICE_FMT, 16, 1, kSliceDeep>;
-  return nullptr;
+  return by_rows_deep<kSliceDeep>(rows, strips);
 }
 #endif

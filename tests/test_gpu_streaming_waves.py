@@ -59,6 +59,19 @@ def test_two_records_ahead_on_tiles_of_sixteen_rows(fmt, ofmt):
         check(y, O.linear(codes[rows], scales[rows], X, ofmt), rows, f"{ofmt.name} N={N} K={K} M={M}: {plan}")
 
 
+@pytest.mark.parametrize("fmt,ofmt", [p for p in PAIRS if REC_K[p[0]] == 128])
+def test_two_records_of_activations_ahead_with_a_scale_per_run(fmt, ofmt):
+    for n_rec, N, M, run in ((18, 2300, 13, 1), (24, 4096, 16, 4), (25, 16 * 130 - 5, 15, 2), (31, 2064, 14, 8)):
+        K, group = 128 * n_rec - 8 * (n_rec % 12), 128 * run
+        plan = ams.ams_linear_plan(fmt, M, N, K, with_workspace=2)
+        assert plan.startswith("slice ") and " x_ahead=2" in plan and " waves=8 " in plan, plan
+        codes, _, rows = problem(fmt, ofmt, N, K, n_rec)
+        scales, packed = scales_per_run(N, K, group, n_rec)
+        X = synth.activations(M, K, 95 + M)
+        y = ams.ams_linear_grouped(dev(ams.ams_pack_codes(fmt, codes)), dev(packed), group, dev(X), N, fmt)
+        check(y, O.linear(codes[rows], scales[rows], X, ofmt, group), rows, f"{ofmt.name} N={N} K={K} M={M}: {plan}")
+
+
 @pytest.mark.parametrize("fmt,ofmt,n_recs", [(ams.FP533, O.FP533, (96, 97, 161)), (ams.FP5, O.FP5_E2M2, (128, 129, 241)), (ams.FP4, O.FP4_E2M1, (96, 111, 161))])
 def test_two_records_ahead_on_one_strip(fmt, ofmt, n_recs):
     # whole rounds of sixteen wavefronts and one record more, one row and two, a last record that ends after 8 channels

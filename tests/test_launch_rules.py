@@ -198,3 +198,10 @@ def test_tiles_of_sixteen_rows_have_eight_wavefronts_where_twelve_leave_a_round_
         want = ("8", "8", "2", "2") if deep else ("16", "12", "1", "1")
         assert (p["waves"], p.get("streams", p["waves"]), p["ahead"], p.get("x_ahead", "1")) == want, p
     assert plan(ams.FP425, M, N, 128 * 16)[1]["streams"] == "12"
+
+
+@pytest.mark.parametrize("fmt", [ams.FP425, ams.FP45, ams.FP5, ams.FP4])
+def test_eight_wavefronts_for_13_to_16_rows_with_a_scale_per_run(fmt):
+    for M, n_rec, deep in ((12, 18, False), (13, 17, False), (13, 18, True), (16, 18, True), (16, 200, True), (17, 18, False)):
+        kind, p = plan(fmt, M, 16 * 200, 128 * n_rec - 8, with_workspace=GROUPED)
+        assert kind == "slice" and ((p["strips_per_wg"], p["waves"], p.get("streams", ""), p.get("x_ahead", "")) == ("1", "8", "", "2")) == deep, p
