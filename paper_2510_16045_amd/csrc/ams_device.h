@@ -338,7 +338,7 @@ constexpr int kSliceRaggedMaxStrips = 4, kSliceRaggedMaxRows = 8;  // of kSliceR
 constexpr bool slice_has_deep(int fmt, int variant, int rows, int strips) {
   const bool rec96 = ams::kFormats[fmt].rec_k == 96;
   if (strips != 1) return false;
-  return variant == kSliceDeepRuns ? rows == 16 && !rec96 : (rows == 4 && ams::side_group(ams::kFormats[fmt]) == 1) || (rows == 16 && rec96);
+  return variant == kSliceDeepRuns ? rows == 16 && !rec96 : (rows == 4 && ams::side_group(ams::kFormats[fmt]) == 1) || rows == 16;
 }
 constexpr int kSliceMaxStrips = 8;  // strips per workgroup it is built for
 constexpr int slice_rows(int M) { return M <= 4 ? 4 : M <= 8 ? 8 : M <= 16 ? 16 : 32; }  // staged activation rows
@@ -362,8 +362,7 @@ constexpr SliceAsk slice_ask(int fmt, int R, int NS, int variant) {
   // seven formats: 5 to 8 rows 1.18 x on one strip, 1.12 on two, 1.08 on three and four (11003 x 4099 FP5.33 M = 5 8.8 / 8.1 us, 4096 x 14339
   // M = 8 14.9 / 12.7); up to four rows 1.07, 1.03, 1.02, 1.01 (twelve streams of 96-weight records 0.94-0.97 x on two strips).
   if (variant == kSliceRagged) return {16, R == 4 && NS == 2 && loads2 && !rec96 ? 12 : 16, NS == 1 ? 1 : 2, 1, 0};
-  if (variant == kSliceDeepRuns) return {8, 8, 1, 2, 0};
-  if (variant == kSliceDeep) return R == 4 ? SliceAsk{16, 16, 2, 2, 0} : SliceAsk{8, 8, 2, 2, 0};
+  if (variant >= kSliceDeep) return R == 4 ? SliceAsk{16, 16, 2, 2, 0} : SliceAsk{8, 8, rec96 ? 2 : 1, 2, 0};
   if (NS == 1) {
     // One strip: many wavefronts that each wait for one record (4096 x 9728 FP4.25 M = 1, sixteen with two records ahead / with
     // one / twelve / eight with two: 1.00 / 1.10 / 1.02 / 1.03 x; two of both only as kSliceDeep).  Up to eight rows eight stay, two ahead of both (one ahead

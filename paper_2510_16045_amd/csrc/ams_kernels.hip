@@ -1510,7 +1510,7 @@ ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
   return slice_plan(p, fmt, M, kSliceRagged);
 }
 
-// One strip: whether to ask for two records ahead (kSliceDeep; kSliceDeepRuns: of activations), not one.  us, one / two:
+// One strip: whether to ask for two records ahead (kSliceDeep, kSliceDeepRuns; 128-weight records at 13 to 16 rows: of activations), not one.  us, one / two:
 //   M <= 2, no side groups, fewer workgroups than 7/8 of the compute units, and a stream that is long against its start: the
 //     memory is not what limits them there, every compute unit waits for its own requests.  1500 shapes of 1 to 223 strips 1.035 x
 //     (FP5.33 M = 1 2560 x 24960 11.64 / 11.04 us, 1024 x 18432 8.89 / 8.59; FP4 3520 x 38400 13.70 / 12.76; M = 2 12.24 / 11.83 on
@@ -1520,12 +1520,15 @@ ColumnPlan ragged_plan(ColumnPlan p, int fmt, int M, int64_t n_strips, int gk) {
 //     stream leave a round half empty and write half as many tiles again.  900 shapes FP4.33 1.04 x (4096 x 2688 M = 15 4.69 / 4.42,
 //     4096 x 1536 3.78 / 3.53), FP6 1.025 x (4.93 / 4.77), FP5.33 1.012 x; from 29 records on FP4.33 1.03 x up to 36, the others 0.99-1.0 x;
 //     below 16 0.98-1.01 x.
-//   One scale per run, 13 to 16 rows of 128-weight records, from 18 of them on: eight wavefronts instead of twelve streams 1.03 x over
-//     340 shapes (4096 x 3072 FP4.25 M = 16 5.34 / 4.91, x 14336 13.92 / 13.54); 9 rows 0.98 x, 12 rows 1.01 x; 6 to 17 records 0.98-1.02 x.
-bool more_ahead_is_faster(int fmt, int variant, int M, int rows, int strips, int grid, int n_rec) {
+//   Tiles of 13 to 16 rows of 128-weight records, from 18 of them on: eight wavefronts instead of twelve streams 1.025 x over
+//     900 shapes, at the first percentile 0.97 x (FP4.25 M = 15 4096 x 3072 4.97 / 4.68, x 14336 12.99 / 12.71; with a scale per run M = 16
+//     5.34 / 4.91, 13.92 / 13.54; 29 to 31 records, three rounds of twelve, 0.96-1.0 x); 9 rows 0.98 x, 12 rows 1.01 x; with a scale per
+//     run on 6 to 17 records 0.98-1.02 x.
+bool more_ahead_is_faster(int fmt, int variant, int M, int tile_rows, int strips, int grid, int n_rec) {
+  const int rows = slice_rows(tile_rows);
   if (!slice_has_deep(fmt, variant, rows, strips)) return false;
-  if (variant == kSliceDeepRuns) return M >= 13 && M <= 16 && n_rec >= 18;
   if (rows == 4) return M <= 2 && grid < kNumCU * 7 / 8 && n_rec >= (fmt == FMT_FP5 ? (M == 1 ? 128 : 240) : (M == 1 ? 96 : 160));
+  if (ams::kFormats[fmt].rec_k != 96) return tile_rows >= 13 && n_rec >= 18;
   return n_rec >= 16 && n_rec <= (fmt == FMT_FP433 ? 36 : 28);
 }
 
@@ -1579,7 +1582,7 @@ ColumnPlan plan_from(ColumnPlan p, int fmt, int M, int64_t n_strips, int n_rec_a
     }
   }
   const int deep = one_scale ? kSliceDeep : kSliceDeepRuns;
-  if (gk == 1 && more_ahead_is_faster(fmt, deep, M, slice_rows((M + p.row_tiles - 1) / p.row_tiles), p.spw, p.grid, n_rec_all)) return slice_plan(p, fmt, M, deep);
+  if (gk == 1 && more_ahead_is_faster(fmt, deep, M, (M + p.row_tiles - 1) / p.row_tiles, p.spw, p.grid, n_rec_all)) return slice_plan(p, fmt, M, deep);
   return slice_plan(p, fmt, M, one_scale ? kSlicePlain : kSliceRunScales);
 }
 ColumnPlan make_plan(int fmt, int M, int64_t n_strips, int n_rec_all, int rec_k, int gk, bool aligned_rows, bool one_scale, bool nt) {

@@ -15,15 +15,15 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("fmt,ofmt", PAIRS)
-@pytest.mark.parametrize("strips,N,Ms", [(2, 16 * 300 - 5, (1, 4)), (1, 16 * 140 - 5, (9, 15))])
+@pytest.mark.parametrize("strips,N,Ms", [(2, 16 * 300 - 5, (1, 4)), (1, 16 * 140 - 5, (9, 12, 15))])
 def test_records_around_the_streaming_wavefronts(fmt, ofmt, strips, N, Ms):
     for n_rec in (11, 12, 13, 24, 25, 48, 49):
-        eight = strips == 1 and REC_K[fmt] == 96 and n_rec in (24, 25)  # wavefronts, which are the faster there
         K = REC_K[fmt] * n_rec - 8 * (n_rec % 3)
         codes, scales, rows = problem(fmt, ofmt, N, K, n_rec)
         packed = dev(ams.ams_pack_codes(fmt, codes))
         run_scales, run_packed = scales_per_run(N, K, 2 * REC_K[fmt], 4)
         for M in Ms:
+            eight = strips == 1 and (n_rec in (24, 25) if REC_K[fmt] == 96 else M == 15 and n_rec >= 18)  # wavefronts, which are the faster there
             plan = ams.ams_linear_plan(fmt, M, N, K)
             assert plan.startswith("slice ") and f"strips_per_wg={strips} " in plan and (" waves=8 " if eight else " waves=16 ") in plan, plan
             X = synth.activations(M, K, 50 + M)
@@ -60,16 +60,19 @@ def test_two_records_ahead_on_tiles_of_sixteen_rows(fmt, ofmt):
 
 
 @pytest.mark.parametrize("fmt,ofmt", [p for p in PAIRS if REC_K[p[0]] == 128])
-def test_two_records_of_activations_ahead_with_a_scale_per_run(fmt, ofmt):
-    for n_rec, N, M, run in ((18, 2300, 13, 1), (24, 4096, 16, 4), (25, 16 * 130 - 5, 15, 2), (31, 2064, 14, 8)):
+def test_two_records_of_activations_ahead(fmt, ofmt):
+    # 13 to 16 rows, one scale per row and one per run; 26 rows: dealt to two workgroups
+    for n_rec, N, M, run in ((18, 2300, 13, 1), (24, 4096, 15, 4), (25, 16 * 130 - 5, 14, 2), (31, 2000, 26, 8)):
         K, group = 128 * n_rec - 8 * (n_rec % 12), 128 * run
-        plan = ams.ams_linear_plan(fmt, M, N, K, with_workspace=2)
-        assert plan.startswith("slice ") and " x_ahead=2" in plan and " waves=8 " in plan, plan
-        codes, _, rows = problem(fmt, ofmt, N, K, n_rec)
-        scales, packed = scales_per_run(N, K, group, n_rec)
+        plan = [ams.ams_linear_plan(fmt, M, N, K, with_workspace=w) for w in (0, 2)]
+        assert all(p.startswith("slice ") and " x_ahead=2" in p and " waves=8 " in p for p in plan), plan
+        codes, scales, rows = problem(fmt, ofmt, N, K, n_rec)
+        run_scales, packed = scales_per_run(N, K, group, n_rec)
         X = synth.activations(M, K, 95 + M)
-        y = ams.ams_linear_grouped(dev(ams.ams_pack_codes(fmt, codes)), dev(packed), group, dev(X), N, fmt)
-        check(y, O.linear(codes[rows], scales[rows], X, ofmt, group), rows, f"{ofmt.name} N={N} K={K} M={M}: {plan}")
+        w, what = dev(ams.ams_pack_codes(fmt, codes)), f"{ofmt.name} N={N} K={K} M={M}: {plan}"
+        check(ams.ams_linear(w, dev(scales), dev(X), N, fmt), O.linear(codes[rows], scales[rows], X, ofmt), rows, what)
+        y = ams.ams_linear_grouped(w, dev(packed), group, dev(X), N, fmt)
+        check(y, O.linear(codes[rows], run_scales[rows], X, ofmt, group), rows, "scales per run, " + what)
 
 
 @pytest.mark.parametrize("fmt,ofmt,n_recs", [(ams.FP533, O.FP533, (96, 97, 161)), (ams.FP5, O.FP5_E2M2, (128, 129, 241)), (ams.FP4, O.FP4_E2M1, (96, 111, 161))])

@@ -201,7 +201,8 @@ def test_tiles_of_sixteen_rows_have_eight_wavefronts_where_twelve_leave_a_round_
 
 
 @pytest.mark.parametrize("fmt", [ams.FP425, ams.FP45, ams.FP5, ams.FP4])
-def test_eight_wavefronts_for_13_to_16_rows_with_a_scale_per_run(fmt):
-    for M, n_rec, deep in ((12, 18, False), (13, 17, False), (13, 18, True), (16, 18, True), (16, 200, True), (17, 18, False)):
-        kind, p = plan(fmt, M, 16 * 200, 128 * n_rec - 8, with_workspace=GROUPED)
+@pytest.mark.parametrize("entry", [0, GROUPED])
+def test_eight_wavefronts_for_13_to_16_rows_of_128_weight_records(fmt, entry):
+    for M, N, n_rec, deep in ((12, 3200, 18, False), (13, 3200, 17, False), (13, 3200, 18, True), (15, 3200, 18, True), (15, 3200, 200, True), (17, 3200, 18, False), (20, 2000, 18, False), (26, 2000, 18, True)):
+        kind, p = plan(fmt, M, N, 128 * n_rec - 8, with_workspace=entry)
         assert kind == "slice" and ((p["strips_per_wg"], p["waves"], p.get("streams", ""), p.get("x_ahead", "")) == ("1", "8", "", "2")) == deep, p
