@@ -146,6 +146,8 @@ PyMODINIT_FUNC PyInit_in_call() {{ return PyModule_Create(&here); }}
 """)
     import __graft_entry__ as g
 
+    if g.binding_includes() is None:
+        pytest.skip("no headers of torch: there is no native binding")
     subprocess.run(g.binding_command(g._hipcc(), g.binding_includes(), str(tmp_path / "in_call.cpp"), str(tmp_path / "in_call.so")), check=True, timeout=300)
     code = """
 import threading, time, torch, in_call
